@@ -145,7 +145,11 @@ DWM_API dwm_status_t dwm_plan_fused_info(const dwm_plan_t* plan, int* n_classes,
 DWM_API dwm_status_t dwm_plan_fused_class(const dwm_plan_t* plan, int i, dwm_fused_class_t* cls);
 DWM_API dwm_status_t dwm_plan_fused_row(const dwm_plan_t* plan, int row, dwm_fused_row_t* out);
 
-/* Bytes of the transformed filter Ugw and of the workspace (the transformed input V, plus
+/* Layers with long reductions are contracted on the bfloat16 matrix cores, every binary32 operand as the sum of three
+ * bfloat16 numbers, with errors no larger than on the fp32 ones (operands that cannot be written so -- infinities, NaN,
+ * the last 2^119 of the range -- take the fp32 ones).  Ugw then also holds the split transformed filter, after the
+ * per-class layout above; asking for a "contract" variant or a "split" other than 0 brings the fp32 kernel.
+ * Bytes of the transformed filter Ugw and of the workspace (the transformed input V, plus
  * partial output tiles and arrival counters of the contraction's split tiles). */
 DWM_API size_t dwm_plan_filter_bytes(const dwm_plan_t* plan);
 DWM_API size_t dwm_plan_workspace_bytes(const dwm_plan_t* plan);
@@ -156,7 +160,7 @@ DWM_API dwm_status_t dwm_plan_set_workspace(dwm_plan_t* plan, void* ws_dev, size
 
 /* Pick a kernel variant for a stage (for tuning and tests; the planner's own choice is the
  * default and variant < 0 restores it).
- *   "contract": tile shape / chunk depth of the contraction kernel: 10..19, the ids of the
+ *   "contract": tile shape / chunk depth of the fp32-MFMA contraction kernel: 10..19, the ids of the
  *               library's internal table of variants (a variant whose chunk depth does not divide
  *               the plan's reduction padding does not apply);
  *   "forward":  0 = input transform + contraction, 1 = single kernel (layers with few input channels

@@ -304,6 +304,7 @@ dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, i
                 sp.pad_h = ph.na - 1 - u0; sp.pad_w = ph.nb - 1 - v0;
                 sp.OH = ph.UH; sp.OW = ph.UW;
                 sp.om = OutMap{H, W, s, ph.oy, s, ph.ox};
+                sp.no_split = s > 1;  // (several sub-convolutions are contracted together, on fp32 MFMAs)
                 st = plan_from_spec(&ph.sub, sp);
                 if (st == DWM_OK) {
                     bp->wtmp_floats = std::max(bp->wtmp_floats, (size_t)C * K * ph.na * ph.nb);

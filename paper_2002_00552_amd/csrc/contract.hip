@@ -456,6 +456,7 @@ static dwm_status_t launch_variant(const dwm_plan& p, const float* U, float* V, 
 
 dwm_status_t launch_contract_output(const dwm_plan& p, const float* U, float* V, float* y, void* stream)
 {
+    if (p.use_split()) return launch_contract_split(p, U, V, y, stream);
     switch (p.geo.variant) {
         case 10: return launch_variant<2, 2, 1, 1, 16, 4>(p, U, V, y, stream);
         case 11: return launch_variant<2, 2, 1, 1, 32, 3>(p, U, V, y, stream);

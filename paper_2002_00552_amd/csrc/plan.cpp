@@ -165,12 +165,82 @@ bool contract_geometry(const dwm_plan& p, int variant, ContractGeometry* out)
     return true;
 }
 
+// The fp32 contraction's time (us) as the planner shares it out: 0.26 us for 16 steps of a 64x64 tile with every CU
+// busy, a fold per plane, and, where each tile is cut, the last workgroup's summing of the pieces.
+static double fp32_contract_us(const dwm_plan& p)
+{
+    const ContractGeometry& g = p.geo;
+    const long long wgs = (long long)g.n_full + g.sk_wgs;
+    return (double)g.ntiles * (double)plane_rows(p) / 16.0 * 0.26 / (double)(wgs < kNumCUs ? wgs : kNumCUs) +
+           0.45 * p.planes.n / (g.sk_f > 1 ? g.sk_f : 1) + (g.sk_f > 1 ? 1.7 * g.sk_f : 0.0) + 9.0;
+}
+
+// The contraction on the bfloat16 matrix cores: whether it takes the layer, with which shape of its workgroup, and into
+// how many pieces each tile is cut.  It is worth considering from 1024 rows of reduction per tile (all planes together)
+// and 32 filters on: below, a tile ends before its loads have caught up, and the input transform is most of the time.
+// The cut is the one that takes the least time by this model, fitted to measurements of twelve layers (within 10 %): a
+// 16-step chunk takes `t[c]` us in each of the c workgroups on a CU, a round of the chip the time of its fullest CUs,
+// less what CUs with fewer workgroups leave to the others; a fold takes 0.45 us, outputs 10 us; a piece's partial output
+// is written and read back once (0.3 us per MB on top of what hides behind the MFMAs), by a kernel of its own (3 us).  A
+// piece is no shorter than 16 chunks: its start takes as long as ten (measured on a 49-tile layer of 256 chunks per
+// tile: 16 pieces 16.8 us, 32 pieces 20.5).  Measured, contraction, fp32 -> here: 7x7 256->256 28x28 N=32 727 -> 500 us,
+// 9x9 14x14 293 -> 205, 3x3 256->256 14x14 N=1 29 -> 17, N=8 30 -> 22; layers of about 200 of its tiles and short planes
+// (3x3 stride 2 128->256 56x56 N=32: 91 against 103) leave a quarter of the CUs idle and stay with the fp32 kernel.
+bool split_geometry(const dwm_plan& p, ContractGeometry* out)
+{
+    if (plane_rows(p) < 1024 || p.d.K < 32) return false;
+    bool found = false;
+    double best = 0.0;
+    for (int v = 0; v < kNumSplitVariants; ++v) {
+        const SplitVariant& sv = kSplitVariants[v];
+        ContractGeometry g{};
+        g.variant = v;
+        g.nkt = (p.d.K + sv.kt() - 1) / sv.kt();
+        g.ntt = (p.d.T + sv.tt() - 1) / sv.tt();
+        const long long ntiles = (long long)g.nkt * g.ntt, n_iter = plane_rows(p) / kSplitChunk;
+        if (ntiles > 0x3fffffLL || n_iter > 0x3fffffLL) continue;
+        g.ntiles = (int)ntiles;
+        g.full8 = 8 * g.nkt * (g.ntt / 8);
+        g.n_iter = (int)n_iter;
+        // (whole tiles for all full rounds of the chip and pieces for the rest measured no better than pieces for all)
+        for (int f = 1; f <= kSplitMaxPieces && (f == 1 || f * 16 <= g.n_iter); ++f) {
+            ContractGeometry c = g;
+            c.n_full = f == 1 ? c.ntiles : 0;
+            c.n_sk_tiles = c.ntiles - c.n_full;
+            c.sk_f = f;
+            c.sk_ipw = (c.n_iter + f - 1) / f;
+            c.sk_wgs = c.n_sk_tiles * f;
+            c.partial_floats = f == 1 ? 0 : (size_t)c.sk_wgs * sv.kt() * sv.tt() * 4;
+            // (a layer whose workspace fitted the static scratch array still does)
+            const size_t v_bytes = p.v_floats * sizeof(float) + 1024;
+            if (v_bytes + p.geo.partial_floats * sizeof(float) <= DWM_STATIC_SCRATCH_BYTES &&
+                v_bytes + c.partial_floats * sizeof(float) > DWM_STATIC_SCRATCH_BYTES)
+                continue;
+            const long long wgs = ntiles * f, slots = (long long)kNumCUs * sv.per_cu, rest = wgs % slots;
+            double per_chunk = (double)(wgs / slots) * sv.t[sv.per_cu - 1];
+            if (rest > 0) {
+                const int on_cu = (int)((rest + kNumCUs - 1) / kNumCUs);  // workgroups on the fullest CUs
+                const double below = on_cu > 1 ? sv.t[on_cu - 2] : 0.0, share = (double)rest / kNumCUs - (on_cu - 1);
+                per_chunk += on_cu == 1 ? sv.t[0] : below + (sv.t[on_cu - 1] - below) * (0.35 + 0.65 * share);
+            }
+            const double t = per_chunk * c.sk_ipw + 0.45 * p.planes.n / f * (double)((wgs + slots - 1) / slots) + 10.0 +
+                             (f > 1 ? 3.0 + 0.3e-6 * 4.0 * (double)c.partial_floats : 0.0);
+            if (found && t >= best) continue;
+            best = t;
+            found = true;
+            *out = c;
+        }
+    }
+    return found && best < 0.97 * fp32_contract_us(p);
+}
+
 }  // namespace dwm
 
 extern "C" {
 
 // One planning pass with the given splitting policy; *out is set on DWM_OK only.
-static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool even_tail, bool widen2 = false)
+static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool even_tail, bool with_split,
+                               bool widen2 = false)
 {
     const int N = sp.N, C = sp.C, H = sp.H, W = sp.W, K = sp.K, R = sp.R, S = sp.S, stride = sp.stride;
     if (N < 1 || C < 1 || H < 1 || W < 1 || K < 1 || R < 1 || S < 1 || stride < 1 || sp.OH < 1 || sp.OW < 1)
@@ -298,6 +368,12 @@ static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool e
     // (the single-kernel path goes with the even-tail splitting only)
     p->fused_ok = even_tail && dwm::fused_setup(*p, &p->fused);
     p->inlds_ok = dwm::input_lds_setup(*p, &p->inlds, 0);
+    if (!p->fused_ok && with_split && !sp.no_split && dwm::split_geometry(*p, &p->split)) {
+        // the split copy of U: six bytes an element (padding included)
+        p->split_ok = true;
+        p->us_begin = p->filter_floats;  // (a multiple of 64: the class layout's sizes are)
+        p->filter_floats += p->filter_floats / 2 * 3;
+    }
     if (p->fused_ok) {
         // the single-kernel path reads its own copy of the transformed filter (see FusedClass)
         size_t uf = (p->filter_floats + 63) / 64 * 64;
@@ -322,11 +398,11 @@ namespace dwm {
 dwm_status_t plan_from_spec(dwm_plan_t** out, const PlanSpec& sp)
 {
     dwm_plan_t* p = nullptr;
-    dwm_status_t st = plan_build(&p, sp, true);
+    dwm_status_t st = plan_build(&p, sp, true, false);
     if (st == DWM_OK && !p->fused_ok) {
         delete p;
         p = nullptr;
-        st = plan_build(&p, sp, false);
+        st = plan_build(&p, sp, false, true);
     }
     if (st == DWM_OK) *out = p;
     return st;
@@ -334,12 +410,12 @@ dwm_status_t plan_from_spec(dwm_plan_t** out, const PlanSpec& sp)
 
 dwm_status_t plan_from_spec_as_printed(dwm_plan_t** out, const PlanSpec& sp)
 {
-    return plan_build(out, sp, false);
+    return plan_build(out, sp, false, false);
 }
 
 dwm_status_t plan_from_spec_widened(dwm_plan_t** out, const PlanSpec& sp)
 {
-    return plan_build(out, sp, true, true);
+    return plan_build(out, sp, true, false, true);
 }
 }  // namespace dwm
 
@@ -467,8 +543,10 @@ dwm_status_t dwm_plan_set_variant(dwm_plan_t* plan, const char* stage, int varia
     if (!std::strcmp(stage, "split")) {  // 0: whole tiles + split remainder, 1: all tiles split evenly
         const int old_mode = plan->sk_mode;
         plan->sk_mode = variant == 1 ? 1 : variant == 2 ? 2 : 0;
+        const bool forced = plan->contract_forced;
         const dwm_status_t st = dwm_plan_set_variant(plan, "contract", plan->geo.variant);
         if (st != DWM_OK) plan->sk_mode = old_mode;
+        plan->contract_forced = forced;  // (a way of sharing out tiles was asked for, not a variant)
         return st;
     }
     if (std::strcmp(stage, "contract") || variant >= dwm::kFirstHalfVariant) return DWM_ERR_INVALID_ARG;
@@ -476,6 +554,7 @@ dwm_status_t dwm_plan_set_variant(dwm_plan_t* plan, const char* stage, int varia
     if (!dwm::contract_geometry(*plan, variant < 0 ? default_contract_variant(plan->lgran, plan->d.K, plan->d.T, plane_rows(*plan)) : variant, &g))
         return DWM_ERR_INVALID_ARG;
     plan->geo = g;
+    plan->contract_forced = variant >= 0;
     return DWM_OK;
 }
 

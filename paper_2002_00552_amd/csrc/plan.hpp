@@ -123,6 +123,23 @@ struct ContractGeometry {
     size_t partial_floats;
 };
 
+// Shapes of the contraction on the bfloat16 matrix cores (contract_split.hip): workgroup of WGM x WGN waves, wave tile
+// 32*WM x 32, how many workgroups a CU holds, and the measured time of a chunk (us) with 1, 2, ... of them on it.
+// Its tiles are whole (n_full) or cut into sk_f pieces of sk_ipw chunks each; ContractGeometry's sk_maxc is not used.
+constexpr int kSplitChunk = 16;      // reduction steps per chunk
+constexpr int kSplitMaxPieces = 16;
+struct SplitVariant {
+    int wgm, wgn, wm, per_cu;
+    double t[3];
+    int kt() const { return 32 * wm * wgm; }
+    int tt() const { return 32 * wgn; }
+};
+constexpr SplitVariant kSplitVariants[] = {
+    {2, 2, 2, 2, {0.395, 0.75}},         // 128 filters x 64 tiles
+    {2, 2, 1, 3, {0.285, 0.48, 0.68}},   // 64 x 64
+};
+constexpr int kNumSplitVariants = sizeof(kSplitVariants) / sizeof(kSplitVariants[0]);
+
 #ifdef __HIPCC__
 // One 2x2 output tile through the output map; rows/columns past the output extent are dropped.
 __device__ __forceinline__ void store_tile(float* __restrict__ y, const OutMap& M, int OH, int OW, size_t plane,
@@ -328,15 +345,22 @@ struct dwm_plan {
                         // LDS-staged input transform does not write their zeros
     dwm::InLdsArgs inlds;
     bool use_fused() const { return fused_ok && variant_forward != 0; }
+    // the contraction on the bfloat16 matrix cores: applies (and U carries its split copy, us_begin floats into
+    // Ugw); a contraction variant or a way of sharing out the tiles that was asked for by number is contract.hip's
+    bool split_ok, contract_forced;
+    dwm::ContractGeometry split;
+    size_t us_begin;
+    bool use_split() const { return split_ok && !contract_forced && sk_mode == 0; }
+    const dwm::ContractGeometry& active() const { return use_split() ? split : geo; }
 
     // workspace layout: [ V | partial outputs | arrival counters ]
-    size_t ws_need_bytes() const { return (v_floats + geo.partial_floats) * sizeof(float) + counters_bytes(); }
-    size_t counters_bytes() const { return ((size_t)geo.n_sk_tiles * sizeof(int) + 255) / 256 * 256; }
+    size_t ws_need_bytes() const { return (v_floats + active().partial_floats) * sizeof(float) + counters_bytes(); }
+    size_t counters_bytes() const { return ((size_t)active().n_sk_tiles * sizeof(int) + 255) / 256 * 256; }
     // (given the workspace's base, so that a call may run on a workspace other than the plan's own)
     float* sk_partial(float* base) const { return base ? base + v_floats : nullptr; }
     int* sk_counters(float* base) const
     {
-        return base ? reinterpret_cast<int*>(base + v_floats + geo.partial_floats) : nullptr;
+        return base ? reinterpret_cast<int*>(base + v_floats + active().partial_floats) : nullptr;
     }
 };
 
@@ -348,6 +372,7 @@ struct PlanSpec {
     int pad_h, pad_w;
     int OH, OW;
     OutMap om;
+    bool no_split;  // not contracted on the bfloat16 matrix cores: no split copy of U
 };
 dwm_status_t plan_from_spec(dwm_plan_t** out, const PlanSpec& sp);
 // For the filter gradient of layers with few channels: phases cut 3,...,3,2,2 and every two-tap
@@ -359,6 +384,8 @@ dwm_status_t plan_from_spec_widened(dwm_plan_t** out, const PlanSpec& sp);
 dwm_status_t plan_from_spec_as_printed(dwm_plan_t** out, const PlanSpec& sp);
 // plan.cpp: geometry of a contraction variant for this plan; false if the variant does not apply
 bool contract_geometry(const dwm_plan& p, int variant, ContractGeometry* out);
+// ... and the shape and the sharing out of the contraction on the bfloat16 matrix cores; false where it does not pay
+bool split_geometry(const dwm_plan& p, ContractGeometry* out);
 // transforms.hip, contract.hip
 dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U, void* stream);
 // `ws` is the base of a workspace laid out as the plan says: V first, then the partial outputs and
@@ -366,6 +393,9 @@ dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U
 dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* ws, void* stream);
 dwm_status_t launch_contract_output(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
 bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish);
+// contract_split.hip: the split copy of a transformed filter, and the contraction that reads it
+dwm_status_t launch_split_filter(const dwm_plan& p, float* U, void* stream);
+dwm_status_t launch_contract_split(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
 // contract_batch.hip
 dwm_status_t launch_contract_batch(const BatchArgs& a, const PlaneTable& pt, int lc, const float* U, const float* V,
                                    float* y, void* stream);

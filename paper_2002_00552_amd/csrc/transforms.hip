@@ -309,7 +309,8 @@ dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U
 {
     dim3 grid((p.d.rows_total + 255) / 256, p.d.Kpad), block(256);
     hipLaunchKernelGGL(filter_transform_kernel, grid, block, 0, (hipStream_t)stream, p.d, w, U);
-    return check_launch();
+    if (!p.split_ok) return check_launch();
+    return check_launch() == DWM_OK ? launch_split_filter(p, U, stream) : DWM_ERR_HIP;
 }
 
 dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* V, void* stream)
@@ -331,7 +332,7 @@ dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* V,
             if (attr != hipSuccess) return DWM_ERR_HIP;
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)(nb * a.ncg)), block, a.lds_bytes, (hipStream_t)stream, d, a, x, V,
-                           p.sk_counters(V), p.geo.n_sk_tiles, variant == 2, p.skip_pad_rows ? 0 : 1);
+                           p.sk_counters(V), p.active().n_sk_tiles, variant == 2, p.skip_pad_rows ? 0 : 1);
         return check_launch();
     }
     int rows_fast = variant;
@@ -339,7 +340,7 @@ dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* V,
     if ((rows_fast ? nb : nr) > 65535) return DWM_ERR_UNSUPPORTED;
     dim3 grid(rows_fast ? nr : nb, rows_fast ? nb : nr);
     hipLaunchKernelGGL(input_transform_kernel, grid, block, 0, (hipStream_t)stream, d, x, V, p.sk_counters(V),
-                       p.geo.n_sk_tiles, rows_fast);
+                       p.active().n_sk_tiles, rows_fast);
     return check_launch();
 }
 

@@ -732,6 +732,7 @@ static dwm_status_t wgrad_build(dwm_bwd_filter_plan_t** out, dwm_plan_t* fwd, in
         return DWM_ERR_ALLOC;
     }
     bp->fwd = fwd;
+    fwd->split_ok = false;  // only its input transform is used
     bp->ws = nullptr;
     bp->direct_flops = fwd->info.direct_flops;
     bp->winograd_flops = fwd->info.winograd_flops;

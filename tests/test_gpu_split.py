@@ -1,0 +1,138 @@
+"""The single-precision contraction on the bfloat16 matrix cores (three-way split operands) through the C ABI: at the edges
+of its tiles, its cuts and its reduction, against FP64 and against the fp32-MFMA contraction of the same layer."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2002_00552_amd as dwm
+from dwm_gpu import Runner
+
+pytestmark = pytest.mark.gpu
+
+# (N, C, H, W, K, R, S, stride, pad): layers that the planner gives to the split contraction (test_planner_takes_it checks
+# that); between them tiles of 128 and of 64 filters, whole tiles and 4 .. 16 pieces, ragged filters, tiles and channels
+SHAPES = [
+    (1, 256, 14, 14, 256, 3, 3, 1, 1),     # 49 tiles of 64: sixteen pieces
+    (2, 64, 9, 9, 33, 4, 4, 1, 1),         # filters just past half a tile, 32 tiles
+    (5, 67, 35, 29, 93, 5, 5, 2, 2),       # nothing a multiple of anything
+    (4, 200, 21, 23, 129, 3, 3, 1, 0),     # one filter past 128, a piece length that does not divide
+    (4, 109, 27, 28, 117, 7, 7, 1, 3),     # tiles of 128 filters cut into pieces
+    (256, 128, 28, 28, 128, 3, 3, 1, 1),   # whole tiles
+    (1, 300, 2, 2, 40, 3, 3, 1, 1),        # a single 2x2 tile
+    (2, 1030, 6, 6, 64, 1, 1, 1, 0),       # one-tap pieces; planes longer than a fold
+]
+
+
+def _data(shape, seed):
+    N, C, H, W, K, R, S, s, P = shape
+    rng = np.random.default_rng(seed)
+    x = rng.uniform(-1, 1, (N, C, H, W)).astype(np.float32)
+    w = (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32)
+    return x, w
+
+
+def _run(shape, x, w, variants=None):
+    r = Runner(*shape, variants=variants)
+    try:
+        r.set_filter(w)
+        return r.forward(x)
+    finally:
+        r.close()
+
+
+def test_planner_takes_it():
+    """The filter buffer of these layers holds the split copy: two and a half times the classes' own floats."""
+    for shape in SHAPES:
+        p = dwm.dwm_plan_create(*shape)
+        info = dwm.dwm_plan_info(p)
+        last = dwm.dwm_plan_class(p, info.n_classes - 1)
+        floats = last.u_offset + (last.len_h + 1) * (last.len_w + 1) * info.Kpad * last.Lpad
+        assert dwm.dwm_plan_filter_bytes(p) == 10 * floats, shape
+        dwm.dwm_plan_destroy(p)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_no_less_exact_than_fp32_mfma(shape):
+    """Sampled outputs against FP64: within 2e-6 of the largest (fp32 sums of up to 1030 x 49 products in runs of at most
+    1024, folded: a few 1e-7 measured), and in the 2-norm no further off than the fp32 contraction (variant 10: it applies
+    to every layer), which rounds every two products where this one rounds every sixteen."""
+    x, w = _data(shape, 1)
+    y = _run(shape, x, w)
+    y32 = _run(shape, x, w, {"contract": 10, "forward": 0})
+    rng = np.random.default_rng(2)
+    idx = rng.choice(y.size, min(y.size, 4000), replace=False)
+    ref = oracle.direct_f64_at(x, w, shape[7], shape[8], idx)
+    scale = np.max(np.abs(ref))
+    e, e32 = y.ravel()[idx] - ref, y32.ravel()[idx] - ref
+    assert np.all(np.isfinite(y))
+    assert np.max(np.abs(e)) / scale <= 2e-6, shape
+    assert np.linalg.norm(e) <= np.linalg.norm(e32) * 1.05, (np.linalg.norm(e), np.linalg.norm(e32))
+
+
+@pytest.mark.parametrize("shape", [SHAPES[2], SHAPES[5], SHAPES[7]])
+def test_repeats_bit_for_bit(shape):
+    x, w = _data(shape, 3)
+    r = Runner(*shape)
+    try:
+        r.set_filter(w)
+        first = r.forward(x)
+        for _ in range(10):
+            r.y.fill_(float("nan"))
+            assert np.array_equal(r.forward(x), first)
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[4], SHAPES[7]])
+def test_values_the_split_cannot_carry(shape, value):
+    """An infinity, a NaN or a value whose bfloat16 rounding overflows, in x or in w: the same outputs are infinite, of the
+    same sign, or NaN as in the fp32 contraction, and the others agree to fp32 rounding of their own largest terms.  (The
+    other operand is scaled to 1e-3, so that no sum comes near the end of the range, where the order decides.)"""
+    for where in ("x", "w"):
+        x, w = _data(shape, 4)
+        a, other = (x, w) if where == "x" else (w, x)
+        other *= np.float32(1e-3)
+        a[tuple(n // 2 for n in a.shape)] = value
+        y = _run(shape, x, w)
+        y32 = _run(shape, x, w, {"contract": 10, "forward": 0})
+        assert np.array_equal(np.isnan(y), np.isnan(y32)), (where, np.isnan(y).sum(), np.isnan(y32).sum())
+        assert np.array_equal(np.where(np.isinf(y), y, 0), np.where(np.isinf(y32), y32, 0)), where
+        assert np.isfinite(value) == bool(np.all(np.isfinite(y32)))
+        small = np.isfinite(y32) & (np.abs(y32) < 1e3)  # outputs that the value does not reach
+        tall = np.isfinite(y32) & ~small
+        if not np.isfinite(value):
+            assert np.max(np.abs(y[small] - y32[small])) <= 4e-6 * np.max(np.abs(y32[small])), where
+        assert np.all(np.abs(y[tall] - y32[tall]) <= 1e-5 * np.max(np.abs(y32[tall]), initial=0.0)), where
+
+
+def test_subnormal_operands():
+    """x of 1e-38 .. 1e-40, w of ordinary size: every part of an operand that the format can hold is kept (the bound: a
+    part of an operand below 2^-134 times the 9 x 256 products of an output)."""
+    shape = SHAPES[0]
+    x, w = _data(shape, 5)
+    x = (x * 1e-38).astype(np.float32)
+    y = _run(shape, x, w)
+    idx = np.arange(0, y.size, 37)
+    ref = oracle.direct_f64_at(x, w, 1, 1, idx)
+    bound = 2e-6 * np.max(np.abs(ref)) + 9 * 256 * 2.0 ** -134 * np.max(np.abs(w)) * 16 + 2.0 ** -140 * 256 * 16
+    assert np.max(np.abs(y.ravel()[idx] - ref)) <= bound
+
+
+def test_chosen_variants_still_run_the_fp32_contraction():
+    """A contraction variant or a way of sharing out the tiles that was asked for by number stays what it was: the layouts
+    of the workspace differ, so the sizes tell which one is in use, and -1 / 0 bring the planner's choice back."""
+    p = dwm.dwm_plan_create(*SHAPES[0])
+    try:
+        own = dwm.dwm_plan_workspace_bytes(p)
+        dwm.dwm_plan_set_variant(p, "split", 2)  # whole tiles: no partial outputs
+        assert dwm.dwm_plan_workspace_bytes(p) < own
+        dwm.dwm_plan_set_variant(p, "split", 0)
+        assert dwm.dwm_plan_workspace_bytes(p) == own
+        dwm.dwm_plan_set_variant(p, "contract", 12)
+        assert dwm.dwm_plan_workspace_bytes(p) != own
+        dwm.dwm_plan_set_variant(p, "contract", -1)
+        assert dwm.dwm_plan_workspace_bytes(p) == own
+    finally:
+        dwm.dwm_plan_destroy(p)
