@@ -5,7 +5,7 @@
 //
 // Steps, all on the caller's stream:
 //   1. V: the forward pass's input transform of x (same kernel, same layout, blocked by 64 tiles).
-//   2. dM = A dY A^T for every plane: the plane's 0/+-1 output pattern applied to the 2x2 block of
+//   2. dM = A dY A^T for every plane that differs from the others by more than sign (at most 16 of up to 81): the plane's 0/+-1 output pattern applied to the 2x2 block of
 //      dy -- the transpose of the forward pass's fold -- written in V's blocked layout,
 //      dM[block][plane][k][64 tiles].
 //   3. Per plane, dU[k][l] = sum_t dM[k][t] * V[l][t]: a GEMM whose reduction runs over the tiles.
@@ -16,6 +16,8 @@
 //   4. The partial dU are summed in a fixed order and G^T (.) G is applied: every tap of dw is
 //      written exactly once (the parts partition the taps), nothing is accumulated atomically,
 //      results do not vary from run to run.
+// Layers with more than 64 filters and enough of everything else run steps 2 and 3 on the bfloat16 matrix cores
+// (wgrad_split.hip): 128x128 tiles, operands split three ways.
 // Layers with few input channels (every class has at most 32 rows) and many tiles take another
 // form of steps 2-3 that never builds dM: see wgrad_small_body / wgrad_small_all_kernel.
 #include <hip/hip_runtime.h>
@@ -25,28 +27,13 @@
 
 #include "dma.hpp"
 #include "plan.hpp"
+#include "wgrad.hpp"
 
 namespace dwm {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-struct WgradArgs {
-    int K, Kp, T, tblocks;       // filters, filters rounded up to 64, tiles, blocks of 64 tiles
-    int dm_rows, vblock_rows;    // rows of one dM block / one V block
-    int n_planes, n_tiles;
-    int splits, chunks_per_split;
-    long long split_floats;      // floats of one split's partial dU
-    int tile0[kMaxPlanes + 1];   // first output tile of each plane
-    int nlt[kMaxPlanes];         // 64-wide l tiles of each plane
-    int vrow[kMaxPlanes];        // first V row of each plane
-    int poff64[kMaxPlanes];      // offset of the plane's dU[Kp][lstride] inside a split, in units of 64 floats
-    int lstride[kMaxPlanes];     // floats between consecutive filters k of the plane's dU
-};
-
 // ---- step 2: dM[block][plane*Kp + k][t] = sum_q pattern_p[q] * dy[n][k][2ty+a][2tx+b] ----
-struct DyShape {
-    int T, K, Kp, TH, TW, OH, OW, dm_rows;
-};
 __global__ __launch_bounds__(256) void wgrad_dy_transform_kernel(DyShape P, PlaneTable PT,
                                                                  const float* __restrict__ dy, float* __restrict__ dM)
 {
@@ -159,7 +146,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgradArgs A, const f
         const int row = s >> 4, cp = s & 15;
         voff[q] = (uint32_t)(row * 64 + ((cp ^ (row & 15)) << 2)) * 4u;
     }
-    const float* sa = dM + ((size_t)c0 * A.dm_rows + (size_t)p * A.Kp + kt * 64) * 64;
+    const int dmp = A.dmp[p];
+    const float* sa = dM + ((size_t)c0 * A.dm_rows + (size_t)(dmp & 255) * A.Kp + kt * 64) * 64;
     const float* sb = V + ((size_t)c0 * A.vblock_rows + A.vrow[p] + lt * 64) * 64;
     const size_t stepA = (size_t)A.dm_rows * 64, stepB = (size_t)A.vblock_rows * 64;
     int ileft = nit;
@@ -233,7 +221,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_gemm_kernel(WgradArgs A, const f
     float* out = partial + (size_t)split * A.split_floats + (size_t)A.poff64[p] * 64 +
                  (size_t)(kt * 64 + wave_m * 32) * Lp64 + lt * 64 + wave_n * 32 + li;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) out[(size_t)(8 * (e >> 2) + 4 * lh + (e & 3)) * Lp64] = acc[e];
+    for (int e = 0; e < 16; ++e)
+        out[(size_t)(8 * (e >> 2) + 4 * lh + (e & 3)) * Lp64] = (dmp & 256) ? -acc[e] : acc[e];
 }
 
 
@@ -483,6 +472,40 @@ __device__ __forceinline__ float gt_col(int l, int a, const float u[4])
     return u[0] + u[1];
 }
 
+// The class's planes of dU at filter k, row l: sums over the splits, in split order; zeros for the planes a class does not
+// have.  All sixteen loads of a split are in flight together (one plane after the other, four splits at a time, the final
+// kernel ran at 1.4 TB/s: 54 us for 256 filters, 2304 rows, 16 planes, two splits).
+__device__ __forceinline__ void sum_planes(const WgradArgs& A, const DevClass& q, const float* __restrict__ partial, int k,
+                                           int l, float (&u)[4][4])
+{
+    const int tw = q.lw + 1;
+    size_t off[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int p = q.plane0 + (i <= q.lh && j <= q.lw ? i * tw + j : 0);
+            off[i][j] = (size_t)A.poff64[p] * 64 + (size_t)k * A.lstride[p] + l;
+            u[i][j] = 0.f;
+        }
+    for (int s = 0; s < A.splits; ++s, partial += A.split_floats) {
+        float v[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[i][j] = partial[off[i][j]];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) u[i][j] += v[i][j];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i > q.lh || j > q.lw) u[i][j] = 0.f;
+}
+
 __global__ __launch_bounds__(256) void wgrad_final_kernel(DevPlan P, WgradArgs A, const float* __restrict__ partial,
                                                           float* __restrict__ dw)
 {
@@ -497,27 +520,8 @@ __global__ __launch_bounds__(256) void wgrad_final_kernel(DevPlan P, WgradArgs A
     const int slot = l / P.C, c = l - slot * P.C;
     const int ai = slot / q.wn, bi = slot - ai * q.wn;
     const DevPiece hp = P.ph[q.h0 + ai], wp = P.pw[q.w0 + bi];
-    const int tw = q.lw + 1;
     float u[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float v = 0.f;
-            if (i <= q.lh && j <= q.lw) {
-                const int p = q.plane0 + i * tw + j;
-                const float* src = partial + (size_t)A.poff64[p] * 64 + (size_t)k * A.lstride[p] + l;
-                // four loads in flight at a time; the additions keep their order
-                int s = 0;
-                for (; s + 4 <= A.splits; s += 4) {
-                    const float a0 = src[(size_t)s * A.split_floats], a1 = src[(size_t)(s + 1) * A.split_floats];
-                    const float a2 = src[(size_t)(s + 2) * A.split_floats], a3 = src[(size_t)(s + 3) * A.split_floats];
-                    v = (((v + a0) + a1) + a2) + a3;
-                }
-                for (; s < A.splits; ++s) v += src[(size_t)s * A.split_floats];
-            }
-            u[i][j] = v;
-        }
+    sum_planes(A, q, partial, k, l, u);
     // columns (G_h^T u), then rows ((.) G_w)
     float t[3][4];
 #pragma unroll
@@ -551,31 +555,14 @@ __global__ __launch_bounds__(256) void wgrad_final_lds_kernel(DevPlan P, WgradAr
     int part0 = 0;
     for (int qi = 0; qi < P.ncls; ++qi) {
         const DevClass q = P.cls[qi];
-        const int tw = q.lw + 1, nslot = q.hn * q.wn;
+        const int nslot = q.hn * q.wn;
         for (int slot = 0; slot < nslot; ++slot) {
             if (((part0 + slot) & 3) != wave) continue;
             const int ai = slot / q.wn, bi = slot - ai * q.wn;
             const DevPiece hp = P.ph[q.h0 + ai], wp = P.pw[q.w0 + bi];
             const int l = slot * P.C + min(c, P.C - 1);
             float u[4][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float v = 0.f;
-                    if (i <= q.lh && j <= q.lw) {
-                        const int p = q.plane0 + i * tw + j;
-                        const float* src = partial + (size_t)A.poff64[p] * 64 + (size_t)k * A.lstride[p] + l;
-                        int s = 0;
-                        for (; s + 4 <= A.splits; s += 4) {
-                            const float a0 = src[(size_t)s * A.split_floats], a1 = src[(size_t)(s + 1) * A.split_floats];
-                            const float a2 = src[(size_t)(s + 2) * A.split_floats], a3 = src[(size_t)(s + 3) * A.split_floats];
-                            v = (((v + a0) + a1) + a2) + a3;
-                        }
-                        for (; s < A.splits; ++s) v += src[(size_t)s * A.split_floats];
-                    }
-                    u[i][j] = v;
-                }
+            sum_planes(A, q, partial, k, l, u);
             float t[3][4];
 #pragma unroll
             for (int a = 0; a < 3; ++a)
@@ -611,6 +598,8 @@ struct dwm_bwd_filter_plan {
     float* ws;
     // short-reduction form (every class has at most 32 rows): one launch for all classes of 16 rows, one for those of 32
     bool small;
+    dwm::PlaneTable dm_table;          // the planes of dM that are written (only coef is used)
+    bool split;                        // the GEMM runs on the bfloat16 matrix cores (wgrad_split.hip)
     int small_kt;                      // 64-filter tiles
     size_t sum_bytes;                  // the summed dU after the partials
     int n_pass;                        // passes: (class, rows r0 .. r0 + 16 * lb) with lb in {1, 2}
@@ -736,61 +725,101 @@ static dwm_status_t wgrad_build(dwm_bwd_filter_plan_t** out, dwm_plan_t* fwd, in
     bp->ws = nullptr;
     bp->direct_flops = fwd->info.direct_flops;
     bp->winograd_flops = fwd->info.winograd_flops;
-    WgradArgs& a = bp->a;
-    a = WgradArgs{};
     const DevPlan& d = fwd->d;
-    a.K = K; a.Kp = (K + 63) / 64 * 64; a.T = d.T; a.tblocks = (d.T + 63) / 64;
-    a.n_planes = fwd->planes.n;
-    a.dm_rows = a.n_planes * a.Kp;
-    a.vblock_rows = d.vblock_rows;
-    long long tiles = 0, floats64 = 0;
-    for (int p = 0; p < a.n_planes; ++p) {
-        const DevPlaneEntry& e = fwd->planes.e[p];
-        a.nlt[p] = (e.Lpad + 63) / 64;
-        a.lstride[p] = a.nlt[p] * 64;
-        a.vrow[p] = (int)e.v_off64;
-        a.tile0[p] = (int)tiles;
-        a.poff64[p] = (int)floats64;
-        tiles += (long long)(a.Kp / 64) * a.nlt[p];
-        floats64 += (long long)a.Kp * a.nlt[p];
+    // The planes of dM that differ by more than sign, and which of them each plane uses
+    int dmp[kMaxPlanes];
+    bp->dm_table = PlaneTable{};
+    for (int p = 0; p < fwd->planes.n; ++p) {
+        const int own = fwd->planes.e[p].coef;
+        int first = 0, flipped = 0, idx = 0;
+        for (int q = 0; q < 4; ++q) {
+            const int cq = (own >> (2 * q)) & 3;
+            if (first == 0) first = cq;
+            flipped |= (cq == 0 ? 0 : cq == 1 ? 3 : 1) << (2 * q);
+        }
+        const int coef = first == 3 ? flipped : own;
+        while (idx < bp->dm_table.n && bp->dm_table.e[idx].coef != coef) ++idx;
+        if (idx == bp->dm_table.n) bp->dm_table.e[bp->dm_table.n++].coef = coef;
+        dmp[p] = idx | (first == 3 ? 256 : 0) | own << 16;
     }
-    a.tile0[a.n_planes] = (int)tiles;
-    a.n_tiles = (int)tiles;
-    a.split_floats = floats64 * 64;
-    // How many ranges the tile axis is cut into.  The chip holds 2 workgroups per CU at a time, so
-    // the launch runs in ceil(tiles*splits / 512) rounds of ceil(tblocks/splits) chunks each
-    // (2.1 us per chunk-round measured: two workgroups share a CU's matrix cores), and every range
-    // writes a partial dU that is read back once (priced at 4 TB/s).  Never fewer than four blocks
-    // of tiles per range.
-    long long splits = 1;
-    {
+    // The GEMM's geometry for output tiles of `tile` filters x `tile` rows, and how many ranges the tile axis is cut
+    // into; *us: its time by the model.  The chip holds 2 workgroups per CU at a time, so the launch runs in
+    // ceil(tiles*splits / 512) rounds of ceil(tblocks/splits) blocks of 64 tiles each (block_us with both, lone_us where
+    // the last round leaves one to a CU), and every range writes a partial dU that is read back once (priced at 4 TB/s).
+    // Never fewer than four blocks of tiles per range.
+    auto geometry = [&](int tile, double block_us, double lone_us, WgradArgs& a, double* us) {
+        a = WgradArgs{};
+        a.K = K; a.Kp = (K + tile - 1) / tile * tile; a.T = d.T; a.tblocks = (d.T + 63) / 64;
+        a.n_planes = fwd->planes.n;
+        for (int p = 0; p < a.n_planes; ++p) a.dmp[p] = dmp[p];
+        a.n_dm = bp->dm_table.n;
+        a.dm_rows = a.n_dm * a.Kp;
+        a.vblock_rows = d.vblock_rows;
+        long long tiles = 0, floats64 = 0;
+        for (int c = 0; c < d.ncls; ++c)
+            for (int i = 0; i < (d.cls[c].lh + 1) * (d.cls[c].lw + 1); ++i) {
+                const int p = d.cls[c].plane0 + i;
+                const DevPlaneEntry& e = fwd->planes.e[p];
+                a.nlt[p] = (e.Lpad + tile - 1) / tile;
+                a.lreal[p] = d.cls[c].L;
+                a.lstride[p] = a.nlt[p] * tile;
+                a.vrow[p] = (int)e.v_off64;
+                a.tile0[p] = (int)tiles;
+                a.poff64[p] = (int)floats64;
+                tiles += (long long)(a.Kp / tile) * a.nlt[p];
+                floats64 += (long long)a.Kp * a.lstride[p] / 64;
+            }
+        a.tile0[a.n_planes] = (int)tiles;
+        a.n_tiles = (int)tiles;
+        a.split_floats = floats64 * 64;
+        long long splits = 1;
         const long long max_splits = std::max(1LL, std::min<long long>(32, (a.tblocks + 3) / 4));
         const double partial_us = 2.0 * (double)floats64 * 64 * sizeof(float) / 4e6;
-        double best = 0.0;
         for (long long sp = 1; sp <= max_splits; ++sp) {
-            const long long rounds = (tiles * sp + 2 * kNumCUs - 1) / (2 * kNumCUs);
+            const long long wgs = tiles * sp, full = wgs / (2 * kNumCUs), rest = wgs - full * 2 * kNumCUs;
             const long long chunks = (a.tblocks + sp - 1) / sp;
-            const double t = 2.1 * (double)(rounds * chunks) + partial_us * (double)sp;
-            if (sp == 1 || t < best * 0.97) {  // a further cut must pay for itself clearly
-                best = t;
+            const double t = (block_us * (double)full + (rest > kNumCUs ? block_us : rest > 0 ? lone_us : 0.0)) * (double)chunks +
+                             partial_us * (double)sp;
+            if (sp == 1 || t < *us * 0.97) {  // a further cut must pay for itself clearly
+                *us = t;
                 splits = sp;
             }
         }
-    }
-    a.chunks_per_split = (int)((a.tblocks + splits - 1) / splits);
-    a.splits = (a.tblocks + a.chunks_per_split - 1) / a.chunks_per_split;
-    const long long lim = (1LL << 31) - 1;
-    if (tiles * a.splits > lim || a.split_floats > lim * 16 || (long long)a.tblocks * a.dm_rows > lim) {
+        a.chunks_per_split = (int)((a.tblocks + splits - 1) / splits);
+        a.splits = (a.tblocks + a.chunks_per_split - 1) / a.chunks_per_split;
+        const long long lim = (1LL << 31) - 1;
+        return tiles * a.splits <= lim && a.split_floats <= lim * 16 && (long long)a.tblocks * a.dm_rows <= lim;
+    };
+    WgradArgs& a = bp->a;
+    double us = 0.0;
+    if (!geometry(64, 2.1, 2.1, a, &us)) {
         dwm_plan_destroy(fwd);
         delete bp;
         return DWM_ERR_UNSUPPORTED;
     }
-    // V, then 64 rows of slack (the last plane's 64-row tile may overhang its rows), dM, partial dU
-    bp->fwd_ws_bytes = (dwm_plan_workspace_bytes(fwd) + (size_t)64 * 64 * sizeof(float) + 255) / 256 * 256;
+    // V, then 128 rows of slack (the last plane's last tile may overhang its rows), dM, partial dU
+    bp->fwd_ws_bytes = (dwm_plan_workspace_bytes(fwd) + (size_t)128 * 64 * sizeof(float) + 255) / 256 * 256;
     bp->dm_bytes = ((size_t)a.tblocks * a.dm_rows * 64 * sizeof(float) + 255) / 256 * 256;
     bp->partial_bytes = (size_t)a.splits * a.split_floats * sizeof(float);
     bp->sum_bytes = 0;
+    bp->split = false;
     bp->small = small_setup(*bp, small_max_rows);
+    // The GEMM on the bfloat16 matrix cores: output tiles of 128x128, a block of 64 tiles takes 5.2 us with two workgroups
+    // on a CU and 3.2 with one; dM is written at 4.3 TB/s (six bytes an element; the fp32 form's at 4.5, four bytes).
+    // Measured, whole gradient, fp32 GEMM -> here (dM shared between planes in both): 7x7 256->256 28x28 N=32 860 -> 703 us,
+    // 3x3 stride 2 128->256 56x56 N=32 165 -> 133, 5x5 128->128 28x28 N=256 1090 -> 915, 9x9 256->256 14x14 N=32
+    // 335 -> 275; the same within 2 % on 3x3 128->128 28x28 N=64, which stays with the fp32 GEMM.
+    WgradArgs as;
+    double split_us = 0.0;
+    if (!bp->small && K > 64 && geometry(kWsplitTile, 5.2, 3.2, as, &split_us) &&
+        split_us + 1.4e-6 * (double)as.tblocks * as.dm_rows * 64 < us + 0.9e-6 * (double)a.tblocks * a.dm_rows * 64) {
+        bp->split = true;
+        a = as;
+        bp->dm_bytes = (size_t)a.tblocks * a.dm_rows * 384;
+        bp->partial_bytes = (size_t)a.splits * a.split_floats * sizeof(float);
+        // (many ranges: a kernel of its own adds them up, element by element on the whole chip)
+        if (a.splits >= 3) bp->sum_bytes = ((size_t)a.split_floats * sizeof(float) + 255) / 256 * 256;
+    }
     *out = bp;
     return DWM_OK;
 }
@@ -890,7 +919,8 @@ dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan, const f
     dwm_status_t st = dwm_input_transform(plan->fwd, x_dev, stream);
     if (st != DWM_OK) return st;
     if (d.T & 63) {
-        hipLaunchKernelGGL(wgrad_zero_tail_kernel, dim3(64), dim3(256), 0, s,
+        const size_t tail = (size_t)a.vblock_rows * (64 - (d.T & 63));
+        hipLaunchKernelGGL(wgrad_zero_tail_kernel, dim3((unsigned)std::min<size_t>((tail + 255) / 256, 4096)), dim3(256), 0, s,
                            V + (size_t)(a.tblocks - 1) * a.vblock_rows * 64, a.vblock_rows, d.T & 63);
     }
     if (plan->small) {
@@ -916,11 +946,26 @@ dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan, const f
     }
     // 2. dM = A dY A^T
     const DyShape ds{d.T, d.K, a.Kp, d.TH, d.TW, d.OH, d.OW, a.dm_rows};
+    if (plan->split) {  // (and 3.)
+        st = launch_wgrad_split(a, ds, plan->dm_table, dy_dev, V, reinterpret_cast<unsigned char*>(dM), partial, s);
+        if (st != DWM_OK) return st;
+        if (plan->sum_bytes > 0) {
+            float* sum = partial + plan->partial_bytes / sizeof(float);
+            hipLaunchKernelGGL(wgrad_reduce_kernel, dim3((unsigned)((a.split_floats + 255) / 256)), dim3(256), 0, s, partial,
+                               sum, a.split_floats, a.splits);
+            WgradArgs fa = a;
+            fa.splits = 1;
+            launch_final(d, fa, sum, dw_dev, s);
+        } else {
+            launch_final(d, a, partial, dw_dev, s);
+        }
+        return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
+    }
     if (d.OW % 4 == 0 && (reinterpret_cast<uintptr_t>(dy_dev) & 15) == 0) {
-        hipLaunchKernelGGL(wgrad_dy_transform2_kernel, dim3(a.tblocks, a.Kp / 8), dim3(256), 0, s, ds, plan->fwd->planes,
+        hipLaunchKernelGGL(wgrad_dy_transform2_kernel, dim3(a.tblocks, a.Kp / 8), dim3(256), 0, s, ds, plan->dm_table,
                            dy_dev, dM);
     } else {
-        hipLaunchKernelGGL(wgrad_dy_transform_kernel, dim3(a.tblocks, a.Kp / 4), dim3(256), 0, s, ds, plan->fwd->planes,
+        hipLaunchKernelGGL(wgrad_dy_transform_kernel, dim3(a.tblocks, a.Kp / 4), dim3(256), 0, s, ds, plan->dm_table,
                            dy_dev, dM);
     }
     // 3. partial dU

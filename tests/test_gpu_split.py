@@ -7,6 +7,7 @@ import torch
 import oracle
 import paper_2002_00552_amd as dwm
 from dwm_gpu import Runner
+from test_gpu_backward import WgradRunner
 
 pytestmark = pytest.mark.gpu
 
@@ -136,3 +137,82 @@ def test_chosen_variants_still_run_the_fp32_contraction():
         assert dwm.dwm_plan_workspace_bytes(p) == own
     finally:
         dwm.dwm_plan_destroy(p)
+
+
+# ---- the filter gradient's GEMM on the bfloat16 matrix cores ----
+# layers that the planner gives to it: odd and even outputs, filters past 64 and past 128, one to three ranges of tiles,
+# strides 1 and 2, pieces of one, two and three taps, a last block of tiles that is nearly empty
+WGRAD_SHAPES = [
+    (14, 200, 27, 14, 88, 7, 7, 2, 1),
+    (8, 128, 20, 18, 209, 4, 4, 1, 1),
+    (3, 198, 12, 18, 196, 5, 5, 1, 2),
+    (25, 297, 31, 17, 79, 4, 4, 2, 1),
+    (7, 300, 14, 23, 261, 3, 3, 2, 2),
+]
+
+
+def _wgrad(shape, x, dy):
+    r = WgradRunner(*shape)
+    try:
+        return r.run(x, dy)
+    finally:
+        r.close()
+
+
+def _wgrad_tiles(shape, tile):
+    p = dwm.dwm_plan_create(*shape)
+    cls = [dwm.dwm_plan_class(p, i) for i in range(dwm.dwm_plan_info(p).n_classes)]
+    dwm.dwm_plan_destroy(p)
+    return sum((c.len_h + 1) * (c.len_w + 1) * -(-shape[4] // tile) * -(-c.Lpad // tile) for c in cls)
+
+
+def _wgrad_data(shape, seed):
+    x, _ = _data(shape, seed)
+    N, C, H, W, K, R, S, s, P = shape
+    OH, OW = (H + 2 * P - R) // s + 1, (W + 2 * P - S) // s + 1
+    return x, np.random.default_rng(seed + 100).standard_normal((N, K, OH, OW)).astype(np.float32)
+
+
+@pytest.mark.parametrize("shape", WGRAD_SHAPES)
+def test_filter_gradient_on_bf16_matrix_cores(shape):
+    """Against FP64, every tap of dw: 1e-6 of the largest (sums of up to 6000 products in at most 64 roundings a run of
+    1024; 2e-7 to 4e-7 measured in the 2-norm), repeats bit for bit."""
+    g = dwm.dwm_bwd_filter_plan_create(*shape)
+    n = dwm.dwm_bwd_filter_plan_info(g).n_tiles
+    dwm.dwm_bwd_filter_plan_destroy(g)
+    assert n == _wgrad_tiles(shape, 128) != _wgrad_tiles(shape, 64)
+    x, dy = _wgrad_data(shape, 7)
+    N, C, H, W, K, R, S, s, P = shape
+    dw = _wgrad(shape, x, dy)
+    ref = oracle.backward_filter_f64(x, dy, (K, C, R, S), s, P)
+    assert np.max(np.abs(dw - ref)) / np.max(np.abs(ref)) <= 2e-6
+    assert np.linalg.norm(dw - ref) / np.linalg.norm(ref) <= 1e-6
+    assert np.array_equal(_wgrad(shape, x, dy), dw)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("where", ["x", "dy"])
+def test_filter_gradient_values_the_split_cannot_carry(where, value):
+    """One such value in x or in dy: what it reaches is not finite where it is not (every tap of its channel, or of its
+    filter, through the transforms), everything else is exact, and a finite one stays finite."""
+    shape = WGRAD_SHAPES[1]
+    N, C, H, W, K, R, S, s, P = shape
+    x, dy = _wgrad_data(shape, 8)
+    a, other = (x, dy) if where == "x" else (dy, x)
+    other *= np.float32(1e-3)
+    a[1, 5, 7, 9] = value
+    dw = _wgrad(shape, x, dy)
+    reach = np.zeros((K, C), bool)
+    reach[:, 5] = where == "x"
+    if where == "dy":
+        reach[5, :] = True
+    ref = oracle.backward_filter_f64(np.where(np.isfinite(x), x, 0).astype(np.float32),
+                                     np.where(np.isfinite(dy), dy, 0).astype(np.float32), (K, C, R, S), s, P)
+    assert np.all(np.isfinite(dw[~reach]))
+    assert np.max(np.abs(dw[~reach] - ref[~reach])) <= 4e-6 * np.max(np.abs(ref[~reach]))
+    if np.isfinite(value):
+        assert np.all(np.isfinite(dw))
+        assert np.max(np.abs(dw[reach] - ref[reach])) <= 4e-6 * np.max(np.abs(ref[reach]))
+    else:
+        # the tap that multiplies the value directly, where it has one, is never finite
+        assert not np.any(np.all(np.isfinite(dw[reach]), axis=(1, 2)))
