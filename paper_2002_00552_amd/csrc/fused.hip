@@ -127,10 +127,11 @@ __device__ __forceinline__ float2 fused_load_a(__amdgpu_buffer_rsrc_t rsrc, unsi
     return make_float2(v.x, v.y);
 }
 
-__device__ __forceinline__ void fused_mfma(float2 a, float bv, floatx4 (&acc)[2])
+template <int HALVES>
+__device__ __forceinline__ void fused_mfma(float2 a, float bv, floatx4 (&acc)[HALVES])
 {
     acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, bv, acc[0], 0, 0, 0);
-    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, bv, acc[1], 0, 0, 0);
+    if (HALVES == 2) acc[HALVES - 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, bv, acc[HALVES - 1], 0, 0, 0);
 }
 
 // A^T of the family: four frequencies (F(2,3), Sec. 3.2) or two (identity).
@@ -147,12 +148,13 @@ __device__ __forceinline__ void fused_at(const floatx4 m[4], floatx4 o[2])
 }
 
 // Y[a][b][half] += sum AT_h[a][fh] AT_w[b][fw] acc[fh][fw][half]
-template <int WH, int WW, bool ADD>
-__device__ __forceinline__ void fused_output(const floatx4 (&acc)[WH ? 4 : 2][WW ? 4 : 2][2], floatx4 (&Y)[2][2][2])
+template <int WH, int WW, bool ADD, int HALVES>
+__device__ __forceinline__ void fused_output(const floatx4 (&acc)[WH ? 4 : 2][WW ? 4 : 2][HALVES],
+                                             floatx4 (&Y)[2][2][HALVES])
 {
     constexpr int NH = WH ? 4 : 2, NW = WW ? 4 : 2;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (int half = 0; half < HALVES; ++half) {
         floatx4 t[NH][2];  // [fh][b]
 #pragma unroll
         for (int fh = 0; fh < NH; ++fh) {
@@ -219,16 +221,16 @@ __device__ __forceinline__ void fused_read_patch_pairs(const float* __restrict__
 // previous slice: the last step fetches the first step's operands of the slice at soff_next.  A
 // slice's loads are then older than the previous slice's stores to y, so that waiting for them
 // (the counter of vector-memory operations runs in issue order) does not wait for those stores.
-// ADD: the class's output is added to Y; otherwise it is stored there.
-template <int WH, int WW, bool PAIRS, bool ADD>
+// ADD: the class's output is added to Y; otherwise it is stored there.  HALVES: 1 where the layer has at most 16 filters.
+template <int WH, int WW, bool PAIRS, bool ADD, int HALVES>
 __device__ __forceinline__ void fused_class(const FusedArgs& F, const FusedClass& fc, const float* __restrict__ xt,
                                          const int4* __restrict__ ri, __amdgpu_buffer_rsrc_t rsrc, unsigned soff,
                                          unsigned soff_next, unsigned voff, float2 (&a)[WH ? 4 : 2][WW ? 4 : 2],
-                                         float (&d0)[WH ? 4 : 2][WW ? 4 : 2], floatx4 (&Y)[2][2][2])
+                                         float (&d0)[WH ? 4 : 2][WW ? 4 : 2], floatx4 (&Y)[2][2][HALVES])
 {
     constexpr int NH = WH ? 4 : 2, NW = WW ? 4 : 2;
     static_assert(!PAIRS || (WH && WW), "pairs of adjacent words: four-column patches only");
-    floatx4 acc[NH][NW][2];  // never cleared: the first step multiplies into zero
+    floatx4 acc[NH][NW][HALVES];  // never cleared: the first step multiplies into zero
     const unsigned plane_bytes = (unsigned)fc.rows * 32u * (unsigned)sizeof(float);
     // A operands travel one step ahead: a plane's registers are refilled for the next step as
     // soon as its MFMAs of this step are issued (the last step refills with itself, or with the next
@@ -254,9 +256,10 @@ __device__ __forceinline__ void fused_class(const FusedArgs& F, const FusedClass
     auto mfma = [&](auto first_tag, int i, int j, float bv, bool on) {
         if constexpr (decltype(first_tag)::value) {
             acc[i][j][0] = on ? __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j].x, bv, zero4, 0, 0, 0) : zero4;
-            acc[i][j][1] = on ? __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j].y, bv, zero4, 0, 0, 0) : zero4;
+            if (HALVES == 2)
+                acc[i][j][HALVES - 1] = on ? __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j].y, bv, zero4, 0, 0, 0) : zero4;
         } else {
-            if (on) fused_mfma(a[i][j], bv, acc[i][j]);
+            if (on) fused_mfma<HALVES>(a[i][j], bv, acc[i][j]);
         }
     };
     auto step = [&](auto first_tag, int st, const float (&d)[NH][NW], float (&dn)[NH][NW]) {
@@ -325,13 +328,15 @@ __device__ __forceinline__ void fused_class(const FusedArgs& F, const FusedClass
 #pragma unroll
             for (int j = 0; j < NW; ++j) d0[i][j] = d1[i][j];
     }
-    fused_output<WH, WW, ADD>(acc, Y);
+    fused_output<WH, WW, ADD, HALVES>(acc, Y);
 }
 
 // MULTI: the layer has more than one class, so their outputs are summed in Y; with a single
 // class (no one-tap pieces) the registers of Y are saved: the class's output is the result.
 // PAIRS (single class of two- and three-tap pieces): patch rows are read as pairs of adjacent words.
-template <bool MULTI, bool PAIRS>
+// SHARE: the four waves have the same 16 tiles, a quarter of every class's steps each; the output transform is linear, so
+// each transforms what it has, and the outputs are added in LDS (in wave order).
+template <bool MULTI, bool PAIRS, bool SHARE, int HALVES>
 __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedArgs F, const float* __restrict__ x,
                                                             const float* __restrict__ U, float* __restrict__ y)
 {
@@ -339,7 +344,8 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
     // LDS: per-row patch offsets | staged input
     constexpr int RI = PAIRS ? 2 : 4;
     int4* rowinfo = reinterpret_cast<int4*>(lds);  // [rows_total][4]: byte offsets [i][j]; PAIRS: [rows_total][2]: [j][i]
-    float* xs = reinterpret_cast<float*>(rowinfo + RI * F.rows_total);  // [C][nrows][nphase][lwp]
+    floatx4* ysum = reinterpret_cast<floatx4*>(rowinfo + RI * F.rows_total);  // SHARE: [wave][a][b][half][lane]
+    float* xs = reinterpret_cast<float*>(rowinfo + RI * F.rows_total) + (SHARE ? kFusedShareBytes / 4 : 0);  // [C][nrows][nphase][lwp]
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -377,17 +383,31 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
     const int slice0 = blockIdx.y * F.slices_per_wg;
     const int slice1 = min(slice0 + F.slices_per_wg, F.nslices);
     const unsigned voff = (unsigned)lane * 8u;
-    const FusedClass fc0 = F.fc[0];
+    // SHARE: this wave's steps of a class; how many of the class's come before them
+    auto mine = [&](FusedClass& fc) {
+        if (!SHARE) return 0;
+        const int per = (fc.nsteps + 3) / 4, s0 = wave * per;
+        const int n = min(per, fc.nsteps - s0);
+        if (n <= 0) {
+            fc.nsteps = 0;
+            return 0;
+        }
+        fc.step0 += s0;
+        fc.nsteps = n;
+        return s0;
+    };
+    FusedClass fc0 = F.fc[0];
     const __amdgpu_buffer_rsrc_t rsrc0 = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float*>(U + fc0.uf_off), 0, (int)((unsigned)(fc0.nfh * fc0.nfw * fc0.rows) * 128u * (unsigned)F.nslices),
         0x00020000);
+    const int before0 = mine(fc0);
     float2 a0[4][4];
     if constexpr (PAIRS) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                a0[i][j] = fused_load_a(rsrc0, voff, (unsigned)(slice0 * 16 + i * 4 + j) * ((unsigned)fc0.rows * 128u));
+                a0[i][j] = fused_load_a(rsrc0, voff, (unsigned)(slice0 * 16 + i * 4 + j) * ((unsigned)fc0.rows * 128u) + before0 * 512u);
     }
 
     // ---- 1. stage the block's input region (padded coordinates).  A unit is (channel, 8 rows);
@@ -435,7 +455,7 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
     __syncthreads();
 
     // this lane's tile: number wave*16 + ln of the block (idle lanes reuse tile 0 and store nothing)
-    const int tl = wave * 16 + ln;
+    const int tl = (SHARE ? 0 : wave * 16) + ln;
     const int by = F.div_bw.div(tl), bx = tl - by * F.BW;
     const int ty = ty0 + by, tx = tx0 + bx;
     const bool tile_ok = by < F.BH && ty < P.TH && tx < P.TW;
@@ -448,48 +468,53 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
     const unsigned yoff0 = (unsigned)(((lq * 4) * P.OH + oh) * P.OW + ow) * 4u, yoff1 = yoff0 + (unsigned)P.OW * 4u;
     const bool row1 = oh + 1 < P.OH;
     float p0[4][4];
-    if constexpr (PAIRS) fused_read_patch_pairs(xt, rowinfo + 2 * lq, p0);
+    if constexpr (PAIRS) fused_read_patch_pairs(xt, rowinfo + 2 * lq + 8 * before0, p0);
     for (int ks = slice0; ks < slice1; ++ks) {
-        floatx4 Y[2][2][2];
-        if (MULTI) {
+        floatx4 Y[2][2][HALVES];
+        if (MULTI || SHARE) {
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) Y[a][c][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    for (int h = 0; h < HALVES; ++h) Y[a][c][h] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
 
         if constexpr (PAIRS) {
             const unsigned sbytes = 16u * (unsigned)fc0.rows * 128u;  // one slice of the filter copy
-            fused_class<1, 1, true, false>(F, fc0, xt, rowinfo + 2 * lq, rsrc0, (unsigned)ks * sbytes,
-                                           (unsigned)(ks + 1 < slice1 ? ks + 1 : ks) * sbytes, voff, a0, p0, Y);
+            if (!SHARE || fc0.nsteps > 0)
+                fused_class<1, 1, true, false, HALVES>(F, fc0, xt, rowinfo + 2 * lq + 8 * before0, rsrc0,
+                                                       (unsigned)ks * sbytes + before0 * 512u,
+                                                       (unsigned)(ks + 1 < slice1 ? ks + 1 : ks) * sbytes + before0 * 512u,
+                                                       voff, a0, p0, Y);
         } else {
             for (int fi = 0; fi < (MULTI ? F.nfc : 1); ++fi) {
-                const FusedClass fc = F.fc[fi];
+                FusedClass fc = F.fc[fi];
                 const unsigned sbytes = (unsigned)(fc.nfh * fc.nfw * fc.rows) * 128u;
                 const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                     const_cast<float*>(U + fc.uf_off), 0, (int)(sbytes * (unsigned)F.nslices), 0x00020000);
-                const int4* ri = rowinfo + 4 * (fc.row0 + lq);
-                const unsigned so = (unsigned)ks * sbytes;
+                const int before = mine(fc);
+                if (SHARE && fc.nsteps == 0) continue;
+                const int4* ri = rowinfo + 4 * (fc.row0 + lq) + 16 * before;
+                const unsigned so = (unsigned)ks * sbytes + before * 512u;
                 if (fc.wide_h) {
                     float2 a[4][4];
                     float d[4][4];
-                    if (fc.wide_w) fused_class<1, 1, false, MULTI>(F, fc, xt, ri, rsrc, so, so, voff, a, d, Y);
+                    if (fc.wide_w) fused_class<1, 1, false, MULTI, HALVES>(F, fc, xt, ri, rsrc, so, so, voff, a, d, Y);
                     else {
                         float2 a2[4][2];
                         float d2[4][2];
-                        fused_class<1, 0, false, MULTI>(F, fc, xt, ri, rsrc, so, so, voff, a2, d2, Y);
+                        fused_class<1, 0, false, MULTI, HALVES>(F, fc, xt, ri, rsrc, so, so, voff, a2, d2, Y);
                     }
                 } else {
                     if (fc.wide_w) {
                         float2 a2[2][4];
                         float d2[2][4];
-                        fused_class<0, 1, false, MULTI>(F, fc, xt, ri, rsrc, so, so, voff, a2, d2, Y);
+                        fused_class<0, 1, false, MULTI, HALVES>(F, fc, xt, ri, rsrc, so, so, voff, a2, d2, Y);
                     } else {
                         float2 a2[2][2];
                         float d2[2][2];
-                        fused_class<0, 0, false, MULTI>(F, fc, xt, ri, rsrc, so, so, voff, a2, d2, Y);
+                        fused_class<0, 0, false, MULTI, HALVES>(F, fc, xt, ri, rsrc, so, so, voff, a2, d2, Y);
                     }
                 }
             }
@@ -500,11 +525,36 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
         // number depends on the lane's tile and filters, so the compiler cannot count past them) would wait for
         // the stores' round trip as well.
         if constexpr (PAIRS) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), nothing else
+        if constexpr (SHARE) {
+#pragma unroll
+            for (int i = 0; i < 4 * HALVES; ++i) ysum[(wave * 4 * HALVES + i) * 64 + lane] = Y[(i / HALVES) >> 1][(i / HALVES) & 1][i % HALVES];
+            __syncthreads();
+            // wave w adds up and stores output row w % 2 of filter half w / 2
+            const int a = wave & 1, half = wave >> 1;
+            if (half < HALVES && tile_ok && oh + a < P.OH) {
+                floatx4 o[2];
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) {
+                    const floatx4* src = ysum + ((a * 2 + b2) * HALVES + half) * 64 + lane;
+                    o[b2] = ((src[0] + src[4 * HALVES * 64]) + src[8 * HALVES * 64]) + src[12 * HALVES * 64];
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k = ks * 32 + half * 16 + lq * 4 + r;
+                    if (k >= P.K) continue;
+                    float* yp = y + (((size_t)n * P.K + k) * P.om.YH + (size_t)(P.om.sy * (oh + a) + P.om.oy)) * P.om.YW +
+                                (P.om.sx * ow + P.om.ox);
+                    yp[0] = o[0][r];
+                    if (ow + 1 < P.OW) yp[P.om.sx] = o[1][r];
+                }
+            }
+            continue;
+        }
         // ---- scatter: lane (ln, lq) holds tile ln and filters 32*ks + 16*half + 4*lq + r ----
         if (tile_ok) {
             if (dense) {
 #pragma unroll
-                for (int half = 0; half < 2; ++half)
+                for (int half = 0; half < HALVES; ++half)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int ku = ks * 32 + half * 16 + r;  // + 4*lq is in the lane's offsets
@@ -518,7 +568,7 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
                     }
             } else {
 #pragma unroll
-                for (int half = 0; half < 2; ++half)
+                for (int half = 0; half < HALVES; ++half)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int k = ks * 32 + half * 16 + lq * 4 + r;
@@ -545,19 +595,24 @@ dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float
 {
     if (!p.fused_ok) return DWM_ERR_INVALID_ARG;
     const FusedArgs& f = p.fused;
-    auto kernel = f.nfc > 1 ? fused_forward_kernel<true, false>
-                            : f.wide ? fused_forward_kernel<false, true> : fused_forward_kernel<false, false>;
+    using Kernel = void (*)(DevPlan, FusedArgs, const float*, const float*, float*);
+    static const Kernel kernels[9] = {
+        fused_forward_kernel<true, false, false, 2>,  fused_forward_kernel<false, true, false, 2>,
+        fused_forward_kernel<false, false, false, 2>, fused_forward_kernel<true, false, true, 2>,
+        fused_forward_kernel<false, true, true, 2>,   fused_forward_kernel<false, false, true, 2>,
+        fused_forward_kernel<true, false, true, 1>,   fused_forward_kernel<false, true, true, 1>,
+        fused_forward_kernel<false, false, true, 1>,
+    };
+    const Kernel kernel = kernels[(f.nfc > 1 ? 0 : f.wide ? 1 : 2) + (!f.share ? 0 : p.d.K > 16 ? 3 : 6)];
     if (f.lds_bytes > 64 * 1024) {
         // once for each instantiation, whichever of them the first plan happens to use
         static const hipError_t attr = [] {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_forward_kernel<true, false>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_forward_kernel<false, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(fused_forward_kernel<false, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            for (Kernel k : kernels) {
+                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+                if (e != hipSuccess) return e;
+            }
+            return hipSuccess;
         }();
         if (attr != hipSuccess) return DWM_ERR_HIP;
     }

@@ -187,6 +187,7 @@ struct FastDiv {
 // rows (part, channel) are padded to a multiple of four, the reduction depth of one MFMA step.
 constexpr int kFusedMaxSteps = 64;
 constexpr int kFusedMaxRows = 4 * kFusedMaxSteps;
+constexpr int kFusedShareBytes = 32 * 1024;  // four waves' outputs of 16 tiles x 32 filters
 struct FusedClass {
     int wide_h, wide_w;  // 1: pieces of 2 or 3 taps (four frequencies), 0: one-tap pieces (two)
     int nfh, nfw;        // frequencies per dimension: 4 or 2
@@ -201,6 +202,7 @@ struct FusedArgs {
     int tile_row_step;              // LDS floats between vertically adjacent tiles' patches
     int nslices;                    // ceil(K / 32)
     int slices_per_wg, nkw;         // K slices per workgroup, workgroups along K
+    int share;                      // 1: a block is 16 tiles, and a workgroup's four waves share it, a quarter of the steps each
     int wide;                       // 1: one class of two- and three-tap pieces only: patch rows are read as
                                     // pairs of adjacent words and operands are carried from slice to slice
     int nfc, rows_total;

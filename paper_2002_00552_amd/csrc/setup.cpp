@@ -74,35 +74,58 @@ bool fused_setup(const dwm_plan& p, FusedArgs* out)
     const size_t table_bytes = (size_t)rows * 64;
     const size_t budget = 72 * 1024;  // two workgroups per CU
 
-    // block of tiles: most useful lanes first, then the smallest staged region
+    // block of `lanes` tiles: most useful lanes first, then the smallest staged region
     double best_eff = 0.0;
     size_t best_x = 0;
-    for (int bw = 1; bw <= 64 && bw <= d.TW; ++bw) {
-        int bh = 64 / bw;
-        if (bh > d.TH) bh = d.TH;
-        if (bh < 1) continue;
-        const int nbh = (d.TH + bh - 1) / bh, nbw = (d.TW + bw - 1) / bw;
-        const double eff = (double)d.TH * d.TW / ((double)nbh * nbw * 64);
-        const long long nrows = 2LL * d.s * (bh - 1) + max_oh + 1;
-        const long long lw_in = 2LL * d.s * (bw - 1) + max_ow + 1;
-        const long long lwp = ((lw_in + f.nphase - 1) / f.nphase) | 1;
-        const long long x_bytes = (long long)d.C * nrows * f.nphase * lwp * (long long)sizeof(float);
-        if (x_bytes + (long long)table_bytes > (long long)budget) continue;
-        if (eff > best_eff + 1e-9 || (eff > best_eff - 1e-9 && (size_t)x_bytes < best_x)) {
-            best_eff = eff; best_x = (size_t)x_bytes;
-            f.BH = bh; f.BW = bw; f.nbh = nbh; f.nbw = nbw;
-            f.nrows = (int)nrows; f.lw_in = (int)lw_in; f.lwp = (int)lwp;
+    auto choose_block = [&](int lanes, size_t limit) {
+        best_eff = 0.0;
+        best_x = 0;
+        for (int bw = 1; bw <= lanes && bw <= d.TW; ++bw) {
+            int bh = lanes / bw;
+            if (bh > d.TH) bh = d.TH;
+            if (bh < 1) continue;
+            const int nbh = (d.TH + bh - 1) / bh, nbw = (d.TW + bw - 1) / bw;
+            const double eff = (double)d.TH * d.TW / ((double)nbh * nbw * lanes);
+            const long long nrows = 2LL * d.s * (bh - 1) + max_oh + 1;
+            const long long lw_in = 2LL * d.s * (bw - 1) + max_ow + 1;
+            const long long lwp = ((lw_in + f.nphase - 1) / f.nphase) | 1;
+            const long long x_bytes = (long long)d.C * nrows * f.nphase * lwp * (long long)sizeof(float);
+            if (x_bytes + (long long)table_bytes > (long long)limit) continue;
+            if (eff > best_eff + 1e-9 || (eff > best_eff - 1e-9 && (size_t)x_bytes < best_x)) {
+                best_eff = eff; best_x = (size_t)x_bytes;
+                f.BH = bh; f.BW = bw; f.nbh = nbh; f.nbw = nbw;
+                f.nrows = (int)nrows; f.lw_in = (int)lw_in; f.lwp = (int)lwp;
+            }
+        }
+    };
+    choose_block(64, budget);
+    if (best_eff < 0.5) return false;
+    long long blocks = (long long)d.N * f.nbh * f.nbw;
+    if (blocks > 0x7fffffffLL) return false;
+    f.nslices = (d.K + 31) / 32;
+    // A handful of blocks: the time is one wave's walk through all the steps, on an idle chip.  Up to half a workgroup per
+    // CU a block is 16 tiles instead of 64, and the workgroup's four waves take a quarter of the steps each and add up
+    // their outputs in LDS (5x5 over 16 channels, one 32x32 image: 4 workgroups of 16 steps a wave 20.8 us, 16 of 4 steps 12.1;
+    // 9x9 over 12 channels, 19x17: 30.5 -> 14.3; 7x7 stride 2 over 3 channels, 224x224: 12.0 -> 11.3).
+    size_t sum_bytes = 0;
+    if (blocks * f.nslices * 2 <= kNumCUs && steps >= 4) {
+        const FusedArgs whole = f;
+        const size_t whole_x = best_x;
+        choose_block(16, budget - kFusedShareBytes);
+        f.share = best_eff > 0.0;
+        if (!f.share) {
+            f = whole;
+            best_x = whole_x;
+        } else {
+            blocks = (long long)d.N * f.nbh * f.nbw;
+            sum_bytes = kFusedShareBytes;
         }
     }
-    if (best_eff < 0.5) return false;
-    const long long blocks = (long long)d.N * f.nbh * f.nbw;
-    if (blocks > 0x7fffffffLL) return false;
     f.row_floats = f.nphase * f.lwp;
     f.chan_floats = f.nrows * f.row_floats;
     f.tile_row_step = 2 * d.s * f.row_floats;
-    f.nslices = (d.K + 31) / 32;
     // with few blocks the filter slices are spread over workgroups as well
-    f.slices_per_wg = blocks >= 2 * kNumCUs ? f.nslices : 1;
+    f.slices_per_wg = blocks >= 2 * kNumCUs && !f.share ? f.nslices : 1;
     f.nkw = (f.nslices + f.slices_per_wg - 1) / f.slices_per_wg;
     if (f.nkw > 65535) return false;
     f.div_bw.init((unsigned)f.BW);
@@ -120,7 +143,7 @@ bool fused_setup(const dwm_plan& p, FusedArgs* out)
         }
     for (int i = 0; i < d.nw; ++i)  // columns two apart are one word apart in a de-interleaved row
         if (f.wide && (f.coff[i][2] != f.coff[i][0] + 1 || f.coff[i][3] != f.coff[i][1] + 1)) return false;
-    f.lds_bytes = table_bytes + best_x;
+    f.lds_bytes = table_bytes + sum_bytes + best_x;
     *out = f;
     return true;
 }
