@@ -50,18 +50,21 @@ __device__ __forceinline__ float bs_g_row(int i, float v0, float v1, float v2)
 // Filter copy UB[chunk][column block][step][plane, lane]: the A operands exactly as a chunk
 // lies in LDS (a chunk padded to whole KB; the padding is copied and never read).  Lane (i, q)
 // of a step holds column 16*cb + i and the step's row q; the rows of a chunk are (pair of
-// pieces, channel of the chunk).  One thread per (column, channel, pair).
+// pieces, channel of the chunk).  One thread per (column, channel, pair); 128x128 filters of
+// 3x3 take 8.5 us (12.2 with the pairs fastest and every plane's store on its own).
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void bwd_small_filter_kernel(BwdSmallArgs F, int R, int S, const float* __restrict__ w,
                                                                float* __restrict__ U)
 {
-    const int kpad = F.nchunks * F.ck;
-    const long long total = (long long)F.ncbp * 16 * kpad * F.npp;  // (blocks that pad the count to whole groups: zeros)
+    // (blocks that pad the count to whole groups: zeros.)  16 columns fastest, then four reduction rows, in the order of the
+    // lanes that read them: a wave's stores of four planes are one kilobyte
+    const long long total = (long long)F.ncbp * 16 * F.nchunks * F.ck * F.npp;
     const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
     if (e >= total) return;
-    const int pp = (int)(e % F.npp);
-    const int k = (int)((e / F.npp) % kpad);
-    const int f = (int)(e / ((long long)F.npp * kpad));
+    const int kk = (int)((e >> 4) % F.ck), pp = (int)((e >> 4) / F.ck % F.npp);
+    const int cb = (int)((e >> 4) / F.ck / F.npp);  // chunk * ncbp + block of 16 columns
+    const int chunk = cb / F.ncbp, k = chunk * F.ck + kk;
+    const int f = (cb - chunk * F.ncbp) * 16 + (int)(e & 15);
     const int ph = pp / F.npw, pw = pp % F.npw;
     const int rho_w = f % F.s, rho_h = (f / F.s) % F.s, c = f / (F.s * F.s);
     const bool real = f < F.nf && k < F.K;
@@ -85,14 +88,25 @@ __global__ __launch_bounds__(256) void bwd_small_filter_kernel(BwdSmallArgs F, i
 #pragma unroll
         for (int j = 0; j < 3; ++j) t[i][j] = bs_g_row(i, g[0][j], g[1][j], g[2][j]);
     const int nfreq = F.four ? 4 : 3, planes = nfreq * nfreq;
-    const int chunk = k / F.ck, row = pp * F.ck + (k % F.ck);
+    const int row = pp * F.ck + kk;
     const int step = row >> 2, lane = (row & 3) * 16 + (f & 15);
-    float* dst = U + ((size_t)chunk * F.ncbp + (f >> 4)) * (size_t)F.us_floats + (size_t)step * (planes * 64);
+    float* dst = U + (size_t)cb * (size_t)F.us_floats + (size_t)step * (planes * 64);
+    float v[16];
 #pragma unroll
     for (int fh = 0; fh < 4; ++fh)
 #pragma unroll
         for (int fw = 0; fw < 4; ++fw)
-            if (fh < nfreq && fw < nfreq) dst[bs_upos(planes, fh * nfreq + fw, lane)] = bs_g_row(fw, t[fh][0], t[fh][1], t[fh][2]);
+            if (F.four || (fh < 3 && fw < 3)) {
+                const float u = bs_g_row(fw, t[fh][0], t[fh][1], t[fh][2]);
+                if (F.four) v[fh * 4 + fw] = u;
+                else v[fh * 3 + fw] = u;
+            }
+    // (a lane's planes in groups of four are adjacent: see bs_upos)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        if (g < planes / 4)
+            *reinterpret_cast<float4*>(dst + bs_upos(planes, 4 * g, lane)) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+    if (!F.four) dst[bs_upos(planes, 8, lane)] = v[8];
 }
 
 // B^T of F(2,3) on a patch of four (Sec. 3.2), or its first three rows on a patch of three

@@ -16,7 +16,7 @@
 // rounding per sixteen products: against 64 bits, whole layers come out 1.6 to 3 times closer than from
 // contract.hip (7x7 over 256 channels 4.1e-7 -> 2.6e-7, 3x3 over 256 channels 4.3e-7 -> 1.6e-7).
 //
-// U is split once, by the filter transform (a copy beside the fp32 one, laid out so that a lane's
+// U is split once, by the filter transform (transforms.hip; a copy beside the fp32 one, laid out so that a lane's
 // fragment is 16 bytes and a DMA instruction's source is 1 KB contiguous):
 //     US[plane][l/16][part h,m,l][(l/8)%2][k][l%8].
 // V stays binary32 in memory and in LDS and is split by the lane that multiplies it, in registers
@@ -41,30 +41,6 @@
 #include "split.hpp"
 
 namespace dwm {
-
-// ---------------------------------------------------------------------------------
-// The split copy of U: a thread takes one filter and eight reduction rows.  64 consecutive threads are 64
-// filters (1 KB contiguous writes per part); the four waves take four neighbouring row groups, so that
-// the 128-byte lines they read are used whole.
-// ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void split_filter_kernel(PlaneTable PT, int Kpad, const float* __restrict__ U,
-                                                           uint32_t* __restrict__ US)
-{
-    const DevPlaneEntry e = PT.e[blockIdx.z];
-    const int lg = blockIdx.x * 4 + (threadIdx.x >> 6);  // group of eight rows
-    const int k = blockIdx.y * 64 + (threadIdx.x & 63);
-    if (lg * 8 >= e.Lpad) return;
-    const float* src = U + (size_t)e.u_off64 * 64 + (size_t)k * e.Lpad + lg * 8;
-    float x[8];
-    *reinterpret_cast<float4*>(x) = *reinterpret_cast<const float4*>(src);
-    *reinterpret_cast<float4*>(x + 4) = *reinterpret_cast<const float4*>(src + 4);
-    bf16x8 f[3];
-    split8(x, f);
-    uint32_t* dst = US + (size_t)e.u_off64 * 96 + ((size_t)(lg >> 1) * 6 + (lg & 1)) * Kpad * 4 + (size_t)k * 4;
-#pragma unroll
-    for (int s = 0; s < 3; ++s)
-        *reinterpret_cast<puint4*>(dst + (size_t)s * 2 * Kpad * 4) = __builtin_bit_cast(puint4, f[s]);
-}
 
 constexpr int kSplitFold = 1024;  // steps summed before a fold
 
@@ -467,16 +443,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void split_sum_kernel(SplitArgs A, 
 // ---------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------
-dwm_status_t launch_split_filter(const dwm_plan& p, float* U, void* stream)
-{
-    int lmax = 0;
-    for (int i = 0; i < p.planes.n; ++i) lmax = p.planes.e[i].Lpad > lmax ? p.planes.e[i].Lpad : lmax;
-    hipLaunchKernelGGL(split_filter_kernel, dim3((lmax / 8 + 3) / 4, p.d.Kpad / 64, p.planes.n), dim3(256), 0,
-                       (hipStream_t)stream, p.planes, p.d.Kpad, static_cast<const float*>(U),
-                       reinterpret_cast<uint32_t*>(U + p.us_begin));
-    return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
-}
-
 template <int WGM, int WGN, int WM, int NS>
 static dwm_status_t launch_variant(const dwm_plan& p, const float* U, float* ws, float* y, void* stream)
 {

@@ -390,13 +390,19 @@ bool contract_geometry(const dwm_plan& p, int variant, ContractGeometry* out);
 bool split_geometry(const dwm_plan& p, ContractGeometry* out);
 // transforms.hip, contract.hip
 dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U, void* stream);
+// the same for a plan whose filter lies in w with other strides: tap (r, s) of its filter k and channel c is element
+// base + k*sk + c*sc + r*sr + s*ss
+struct FilterSource {
+    long long base, sk, sc;
+    int sr, ss;
+};
+dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource& src, const float* w, float* U, void* stream);
 // `ws` is the base of a workspace laid out as the plan says: V first, then the partial outputs and
 // the arrival counters of the contraction's split tiles
 dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* ws, void* stream);
 dwm_status_t launch_contract_output(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
 bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish);
-// contract_split.hip: the split copy of a transformed filter, and the contraction that reads it
-dwm_status_t launch_split_filter(const dwm_plan& p, float* U, void* stream);
+// contract_split.hip
 dwm_status_t launch_contract_split(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
 // contract_batch.hip
 dwm_status_t launch_contract_batch(const BatchArgs& a, const PlaneTable& pt, int lc, const float* U, const float* V,

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "plan.hpp"
+#include "split.hpp"
 #include "xform.hpp"
 
 namespace dwm {
@@ -13,9 +14,36 @@ namespace dwm {
 // ---------------------------------------------------------------------------------
 // Filter transform: U = G_lh g G_lw^T for every part (Sec. 4.1 "Transformation")
 // One thread per (row of the flattened (class, l) space, k); writes all planes of its
-// class, zeros in the padding.
+// class, zeros in the padding.  w is read where it lies (FilterSource), also by the data gradient.
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, const float* __restrict__ w,
+__device__ __forceinline__ void filter_part(const DevPlan& P, const DevClass& q, const FilterSource& F,
+                                            const float* __restrict__ w, int l, int k, float (&u)[4][4])
+{
+    const int th = q.lh + 1, tw = q.lw + 1;
+    const bool real = l < q.L && k < P.K;
+    const int slot = real ? l / P.C : 0, c = real ? l - slot * P.C : 0;
+    const int a = slot / q.wn, b = slot - a * q.wn;
+    const DevPiece hp = P.ph[q.h0 + a], wp = P.pw[q.w0 + b];
+    const float* wk = w + F.base + (real ? k * F.sk + c * F.sc : 0);
+    float g[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            g[i][j] = real && i < q.lh && j < q.lw
+                          ? wk[(P.s * (hp.j + i) + hp.p) * F.sr + (P.s * (wp.j + j) + wp.p) * F.ss] : 0.f;
+    float t[4][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) t[i][j] = (i < th) ? g_row(q.lh, i, g[0][j], g[1][j], g[2][j]) : 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[i][j] = (i < th && j < tw) ? g_row(q.lw, j, t[i][0], t[i][1], t[i][2]) : 0.f;
+}
+
+__global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, FilterSource F, const float* __restrict__ w,
                                                                float* __restrict__ U)
 {
     const int row = blockIdx.x * blockDim.x + threadIdx.x;
@@ -27,37 +55,7 @@ __global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, const 
     const int th = q.lh + 1, tw = q.lw + 1;
 
     float u[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) u[i][j] = 0.f;
-
-    if (l < q.L && k < P.K) {
-        const int slot = l / P.C, c = l - slot * P.C;
-        const int a = slot / q.wn, b = slot - a * q.wn;
-        const DevPiece hp = P.ph[q.h0 + a], wp = P.pw[q.w0 + b];
-        float g[3][3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                float v = 0.f;
-                if (i < q.lh && j < q.lw) {
-                    const int r = P.s * (hp.j + i) + hp.p, s2 = P.s * (wp.j + j) + wp.p;
-                    v = w[(((size_t)k * P.C + c) * P.R + r) * P.S + s2];
-                }
-                g[i][j] = v;
-            }
-        float t[4][3];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) t[i][j] = (i < th) ? g_row(q.lh, i, g[0][j], g[1][j], g[2][j]) : 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) u[i][j] = (i < th && j < tw) ? g_row(q.lw, j, t[i][0], t[i][1], t[i][2]) : 0.f;
-    }
+    filter_part(P, q, F, w, l, k, u);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -65,6 +63,54 @@ __global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, const 
             if (i < th && j < tw) {
                 U[(size_t)q.u_off + ((size_t)(i * tw + j) * P.Kpad + k) * q.Lpad + l] = u[i][j];
             }
+}
+
+// The same, and beside it U split three ways for contract_split.hip (its layout is described there).  A workgroup takes
+// 32 rows x 8 filters, a thread one of each: the stores of U are whole 128-byte lines.  The split copy has eight rows
+// side by side in a lane and the filters next to each other, so the planes pass through LDS, and a thread then splits
+// eight rows of one filter: again whole lines.  Bound by its 65 MB of stores and the scattered reads of w: 24.6 us for
+// 256x256 filters of 7x7, read flipped and transposed by the data gradient; 58 us as a gather of w, a transform and a
+// pass that split U.  (A thread with eight rows of its own and no LDS leaves the chip short of waves: 40 us.)
+constexpr int kFtRows = 32, kFtK = 8, kFtPitch = kFtRows + 4;
+__global__ __launch_bounds__(256) void filter_transform_split_kernel(DevPlan P, FilterSource F, const float* __restrict__ w,
+                                                                     float* __restrict__ U, uint32_t* __restrict__ US)
+{
+    __shared__ alignas(16) float sm[16][kFtK][kFtPitch];
+    const int t = threadIdx.x, rbase = blockIdx.x * kFtRows, kbase = blockIdx.y * kFtK;
+    {
+        const int r = t & (kFtRows - 1), kk = t / kFtRows, row = rbase + r, k = kbase + kk;
+        if (row < P.rows_total) {
+            const DevClass q = P.cls[find_class(P, row)];
+            const int l = row - q.row0, tw = q.lw + 1;
+            float u[4][4];
+            filter_part(P, q, F, w, l, k, u);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (i <= q.lh && j <= q.lw) {
+                        U[(size_t)q.u_off + ((size_t)(i * tw + j) * P.Kpad + k) * q.Lpad + l] = u[i][j];
+                        sm[i * tw + j][kk][r] = u[i][j];
+                    }
+        }
+    }
+    __syncthreads();
+    const int kk = t & (kFtK - 1), rg = (t / kFtK) & 3, row = rbase + rg * 8;  // eight rows are of one class
+    if (row >= P.rows_total) return;
+    const DevClass q = P.cls[find_class(P, row)];
+    const int l = row - q.row0, planes = (q.lh + 1) * (q.lw + 1);
+    uint32_t* dst = US + (size_t)q.u_off / 2 * 3 + ((size_t)(l >> 4) * 6 + ((l >> 3) & 1)) * P.Kpad * 4 + (size_t)(kbase + kk) * 4;
+    for (int p = t >> 5; p < planes; p += 8) {
+        float x[8];
+        *reinterpret_cast<float4*>(x) = *reinterpret_cast<const float4*>(&sm[p][kk][rg * 8]);
+        *reinterpret_cast<float4*>(x + 4) = *reinterpret_cast<const float4*>(&sm[p][kk][rg * 8 + 4]);
+        bf16x8 f[3];
+        split8(x, f);
+        uint32_t* dp = dst + (size_t)p * P.Kpad * q.Lpad / 2 * 3;
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+            *reinterpret_cast<puint4*>(dp + (size_t)part * 2 * P.Kpad * 4) = __builtin_bit_cast(puint4, f[part]);
+    }
 }
 
 // ---------------------------------------------------------------------------------
@@ -305,12 +351,23 @@ static dwm_status_t check_launch()
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
 }
 
+dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource& src, const float* w, float* U, void* stream)
+{
+    const DevPlan& d = p.d;
+    if (p.split_ok) {
+        hipLaunchKernelGGL(filter_transform_split_kernel, dim3((d.rows_total + kFtRows - 1) / kFtRows, d.Kpad / kFtK), dim3(256), 0,
+                           (hipStream_t)stream, d, src, w, U, reinterpret_cast<uint32_t*>(U + p.us_begin));
+    } else {
+        hipLaunchKernelGGL(filter_transform_kernel, dim3((d.rows_total + 255) / 256, d.Kpad), dim3(256), 0,
+                           (hipStream_t)stream, d, src, w, U);
+    }
+    return check_launch();
+}
+
 dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U, void* stream)
 {
-    dim3 grid((p.d.rows_total + 255) / 256, p.d.Kpad), block(256);
-    hipLaunchKernelGGL(filter_transform_kernel, grid, block, 0, (hipStream_t)stream, p.d, w, U);
-    if (!p.split_ok) return check_launch();
-    return check_launch() == DWM_OK ? launch_split_filter(p, U, stream) : DWM_ERR_HIP;
+    const long long rs = (long long)p.d.R * p.d.S;
+    return launch_filter_transform_from(p, FilterSource{0, rs * p.d.C, rs, p.d.S, 1}, w, U, stream);
 }
 
 dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* V, void* stream)

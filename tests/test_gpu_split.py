@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2002_00552_amd as dwm
 from dwm_gpu import Runner
-from test_gpu_backward import WgradRunner
+from test_gpu_backward import BwdRunner, WgradRunner
 
 pytestmark = pytest.mark.gpu
 
@@ -69,6 +69,58 @@ def test_no_less_exact_than_fp32_mfma(shape):
     assert np.all(np.isfinite(y))
     assert np.max(np.abs(e)) / scale <= 2e-6, shape
     assert np.linalg.norm(e) <= np.linalg.norm(e32) * 1.05, (np.linalg.norm(e), np.linalg.norm(e32))
+
+
+G = {1: np.array([[1.0], [1.0]]), 2: np.array([[1, 0], [1, 1], [0, 1.0]]),
+     3: np.array([[1, 0, 0], [.5, .5, .5], [.5, -.5, .5], [0, 0, 1.0]])}
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_filter_copy(shape):
+    """The transformed filter, plane by plane, and its split copy: the parts are the bfloat16 nearest to U, to what is left
+    and the rest, and they add up to U (24 bits; nothing here is near the subnormals); padding is zero in both."""
+    N, C, H, W, K, R, S, s, P = shape
+    _, w = _data(shape, 9)
+    r = Runner(*shape)
+    try:
+        r.Ugw.fill_(float("nan"))
+        r.set_filter(w)
+        U = r.Ugw.cpu().numpy()
+        classes, parts, Kpad = r.classes(), r.parts(), r.info.Kpad
+    finally:
+        r.close()
+    end = len(U) * 2 // 5
+    copy = U[end:].view(np.uint16).astype(np.uint32) << 16
+    copy = copy.view(np.float32).astype(np.float64)
+    for i, c in enumerate(classes):
+        planes = (c.len_h + 1) * (c.len_w + 1)
+        got = U[c.u_offset:c.u_offset + planes * Kpad * c.Lpad].reshape(planes, Kpad, c.Lpad).astype(np.float64)
+        sp = copy[3 * c.u_offset:3 * (c.u_offset + planes * Kpad * c.Lpad)]
+        sp = sp.reshape(planes, c.Lpad // 16, 3, 2, Kpad, 8).transpose(2, 0, 4, 1, 3, 5).reshape(3, planes, Kpad, c.Lpad)
+        want = np.zeros_like(got)
+        for q in parts:
+            if q.cls != i:
+                continue
+            g = w[:, :, q.phase_h + s * q.off_h:, q.phase_w + s * q.off_w:][:, :, ::s, ::s][:, :, :q.len_h, :q.len_w]
+            u = np.einsum("ia,kcab,jb->ijkc", np.atleast_2d(G[q.len_h]), g.astype(np.float64), np.atleast_2d(G[q.len_w]))
+            want[:, :K, q.slot * C:(q.slot + 1) * C] = u.reshape(planes, K, C)
+        scale = np.max(np.abs(w))
+        assert np.max(np.abs(got - want)) <= 4 * 2.0 ** -24 * 2.25 * scale, (shape, i)  # four roundings, sums of nine
+        assert np.array_equal(sp.sum(axis=0), got), (shape, i)
+        assert np.all(np.abs(got - sp[0]) <= 2.0 ** -8 * np.abs(sp[0])) and np.all(np.abs(sp[2]) <= 2.0 ** -16 * np.abs(sp[0]))
+
+
+# filters straight from w, flipped and with their channels: rows past a block of 32, filters past a block of eight
+@pytest.mark.parametrize("shape", [(2, 90, 20, 22, 271, 4, 6, 1, 2), (4, 33, 30, 29, 150, 7, 3, 1, 1), (1, 67, 14, 14, 259, 3, 3, 1, 1)])
+def test_data_gradient(shape):
+    N, C, H, W, K, R, S, s, P = shape
+    _, w = _data(shape, 10)
+    dy = np.random.default_rng(11).standard_normal((N, K, H + 2 * P - R + 1, W + 2 * P - S + 1)).astype(np.float32)
+    r = BwdRunner(*shape, path=0)
+    dx = r.run(dy, w)
+    r.close()
+    ref = oracle.backward_data_f64(dy, w, (N, C, H, W), s, P)
+    assert np.max(np.abs(dx - ref)) <= 2e-6 * np.max(np.abs(ref)), shape
 
 
 @pytest.mark.parametrize("shape", [SHAPES[2], SHAPES[5], SHAPES[7]])
