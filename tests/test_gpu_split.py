@@ -268,3 +268,22 @@ def test_filter_gradient_values_the_split_cannot_carry(where, value):
     else:
         # the tap that multiplies the value directly, where it has one, is never finite
         assert not np.any(np.all(np.isfinite(dw[reach]), axis=(1, 2)))
+
+
+@pytest.mark.parametrize("shape, splits", [
+    ((1, 3, 256, 256, 448, 3, 3, 1, 1), 69),   # four groups of sixteen ranges, then five
+    ((1, 3, 256, 256, 40, 3, 3, 1, 1), 256),   # whole groups only
+    ((8, 128, 20, 18, 209, 4, 4, 1, 1), None), # few ranges: a thread sums them all
+])
+def test_partial_filter_gradients_are_summed(shape, splits):
+    """The kernel that adds up the ranges' partial sums: every tap of dw against FP64 (2e-6 of the largest, as above)."""
+    g = dwm.dwm_bwd_filter_plan_create(*shape)
+    n = dwm.dwm_bwd_filter_plan_info(g).splits
+    dwm.dwm_bwd_filter_plan_destroy(g)
+    assert n == splits if splits else 3 <= n < 16
+    x, dy = _wgrad_data(shape, 12)
+    N, C, H, W, K, R, S, s, P = shape
+    dw = _wgrad(shape, x, dy)
+    ref = oracle.backward_filter_f64(x, dy, (K, C, R, S), s, P)
+    assert np.max(np.abs(dw - ref)) <= 2e-6 * np.max(np.abs(ref))
+    assert np.array_equal(_wgrad(shape, x, dy), dw)
