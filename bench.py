@@ -35,6 +35,15 @@ if ROOT not in sys.path:
 METRIC = "direct-conv-equivalent TFLOP/s of DWM conv (fp32, 1 GPU); MSE vs FP64 direct"
 PEAK_MFMA_F32 = 157.3  # TFLOP/s, dense fp32 MFMA, MI355X
 PEAK_HBM = 8000.0      # GB/s
+# single precision on the bfloat16 matrix cores: six products of bfloat16 parts each (2.5 PFLOP/s dense)
+PEAK_SPLIT_F32 = 2500.0 / 6
+
+
+def contracts_split(dwm, plan):
+    """Whether the plan's contraction runs on the bfloat16 matrix cores: its filter buffer then holds a split copy too."""
+    info = dwm.dwm_plan_info(plan)
+    last = dwm.dwm_plan_class(plan, info.n_classes - 1)
+    return dwm.dwm_plan_filter_bytes(plan) == 10 * (last.u_offset + (last.len_h + 1) * (last.len_w + 1) * info.Kpad * last.Lpad)
 
 
 def hbm_traffic(workload, kernel):
@@ -127,6 +136,12 @@ def bench_backward_data(args, L, x, w):
         dwm.dwm_conv_backward_data(plan, dyd.data_ptr(), U.data_ptr(), dx.data_ptr(), st)
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / args.steps
+    peak = PEAK_MFMA_F32
+    if L.stride == 1 and not single and L.R == L.S:  # one sub-convolution: this one
+        sub = dwm.dwm_plan_create(L.N, L.K, OH, OW, L.C, L.R, L.S, 1, L.R - 1 - L.pad)
+        if contracts_split(dwm, sub):
+            peak = PEAK_SPLIT_F32
+        dwm.dwm_plan_destroy(sub)
     out = {
         "metric": "direct-conv-equivalent TFLOP/s of the DWM data gradient (fp32, 1 GPU); MSE vs FP64 definition",
         "value": info.direct_flops / dt / 1e12, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps,
@@ -136,7 +151,7 @@ def bench_backward_data(args, L, x, w):
                    "path": "single kernel" if single else "sub-convolutions",
                    "direct_GFLOP": info.direct_flops / 1e9, "winograd_GFLOP": info.winograd_flops / 1e9},
         "roofline": {"kernel": "bwd_small_kernel" if single else "all sub-convolutions", "bound": "mfma", "achieved": info.winograd_flops / dt / 1e12,
-                     "peak": PEAK_MFMA_F32, "unit": "TFLOP/s", "frac": info.winograd_flops / dt / 1e12 / PEAK_MFMA_F32,
+                     "peak": peak, "unit": "TFLOP/s", "frac": info.winograd_flops / dt / 1e12 / peak,
                      "traffic": None},
     }
     if not args.no_check:
@@ -179,6 +194,12 @@ def bench_backward_filter(args, L, x, w):
         dwm.dwm_conv_backward_filter(plan, xd.data_ptr(), dyd.data_ptr(), dw.data_ptr(), st)
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / args.steps
+    fwd = dwm.dwm_plan_create(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad)
+    cls = [dwm.dwm_plan_class(fwd, i) for i in range(dwm.dwm_plan_info(fwd).n_classes)]
+    dwm.dwm_plan_destroy(fwd)
+    tiles = [sum((c.len_h + 1) * (c.len_w + 1) * -(-L.K // t) * -(-c.Lpad // t) for c in cls) for t in (64, 128)]
+    split = info.n_tiles == tiles[1] != tiles[0]  # tiles of 128: the GEMM on the bfloat16 matrix cores
+    peak = PEAK_SPLIT_F32 if split else PEAK_MFMA_F32
     out = {
         "metric": "direct-conv-equivalent TFLOP/s of the DWM filter gradient (fp32, 1 GPU); MSE vs FP64 definition",
         "value": info.direct_flops / dt / 1e12, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps,
@@ -187,9 +208,9 @@ def bench_backward_filter(args, L, x, w):
         "config": {"workload": L.name + "_backward_filter", "planes": info.n_planes, "tiles": info.n_tiles,
                    "splits": info.splits, "direct_GFLOP": info.direct_flops / 1e9,
                    "winograd_GFLOP": info.winograd_flops / 1e9, "workspace_MB": ws.numel() * 4 / 1e6},
-        "roofline": {"kernel": "wgrad_gemm_kernel (whole step timed)", "bound": "mfma",
-                     "achieved": info.winograd_flops / dt / 1e12, "peak": PEAK_MFMA_F32, "unit": "TFLOP/s",
-                     "frac": info.winograd_flops / dt / 1e12 / PEAK_MFMA_F32, "traffic": None},
+        "roofline": {"kernel": ("wgrad_split_kernel" if split else "wgrad_gemm_kernel") + " (whole step timed)", "bound": "mfma",
+                     "achieved": info.winograd_flops / dt / 1e12, "peak": peak, "unit": "TFLOP/s",
+                     "frac": info.winograd_flops / dt / 1e12 / peak, "traffic": None},
     }
     if not args.no_check:
         import oracle
@@ -390,21 +411,23 @@ def measure_forward(L, index, steps, warmup, args, check=True):
     else:
         in_ms = timed(lambda: dwm.dwm_input_transform(plan, xp, st), steps)
         ct_ms = timed(lambda: dwm.dwm_contract_output(plan, Up, yp, st), steps)
+        ct_kernel, ct_peak = ("contract_split_kernel", PEAK_SPLIT_F32) if contracts_split(dwm, plan) else (
+            "contract_kernel", PEAK_MFMA_F32)
         stages = {
             "input_transform": {"ms": in_ms, "bound": "hbm", "algorithmic_bytes": x_bytes + v_bytes,
                                 "achieved_GBps": (x_bytes + v_bytes) / in_ms / 1e6,
                                 "frac_of_hbm_peak": (x_bytes + v_bytes) / in_ms / 1e6 / PEAK_HBM},
             "contract_output": {"ms": ct_ms, "bound": "mfma", "algorithmic_flops": info.winograd_flops,
                                 "achieved_TFLOPs": info.winograd_flops / ct_ms / 1e9,
-                                "frac_of_mfma_peak": info.winograd_flops / ct_ms / 1e9 / PEAK_MFMA_F32,
+                                "frac_of_mfma_peak": info.winograd_flops / ct_ms / 1e9 / ct_peak,
                                 "hbm_GBps_on_V_U_y": (v_bytes + y_bytes + 4.0 * U.numel()) / ct_ms / 1e6},
             "filter_transform_once": {"ms": filter_ms},
         }
         if ct_ms >= in_ms:
-            roofline = {"kernel": "contract_kernel", "bound": "mfma",
-                        "achieved": info.winograd_flops / ct_ms / 1e9, "peak": PEAK_MFMA_F32, "unit": "TFLOP/s",
-                        "frac": info.winograd_flops / ct_ms / 1e9 / PEAK_MFMA_F32,
-                        "traffic": hbm_traffic(L.name, "contract_kernel")}
+            roofline = {"kernel": ct_kernel, "bound": "mfma",
+                        "achieved": info.winograd_flops / ct_ms / 1e9, "peak": ct_peak, "unit": "TFLOP/s",
+                        "frac": info.winograd_flops / ct_ms / 1e9 / ct_peak,
+                        "traffic": hbm_traffic(L.name, ct_kernel)}
         else:
             roofline = {"kernel": "input_transform_lds_kernel", "bound": "hbm",
                         "achieved": (x_bytes + v_bytes) / in_ms / 1e6, "peak": PEAK_HBM, "unit": "GB/s",
