@@ -146,8 +146,10 @@ DWM_API dwm_status_t dwm_plan_fused_class(const dwm_plan_t* plan, int i, dwm_fus
 DWM_API dwm_status_t dwm_plan_fused_row(const dwm_plan_t* plan, int row, dwm_fused_row_t* out);
 
 /* Layers with long reductions are contracted on the bfloat16 matrix cores, every binary32 operand as the sum of three
- * bfloat16 numbers, with errors no larger than on the fp32 ones (operands that cannot be written so -- infinities, NaN,
- * the last 2^119 of the range -- take the fp32 ones).  Ugw then also holds the split transformed filter, after the
+ * bfloat16 numbers, with errors no larger than on the fp32 ones.  Operands that cannot be written so take the fp32 ones,
+ * for the parts of the output that they reach, and time (the longest layers about three times as long if every filter is
+ * such): infinities, NaN, transformed inputs of 2^112 or more, transformed filters other than zero below 2^-110 or in the
+ * last 2^119 of the range, and sums that reach 2^112.  Ugw then also holds the split transformed filter, after the
  * per-class layout above; asking for a "contract" variant or a "split" other than 0 brings the fp32 kernel.
  * Bytes of the transformed filter Ugw and of the workspace (the transformed input V, plus
  * partial output tiles and arrival counters of the contraction's split tiles). */

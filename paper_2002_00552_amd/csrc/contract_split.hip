@@ -20,7 +20,7 @@
 // fragment is 16 bytes and a DMA instruction's source is 1 KB contiguous):
 //     US[plane][l/16][part h,m,l][(l/8)%2][k][l%8].
 // V stays binary32 in memory and in LDS and is split by the lane that multiplies it, in registers
-// (5.5 vector instructions an element): V is the larger traffic, and a split V would be half again as much.
+// (6.5 vector instructions an element): V is the larger traffic, and a split V would be half again as much.
 //
 // What bounds it, measured on the 7x7 layer with 256 channels (28x28, N = 32; 500 us = 165 TFLOP/s of the
 // layer's multiplications, 0.99 PFLOP/s of bfloat16; contract.hip 727 us): with one thing compiled out at a
@@ -29,11 +29,14 @@
 // 128x128 tiles with eight waves (518) or with four of 128x32 (570: one wave per SIMD hides nothing), V split
 // once per workgroup through LDS (540), operands requested a chunk later (531).
 //
-// Values the split cannot carry: an infinity or NaN (inf - inf), and |x| >= 2^128 - 2^119, whose h rounds
-// to infinity.  Any of them makes an output of the tile non-finite; a wave that finds one among its
-// outputs computes its part of the tile again with fp32 MFMAs from the fp32 operands (exact_segment), so
-// such inputs give what contract.hip gives.  Below 2^-109 l loses bits to the subnormal range: an error
-// of at most 2^-134 of an operand.
+// Small operands: V is split as V * 2^16 and the fold multiplies by 2^-16, both exact, so that a V of any size is the
+// sum of its parts (split.hpp).  U's copy is the parts of U as it is; where those are not U (0 < |U| < 2^-110) the filter
+// transform writes NaN for them.  (7x7 layer below: 0.4 % of the call for V's multiplications, which go where the vector
+// unit would wait for the first terms.)
+// Values the split cannot carry: those, an infinity or NaN (inf - inf), and |V| >= 2^112 - 2^103 or |U| >= 2^128 - 2^119, whose h
+// becomes infinite.  Any of them, and an output of 2^112 or more before the fold, makes an output of the tile
+// non-finite; a wave that finds one among its outputs computes its part of the tile again with fp32 MFMAs from the fp32
+// operands (exact_segment), so such inputs give what contract.hip gives.
 #include <hip/hip_runtime.h>
 
 #include "dma.hpp"
@@ -89,6 +92,13 @@ __device__ __forceinline__ void put_tile(const SplitArgs& A, float* __restrict__
     }
 }
 
+__device__ __forceinline__ int lane_again()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
 // Workgroup of WGM x WGN waves, wave tile 32*WM filters x 32 tiles, a ring of NS stages of LC = 16 reduction steps.
 template <int WGM, int WGN, int WM, int NS, bool MAPPED>
 __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split_kernel(
@@ -137,12 +147,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
     floatx16 acc[WM][2];
     floatx16 Y[WM][4];
 
-    auto fold_into = [&](floatx16 (&yb)[4], const floatx16& ab, int coef) {
+    auto fold_into = [&](floatx16 (&yb)[4], const floatx16& ab, int coef, float one) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int cq = (coef >> (2 * q)) & 3;
             if (cq != 0) {
-                const float sg = cq == 1 ? 1.f : -1.f;
+                const float sg = cq == 1 ? one : -one;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) yb[q][e] = fmaf(sg, ab[e], yb[q][e]);
             }
@@ -221,6 +231,12 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
 #pragma unroll
             for (int i = 0; i < 8; ++i) r[i] = *reinterpret_cast<const float*>(bl + i * 256);
         };
+        auto split_b = [&](const float (&r)[8], int i, uint32_t (&w)[3][4]) {
+            split2(r[2 * i], r[2 * i + 1], w[0][i], w[1][i], w[2][i]);
+        };
+        auto put_b = [&](const uint32_t (&w)[3][4], int s) {
+            bf[s] = __builtin_bit_cast(bf16x8, puint4{w[s][0], w[s][1], w[s][2], w[s][3]});
+        };
         auto term = [&](int ta, int tb) {
             const int c = ta + tb > 0;
 #pragma unroll
@@ -231,10 +247,16 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
         __syncthreads();
         {
             float r[8];
+            uint32_t w[3][4];
             read_b(smem_s + b_lane, r);
 #pragma unroll
             for (int s = 0; s < 3; ++s) read_a(smem_s + a_lane, s);
-            split8(r, bf);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) r[i] *= kSplitScale;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) split_b(r, i, w);
+#pragma unroll
+            for (int s = 0; s < 3; ++s) put_b(w, s);
         }
 
         uint32_t next = STAGE, refill = (NS - 1) * STAGE;  // offsets of the next chunk's stage and of the one that is free
@@ -260,22 +282,25 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
             for (int d = 0; d < N_DMA / 4; ++d) issue_one(d, ls);
             __builtin_amdgcn_sched_barrier(0);
             term(1, 1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) r[i] *= kSplitScale;
+            interleave<WM, 8 / WM>();
             read_a(al, 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int d = N_DMA / 4; d < 2 * N_DMA / 4; ++d) issue_one(d, ls);
             __builtin_amdgcn_sched_barrier(0);
             term(0, 1);
-            split2(r[0], r[1], w[0][0], w[1][0], w[2][0]);
-            split2(r[2], r[3], w[0][1], w[1][1], w[2][1]);
+            split_b(r, 0, w);
+            split_b(r, 1, w);
             interleave<WM, (22 + WM - 1) / WM>();
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int d = 2 * N_DMA / 4; d < 3 * N_DMA / 4; ++d) issue_one(d, ls);
             __builtin_amdgcn_sched_barrier(0);
             term(0, 2);
-            split2(r[4], r[5], w[0][2], w[1][2], w[2][2]);
-            split2(r[6], r[7], w[0][3], w[1][3], w[2][3]);
+            split_b(r, 2, w);
+            split_b(r, 3, w);
             interleave<WM, (22 + WM - 1) / WM>();
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -285,7 +310,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
             read_a(al, 0);
 #pragma unroll
             for (int s = 0; s < 3; ++s) {
-                bf[s] = __builtin_bit_cast(bf16x8, puint4{w[s][0], w[s][1], w[s][2], w[s][3]});
+                put_b(w, s);
                 asm volatile("" : "+v"(bf[s]));  // made here, not sunk to where it is used
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -304,7 +329,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
             for (int mi = 0; mi < WM; ++mi) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[mi][0][e] += acc[mi][1][e];
-                fold_into(Y[mi], acc[mi][0], coef);
+                fold_into(Y[mi], acc[mi][0], coef, 1.f / kSplitScale);
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[mi][0][e] = acc[mi][1][e] = 0.f;
             }
@@ -322,12 +347,29 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
         __syncthreads();
     };
 
+    // Workgroups 0 .. n_full-1 own a whole tile; the others own piece g / n_sk_tiles of tile g % n_sk_tiles (equal
+    // ranges of its iterations), so that workgroups launched together read the same part of U.
+    const int b = blockIdx.x;
+    const bool whole = b < G.n_full;
+    const int g = b - G.n_full;
+    const int trel = whole ? b : g % G.n_sk_tiles;
+    const int piece = whole ? 0 : g / G.n_sk_tiles;
+    const int it0 = piece * G.sk_ipw;
+    const int nit = whole ? G.n_iter : min(G.sk_ipw, G.n_iter - it0);
+    if (nit <= 0) return;
+    int kt, tt;
+    tile_coords(G, whole ? trel : G.n_full + trel, kt, tt);
+    run_segment(kt, tt, it0, nit);
+
+    // (the lane's place, kept beside the chunk loop's registers, would be spilled)
+    const int ln = lane_again(), half = ln >> 5, col = wave_n * 32 + (ln & 31);
+
     // ---- the same segment on fp32 MFMAs, straight from memory: for operands the split cannot carry ----
-    auto exact_segment = [&](int kt, int tt, int it0, int nit) {
-        const float* vcol = V + (size_t)(tt * (TT / 64) + (bcol >> 6)) * A.vblock + (bcol & 63) + lh * 64;
+    auto exact_segment = [&] {
+        const float* vcol = V + (size_t)(tt * (TT / 64) + (col >> 6)) * A.vblock + (col & 63) + half * 8 * 64;
 #pragma unroll
         for (int mi = 0; mi < WM; ++mi) {
-            const size_t urow = (size_t)(kt * KT + (wave_m * WM + mi) * 32 + li);
+            const size_t urow = (size_t)(kt * KT + (wave_m * WM + mi) * 32 + (ln & 31));
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -343,22 +385,29 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
                     continue;
                 }
                 const int take = min(left, min(n - ch, kFoldSteps / LC));
-                const float* ua = U + (size_t)e.u_off64 * 64 + urow * e.Lpad + ch * LC + lh;
+                const float* ua = U + (size_t)e.u_off64 * 64 + urow * e.Lpad + ch * LC + half * 8;
                 const float* vb = vcol + ((size_t)e.v_off64 + ch * LC) * 64;
                 floatx16 m;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) m[i] = 0.f;
 #pragma unroll 1
-                for (int l = 0; l < take * LC; l += 2)
-                    m = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[l], vb[(size_t)l * 64], m, 0, 0, 0);
-                fold_into(Y[mi], m, e.coef);
+                for (int c = 0; c < take; ++c, ua += LC, vb += LC * 64) {  // (a chunk's loads together: 4.2 -> 1.35 ms for the whole 7x7 layer)
+                    float a[8], v[8];
+                    *reinterpret_cast<float4*>(a) = *reinterpret_cast<const float4*>(ua);
+                    *reinterpret_cast<float4*>(a + 4) = *reinterpret_cast<const float4*>(ua + 4);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = vb[i * 64];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) m = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], v[i], m, 0, 0, 0);
+                }
+                fold_into(Y[mi], m, e.coef, 1.f);
                 left -= take;
                 ch += take;
             }
         }
     };
     // (columns past the last tile hold whatever the workspace held)
-    auto all_finite = [&](int tt) {
+    auto all_finite = [&] {
         float s = 0.f;
 #pragma unroll
         for (int mi = 0; mi < WM; ++mi)
@@ -366,26 +415,13 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) s = fmaf(Y[mi][q][e], 0.f, s);
-        return __builtin_amdgcn_ballot_w64(s != 0.f && tt * TT + bcol < A.T) == 0;
+        return __builtin_amdgcn_ballot_w64(s != 0.f && tt * TT + col < A.T) == 0;
     };
 
-    // Workgroups 0 .. n_full-1 own a whole tile; the others own piece g / n_sk_tiles of tile g % n_sk_tiles (equal
-    // ranges of its iterations), so that workgroups launched together read the same part of U.
-    const int b = blockIdx.x;
-    const bool whole = b < G.n_full;
-    const int g = b - G.n_full;
-    const int trel = whole ? b : g % G.n_sk_tiles;
-    const int piece = whole ? 0 : g / G.n_sk_tiles;
-    const int it0 = piece * G.sk_ipw;
-    const int nit = whole ? G.n_iter : min(G.sk_ipw, G.n_iter - it0);
-    if (nit <= 0) return;
-    int kt, tt;
-    tile_coords(G, whole ? trel : G.n_full + trel, kt, tt);
-    run_segment(kt, tt, it0, nit);
-    if (!all_finite(tt)) exact_segment(kt, tt, it0, nit);
+    if (!all_finite()) exact_segment();
     if (!whole) {
         // partial outputs [tile][piece][(block*4 + q)*4 + e/4][thread][4 floats]
-        float* out = partial + ((size_t)trel * G.sk_f + piece) * (KT * TT * 4) + tid * 4;
+        float* out = partial + ((size_t)trel * G.sk_f + piece) * (KT * TT * 4) + (wave * 64 + ln) * 4;
 #pragma unroll
         for (int mi = 0; mi < WM; ++mi)
 #pragma unroll
@@ -398,14 +434,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
                 }
         return;
     }
-    // lane holds column t and rows k = 8*(e/4) + 4*lh + e%4 of each block
-    const int t = tt * TT + bcol;
+    // lane holds column t and rows k = 8*(e/4) + 4*half + e%4 of each block
+    const int t = tt * TT + col;
     if (t >= A.T) return;
 #pragma unroll
     for (int mi = 0; mi < WM; ++mi)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            put_tile<MAPPED>(A, y, t, kt * KT + (wave_m * WM + mi) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3), Y[mi][0][e],
+            put_tile<MAPPED>(A, y, t, kt * KT + (wave_m * WM + mi) * 32 + 8 * (e >> 2) + 4 * half + (e & 3), Y[mi][0][e],
                              Y[mi][1][e], Y[mi][2][e], Y[mi][3][e]);
 }
 

@@ -1,11 +1,20 @@
 // Binary32 operands as sums of three bfloat16 numbers (h = rn(x), m = rn(x - h), l = x - h - m), for the kernels that
 // multiply them on the bfloat16 matrix cores: contract_split.hip has the reasons and what it measured.
+//
+// The three parts are the number itself as long as its last bit is one that bfloat16 has: 2^-133, that of its
+// subnormals, which the matrix cores keep.  From |x| = 2^-110 on that is so; below, the last part loses bits, then the
+// middle one (x around 1e-35 is off by 5e-6 of itself, around 1e-37 by 5e-4).  What is split on the fly is therefore
+// split as x * 2^16: every binary32 number, the subnormals too, is then its parts' sum, up to the 2^112 where h
+// becomes an infinity.
 #pragma once
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
 namespace dwm {
+
+constexpr float kSplitScale = 0x1p16f;   // what an operand is multiplied by before it is split
+constexpr float kSplitMin = 0x1p-110f;   // the smallest magnitude whose parts are exact unscaled
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));

@@ -104,6 +104,10 @@ __global__ __launch_bounds__(256) void filter_transform_split_kernel(DevPlan P, 
         float x[8];
         *reinterpret_cast<float4*>(x) = *reinterpret_cast<const float4*>(&sm[p][kk][rg * 8]);
         *reinterpret_cast<float4*>(x + 4) = *reinterpret_cast<const float4*>(&sm[p][kk][rg * 8 + 4]);
+        // (what its parts cannot hold is marked: contract_split.hip takes such filters on the fp32 matrix cores)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (x[i] != 0.f && fabsf(x[i]) < kSplitMin) x[i] = __builtin_nanf("");
         bf16x8 f[3];
         split8(x, f);
         uint32_t* dp = dst + (size_t)p * P.Kpad * q.Lpad / 2 * 3;

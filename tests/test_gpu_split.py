@@ -161,16 +161,95 @@ def test_values_the_split_cannot_carry(shape, value):
 
 
 def test_subnormal_operands():
-    """x of 1e-38 .. 1e-40, w of ordinary size: every part of an operand that the format can hold is kept (the bound: a
-    part of an operand below 2^-134 times the 9 x 256 products of an output)."""
+    """x of 1e-38 .. 1e-40, w of ordinary size: within 2e-6 of the largest output, as at any other scale, and what 2304
+    roundings of outputs near the end of the range add (2^-150 each; 1e-5 of the largest here)."""
     shape = SHAPES[0]
     x, w = _data(shape, 5)
     x = (x * 1e-38).astype(np.float32)
     y = _run(shape, x, w)
     idx = np.arange(0, y.size, 37)
     ref = oracle.direct_f64_at(x, w, 1, 1, idx)
-    bound = 2e-6 * np.max(np.abs(ref)) + 9 * 256 * 2.0 ** -134 * np.max(np.abs(w)) * 16 + 2.0 ** -140 * 256 * 16
+    bound = 2e-6 * np.max(np.abs(ref)) + 9 * 256 * 16 * 2.0 ** -150
+    assert bound < 2e-3 * np.max(np.abs(ref))
     assert np.max(np.abs(y.ravel()[idx] - ref)) <= bound
+
+
+def _off(a, ref):
+    """2-norm of the difference over that of the reference, whatever its scale."""
+    scale = np.max(np.abs(ref))
+    return np.linalg.norm((a - ref) / scale) / np.linalg.norm(ref / scale)
+
+
+def _small(a, other, how):
+    """(a, other) with a, or its even channels, brought to where its parts leave bfloat16's normal range; other stays or
+    makes up for it."""
+    scale, up, every = how
+    a, other = a.copy(), other.copy()
+    a[:, ::every] *= np.float32(scale)
+    other[:, ::every] *= np.float32(up)
+    return a, other
+
+
+SMALL = [(1e-31, 1, 1), (1e-34, 1, 1), (1e-36, 1, 1), (1e-38, 1, 1), (1e-34, 1e30, 1), (1e-38, 1e30, 1), (1e-36, 1e34, 2)]
+
+
+@pytest.mark.parametrize("how", SMALL)
+@pytest.mark.parametrize("where", ["x", "w"])
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[2], SHAPES[7]])
+def test_small_operands(shape, where, how):
+    """x or w far below 1 (ordinary binary32 numbers whose lower parts bfloat16 has no room for), all of it or every other
+    channel, the other operand ordinary or as much larger: in the 2-norm no further from FP64 than the fp32 contraction.
+    (Where w is small both run on fp32 matrix cores and differ in the order of their sums: 1.1 is between two draws of the
+    same error over 4000 outputs.)"""
+    x, w = _data(shape, 4)
+    if where == "x":
+        x, w = _small(x, w, how)
+    else:
+        w, x = _small(w, x, how)
+    y = _run(shape, x, w)
+    y32 = _run(shape, x, w, {"contract": 10, "forward": 0})
+    idx = np.random.default_rng(2).choice(y.size, min(y.size, 4000), replace=False)
+    ref = oracle.direct_f64_at(x, w, shape[7], shape[8], idx)
+    off, off32 = _off(y.ravel()[idx], ref), _off(y32.ravel()[idx], ref)
+    assert off <= 1.1 * off32 and off32 < 1e-5, (off, off32)
+
+
+@pytest.mark.parametrize("value", [1e34, -3.4e38])
+@pytest.mark.parametrize("where", ["x", "w"])
+def test_large_finite_operands(where, value):
+    """A finite value whose h part, or whose scaled h part, is infinite: the outputs it reaches as in the fp32 contraction,
+    those that it does not (below 1: the other operand is 1e-3) to fp32 rounding, and no output lost."""
+    shape = SHAPES[0]
+    x, w = _data(shape, 6)
+    a, other = (x, w) if where == "x" else (w, x)
+    other *= np.float32(1e-3)
+    a[tuple(n // 2 for n in a.shape)] = value
+    y = _run(shape, x, w)
+    y32 = _run(shape, x, w, {"contract": 10, "forward": 0})
+    far = np.abs(y32) < 1.0
+    assert np.all(np.isfinite(y)) and 0.3 < np.mean(far) < 1.0
+    assert np.max(np.abs(y[far] - y32[far])) <= 4e-6 * np.max(np.abs(y32[far]))
+    assert np.max(np.abs(y[~far] - y32[~far])) <= 1e-5 * np.max(np.abs(y32[~far]))
+
+
+@pytest.mark.parametrize("where, how", [("dy", SMALL[2]), ("w", SMALL[2]), ("dy", SMALL[6])])
+def test_data_gradient_of_small_operands(where, how):
+    """As test_data_gradient: 2e-6 of the largest, at any scale.  (Channels of dy and filters of w are summed over.)"""
+    shape = (4, 33, 30, 29, 150, 7, 3, 1, 1)
+    N, C, H, W, K, R, S, s, P = shape
+    _, w = _data(shape, 10)
+    dy = np.random.default_rng(11).standard_normal((N, K, H + 2 * P - R + 1, W + 2 * P - S + 1)).astype(np.float32)
+    wt = w.transpose(1, 0, 2, 3)
+    if where == "dy":
+        dy, wt = _small(dy, wt, how)
+    else:
+        wt, dy = _small(wt, dy, how)
+    w = np.ascontiguousarray(wt.transpose(1, 0, 2, 3))
+    r = BwdRunner(*shape, path=0)
+    dx = r.run(dy, w)
+    r.close()
+    ref = oracle.backward_data_f64(dy, w, (N, C, H, W), s, P)
+    assert np.max(np.abs(dx - ref)) <= 2e-6 * np.max(np.abs(ref))
 
 
 def test_chosen_variants_still_run_the_fp32_contraction():
