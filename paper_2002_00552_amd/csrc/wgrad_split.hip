@@ -3,7 +3,9 @@
 // with every binary32 operand the sum of three bfloat16 numbers and six products per product, in two
 // accumulators: contract_split.hip has the arithmetic, its error and why.  dM is written split (nobody else reads it,
 // and it is the smaller operand: planes x K against planes x parts x C rows), V stays binary32 and is split in
-// registers by the wave that multiplies it.
+// registers by the wave that multiplies it.  Both are split as 2^16 times what they are, which every binary32 number's
+// parts can hold (split.hpp), and the sums are multiplied by 2^-32, all of it exact; sums of 2^96 and more are computed again
+// on fp32 MFMAs.  (V's multiplications take 2 % of the kernel on the layer below, wherever they stand among the terms.)
 //
 // There is nothing to fold here, so a wave's registers hold a 64x64 tile (two waves per SIMD), which needs half the
 // LDS reads per MFMA of the forward contraction's 64x32: per 16 tiles a wave reads 6 KB of dM and 4 KB of V for 24
@@ -21,7 +23,7 @@
 namespace dwm {
 
 // ---------------------------------------------------------------------------------
-// DMS[block of 64 tiles][distinct plane][t/16][part h,m,l][(t/8)%2][k][t%8], t inside the block.  A workgroup takes 64 filters,
+// DMS[block of 64 tiles][distinct plane][t/16][part h,m,l][(t/8)%2][k][t%8], t inside the block: the parts of dM * 2^16.  A workgroup takes 64 filters,
 // 32 tiles and up to kDyPlanes planes.  dy comes in along the tiles (a wave's load: one filter, 32 tiles' two pixel rows,
 // 256 contiguous bytes each) and goes out along the filters (64 of them, 1 KB contiguous), through LDS; reading it with a
 // thread per filter, 64 bytes a lane, took 96 us where this takes 80 (256 filters, 6272 tiles, 36 planes: 347 MB written; 46 us for the 16 distinct ones).
@@ -80,7 +82,7 @@ __global__ __launch_bounds__(256) void wgrad_dy_split_kernel(DyShape P, PlaneTab
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int cq = (coef >> (2 * q)) & 3;
-            s[q] = cq == 1 ? 1.f : cq == 3 ? -1.f : 0.f;
+            s[q] = cq == 1 ? kSplitScale : cq == 3 ? -kSplitScale : 0.f;
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -191,6 +193,12 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(WgradArgs A, DyShap
             *reinterpret_cast<float4*>(v[nj] + 4) = *reinterpret_cast<const float4*>(st + b_lane1 + nj * 2048);
         }
     };
+    auto split_b = [&](const float (&v)[2][8], int nj, int i, uint32_t (&w)[2][3][4]) {
+        split2(v[nj][2 * i] * kSplitScale, v[nj][2 * i + 1] * kSplitScale, w[nj][0][i], w[nj][1][i], w[nj][2][i]);
+    };
+    auto put_b = [&](const uint32_t (&w)[2][3][4], int nj, int s) {
+        bf[nj][s] = __builtin_bit_cast(bf16x8, puint4{w[nj][s][0], w[nj][s][1], w[nj][s][2], w[nj][s][3]});
+    };
     auto term = [&](int ta, int tb) {
         const int c = ta + tb > 0;
 #pragma unroll
@@ -203,11 +211,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(WgradArgs A, DyShap
     __syncthreads();
     {
         float v[2][8];
+        uint32_t w[2][3][4];
         read_b(smem_w, v);
 #pragma unroll
         for (int s = 0; s < 3; ++s) read_a(smem_w, s);
-        split8(v[0], bf[0]);
-        split8(v[1], bf[1]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) split_b(v, i >> 2, i & 3, w);
+#pragma unroll
+        for (int i = 0; i < 6; ++i) put_b(w, i & 1, i >> 1);
     }
     uint32_t next = STAGE, refill = (NS - 1) * STAGE;  // offsets of the next chunk's stage and of the one that is free
     // The chunk's operands are in registers; those of the next one are read and split beside its MFMAs, the barrier and
@@ -234,29 +245,29 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(WgradArgs A, DyShap
         __builtin_amdgcn_sched_barrier(0);
         term(0, 1);
 #pragma unroll
-        for (int i = 0; i < 3; ++i) split2(v[0][2 * i], v[0][2 * i + 1], w[0][0][i], w[0][1][i], w[0][2][i]);
-        interleave<4, 9>();
+        for (int i = 0; i < 3; ++i) split_b(v, 0, i, w);
+        interleave<4, 10>();
         __builtin_amdgcn_sched_barrier(0);
         issue_one(2, ls);
         __builtin_amdgcn_sched_barrier(0);
         term(0, 2);
-        split2(v[0][6], v[0][7], w[0][0][3], w[0][1][3], w[0][2][3]);
+        split_b(v, 0, 3, w);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) split2(v[1][2 * i], v[1][2 * i + 1], w[1][0][i], w[1][1][i], w[1][2][i]);
-        interleave<4, 9>();
+        for (int i = 0; i < 2; ++i) split_b(v, 1, i, w);
+        interleave<4, 10>();
         __builtin_amdgcn_sched_barrier(0);
         issue_one(3, ls);
         __builtin_amdgcn_sched_barrier(0);
         term(0, 0);
 #pragma unroll
-        for (int i = 2; i < 4; ++i) split2(v[1][2 * i], v[1][2 * i + 1], w[1][0][i], w[1][1][i], w[1][2][i]);
-        interleave<4, 6>();
+        for (int i = 2; i < 4; ++i) split_b(v, 1, i, w);
+        interleave<4, 7>();
         read_a(st, 0);
 #pragma unroll
         for (int nj = 0; nj < 2; ++nj)
 #pragma unroll
             for (int s = 0; s < 3; ++s) {
-                bf[nj][s] = __builtin_bit_cast(bf16x8, puint4{w[nj][s][0], w[nj][s][1], w[nj][s][2], w[nj][s][3]});
+                put_b(w, nj, s);
                 asm volatile("" : "+v"(bf[nj][s]));  // made here, not sunk to where it is used
             }
         __builtin_amdgcn_sched_barrier(0);
@@ -283,8 +294,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(WgradArgs A, DyShap
                 acc[mi][nj][0][e] += acc[mi][nj][1][e];
                 s = fmaf(acc[mi][nj][0][e], 0.f, s);
             }
-        // operands the split cannot carry (infinities, NaN, the last 2^119 of the range): again on fp32 MFMAs, dM from
-        // dy (columns past the class's rows hold what the workspace held)
+        float factor = (dmp & 256 ? -1.f : 1.f) / (kSplitScale * kSplitScale);
+        // operands the split cannot carry (infinities, NaN, from about 2^112 on) and scaled sums past the range: again
+        // on fp32 MFMAs, dM from dy (columns past the class's rows hold what the workspace held)
         if (__builtin_amdgcn_ballot_w64(s != 0.f && lcol + nj * 32 < lreal) != 0) {
             const int coef = (dmp >> 16) & 255, tiles = P.TH * P.TW;
 #pragma unroll
@@ -314,17 +326,14 @@ __global__ __launch_bounds__(256, 2) void wgrad_split_kernel(WgradArgs A, DyShap
                     m = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, m, 0, 0, 0);
                 }
                 acc[mi][nj][0] = m;
-                if (dmp & 256) {  // (the pattern is the plane's own; below the sign is undone for the shared dM)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[mi][nj][0][e] = -m[e];
-                }
             }
+            factor = 1.f;  // (the pattern was the plane's own)
         }
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                out[(size_t)(mi * 32 + 8 * (e >> 2) + 4 * lh + (e & 3)) * Lp + nj * 32] = (dmp & 256) ? -acc[mi][nj][0][e] : acc[mi][nj][0][e];
+                out[(size_t)(mi * 32 + 8 * (e >> 2) + 4 * lh + (e & 3)) * Lp + nj * 32] = acc[mi][nj][0][e] * factor;
     }
 }
 

@@ -321,7 +321,27 @@ def test_filter_gradient_on_bf16_matrix_cores(shape):
     assert np.array_equal(_wgrad(shape, x, dy), dw)
 
 
-@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38])
+@pytest.mark.parametrize("how", SMALL)
+@pytest.mark.parametrize("where", ["x", "dy"])
+@pytest.mark.parametrize("shape", WGRAD_SHAPES[1:3])
+def test_filter_gradient_of_small_operands(shape, where, how):
+    """x or dy far below 1, the other ordinary or as much larger: within 1e-6 in the 2-norm, as at any other scale.  (The
+    channels of both are free here, so those that are small and those that are large are compared each by themselves.)"""
+    N, C, H, W, K, R, S, s, P = shape
+    x, dy = _wgrad_data(shape, 13)
+    if where == "x":
+        x, dy = _small(x, dy, how)
+    else:
+        dy, x = _small(dy, x, how)
+    dw = _wgrad(shape, x, dy)
+    ref = oracle.backward_filter_f64(x, dy, (K, C, R, S), s, P)
+    for k in range(how[2]):
+        for c in range(how[2]):
+            a, b = dw[k::how[2], c::how[2]], ref[k::how[2], c::how[2]]
+            assert np.all(np.isfinite(a)) and _off(a, b) <= 1e-6, (k, c)
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, 1e34])
 @pytest.mark.parametrize("where", ["x", "dy"])
 def test_filter_gradient_values_the_split_cannot_carry(where, value):
     """One such value in x or in dy: what it reaches is not finite where it is not (every tap of its channel, or of its
