@@ -821,7 +821,8 @@ static dwm_status_t wgrad_build(dwm_bwd_filter_plan_t** out, dwm_plan_t* fwd, in
         a.chunks_per_split = (int)((a.tblocks + splits - 1) / splits);
         a.splits = (a.tblocks + a.chunks_per_split - 1) / a.chunks_per_split;
         const long long lim = (1LL << 31) - 1;
-        return tiles * a.splits <= lim && a.split_floats <= lim * 16 && (long long)a.tblocks * a.dm_rows <= lim;
+        // (dM's limit counts every plane, not only those that are written: what was beyond it stays so)
+        return tiles * a.splits <= lim && a.split_floats <= lim * 16 && (long long)a.tblocks * a.n_planes * a.Kp <= lim;
     };
     WgradArgs& a = bp->a;
     double us = 0.0;

@@ -272,3 +272,22 @@ def test_workspace_holds_the_partial_outputs_of_tiles_cut_into_ranges():
     assert tiles == 148 and e < slot
     e, tiles = extra((8, 16, 56, 56, 256, 5, 5, 1, 2))   # 392 tiles: one round of whole tiles + ranges
     assert tiles == 392 and e < tiles * 2 * slot
+
+
+@pytest.mark.parametrize("shape", [
+    (1694, 2, 2054, 57, 4, 11, 8, 1, 1),   # at most 16 planes differ: what dM takes is not what is counted
+    (25700, 1, 353, 28, 7, 7, 7, 1, 0),    # the short-reduction form, which writes no dM
+    (102, 4, 2849, 616, 7, 10, 10, 1, 6),
+])
+def test_filter_gradient_size_limit(shape):
+    """The filter gradient's plans end where (blocks of 64 tiles) x planes x (filters up to 64) reaches 2^31, whatever of
+    it is written to memory; the forward plan of the same layer has no such limit, and half the images are planned."""
+    def status(n):
+        h = ctypes.c_void_p()
+        st = ctypes.CDLL(dwm.LIB_PATH).dwm_bwd_filter_plan_create(ctypes.byref(h), n, *shape[1:])
+        if st == dwm.DWM_OK:
+            dwm.dwm_bwd_filter_plan_destroy(h)
+        return st
+    dwm.dwm_plan_destroy(dwm.dwm_plan_create(*shape))
+    assert status(shape[0]) == dwm.DWM_ERR_UNSUPPORTED
+    assert status(shape[0] // 2) == dwm.DWM_OK
