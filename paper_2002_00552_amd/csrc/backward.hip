@@ -33,7 +33,7 @@ struct dwm_bwd_data_plan {
         size_t u_off;        // its transformed filter inside Ugw (floats)
     };
     std::vector<Phase> phases;
-    size_t wtmp_floats;      // start of Ugw: scratch for one phase's gathered, flipped weights
+    size_t wtmp_floats;      // start of Ugw: gathered, flipped weights of a phase on the single-kernel forward path, if any is
     size_t filter_floats, ws_bytes;
     double direct_flops;
     // all sub-convolutions contracted in one launch (contract_batch.hip): each then has its own
@@ -307,7 +307,7 @@ dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, i
                 sp.no_split = s > 1;  // (several sub-convolutions are contracted together, on fp32 MFMAs)
                 st = plan_from_spec(&ph.sub, sp);
                 if (st == DWM_OK) {
-                    bp->wtmp_floats = std::max(bp->wtmp_floats, (size_t)C * K * ph.na * ph.nb);
+                    if (ph.sub->fused_ok) bp->wtmp_floats = std::max(bp->wtmp_floats, (size_t)C * K * ph.na * ph.nb);
                     bp->ws_bytes = std::max(bp->ws_bytes, dwm_plan_workspace_bytes(ph.sub));
                 }
             }

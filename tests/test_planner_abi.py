@@ -291,3 +291,21 @@ def test_filter_gradient_size_limit(shape):
     dwm.dwm_plan_destroy(dwm.dwm_plan_create(*shape))
     assert status(shape[0]) == dwm.DWM_ERR_UNSUPPORTED
     assert status(shape[0] // 2) == dwm.DWM_OK
+
+
+@pytest.mark.parametrize("shape, gathers", [
+    ((32, 256, 28, 28, 256, 7, 7, 1, 3), False),  # its filter transform reads w in place
+    ((2, 24, 14, 14, 40, 7, 7, 1, 3), False),
+    ((2, 40, 30, 30, 9, 7, 7, 1, 3), True),       # a single-kernel sub-convolution: its weights are gathered first
+])
+def test_data_gradient_filter_buffer_holds_what_is_used(shape, gathers):
+    """At stride 1 the buffer is the sub-convolution's transformed filter and, only where the weights are gathered, room
+    for them.  (None of these layers has the one-kernel gradient's copy.)"""
+    N, C, H, W, K, R, S, s, P = shape
+    b = dwm.dwm_bwd_data_plan_create(*shape)
+    sub = dwm.dwm_plan_create(N, K, H + 2 * P - R + 1, W + 2 * P - S + 1, C, R, S, 1, R - 1 - P)
+    w = -(-C * K * R * S // 64) * 256
+    assert bool(dwm.dwm_plan_info(sub).forward_path) == gathers
+    assert dwm.dwm_bwd_data_filter_bytes(b) == dwm.dwm_plan_filter_bytes(sub) + (w if gathers else 0)
+    dwm.dwm_plan_destroy(sub)
+    dwm.dwm_bwd_data_plan_destroy(b)
