@@ -52,7 +52,6 @@ struct SplitArgs {
     int OH, OW, TH, TW;
     int vblock;  // floats of one 64-tile block of V
     ContractGeometry g;
-    OutMap om;   // used by the MAPPED instantiation only
 };
 
 // tile index -> (kt, tt): the K tiles of one T tile on consecutive slots of one XCD (see contract.hip)
@@ -65,7 +64,6 @@ __device__ __forceinline__ void tile_coords(const ContractGeometry& G, int tile,
 }
 
 // the 2x2 outputs of filter k and tile t
-template <bool MAPPED>
 __device__ __forceinline__ void put_tile(const SplitArgs& A, float* __restrict__ y, int t, int k, float y00, float y01,
                                          float y10, float y11)
 {
@@ -74,10 +72,6 @@ __device__ __forceinline__ void put_tile(const SplitArgs& A, float* __restrict__
     const int n = t / tiles, rem = t - n * tiles;
     const int ty = rem / A.TW, tx = rem - ty * A.TW;
     const int oh = 2 * ty, ow = 2 * tx;
-    if (MAPPED) {
-        store_tile(y, A.om, A.OH, A.OW, (size_t)n * A.K + k, oh, ow, y00, y01, y10, y11);
-        return;
-    }
     float* yp = y + (((size_t)n * A.K + k) * A.OH + oh) * A.OW + ow;
     if ((A.OW & 1) == 0) {
         *reinterpret_cast<float2*>(yp) = make_float2(y00, y01);
@@ -100,7 +94,7 @@ __device__ __forceinline__ int lane_again()
 }
 
 // Workgroup of WGM x WGN waves, wave tile 32*WM filters x 32 tiles, a ring of NS stages of LC = 16 reduction steps.
-template <int WGM, int WGN, int WM, int NS, bool MAPPED>
+template <int WGM, int WGN, int WM, int NS>
 __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split_kernel(
     SplitArgs A, PlaneTable PT, const float* __restrict__ U, const unsigned char* __restrict__ US,
     const float* __restrict__ V, float* __restrict__ y, float* __restrict__ partial)
@@ -441,7 +435,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
     for (int mi = 0; mi < WM; ++mi)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            put_tile<MAPPED>(A, y, t, kt * KT + (wave_m * WM + mi) * 32 + 8 * (e >> 2) + 4 * half + (e & 3), Y[mi][0][e],
+            put_tile(A, y, t, kt * KT + (wave_m * WM + mi) * 32 + 8 * (e >> 2) + 4 * half + (e & 3), Y[mi][0][e],
                              Y[mi][1][e], Y[mi][2][e], Y[mi][3][e]);
 }
 
@@ -449,7 +443,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
 // workgroup per (tile, block of 32 filters, four of its sixteen rows): the whole chip reads the partials, where the last
 // workgroup to arrive (contract.hip's way) reads a tile's alone (3x3 over 256 channels, one 14x14 image, eight pieces of
 // four tiles: 38 -> 22 us).
-template <int WGM, int WGN, int WM, bool MAPPED>
+template <int WGM, int WGN, int WM>
 __global__ __launch_bounds__(64 * WGM * WGN) void split_sum_kernel(SplitArgs A, const float* __restrict__ partial,
                                                                    float* __restrict__ y)
 {
@@ -472,7 +466,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void split_sum_kernel(SplitArgs A, 
     if (t >= A.T) return;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        put_tile<MAPPED>(A, y, t, kt * KT + (wave / WGN * WM + mi) * 32 + 8 * e4 + 4 * lh + e, v[0][e], v[1][e], v[2][e],
+        put_tile(A, y, t, kt * KT + (wave / WGN * WM + mi) * 32 + 8 * e4 + 4 * lh + e, v[0][e], v[1][e], v[2][e],
                          v[3][e]);
 }
 
@@ -491,28 +485,23 @@ static dwm_status_t launch_variant(const dwm_plan& p, const float* U, float* ws,
     a.g = p.split;
     // the geometry was computed for exactly this shape of variant
     if (a.g.nkt != (p.d.K + KT - 1) / KT || a.g.ntt != (p.d.T + TT - 1) / TT) return DWM_ERR_INVALID_ARG;
+    // outputs lie densely in y: a forward pass, or a data gradient at stride 1
     const OutMap& m = p.d.om;
-    a.om = m;
-    const bool dense = m.sy == 1 && m.sx == 1 && m.oy == 0 && m.ox == 0 && m.YH == p.d.OH && m.YW == p.d.OW;
+    if (m.sy != 1 || m.sx != 1 || m.oy != 0 || m.ox != 0 || m.YH != p.d.OH || m.YW != p.d.OW) return DWM_ERR_INVALID_ARG;
     constexpr int lds_bytes = NS * (6 * KT * 16 + kSplitChunk * TT * 4);
     static_assert(lds_bytes <= (WM > 1 ? 80 : 53) * 1024, "LDS");
-    auto kd = contract_split_kernel<WGM, WGN, WM, NS, false>;
-    auto km = contract_split_kernel<WGM, WGN, WM, NS, true>;
+    auto kernel = contract_split_kernel<WGM, WGN, WM, NS>;
     if (lds_bytes > 64 * 1024) {
-        static const hipError_t attr_d = hipFuncSetAttribute(reinterpret_cast<const void*>(kd),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        static const hipError_t attr_m = hipFuncSetAttribute(reinterpret_cast<const void*>(km),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        if (attr_d != hipSuccess || attr_m != hipSuccess) return DWM_ERR_HIP;
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        if (attr != hipSuccess) return DWM_ERR_HIP;
     }
     float* partial = p.sk_partial(ws);
-    hipLaunchKernelGGL(dense ? kd : km, dim3((unsigned)(a.g.n_full + a.g.sk_wgs)), dim3(64 * WGM * WGN), lds_bytes,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(a.g.n_full + a.g.sk_wgs)), dim3(64 * WGM * WGN), lds_bytes,
                        (hipStream_t)stream, a, p.planes, U, reinterpret_cast<const unsigned char*>(U + p.us_begin),
                        static_cast<const float*>(ws), y, partial);
     if (a.g.n_sk_tiles > 0) {
-        auto sd = split_sum_kernel<WGM, WGN, WM, false>;
-        auto sm = split_sum_kernel<WGM, WGN, WM, true>;
-        hipLaunchKernelGGL(dense ? sd : sm, dim3((unsigned)a.g.n_sk_tiles, WM * 4), dim3(64 * WGM * WGN), 0,
+        hipLaunchKernelGGL((split_sum_kernel<WGM, WGN, WM>), dim3((unsigned)a.g.n_sk_tiles, WM * 4), dim3(64 * WGM * WGN), 0,
                            (hipStream_t)stream, a, static_cast<const float*>(partial), y);
     }
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
