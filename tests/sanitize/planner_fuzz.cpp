@@ -353,6 +353,23 @@ int main(int argc, char** argv)
             CHECK(dwm_plan_destroy(p) == DWM_OK);
         }
     }
+    // the single kernel's blocks of 16 tiles shared by four waves (1) or of 64 (0): the layers of
+    // tests/test_gpu_shared_block.py, both sides of "four steps or more" and of half a workgroup per CU
+    {
+        const int pinned[][10] = {
+            {1, 16, 32, 32, 16, 5, 5, 1, 2, 1}, {1, 16, 31, 29, 17, 5, 5, 1, 2, 1}, {1, 5, 16, 15, 7, 3, 3, 1, 1, 0},
+            {2, 3, 15, 16, 33, 4, 4, 1, 1, 0},  {1, 9, 18, 18, 40, 5, 5, 1, 0, 1},  {1, 7, 21, 18, 64, 7, 7, 1, 3, 1},
+            {1, 6, 32, 30, 20, 3, 3, 2, 1, 1},  {3, 2, 31, 31, 16, 9, 9, 2, 4, 1},  {1, 12, 40, 16, 48, 3, 5, 1, 1, 1},
+            {16, 3, 64, 64, 64, 7, 7, 2, 3, 1}, {17, 3, 64, 64, 64, 7, 7, 2, 3, 0},
+        };
+        for (const auto& f : pinned) {
+            dwm_plan_t* p = nullptr;
+            CHECK(dwm_plan_create(&p, f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7], f[8]) == DWM_OK);
+            CHECK(p->fused_ok && p->fused.share == f[9]);
+            CHECK(p->fused.share ? p->fused.BH * p->fused.BW <= 16 : p->fused.BH * p->fused.BW <= 64);
+            CHECK(dwm_plan_destroy(p) == DWM_OK);
+        }
+    }
     CHECK(dwm_plan_create(nullptr, 1, 1, 3, 3, 1, 3, 3, 1, 1) == DWM_ERR_INVALID_ARG);
     CHECK(dwm_plan_destroy(nullptr) == DWM_ERR_INVALID_ARG);
     CHECK(dwm_plan_filter_bytes(nullptr) == 0 && dwm_plan_workspace_bytes(nullptr) == 0);

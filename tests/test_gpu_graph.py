@@ -30,6 +30,8 @@ def _setup(shape, forward_variant):
     ((1, 16, 32, 32, 16, 5, 5, 1, 2), None),   # single-kernel path
     ((1, 16, 32, 32, 16, 5, 5, 1, 2), 0),      # staged path with split tiles (arrival counters)
     ((2, 64, 30, 30, 64, 3, 3, 1, 1), 0),      # staged path, whole and split tiles
+    ((2, 64, 9, 9, 33, 4, 4, 1, 1), None),     # bfloat16 matrix cores: pieces and the kernel that adds them up
+    ((256, 128, 28, 28, 128, 3, 3, 1, 1), None),  # ... whole tiles
 ])
 def test_forward_replays_from_a_graph(shape, forward_variant):
     plan, x, w, U, ws, y = _setup(shape, forward_variant)
@@ -78,6 +80,7 @@ def _replay_and_compare(g, out, eager, eager_again):
     (2, 10, 20, 24, 150, 3, 3, 2, 1),    # four sub-convolutions, one merged input transform, one batched contraction
     (2, 24, 14, 14, 40, 7, 7, 1, 3),     # one sub-convolution on the forward kernels (tiles cut into ranges)
     (2, 3, 37, 35, 33, 7, 7, 2, 3),      # three channels: the whole gradient in one kernel
+    (1, 67, 14, 14, 259, 3, 3, 1, 1),    # one sub-convolution on the bfloat16 matrix cores
 ])
 def test_backward_data_replays_from_a_graph(shape):
     N, C, H, W, K, R, S, s, P = shape
@@ -113,6 +116,8 @@ def test_backward_data_replays_from_a_graph(shape):
 @pytest.mark.parametrize("shape", [
     (2, 66, 12, 12, 67, 3, 3, 1, 1),     # GEMM form: input transform, dy transform, GEMM over ranges, final
     (16, 6, 130, 127, 16, 3, 3, 2, 1),   # short-reduction form: class kernels in one launch, reduce, final
+    (8, 128, 20, 18, 209, 4, 4, 1, 1),   # bfloat16 matrix cores: three ranges, added up by a kernel of their own
+    (25, 297, 31, 17, 79, 4, 4, 2, 1),   # ... two ranges, added up by the final kernel
 ])
 def test_backward_filter_replays_from_a_graph(shape):
     N, C, H, W, K, R, S, s, P = shape

@@ -369,6 +369,32 @@ def test_filter_gradient_values_the_split_cannot_carry(where, value):
         assert not np.any(np.all(np.isfinite(dw[reach]), axis=(1, 2)))
 
 
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3.4e38, 1e34])
+@pytest.mark.parametrize("where", ["x", "dy"])
+@pytest.mark.parametrize("shape", [WGRAD_SHAPES[1], WGRAD_SHAPES[4]])
+def test_filter_gradient_is_infinite_where_the_fp32_one_is(shape, where, value):
+    """The same taps of dw are infinite, of the same sign, or NaN as from the fp32 matrix cores, and the others agree.
+    (A filter's gradient depends on its own channel of dy only, and plans of up to 64 filters run on fp32 matrix cores:
+    the comparison is the same gradient, 64 filters at a time.)"""
+    N, C, H, W, K, R, S, s, P = shape
+    x, dy = _wgrad_data(shape, 14)
+    a, other = (x, dy) if where == "x" else (dy, x)
+    other *= np.float32(1e-3)
+    a[1, 5, min(7, a.shape[2] - 1), min(9, a.shape[3] - 1)] = value
+    dw = _wgrad(shape, x, dy)
+    parts = [_wgrad((N, C, H, W, min(64, K - k), R, S, s, P), x, dy[:, k:k + 64]) for k in range(0, K, 64)]
+    dw32 = np.concatenate(parts)
+    assert np.array_equal(np.isnan(dw), np.isnan(dw32))
+    assert np.array_equal(np.where(np.isinf(dw), dw, 0), np.where(np.isinf(dw32), dw32, 0))
+    if np.isfinite(value):
+        assert np.all(np.isfinite(dw32))
+    ordinary = np.isfinite(dw32) & (np.abs(dw32) < 1e3)  # (what a finite value reaches is 1e31 and more)
+    tall = np.isfinite(dw32) & ~ordinary
+    assert np.mean(ordinary) > 0.9
+    assert np.max(np.abs(dw[ordinary] - dw32[ordinary])) <= 4e-6 * np.max(np.abs(dw32[ordinary]))
+    assert np.all(np.abs(dw[tall] - dw32[tall]) <= 1e-5 * np.max(np.abs(dw32[tall]), initial=0.0))
+
+
 @pytest.mark.parametrize("shape, splits", [
     ((1, 3, 256, 256, 448, 3, 3, 1, 1), 69),   # four groups of sixteen ranges, then five
     ((1, 3, 256, 256, 40, 3, 3, 1, 1), 256),   # whole groups only
