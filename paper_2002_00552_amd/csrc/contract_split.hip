@@ -3,8 +3,8 @@
 //
 // What it computes, how the tiles are shared out and how the planes are folded into the 2x2 outputs is
 // contract.hip's; what differs is the multiplication.  An fp32 MFMA runs at the vector rate (157 TFLOP/s)
-// and keeps the vector unit busy while it does; a bfloat16 MFMA is sixteen times as fast and leaves the
-// vector unit free.  Every binary32 operand is therefore written as the sum of three bfloat16 numbers,
+// and keeps the vector unit busy while it does; a bfloat16 MFMA takes a sixteenth of the cycles and leaves
+// the vector unit free.  Every binary32 operand is therefore written as the sum of three bfloat16 numbers,
 //     x = h + m + l,   h = rn(x), m = rn(x - h), l = x - h - m   (8 + 8 + 8 significant bits: l is exact),
 // and a product is the six terms h*h, h*m, m*h, m*m, h*l, l*h, each exact in the matrix core's binary32
 // accumulation; what is left out (m*l, l*m, l*l) is at most 2^-24 of the product and of either sign.
@@ -22,12 +22,12 @@
 // V stays binary32 in memory and in LDS and is split by the lane that multiplies it, in registers
 // (6.5 vector instructions an element): V is the larger traffic, and a split V would be half again as much.
 //
-// What bounds it, measured on the 7x7 layer with 256 channels (28x28, N = 32; 500 us = 165 TFLOP/s of the
-// layer's multiplications, 0.99 PFLOP/s of bfloat16; contract.hip 727 us): with one thing compiled out at a
-// time, all loads 370 us, V's misses 440, V's split 455; a loop of the same instructions over data in L2
+// What bounds it, measured on the 7x7 layer with 256 channels (28x28, N = 32; 480 us = 171 TFLOP/s of the
+// layer's multiplications, 1.03 PFLOP/s of bfloat16; contract.hip 650 to 700 us): with one thing compiled out at a
+// time, at 500 us, all loads 370 us, V's misses 440, V's split 455; a loop of the same instructions over data in L2
 // reaches 0.26 PFLOP/s x 6, held by the chip's power (the clock falls to 1.8 GHz).  Tried and no faster:
 // 128x128 tiles with eight waves (518) or with four of 128x32 (570: one wave per SIMD hides nothing), V split
-// once per workgroup through LDS (540), operands requested a chunk later (531).
+// once per workgroup through LDS (540), operands requested a chunk later (531), each against 475 to 500.
 //
 // Small operands: V is split as V * 2^16 and the fold multiplies by 2^-16, both exact, so that a V of any size is the
 // sum of its parts (split.hpp).  U's copy is the parts of U as it is; where those are not U (0 < |U| < 2^-110) the filter
@@ -441,8 +441,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
 
 // The tiles that were cut into pieces: y = the sum of their partial outputs, in piece order.  A kernel of its own, a
 // workgroup per (tile, block of 32 filters, four of its sixteen rows): the whole chip reads the partials, where the last
-// workgroup to arrive (contract.hip's way) reads a tile's alone (3x3 over 256 channels, one 14x14 image, eight pieces of
-// four tiles: 38 -> 22 us).
+// workgroup to arrive (contract.hip's way) reads a tile's alone (3x3 over 256 channels, one 14x14 image, cut into eight
+// pieces: 38 -> 22 us for the contraction and this; in sixteen, as it is now, 11.4 + 6.6).
 template <int WGM, int WGN, int WM>
 __global__ __launch_bounds__(64 * WGM * WGN) void split_sum_kernel(SplitArgs A, const float* __restrict__ partial,
                                                                    float* __restrict__ y)

@@ -183,8 +183,8 @@ static double fp32_contract_us(const dwm_plan& p)
 // less what CUs with fewer workgroups leave to the others; a fold takes 0.45 us, outputs 10 us; a piece's partial output
 // is written and read back once (0.3 us per MB on top of what hides behind the MFMAs), by a kernel of its own (3 us).  A
 // piece is no shorter than 16 chunks: its start takes as long as ten (measured on a 49-tile layer of 256 chunks per
-// tile: 16 pieces 16.8 us, 32 pieces 20.5).  Measured, contraction, fp32 -> here: 7x7 256->256 28x28 N=32 727 -> 500 us,
-// 9x9 14x14 293 -> 205, 3x3 256->256 14x14 N=1 29 -> 17, N=8 30 -> 22; layers of about 200 of its tiles and short planes
+// tile: 16 pieces 16.8 us, 32 pieces 20.5).  Measured, contraction, fp32 -> here: 7x7 256->256 28x28 N=32 698 -> 508 us,
+// 9x9 14x14 293 -> 205, 3x3 256->256 14x14 N=1 29 -> 18, N=8 30 -> 22; layers of about 200 of its tiles and short planes
 // (3x3 stride 2 128->256 56x56 N=32: 91 against 103) leave a quarter of the CUs idle and stay with the fp32 kernel.
 bool split_geometry(const dwm_plan& p, ContractGeometry* out)
 {
