@@ -31,8 +31,8 @@
 //
 // Small operands: V is split as V * 2^16 and the fold multiplies by 2^-16, both exact, so that a V of any size is the
 // sum of its parts (split.hpp).  U's copy is the parts of U as it is; where those are not U (0 < |U| < 2^-110) the filter
-// transform writes NaN for them.  (7x7 layer below: 0.4 % of the call for V's multiplications, which go where the vector
-// unit would wait for the first terms.)
+// transform writes NaN for them.  (V's multiplications take 0.4 % of the call on the 7x7 layer below, standing where the
+// vector unit would wait for the first terms, and 1 to 2 % on small layers, wherever they stand.)
 // Values the split cannot carry: those, an infinity or NaN (inf - inf), and |V| >= 2^112 - 2^103 or |U| >= 2^128 - 2^119, whose h
 // becomes infinite.  Any of them, and an output of 2^112 or more before the fold, makes an output of the tile
 // non-finite; a wave that finds one among its outputs computes its part of the tile again with fp32 MFMAs from the fp32
