@@ -339,7 +339,8 @@ DWM_API dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan,
  * caller-owned device memory, kernels go to `stream`, nothing is allocated or synchronised, errors
  * are return codes.  Workspace: dwm_f16_workspace_bytes, 256-byte aligned (V in binary16, partial
  * outputs, arrival counters).  U_dev: dwm_f16_filter_bytes (the staged path's U, then the single
- * kernel's copy where that path applies; dwm_f16_filter_transform writes both).
+ * kernel's copy and the copy of the kernel for many channels where C is not a multiple of 16, where those paths
+ * apply; dwm_f16_filter_transform writes all).
  * dwm_f16_set_variant(plan, "contract", v): v in 30..47 selects the contraction's tile shape
  * (v < 0: the planner's choice; before dwm_f16_set_workspace only); (plan, "input", v): 0 = gather form of the input transform,
  * 1 = LDS-staged form (C a multiple of 8, or at most 64, and a staged region that fits), v < 0: the planner's
@@ -352,6 +353,11 @@ DWM_API dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan,
  * least half of a workgroup's lanes hold a tile); dwm_f16_plan_info's forward_path says which is in use.
  * (plan, "classes", v): 0 = always the general single kernel, v < 0: the one built for the layer's list
  * of classes where there is one (the same arithmetic in the same order: for tests).
+ * (plan, "wide", v): 1 = the kernel from x to y for layers with many input channels (V stays in LDS, the products go
+ * straight into the 2x2 outputs, same rounding points), DWM_ERR_INVALID_ARG where it does not apply or the planner expects
+ * nothing of it (it needs 16 channels or more, an even W and a staged region that fits in LDS); 0 = never; v < 0: the
+ * planner's choice (wherever it applies, unless a path or a stage's variant was asked for).  An x that is not on a
+ * four-byte boundary takes the staged path.  It too needs the workspace to be set; forward_path stays 0.
  * dwm_f16_conv_forward_f32out is the same computation with y left in FP32 (not rounded): it
  * exists so that tests can compare everything before the last rounding.
  * dwm_f16_input_transform / dwm_f16_contract_output are the two stages of dwm_f16_conv_forward,

@@ -246,6 +246,37 @@ struct Fused16Args {
 };
 bool fused16_setup(const dwm_plan& p, Fused16Args* out);
 
+// Geometry of the 16-bit kernel that takes a layer of many input channels from x to y (half_wide.inc).  A workgroup of
+// eight waves owns 128 filters x 64 consecutive tiles and a range of the channels, sixteen at a time; a stage is one part
+// of sixteen channels.  LDS: the transformed input of two stages, the staged pixels of two chunks of channels
+// ([group of four channels][row][column phase][column / phases][4 channels]), tables of the parts and of the pairs of pixels.
+constexpr int kWideK = 128, kWideT = 64, kWideC = 16;
+constexpr int kWideMaxPieces = 32;              // pieces a layer's channels are cut into at most
+constexpr int kWideExchangeBytes = 128 * 1024;  // the two halves' outputs at the end
+struct Wide16Class {                            // by index (3 - len_h) * 3 + (3 - len_w)
+    int n, wn, h0, w0;                          // parts (0: the layer has no such class), pieces along w, first pieces
+    unsigned u_off, plane_bytes;                // bytes from the start of the filter copy it reads; between planes
+};
+struct Wide16Args {
+    int chunks, nkt, ntt;       // chunks of channels, blocks of filters, blocks of tiles
+    int nsplit, cpw;            // pieces along the channels, chunks per piece
+    int nparts, rows_per_part;  // parts, rows of a part in the filter (C, or C rounded up to whole chunks)
+    int own_copy;               // 1: the filter has a copy of its own whose parts are padded to whole chunks
+    int nphase, lwp, row_px;    // column phases (2 * stride), pixels per (row, phase), per row
+    int lw_in, foot_h, rows_full, max_rows;
+    int npairs;                 // pairs of pixels of an image row
+    int v_bytes, x_bytes, x_px; // one stage's V, one chunk's pixels; pixels of a group of channels
+    FastDiv div_tw, div_th, div_np, div_phase;
+    int row_step;               // LDS bytes between the rows of a patch
+    int roff[kMaxPieces], coff[kMaxPieces][2];  // LDS bytes of patch row 0; of columns 0 and 1 (columns 2, 3: a pixel on)
+    int has;                    // bit i: class i is there
+    Wide16Class cls[kMaxClasses];
+    size_t lds_bytes, u_bytes, uw_words;
+    double us;                  // time by the planner's model
+};
+// partial_room: bytes that the pieces' outputs may take in the workspace; false where it does not apply or does not pay
+bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out);
+
 // Geometry of the LDS-staged input transform (transforms.hip): a workgroup stages the input
 // rows that one 64-tile block needs, for `cg` channels, and builds every part's V from LDS.
 struct InLdsArgs {

@@ -3,6 +3,7 @@
 // the LDS-staged input transform stages its rows (transforms.hip).  Pure integer logic, no GPU
 // call: this file and plan.cpp also build with a plain host compiler (sanitizer builds).
 #include <algorithm>
+#include <cmath>
 
 #include "plan.hpp"
 
@@ -208,6 +209,114 @@ bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish)
         }
     a.lds_bytes = (size_t)cg * chan_bytes;
     *out = a;
+    return true;
+}
+
+// ---------------------------------------------------------------------------------
+// 16-bit kernel from x to y for many input channels (half_wide.inc)
+// ---------------------------------------------------------------------------------
+bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out)
+{
+    const DevPlan& d = p.d;
+    Wide16Args f{};
+    if (d.om.sy != 1 || d.om.sx != 1 || d.om.oy != 0 || d.om.ox != 0 || d.om.YH != d.OH || d.om.YW != d.OW) return false;
+    if (d.Ph < 0 || d.Pw < 0 || d.C < kWideC || d.s > 64 || (d.W & 1)) return false;
+    int max_oh = 0, max_ow = 0, planes = 0;
+    for (int i = 0; i < d.nh; ++i) max_oh = std::max(max_oh, d.s * (d.ph[i].j + d.ph[i].l) + d.ph[i].p);
+    for (int i = 0; i < d.nw; ++i) max_ow = std::max(max_ow, d.s * (d.pw[i].j + d.pw[i].l) + d.pw[i].p);
+    for (int i = 0; i < d.ncls; ++i) planes = std::max(planes, (d.cls[i].lh + 1) * (d.cls[i].lw + 1));
+    f.v_bytes = planes * kWideT * kWideC * 2;
+    f.nphase = 2 * d.s;
+    f.foot_h = max_oh + 1;
+    const long long lw_in = 2LL * d.s * (d.TW - 1) + max_ow + 1, rows_full = 2LL * d.s * (d.TH - 1) + f.foot_h;
+    if (lw_in > 4096 || rows_full > (1 << 20)) return false;
+    f.lw_in = (int)lw_in;
+    f.lwp = (f.lw_in + f.nphase - 1) / f.nphase;
+    f.row_px = f.nphase * f.lwp;
+    f.rows_full = (int)rows_full;
+    f.npairs = d.W / 2;
+    const int s2 = 2 * d.s;
+    const long long row_bytes = (long long)f.row_px * 2 * kWideC, px_bytes = 2 * kWideC,
+                    room = 160 * 1024 - 2LL * f.v_bytes - 2 * px_bytes - 16LL * p.info.n_parts;
+    const long long per = (long long)d.TH * d.TW, nb = (d.T + kWideT - 1) / kWideT;
+    long long max_rows = 0;
+    for (long long bt = 0; bt < std::min(nb, per); ++bt) {
+        const long long t0 = bt * kWideT, t1 = std::min<long long>(t0 + kWideT - 1, d.T - 1);
+        const long long g0 = t0 / d.TW, g1 = t1 / d.TW, n0 = g0 / d.TH, n1 = g1 / d.TH;
+        const long long ty_a0 = g0 - n0 * d.TH, ty_b1 = g1 - n1 * d.TH;
+        const long long rows0 = s2 * ((n1 == n0 ? ty_b1 : d.TH - 1) - ty_a0) + f.foot_h;
+        max_rows = std::max(max_rows, n1 == n0 ? rows0 : rows0 + (n1 - n0 - 1) * rows_full + s2 * ty_b1 + f.foot_h);
+        if (max_rows * (2 * row_bytes + 8LL * f.npairs) > room) return false;
+    }
+    f.max_rows = (int)max_rows;
+    f.x_px = (int)(max_rows * f.row_px) + 1;  // (a last pixel for what is staged nowhere)
+    f.x_bytes = (f.x_px * 2 * kWideC + 15) / 16 * 16;
+    f.lds_bytes = std::max<size_t>((size_t)2 * (f.v_bytes + f.x_bytes) + 16 * (size_t)p.info.n_parts +
+                                       8 * (size_t)f.max_rows * f.npairs, kWideExchangeBytes);
+    // a block's images are addressed through a 31-bit buffer offset
+    if ((kWideT / per + 2) * d.C * d.H * d.W * 2 >= (1LL << 31)) return false;
+    f.div_tw.init((unsigned)d.TW);
+    f.div_th.init((unsigned)d.TH);
+    f.div_np.init((unsigned)f.npairs);
+    f.div_phase.init((unsigned)f.nphase);
+    const int px = 8;  // LDS bytes of a pixel: four channels
+    f.row_step = d.s * f.row_px * px;
+    for (int i = 0; i < kMaxPieces; ++i) {
+        f.roff[i] = i < d.nh ? (d.s * d.ph[i].j + d.ph[i].p) * f.row_px * px : 0;
+        for (int k = 0; k < 2; ++k) {
+            const int ow = i < d.nw ? d.s * (d.pw[i].j + k) + d.pw[i].p : 0;
+            f.coff[i][k] = ((ow % f.nphase) * f.lwp + ow / f.nphase) * px;
+        }
+    }
+    f.chunks = (d.C + kWideC - 1) / kWideC;
+    f.nkt = (d.K + kWideK - 1) / kWideK;
+    f.ntt = (int)nb;
+    f.nparts = p.info.n_parts;
+    // the staged path's filter serves where the parts' rows are whole chunks
+    f.own_copy = d.C % kWideC != 0;
+    f.rows_per_part = f.chunks * kWideC;
+    long long words = 0;  // of 16 bytes
+    for (int i = 0; i < d.ncls; ++i) {
+        const DevClass& q = d.cls[i];
+        Wide16Class& c = f.cls[(3 - q.lh) * 3 + (3 - q.lw)];
+        const long long plane = (f.own_copy ? (long long)q.hn * q.wn * f.rows_per_part : q.Lpad) * d.Kpad / 8;
+        f.has |= 1 << ((3 - q.lh) * 3 + (3 - q.lw));
+        c.n = q.hn * q.wn;
+        c.wn = q.wn; c.h0 = q.h0; c.w0 = q.w0;
+        c.plane_bytes = (unsigned)(plane * 16);
+        c.u_off = (unsigned)(words * 16);  // (the staged filter's classes lie one after the other too)
+        words += (q.lh + 1) * (q.lw + 1) * plane;
+        if (words * 16 >= (1LL << 31)) return false;
+    }
+    f.u_bytes = (size_t)words * 16;
+    f.uw_words = f.own_copy ? (size_t)words : 0;
+
+    // Into how many pieces the channels are cut, and whether the kernel is worth taking (us; fitted to 23 layers, within 20 %
+    // on most: csrc/half_wide.inc lists some).  A workgroup fills a CU; its launch, first loads and last stores take 9; a stage
+    // 0.75 and 0.055 for each of its planes (a share of pixels that no longer fits beside the products 0.7 per 1024 items);
+    // pieces are added up by a kernel of its own, 4 and 0.2 per MB.
+    double stages = 0.0;  // of one chunk
+    const double items = (double)f.max_rows * f.npairs * 4 / f.nparts;
+    for (int i = 0; i < kMaxClasses; ++i)
+        stages += f.cls[i].n * (0.75 + 0.055 * (4 - i / 3) * (4 - i % 3) + 0.7 * std::floor(items / 1024.0));
+    f.us = 1e30;
+    for (int n = 1; n <= kWideMaxPieces && n <= f.chunks; ++n) {
+        const int cpw = (f.chunks + n - 1) / n, pieces = (f.chunks + cpw - 1) / cpw;
+        const long long wgs = (long long)f.nkt * f.ntt * pieces;
+        const size_t partial = (size_t)wgs * kWideK * kWideT * 4 * sizeof(float);
+        if (pieces != n || (n > 1 && partial > partial_room)) continue;
+        const double us = (double)((wgs + kNumCUs - 1) / kNumCUs) * (9.0 + cpw * stages) + (n > 1 ? 4.0 + 0.2e-6 * (double)partial : 0.0);
+        if (us >= f.us) continue;
+        f.us = us;
+        f.nsplit = n;
+        f.cpw = cpw;
+    }
+    // the staged path: V written and read and x read at 5 TB/s, its products at 400 TFLOP/s, 15 for launches and start-up, and
+    // what few tiles cannot hide of a chunk's latency (49.6 us for 240 chunks of seven tiles, 18.4 for 16 of two)
+    const double v = (double)p.info.mults_per_tile * d.C * d.T;
+    const double staged = 15.0 + (4.0 * v + 2.0 * d.N * d.C * d.H * d.W) / 5e6 + 2.0 * v * d.K / 4e8 + 0.15 * p.geo.n_iter;
+    if (f.us >= staged) return false;
+    *out = f;
     return true;
 }
 
