@@ -439,35 +439,53 @@ __global__ __launch_bounds__(64 * WGM * WGN, WM > 1 ? 2 : 3) void contract_split
                              Y[mi][1][e], Y[mi][2][e], Y[mi][3][e]);
 }
 
-// The tiles that were cut into pieces: y = the sum of their partial outputs, in piece order.  A kernel of its own, a
-// workgroup per (tile, block of 32 filters, four of its sixteen rows): the whole chip reads the partials, where the last
-// workgroup to arrive (contract.hip's way) reads a tile's alone (3x3 over 256 channels, one 14x14 image, cut into eight
-// pieces: 38 -> 22 us for the contraction and this; in sixteen, as it is now, 11.4 + 6.6).
-template <int WGM, int WGN, int WM>
-__global__ __launch_bounds__(64 * WGM * WGN) void split_sum_kernel(SplitArgs A, const float* __restrict__ partial,
-                                                                   float* __restrict__ y)
+// One row of a tile's 2x2 outputs (a = 0, 1), filter k.
+__device__ __forceinline__ void put_row(const SplitArgs& A, float* __restrict__ y, int t, int k, int a, float y0, float y1)
 {
-    constexpr int NT = 64 * WGM * WGN, KT = 32 * WM * WGM, TT = 32 * WGN;
-    const int tid = threadIdx.x, wave = tid >> 6, li = tid & 31, lh = (tid >> 5) & 1;
-    const int trel = blockIdx.x, mi = blockIdx.y >> 2, e4 = blockIdx.y & 3;
+    if (k >= A.K) return;
+    const int tiles = A.TH * A.TW;
+    const int n = t / tiles, rem = t - n * tiles;
+    const int ty = rem / A.TW, tx = rem - ty * A.TW;
+    const int oh = 2 * ty + a, ow = 2 * tx;
+    if (oh >= A.OH) return;
+    float* yp = y + (((size_t)n * A.K + k) * A.OH + oh) * A.OW + ow;
+    if ((A.OW & 1) == 0) {
+        *reinterpret_cast<float2*>(yp) = make_float2(y0, y1);
+    } else {
+        yp[0] = y0;
+        if (ow + 1 < A.OW) yp[1] = y1;
+    }
+}
+
+// The tiles that were cut into pieces: y = the sum of their partial outputs, in piece order.  A kernel of its own, so that
+// the whole chip reads the partials, where the last workgroup to arrive (contract.hip's way) reads a tile's alone: a wave per
+// (tile, wave of the contraction, block of 32 filters, four of its sixteen rows, output row), eight pieces' loads in
+// flight.  3x3 over 256 channels on one 14x14 image, cut into eight pieces: 38 -> 22 us for the contraction and this; in
+// sixteen, as it is now, 11.4 + 4.8 (6.5 with four waves a workgroup, both output rows a wave and one piece's loads at a
+// time: sixteen workgroups).
+template <int WGM, int WGN, int WM>
+__global__ __launch_bounds__(64) void split_sum_kernel(SplitArgs A, const float* __restrict__ partial, float* __restrict__ y)
+{
+    constexpr int NT = 64 * WGM * WGN, KT = 32 * WM * WGM, TT = 32 * WGN, STEP = KT * TT * 4;
+    const int lane = threadIdx.x, li = lane & 31, lh = lane >> 5;
+    const int trel = blockIdx.x, mi = (blockIdx.y >> 2) % WM, e4 = blockIdx.y & 3, wave = (blockIdx.y >> 2) / WM, a = blockIdx.z;
     const int nc = (A.g.n_iter + A.g.sk_ipw - 1) / A.g.sk_ipw;
     int kt, tt;
     tile_coords(A.g, A.g.n_full + trel, kt, tt);
-    const float* src = partial + (size_t)trel * A.g.sk_f * (KT * TT * 4) + (size_t)(mi * 16 + e4) * NT * 4 + tid * 4;
-    pfloat4 v[4];
+    const float* src = partial + (size_t)trel * A.g.sk_f * STEP + (size_t)(mi * 16 + a * 8 + e4) * NT * 4 + (wave * 64 + lane) * 4;
+    pfloat4 v[2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const pfloat4*>(src + q * 4 * NT * 4);
+    for (int b = 0; b < 2; ++b) v[b] = *reinterpret_cast<const pfloat4*>(src + b * 4 * NT * 4);
+#pragma unroll 8
     for (int c = 1; c < nc; ++c) {
-        src += KT * TT * 4;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] += *reinterpret_cast<const pfloat4*>(src + q * 4 * NT * 4);
+        for (int b = 0; b < 2; ++b) v[b] += *reinterpret_cast<const pfloat4*>(src + (size_t)c * STEP + b * 4 * NT * 4);
     }
     const int t = tt * TT + wave % WGN * 32 + li;
     if (t >= A.T) return;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        put_tile(A, y, t, kt * KT + (wave / WGN * WM + mi) * 32 + 8 * e4 + 4 * lh + e, v[0][e], v[1][e], v[2][e],
-                         v[3][e]);
+        put_row(A, y, t, kt * KT + (wave / WGN * WM + mi) * 32 + 8 * e4 + 4 * lh + e, a, v[0][e], v[1][e]);
 }
 
 // ---------------------------------------------------------------------------------
@@ -501,7 +519,7 @@ static dwm_status_t launch_variant(const dwm_plan& p, const float* U, float* ws,
                        (hipStream_t)stream, a, p.planes, U, reinterpret_cast<const unsigned char*>(U + p.us_begin),
                        static_cast<const float*>(ws), y, partial);
     if (a.g.n_sk_tiles > 0) {
-        hipLaunchKernelGGL((split_sum_kernel<WGM, WGN, WM>), dim3((unsigned)a.g.n_sk_tiles, WM * 4), dim3(64 * WGM * WGN), 0,
+        hipLaunchKernelGGL((split_sum_kernel<WGM, WGN, WM>), dim3((unsigned)a.g.n_sk_tiles, WM * 4 * WGM * WGN, 2), dim3(64), 0,
                            (hipStream_t)stream, a, static_cast<const float*>(partial), y);
     }
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
