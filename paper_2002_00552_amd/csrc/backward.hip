@@ -43,8 +43,12 @@ struct dwm_bwd_data_plan {
     dwm::BatchArgs batch;
     dwm::PlaneTable batch_planes;
     std::vector<size_t> ws_off;
+    size_t partial_off;      // bytes from the start of the workspace to the partial outputs of tiles cut into pieces
     float* ws;
-    // ... and, where their tile grids coincide, ONE input transform for all of them: a plan that
+    // ... their filters transformed in one launch too, where their tables fit its arguments
+    bool filter_batched;
+    dwm::FilterBatchArgs filter_batch;
+    // ... and, where their pieces and classes fit one plan, ONE input transform for all of them: a plan that
     // holds every sub-convolution's pieces and classes (used by the input transform only)
     dwm_plan_t* merged;
     // few input channels: the whole gradient in one kernel (backward_small.hip), its filter copy
@@ -107,29 +111,37 @@ static void setup_batch_unmerged_planes(dwm_bwd_data_plan& bp, const std::vector
 // 2*ty + j' + i - Ph for all of them, so one plan can hold the pieces of every phase (those of
 // phase a once, shifted), and one class per (sub-convolution, class) whose parts are the products
 // of ITS phases' pieces.  The staged rows of dy are then fetched once instead of once per phase.
-// Applies when the tile grids coincide and the pieces and classes fit the plan's tables.
+// The tile grid is the largest of theirs (they differ by a row or a column of tiles at most, where the image's sides do not
+// divide by twice the stride): patches past the image read zeros, outputs past a sub-convolution's extent are dropped.
+// Applies when the pieces and classes fit the plan's tables.
 static void setup_merged(dwm_bwd_data_plan& bp, const std::vector<int>& subs)
 {
     using namespace dwm;
     bp.merged = nullptr;
     const dwm_plan_t* first = bp.phases[subs[0]].sub;
-    int Ph = first->d.Ph, Pw = first->d.Pw, ncls = 0;
+    int Ph = first->d.Ph, Pw = first->d.Pw, ncls = 0, TH = 0, TW = 0;
+    long long sum_t = 0;
     for (int i : subs) {
         const DevPlan& d = bp.phases[i].sub->d;
-        if (d.TH != first->d.TH || d.TW != first->d.TW || d.T != first->d.T || d.OH != first->d.OH ||
-            d.OW != first->d.OW)
-            return;
+        TH = std::max(TH, d.TH);
+        TW = std::max(TW, d.TW);
+        sum_t += d.T;
         Ph = std::max(Ph, d.Ph);
         Pw = std::max(Pw, d.Pw);
         ncls += d.ncls;
     }
     if (ncls > kMaxClasses) return;
+    // (a common grid more than a quarter larger than theirs costs more in the contraction than the shared staging gains)
+    const long long T = (long long)bp.N * TH * TW, Tpad = (T + kTAlign - 1) / kTAlign * kTAlign;
+    if (Tpad >= (1LL << 31) - 1 || T * (long long)subs.size() * 4 > sum_t * 5) return;
     dwm_plan* m = new (std::nothrow) dwm_plan;
     if (!m) return;
     std::memset(m, 0, sizeof(*m));
     DevPlan& d = m->d;
     d = first->d;
     d.Ph = Ph; d.Pw = Pw;
+    d.TH = TH; d.TW = TW;
+    d.T = (int)T; d.Tpad = (int)Tpad;
     d.nh = d.nw = d.ncls = d.rows_total = d.vblock_rows = 0;
     // pieces: those of phase a (rows) / b (columns) once
     std::vector<int> hoff(bp.s, -1), woff(bp.s, -1);
@@ -189,11 +201,84 @@ static void setup_merged(dwm_bwd_data_plan& bp, const std::vector<int>& subs)
     m->variant_forward = 0;
     m->inlds_ok = input_lds_setup(*m, &m->inlds, 0);
     for (int q = 0; q < bp.batch.nprob; ++q) {
-        bp.batch.p[q].vblock = d.vblock_rows * 64;
-        bp.batch.p[q].v_base = 0;
+        BatchProb& P = bp.batch.p[q];
+        P.vblock = d.vblock_rows * 64;
+        P.v_base = 0;
+        P.TH = TH; P.TW = TW; P.T = (int)T;
+        P.tile0 = q * bp.batch.nkt * (int)((T + 63) / 64);
     }
+    bp.batch.ntiles = bp.batch.nprob * bp.batch.nkt * (int)((T + 63) / 64);
     bp.ws_bytes = std::max<size_t>((m->v_floats * sizeof(float) + 255) / 256 * 256 + 256, 256);
     bp.merged = m;
+}
+
+// Fewer tiles than CUs: each is cut into pieces.  By this model (us; a 32-step chunk takes 0.8 in a workgroup alone on its CU
+// -- latency -- and 0.45 of the CU's matrix cores; pieces are added up by a launch of its own, 5 and 0.2 per MB) whole tiles
+// stay where cutting them gains less than a tenth; a piece has four chunks at least.
+static void setup_pieces(dwm_bwd_data_plan& bp)
+{
+    using namespace dwm;
+    BatchArgs& A = bp.batch;
+    int longest = 0;
+    for (int q = 0; q < A.nprob; ++q) longest = std::max(longest, A.p[q].n_iter);
+    auto tiles = [&](int q) { return (q + 1 < A.nprob ? A.p[q + 1].tile0 : A.ntiles) - A.p[q].tile0; };
+    const double unit = bp.batch_lc / 32.0;
+    double best = 0.9 * longest * unit * std::max(0.8, 0.45 * ((A.ntiles + kNumCUs - 1) / kNumCUs));
+    A.ipw = 0;
+    for (int f = 2; f <= 16 && A.ntiles < kNumCUs && longest >= 4 * f; ++f) {
+        const int ipw = (longest + f - 1) / f;
+        int blocks = 0;
+        for (int q = 0; q < A.nprob; ++q) blocks += tiles(q) * ((A.p[q].n_iter + ipw - 1) / ipw);
+        const double us = ipw * unit * std::max(0.8, 0.45 * ((blocks + kNumCUs - 1) / kNumCUs)) + 5.0 + 0.2e-6 * 65536.0 * blocks;
+        if (us >= best) continue;
+        best = us;
+        A.ipw = ipw;
+    }
+    A.nblocks = 0;
+    for (int q = 0; q < A.nprob; ++q) {
+        A.p[q].pieces = A.ipw > 0 ? (A.p[q].n_iter + A.ipw - 1) / A.ipw : 1;
+        A.p[q].block0 = A.nblocks;
+        A.nblocks += tiles(q) * A.p[q].pieces;
+    }
+    bp.partial_off = (bp.ws_bytes + 255) / 256 * 256;
+    if (A.ipw > 0) bp.ws_bytes = bp.partial_off + (size_t)A.nblocks * 65536;
+}
+
+static void setup_filter_batch(dwm_bwd_data_plan& bp, const std::vector<int>& subs)
+{
+    using namespace dwm;
+    bp.filter_batched = false;
+    if (subs.size() > (size_t)kMaxFilterBatch) return;
+    FilterBatchArgs& F = bp.filter_batch;
+    F = FilterBatchArgs{};
+    const long long rs = (long long)bp.R * bp.S;
+    const DevPlan& d0 = bp.phases[subs[0]].sub->d;
+    F.K = d0.K; F.C = d0.C; F.Kpad = d0.Kpad;
+    F.sk = rs; F.sc = rs * bp.C;
+    F.sr = -bp.s * bp.S; F.ss = -bp.s;
+    for (int i : subs) {
+        const auto& ph = bp.phases[i];
+        const DevPlan& d = ph.sub->d;
+        if (ph.sub->fused_ok || ph.sub->split_ok || d.ncls > 4) return;
+        FilterBatchProb& P = F.p[F.nprob++];
+        P.ncls = d.ncls;
+        P.rows_total = d.rows_total;
+        P.base = (long long)(bp.s * (ph.na - 1) + ph.a) * bp.S + bp.s * (ph.nb - 1) + ph.b;
+        for (int q = 0; q < d.nh; ++q) {
+            if (d.ph[q].p != 0 || d.ph[q].j > 127) return;
+            P.jh[q] = (signed char)d.ph[q].j;
+        }
+        for (int q = 0; q < d.nw; ++q) {
+            if (d.pw[q].p != 0 || d.pw[q].j > 127) return;
+            P.jw[q] = (signed char)d.pw[q].j;
+        }
+        for (int c = 0; c < d.ncls; ++c) {
+            const DevClass& q = d.cls[c];
+            P.cls[c] = FilterBatchClass{q.lh, q.lw, q.wn, q.L, q.Lpad, q.row0, q.h0, q.w0, (long long)ph.u_off + q.u_off};
+        }
+        F.max_rows = std::max(F.max_rows, d.rows_total);
+    }
+    bp.filter_batched = true;
 }
 
 // One launch for the contractions of all sub-convolutions where that applies: at least two of
@@ -203,6 +288,8 @@ static void setup_batch(dwm_bwd_data_plan& bp)
 {
     using namespace dwm;
     bp.batched = false;
+    bp.filter_batched = false;
+    bp.partial_off = 0;
     bp.merged = nullptr;
     bp.ws = nullptr;
     bp.ws_off.assign(bp.phases.size(), 0);
@@ -260,6 +347,8 @@ static void setup_batch(dwm_bwd_data_plan& bp)
     bp.ws_bytes = std::max<size_t>(ws, 256);
     bp.batched = true;
     setup_merged(bp, subs);
+    setup_pieces(bp);
+    setup_filter_batch(bp, subs);
 }
 
 extern "C" {
@@ -424,8 +513,12 @@ dwm_status_t dwm_bwd_data_filter_transform(const dwm_bwd_data_plan_t* plan, cons
     // (a layer in which no tap reaches any pixel of dx -- stride above the kernel size on a narrow image -- has no
     // transformed filter at all: zero bytes, and no buffer to ask for)
     if (!plan || !w_dev || (!Ugw_dev && plan->filter_floats > 0)) return DWM_ERR_INVALID_ARG;
+    if (plan->filter_batched) {
+        const dwm_status_t st = dwm::launch_filter_batch(plan->filter_batch, w_dev, Ugw_dev, stream);
+        if (st != DWM_OK) return st;
+    }
     for (const auto& ph : plan->phases) {
-        if (!ph.sub) continue;
+        if (!ph.sub || plan->filter_batched) continue;
         if (!ph.sub->fused_ok) {
             // straight from w: flipped taps of the phase, filters and channels swapped (gathering them first took 17 us of
             // 58 for 256x256 filters of 7x7)
@@ -482,8 +575,8 @@ dwm_status_t dwm_conv_backward_data(const dwm_bwd_data_plan_t* plan, const float
         if (st != DWM_OK) return st;
     }
     if (plan->batched)
-        return dwm::launch_contract_batch(plan->batch, plan->batch_planes, plan->batch_lc, Ugw_dev, plan->ws, dx_dev,
-                                          stream);
+        return dwm::launch_contract_batch(plan->batch, plan->batch_planes, plan->batch_lc, Ugw_dev, plan->ws,
+                                          plan->ws + plan->partial_off / sizeof(float), dx_dev, stream);
     return DWM_OK;
 }
 

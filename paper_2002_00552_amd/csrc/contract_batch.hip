@@ -6,8 +6,10 @@
 // stride-2 3x3 layer's four have 196 each on 256 CUs, one workgroup per CU, a fifth of the
 // CUs idle -- and they run one after the other on the caller's stream.  Here their tiles form one
 // grid, longest sub-convolution first, so that every CU holds two workgroups until the work
-// runs out.  A workgroup owns one whole tile of one sub-convolution (no tile is split: the
-// grid is several rounds of the CUs deep) and does what the single-problem kernel does:
+// runs out.  A workgroup owns one whole tile of one sub-convolution -- or, where there are fewer tiles
+// than CUs, a piece of one: a range of its chunks, whose outputs batch_sum_kernel adds up in order (5x5 at
+// stride 2, 67 and 93 channels, five 35x29 images: 44 tiles of up to 48 chunks, 38.6 us as whole tiles,
+// 13.5 in 300 pieces and 6.7 for adding them up) -- and does what the single-problem kernel does:
 // operands through a ring of LDS stages filled by global->LDS DMA, one MFMA accumulator folded
 // per plane into four running outputs, outputs written through the sub-convolution's output map
 // (its phase of dx).
@@ -23,7 +25,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 template <int LC, int NS>
 __global__ __launch_bounds__(256, 2) void contract_batch_kernel(BatchArgs A, PlaneTable PT,
                                                                 const float* __restrict__ U, const float* __restrict__ V,
-                                                                float* __restrict__ y)
+                                                                float* __restrict__ partial, float* __restrict__ y)
 {
     constexpr int NW = 4, KT = 64, TT = 64;
     constexpr int A_FLOATS = KT * LC, B_FLOATS = LC * TT, STAGE = A_FLOATS + B_FLOATS;
@@ -43,12 +45,12 @@ __global__ __launch_bounds__(256, 2) void contract_batch_kernel(BatchArgs A, Pla
 
     // which sub-convolution, which of its tiles
     int pi = 0;
-    while (pi + 1 < A.nprob && (int)blockIdx.x >= A.p[pi + 1].tile0) ++pi;
+    while (pi + 1 < A.nprob && (int)blockIdx.x >= A.p[pi + 1].block0) ++pi;
     const BatchProb Q = A.p[pi];
     // Workgroups are dealt round-robin to the 8 XCDs: the K tiles of one T tile take launch
     // positions that differ by multiples of 8, so they run on one XCD and share its L2.
-    const int r0 = (int)blockIdx.x - Q.tile0;
     const int ntt = (Q.T + TT - 1) / TT, full8 = 8 * A.nkt * (ntt / 8);
+    const int b0 = (int)blockIdx.x - Q.block0, piece = A.ipw > 0 ? b0 / (A.nkt * ntt) : 0, r0 = b0 - piece * A.nkt * ntt;
     int kt, tt;
     if (r0 < full8) {
         kt = (r0 >> 3) % A.nkt;
@@ -91,13 +93,18 @@ __global__ __launch_bounds__(256, 2) void contract_batch_kernel(BatchArgs A, Pla
 #pragma unroll
         for (int e = 0; e < 16; ++e) Y[q][e] = 0.f;
 
-    const int nit = Q.n_iter;
-    int p = Q.plane0, j = 0, jf = 0;  // jf: chunks in the accumulator since the last fold
+    const int it0 = piece * A.ipw, nit = A.ipw > 0 ? min(A.ipw, Q.n_iter - it0) : Q.n_iter;
+    int p = Q.plane0, j = it0, jf = 0;  // jf: chunks in the accumulator since the last fold
     int nch = PT.e[p].Lpad / LC;
+    while (j >= nch) {
+        j -= nch;
+        ++p;
+        nch = PT.e[p].Lpad / LC;
+    }
 
     // issue cursor: the chunk whose loads go out next; parks on the last chunk.  A DMA address is
     // (uniform chunk base) + (the lane's byte offset inside the chunk): moving on is scalar arithmetic.
-    int ip = p, ij = 0, inch = nch, ileft = nit;
+    int ip = p, ij = j, inch = nch, ileft = nit;
     const float* sa;
     const float* sb;
     uint32_t ilpad;
@@ -108,6 +115,8 @@ __global__ __launch_bounds__(256, 2) void contract_batch_kernel(BatchArgs A, Pla
         ilpad = (uint32_t)e.Lpad;
     };
     point_at(ip);
+    sa += ij * LC;
+    sb += ij * LC * 64;
     auto issue_one = [&](int d, int istage) {
         const uint32_t ls = lds0 + (uint32_t)(istage * STAGE * 4);
         if (d < A_I) dma16s(sa, __umul24(a_row4[d], ilpad) + a_col4[d], ls + (wave * A_I + d) * 1024);
@@ -164,7 +173,7 @@ __global__ __launch_bounds__(256, 2) void contract_batch_kernel(BatchArgs A, Pla
         advance_issue();
 
         const bool plane_done = ++j == nch;
-        if (plane_done || ++jf == kFoldSteps / LC) {
+        if (plane_done || it + 1 == nit || ++jf == kFoldSteps / LC) {
             jf = 0;
             // fold M_p (or what the accumulator holds of it: long reductions are folded every
             // kFoldSteps steps to keep fp32 partial sums short) into the 2x2 outputs
@@ -198,12 +207,23 @@ __global__ __launch_bounds__(256, 2) void contract_batch_kernel(BatchArgs A, Pla
     // every DMA write (the parked re-loads too) has landed before the workgroup ends
     wait_vmcnt<0>();
 
+    if (A.ipw > 0) {
+        // partial outputs [workgroup][output][e/4][thread][4 floats]
+        float4* out = reinterpret_cast<float4*>(partial) + (size_t)blockIdx.x * (KT * TT) + tid;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4)
+                out[(q * 4 + e4) * 256] = make_float4(Y[q][4 * e4], Y[q][4 * e4 + 1], Y[q][4 * e4 + 2], Y[q][4 * e4 + 3]);
+        return;
+    }
     // lane holds column t and rows k = 8*(e/4) + 4*lh + e%4 of its 32x32 block
     const int t = tt * TT + wave_n * 32 + li;
     if (t >= Q.T) return;
     const int tiles = Q.TH * Q.TW;
     const int n = t / tiles, rem = t - n * tiles;
     const int ty = rem / Q.TW, tx = rem - ty * Q.TW;
+    if (2 * ty >= Q.OH || 2 * tx >= Q.OW) return;  // (a tile grid common to sub-convolutions of unequal size)
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const int k = kt * KT + wave_m * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
@@ -212,9 +232,57 @@ __global__ __launch_bounds__(256, 2) void contract_batch_kernel(BatchArgs A, Pla
     }
 }
 
+// The tiles of a sub-convolution that were cut into pieces: the sum of the pieces' outputs, in their order.  A wave per (tile,
+// wave of the contraction, four of its sixteen rows).
+__global__ __launch_bounds__(64) void batch_sum_kernel(BatchArgs A, const float* __restrict__ partial, float* __restrict__ y)
+{
+    constexpr int KT = 64, TT = 64;
+    const int lane = threadIdx.x, li = lane & 31, lh = lane >> 5;
+    const int wave = blockIdx.y >> 2, e4 = blockIdx.y & 3;
+    int pi = 0;
+    while (pi + 1 < A.nprob && (int)blockIdx.x >= A.p[pi + 1].tile0) ++pi;
+    const BatchProb Q = A.p[pi];
+    const int ntt = (Q.T + TT - 1) / TT, full8 = 8 * A.nkt * (ntt / 8), r0 = (int)blockIdx.x - Q.tile0;
+    int kt, tt;
+    if (r0 < full8) {
+        kt = (r0 >> 3) % A.nkt;
+        tt = ((r0 >> 3) / A.nkt) * 8 + (r0 & 7);
+    } else {
+        kt = (r0 - full8) % A.nkt;
+        tt = (ntt / 8) * 8 + (r0 - full8) / A.nkt;
+    }
+    const size_t step = (size_t)A.nkt * ntt * (KT * TT);
+    const float4* src = reinterpret_cast<const float4*>(partial) + (size_t)(Q.block0 + r0) * (KT * TT) + e4 * 256 + wave * 64 + lane;
+    float v[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<float4*>(v[q]) = src[q * 1024];
+#pragma unroll 4
+    for (int c = 1; c < Q.pieces; ++c) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 a = src[c * step + q * 1024];
+            v[q][0] += a.x;
+            v[q][1] += a.y;
+            v[q][2] += a.z;
+            v[q][3] += a.w;
+        }
+    }
+    const int t = tt * TT + (wave & 1) * 32 + li;
+    if (t >= Q.T) return;
+    const int tiles = Q.TH * Q.TW;
+    const int n = t / tiles, rem = t - n * tiles;
+    const int ty = rem / Q.TW, tx = rem - ty * Q.TW;
+    if (2 * ty >= Q.OH || 2 * tx >= Q.OW) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int k = kt * KT + (wave >> 1) * 32 + 8 * e4 + 4 * lh + e;
+        if (k < A.K) store_tile(y, Q.om, Q.OH, Q.OW, (size_t)n * A.K + k, 2 * ty, 2 * tx, v[0][e], v[1][e], v[2][e], v[3][e]);
+    }
+}
+
 template <int LC, int NS>
-static dwm_status_t launch_batch(const BatchArgs& a, const PlaneTable& pt, const float* U, const float* V, float* y,
-                                 hipStream_t stream)
+static dwm_status_t launch_batch(const BatchArgs& a, const PlaneTable& pt, const float* U, const float* V, float* partial,
+                                 float* y, hipStream_t stream)
 {
     constexpr int lds_bytes = NS * (64 + 64) * LC * 4;
     auto kernel = contract_batch_kernel<LC, NS>;
@@ -223,17 +291,19 @@ static dwm_status_t launch_batch(const BatchArgs& a, const PlaneTable& pt, const
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (attr != hipSuccess) return DWM_ERR_HIP;
     }
-    hipLaunchKernelGGL(kernel, dim3((unsigned)a.ntiles), dim3(256), lds_bytes, stream, a, pt, U, V, y);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)a.nblocks), dim3(256), lds_bytes, stream, a, pt, U, V, partial, y);
+    if (a.ipw > 0)
+        hipLaunchKernelGGL(batch_sum_kernel, dim3((unsigned)a.ntiles, 16), dim3(64), 0, stream, a, static_cast<const float*>(partial), y);
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
 }
 
 dwm_status_t launch_contract_batch(const BatchArgs& a, const PlaneTable& pt, int lc, const float* U, const float* V,
-                                   float* y, void* stream)
+                                   float* partial, float* y, void* stream)
 {
     switch (lc) {
-        case 64: return launch_batch<64, 2>(a, pt, U, V, y, (hipStream_t)stream);
-        case 32: return launch_batch<32, 3>(a, pt, U, V, y, (hipStream_t)stream);
-        case 16: return launch_batch<16, 4>(a, pt, U, V, y, (hipStream_t)stream);
+        case 64: return launch_batch<64, 2>(a, pt, U, V, partial, y, (hipStream_t)stream);
+        case 32: return launch_batch<32, 3>(a, pt, U, V, partial, y, (hipStream_t)stream);
+        case 16: return launch_batch<16, 4>(a, pt, U, V, partial, y, (hipStream_t)stream);
         default: return DWM_ERR_INVALID_ARG;
     }
 }

@@ -344,6 +344,7 @@ constexpr int kMaxBatch = 16;
 struct BatchProb {
     int plane0, n_iter;  // first plane in the table, chunks per tile (sum over its planes of Lpad/LC)
     int tile0, vblock;   // first tile in the grid, floats of one 64-tile block of its V
+    int block0, pieces;  // first workgroup, pieces each of its tiles is cut into
     OutMap om;
     int OH, OW, TH, TW, T;
     int pad_;
@@ -351,7 +352,30 @@ struct BatchProb {
 };
 struct BatchArgs {
     int K, nkt, nprob, ntiles;
+    int ipw;             // chunks per piece; 0: whole tiles
+    int nblocks;
     BatchProb p[kMaxBatch];
+};
+
+// The transformed filters of several sub-convolutions in one launch (transforms.hip): of each what DevPlan says, in short
+// (their pieces have phase 0).
+constexpr int kMaxFilterBatch = 9;
+struct FilterBatchClass {
+    int lh, lw, wn, L, Lpad, row0;
+    int h0, w0;
+    long long u_off;  // floats from the start of the filter buffer
+};
+struct FilterBatchProb {
+    int ncls, rows_total;
+    long long base;   // of its taps in w (FilterSource)
+    signed char jh[kMaxPieces], jw[kMaxPieces];
+    FilterBatchClass cls[4];
+};
+struct FilterBatchArgs {
+    int K, C, Kpad, nprob, max_rows;  // of the sub-convolutions: their filters, their channels
+    long long sk, sc;
+    int sr, ss;
+    FilterBatchProb p[kMaxFilterBatch];
 };
 
 }  // namespace dwm
@@ -437,7 +461,8 @@ bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish);
 dwm_status_t launch_contract_split(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
 // contract_batch.hip
 dwm_status_t launch_contract_batch(const BatchArgs& a, const PlaneTable& pt, int lc, const float* U, const float* V,
-                                   float* y, void* stream);
+                                   float* partial, float* y, void* stream);
+dwm_status_t launch_filter_batch(const FilterBatchArgs& a, const float* w, float* U, void* stream);
 // setup.cpp / backward_small.hip: the single-kernel data gradient
 bool bwd_small_setup(int N, int C, int H, int W, int K, int R, int S, int stride, int pad, BwdSmallArgs* out);
 dwm_status_t launch_bwd_small_filter(const BwdSmallArgs& a, int R, int S, const float* w, float* U, void* stream);

@@ -65,6 +65,38 @@ __global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, Filter
             }
 }
 
+// The same for several stride-1 sub-convolutions that read one w (the phases of a data gradient), one grid plane each: four
+// launches of 4.3 us and the gaps between them for a 5x5 layer at stride 2 with 67 and 93 channels become one.
+__global__ __launch_bounds__(256) void filter_transform_batch_kernel(FilterBatchArgs A, const float* __restrict__ w, float* __restrict__ U)
+{
+    const FilterBatchProb& P = A.p[blockIdx.z];
+    const int row = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
+    if (row >= P.rows_total) return;
+    int qi = 0;
+    while (qi + 1 < P.ncls && row >= P.cls[qi + 1].row0) ++qi;
+    const FilterBatchClass q = P.cls[qi];
+    const int l = row - q.row0, th = q.lh + 1, tw = q.lw + 1;
+    const bool real = l < q.L && k < A.K;
+    const int slot = real ? l / A.C : 0, c = real ? l - slot * A.C : 0;
+    const int a = slot / q.wn, b = slot - a * q.wn;
+    const float* wk = w + P.base + (real ? k * A.sk + c * A.sc + P.jh[q.h0 + a] * A.sr + P.jw[q.w0 + b] * A.ss : 0);
+    float g[3][3], t[4][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) g[i][j] = real && i < q.lh && j < q.lw ? wk[i * A.sr + j * A.ss] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) t[i][j] = i < th ? g_row(q.lh, i, g[0][j], g[1][j], g[2][j]) : 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i < th && j < tw)
+                U[(size_t)q.u_off + ((size_t)(i * tw + j) * A.Kpad + k) * q.Lpad + l] = g_row(q.lw, j, t[i][0], t[i][1], t[i][2]);
+}
+
 // The same, and beside it U split three ways for contract_split.hip (its layout is described there).  A workgroup takes
 // 32 rows x 8 filters, a thread one of each: the stores of U are whole 128-byte lines.  The split copy has eight rows
 // side by side in a lane and the filters next to each other, so the planes pass through LDS, and a thread then splits
@@ -365,6 +397,13 @@ dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource&
         hipLaunchKernelGGL(filter_transform_kernel, dim3((d.rows_total + 255) / 256, d.Kpad), dim3(256), 0,
                            (hipStream_t)stream, d, src, w, U);
     }
+    return check_launch();
+}
+
+dwm_status_t launch_filter_batch(const FilterBatchArgs& a, const float* w, float* U, void* stream)
+{
+    hipLaunchKernelGGL(filter_transform_batch_kernel, dim3((a.max_rows + 255) / 256, a.Kpad, a.nprob), dim3(256), 0, (hipStream_t)stream,
+                       a, w, U);
     return check_launch();
 }
 
