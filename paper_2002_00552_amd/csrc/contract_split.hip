@@ -458,34 +458,41 @@ __device__ __forceinline__ void put_row(const SplitArgs& A, float* __restrict__ 
 }
 
 // The tiles that were cut into pieces: y = the sum of their partial outputs, in piece order.  A kernel of its own, so that
-// the whole chip reads the partials, where the last workgroup to arrive (contract.hip's way) reads a tile's alone: a wave per
-// (tile, wave of the contraction, block of 32 filters, four of its sixteen rows, output row), eight pieces' loads in
-// flight.  3x3 over 256 channels on one 14x14 image, cut into eight pieces: 38 -> 22 us for the contraction and this; in
-// sixteen, as it is now, 11.4 + 4.8 (6.5 with four waves a workgroup, both output rows a wave and one piece's loads at a
-// time: sixteen workgroups).
-template <int WGM, int WGN, int WM>
-__global__ __launch_bounds__(64) void split_sum_kernel(SplitArgs A, const float* __restrict__ partial, float* __restrict__ y)
+// the whole chip reads the partials, where the last workgroup to arrive (contract.hip's way) reads a tile's alone: 3x3 over
+// 256 channels on one 14x14 image, cut into eight pieces, 38 -> 22 us for the contraction and this.  FEW: a wave per (tile,
+// wave of the contraction, block of 32 filters, four of its sixteen rows, output row), eight pieces' loads in flight: that
+// layer, now in sixteen pieces, 11.4 + 4.8 (6.5 in the other form, whose sixteen workgroups leave the chip idle).  Else a
+// workgroup of the contraction's waves per (tile, block, four rows), both output rows a wave: 28 us for the 7x7 layer over
+// 256 channels (196 tiles in five pieces; 34 in the first form).
+template <int WGM, int WGN, int WM, bool FEW>
+__global__ __launch_bounds__(FEW ? 64 : 64 * WGM * WGN) void split_sum_kernel(SplitArgs A, const float* __restrict__ partial,
+                                                                              float* __restrict__ y)
 {
-    constexpr int NT = 64 * WGM * WGN, KT = 32 * WM * WGM, TT = 32 * WGN, STEP = KT * TT * 4;
-    const int lane = threadIdx.x, li = lane & 31, lh = lane >> 5;
-    const int trel = blockIdx.x, mi = (blockIdx.y >> 2) % WM, e4 = blockIdx.y & 3, wave = (blockIdx.y >> 2) / WM, a = blockIdx.z;
+    constexpr int NT = 64 * WGM * WGN, KT = 32 * WM * WGM, TT = 32 * WGN, STEP = KT * TT * 4, ROWS = FEW ? 1 : 2, AHEAD = FEW ? 8 : 1;
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int trel = blockIdx.x, mi = (blockIdx.y >> 2) % WM, e4 = blockIdx.y & 3;
+    const int wave = FEW ? (blockIdx.y >> 2) / WM : threadIdx.x >> 6, a0 = FEW ? blockIdx.z : 0;
     const int nc = (A.g.n_iter + A.g.sk_ipw - 1) / A.g.sk_ipw;
     int kt, tt;
     tile_coords(A.g, A.g.n_full + trel, kt, tt);
-    const float* src = partial + (size_t)trel * A.g.sk_f * STEP + (size_t)(mi * 16 + a * 8 + e4) * NT * 4 + (wave * 64 + lane) * 4;
-    pfloat4 v[2];
+    const float* src = partial + (size_t)trel * A.g.sk_f * STEP + (size_t)(mi * 16 + a0 * 8 + e4) * NT * 4 + (wave * 64 + lane) * 4;
+    pfloat4 v[2 * ROWS];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) v[b] = *reinterpret_cast<const pfloat4*>(src + b * 4 * NT * 4);
-#pragma unroll 8
+    for (int b = 0; b < 2 * ROWS; ++b) v[b] = *reinterpret_cast<const pfloat4*>(src + b * 4 * NT * 4);
+#pragma unroll AHEAD
     for (int c = 1; c < nc; ++c) {
+        src += STEP;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) v[b] += *reinterpret_cast<const pfloat4*>(src + (size_t)c * STEP + b * 4 * NT * 4);
+        for (int b = 0; b < 2 * ROWS; ++b) v[b] += *reinterpret_cast<const pfloat4*>(src + b * 4 * NT * 4);
     }
     const int t = tt * TT + wave % WGN * 32 + li;
     if (t >= A.T) return;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        put_row(A, y, t, kt * KT + (wave / WGN * WM + mi) * 32 + 8 * e4 + 4 * lh + e, a, v[0][e], v[1][e]);
+    for (int e = 0; e < 4; ++e) {
+        const int k = kt * KT + (wave / WGN * WM + mi) * 32 + 8 * e4 + 4 * lh + e;
+        if constexpr (FEW) put_row(A, y, t, k, a0, v[0][e], v[1][e]);
+        else put_tile(A, y, t, k, v[0][e], v[1][e], v[2][e], v[3][e]);
+    }
 }
 
 // ---------------------------------------------------------------------------------
@@ -519,8 +526,13 @@ static dwm_status_t launch_variant(const dwm_plan& p, const float* U, float* ws,
                        (hipStream_t)stream, a, p.planes, U, reinterpret_cast<const unsigned char*>(U + p.us_begin),
                        static_cast<const float*>(ws), y, partial);
     if (a.g.n_sk_tiles > 0) {
-        hipLaunchKernelGGL((split_sum_kernel<WGM, WGN, WM>), dim3((unsigned)a.g.n_sk_tiles, WM * 4 * WGM * WGN, 2), dim3(64), 0,
-                           (hipStream_t)stream, a, static_cast<const float*>(partial), y);
+        const float* part = partial;
+        if (a.g.n_sk_tiles * WM * 4 < 2 * kNumCUs)
+            hipLaunchKernelGGL((split_sum_kernel<WGM, WGN, WM, true>), dim3((unsigned)a.g.n_sk_tiles, WM * 4 * WGM * WGN, 2), dim3(64), 0,
+                               (hipStream_t)stream, a, part, y);
+        else
+            hipLaunchKernelGGL((split_sum_kernel<WGM, WGN, WM, false>), dim3((unsigned)a.g.n_sk_tiles, WM * 4), dim3(64 * WGM * WGN), 0,
+                               (hipStream_t)stream, a, part, y);
     }
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
 }
