@@ -455,6 +455,10 @@ dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource&
 // `ws` is the base of a workspace laid out as the plan says: V first, then the partial outputs and
 // the arrival counters of the contraction's split tiles
 dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* ws, void* stream);
+// the same, and V's columns past the last tile, up to the end of its block, are written as zeros -- by the LDS-staged forms
+// only, which input_zeroes_tail says are in use
+dwm_status_t launch_input_transform_zero_tail(const dwm_plan& p, const float* x, float* ws, void* stream);
+bool input_zeroes_tail(const dwm_plan& p);
 dwm_status_t launch_contract_output(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
 bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish);
 // contract_split.hip

@@ -265,23 +265,27 @@ __global__ __launch_bounds__(256) void input_transform_kernel(DevPlan P, const f
 // other: a wave reads only what it staged itself.
 // The 64 tiles of a block span a few tile rows, possibly of several images: the staged rows
 // are the union per image ("segments"), stored one after the other.
+// SHARED: a workgroup owns one channel, its waves take a quarter of the rows and then of the parts each.  For layers whose
+// workgroups of four channels leave CUs without one, where a wave's chain of loads, rows and parts is the time: 13.0 ->
+// 11.7 us for a 5x5 layer at stride 2 (67 channels, five 35x29 images).
 // ---------------------------------------------------------------------------------
-template <int LH, int LW>
+template <int LH, int LW, bool SHARED>
 __device__ __forceinline__ void lds_class_rows(const DevPlan& P, const InLdsArgs& A, const DevClass& q,
                                                const float* __restrict__ xl, float* __restrict__ vb, int c0,
-                                               int cn, int wave, bool valid)
+                                               int cn, int wave, bool valid, int& part)
 {
     constexpr int TH_ = LH + 1, TW_ = LW + 1;
     const size_t plane = (size_t)q.Lpad * 64;
     for (int a = 0; a < q.hn; ++a)
         for (int b = 0; b < q.wn; ++b) {
+            if (SHARED && (part++ & 3) != wave) continue;
             int ro[TH_], co[TW_];
 #pragma unroll
             for (int i = 0; i < TH_; ++i) ro[i] = A.roff[q.h0 + a][i];
 #pragma unroll
             for (int j = 0; j < TW_; ++j) co[j] = A.coff[q.w0 + b][j];
             const int lbase = (a * q.wn + b) * P.C + c0;
-            for (int cl = wave; cl < cn; cl += 4) {
+            for (int cl = SHARED ? 0 : wave; cl < cn; cl += 4) {
                 const float* xc = xl + cl * A.chan_floats;
                 float d[TH_][TW_];
 #pragma unroll
@@ -315,6 +319,8 @@ __device__ __forceinline__ void lds_class_rows(const DevPlan& P, const InLdsArgs
         }
 }
 
+// TAIL: the columns past the last tile of the last block are written as zeros (a run-time switch cost the 7x7 layer 1 %)
+template <bool SHARED, bool TAIL>
 __global__ __launch_bounds__(256) void input_transform_lds_kernel(DevPlan P, InLdsArgs A,
                                                                   const float* __restrict__ x,
                                                                   float* __restrict__ V, int* __restrict__ counters,
@@ -342,8 +348,13 @@ __global__ __launch_bounds__(256) void input_transform_lds_kernel(DevPlan P, InL
     // kInLdsBatch loads, segment by segment.  Rows above or below the image are written as
     // zeros; columns left or right of it are loaded from a clamped (legal) address and
     // replaced by zero on the way to LDS.
-    for (int cl = wave; cl < cn; cl += 4)
-        stage_channels<float, 1>(P, A, x, xs + cl * A.chan_floats, c0 + cl, 4, n0, n1, ty_a0, ty_b1, lane);
+    if constexpr (SHARED) {
+        stage_channels<float, 1, true>(P, A, x, xs, c0, 4, n0, n1, ty_a0, ty_b1, lane, wave);
+        __syncthreads();
+    } else {
+        for (int cl = wave; cl < cn; cl += 4)
+            stage_channels<float, 1>(P, A, x, xs + cl * A.chan_floats, c0 + cl, 4, n0, n1, ty_a0, ty_b1, lane);
+    }
 
     // ---- 2. every part of every class for those channels ----
     const int t = t0 + lane;
@@ -357,18 +368,19 @@ __global__ __launch_bounds__(256) void input_transform_lds_kernel(DevPlan P, InL
     }
     const float* xl = xs + lane_base;
     float* vb = V + (size_t)bt * P.vblock_rows * 64 + lane;
+    int part = 0;
     for (int qi = 0; qi < P.ncls; ++qi) {
         const DevClass q = P.cls[qi];
         switch (q.lh * 4 + q.lw) {
-            case 3 * 4 + 3: lds_class_rows<3, 3>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            case 3 * 4 + 2: lds_class_rows<3, 2>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            case 3 * 4 + 1: lds_class_rows<3, 1>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            case 2 * 4 + 3: lds_class_rows<2, 3>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            case 2 * 4 + 2: lds_class_rows<2, 2>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            case 2 * 4 + 1: lds_class_rows<2, 1>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            case 1 * 4 + 3: lds_class_rows<1, 3>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            case 1 * 4 + 2: lds_class_rows<1, 2>(P, A, q, xl, vb, c0, cn, wave, valid); break;
-            default: lds_class_rows<1, 1>(P, A, q, xl, vb, c0, cn, wave, valid); break;
+            case 3 * 4 + 3: lds_class_rows<3, 3, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 3 * 4 + 2: lds_class_rows<3, 2, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 3 * 4 + 1: lds_class_rows<3, 1, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 2 * 4 + 3: lds_class_rows<2, 3, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 2 * 4 + 2: lds_class_rows<2, 2, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 2 * 4 + 1: lds_class_rows<2, 1, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 1 * 4 + 3: lds_class_rows<1, 3, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 1 * 4 + 2: lds_class_rows<1, 2, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            default: lds_class_rows<1, 1, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
         }
         // rows past the class's reduction length are zeros (the contraction multiplies them)
         if (bc == 0 && valid && write_pad_rows) {
@@ -377,11 +389,23 @@ __global__ __launch_bounds__(256) void input_transform_lds_kernel(DevPlan P, InL
                 for (int pl = 0; pl < planes; ++pl) vb[((size_t)q.v_row0 + (size_t)pl * q.Lpad + l) * 64] = 0.f;
         }
     }
+    if (TAIL && !valid) {
+        for (int qi = 0; qi < P.ncls; ++qi) {
+            const DevClass q = P.cls[qi];
+            const int planes = (q.lh + 1) * (q.lw + 1), pads = bc == 0 && write_pad_rows ? q.Lpad - q.L : 0;
+            for (int i = wave; i < q.hn * q.wn * cn + pads; i += 4) {
+                const int l = i < q.hn * q.wn * cn ? i / cn * P.C + c0 + i % cn : q.L + i - q.hn * q.wn * cn;
+                for (int pl = 0; pl < planes; ++pl) vb[((size_t)q.v_row0 + (size_t)pl * q.Lpad + l) * 64] = 0.f;
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------
+constexpr long long kSharedInput = kNumCUs;
+
 static dwm_status_t check_launch()
 {
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
@@ -413,23 +437,45 @@ dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U
     return launch_filter_transform_from(p, FilterSource{0, rs * p.d.C, rs, p.d.S, 1}, w, U, stream);
 }
 
-dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* V, void* stream)
+// variants: 0/1 = gather form (blocks-fast / rows-fast), 2/3 = LDS-staged form (channel groups
+// fastest / blocks fastest); planner's choice: LDS-staged where it applies
+static int input_variant(const dwm_plan& p)
+{
+    const DevPlan& d = p.d;
+    if (p.variant_input >= 0) return p.variant_input;
+    return p.inlds_ok ? 2 : ((size_t)d.N * d.C * d.H * d.W * sizeof(float) > ((size_t)64 << 20));
+}
+
+bool input_zeroes_tail(const dwm_plan& p) { return input_variant(p) >= 2; }
+
+static dwm_status_t launch_input(const dwm_plan& p, const float* x, float* V, void* stream, bool zero_tail)
 {
     const DevPlan& d = p.d;
     const int nb = d.Tpad / 64, nr = d.rows_total / 16;
     dim3 block(256);
-    // variants: 0/1 = gather form (blocks-fast / rows-fast), 2/3 = LDS-staged form (channel groups
-    // fastest / blocks fastest); planner's choice: LDS-staged where it applies
-    int variant = p.variant_input;
-    if (variant < 0) variant = p.inlds_ok ? 2 : ((size_t)d.N * d.C * d.H * d.W * sizeof(float) > ((size_t)64 << 20));
+    const int variant = input_variant(p);
     if (variant >= 2) {
         if (!p.inlds_ok) return DWM_ERR_INVALID_ARG;
-        const InLdsArgs& a = p.inlds;
-        auto kernel = input_transform_lds_kernel;
+        InLdsArgs a = p.inlds;
+        int parts = 0;
+        for (int i = 0; i < d.ncls; ++i) parts += d.cls[i].hn * d.cls[i].wn;
+        auto kernel = zero_tail ? input_transform_lds_kernel<false, true> : input_transform_lds_kernel<false, false>;
+        // a channel a workgroup: up to one workgroup of four channels a CU (beyond, others' waves hide a wave's chain: 5x5
+        // at stride 2 over 73 channels with 437 of them, whole call, 36.0 -> 37.8), and a part for every wave
+        if (p.variant_input < 0 && a.cg == 4 && (long long)((d.T + 63) / 64) * a.ncg <= kSharedInput &&
+            parts >= 4) {
+            a.cg = 1;
+            a.ncg = d.C;
+            a.lds_bytes = (size_t)a.chan_floats * sizeof(float);
+            kernel = zero_tail ? input_transform_lds_kernel<true, true> : input_transform_lds_kernel<true, false>;
+        }
         if (a.lds_bytes > 64 * 1024) {
-            static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (attr != hipSuccess) return DWM_ERR_HIP;
+            // (a single channel's region is at most 64 KB: only the form of several needs more)
+            static const hipError_t attr0 = hipFuncSetAttribute(reinterpret_cast<const void*>(input_transform_lds_kernel<false, false>),
+                                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            static const hipError_t attr1 = hipFuncSetAttribute(reinterpret_cast<const void*>(input_transform_lds_kernel<false, true>),
+                                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (attr0 != hipSuccess || attr1 != hipSuccess) return DWM_ERR_HIP;
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)(nb * a.ncg)), block, a.lds_bytes, (hipStream_t)stream, d, a, x, V,
                            p.sk_counters(V), p.active().n_sk_tiles, variant == 2, p.skip_pad_rows ? 0 : 1);
@@ -442,6 +488,16 @@ dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* V,
     hipLaunchKernelGGL(input_transform_kernel, grid, block, 0, (hipStream_t)stream, d, x, V, p.sk_counters(V),
                        p.active().n_sk_tiles, rows_fast);
     return check_launch();
+}
+
+dwm_status_t launch_input_transform(const dwm_plan& p, const float* x, float* V, void* stream)
+{
+    return launch_input(p, x, V, stream, false);
+}
+
+dwm_status_t launch_input_transform_zero_tail(const dwm_plan& p, const float* x, float* V, void* stream)
+{
+    return launch_input(p, x, V, stream, true);
 }
 
 }  // namespace dwm

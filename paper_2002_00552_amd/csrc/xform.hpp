@@ -88,11 +88,14 @@ __device__ __forceinline__ void stage_rows(const char* __restrict__ xrow, unsign
 // by image ("segments", stored one after the other).  Rows above or below the image are written
 // as zeros; columns left or right of it are loaded from a clamped (legal) address and replaced by
 // zero on the way to LDS.  Columns are de-interleaved modulo 2*stride.  xsc: where channel c goes.
-template <typename T, int NC>
+// SHARED: four waves stage the same channel, a batch of rows each in turn (wave: which of them this is).
+template <typename T, int NC, bool SHARED = false>
 __device__ __forceinline__ void stage_channels(const DevPlan& P, const InLdsArgs& A, const T* __restrict__ x,
                                                float* __restrict__ xsc, int c, int cstep, int n0, int n1,
-                                               int ty_a0, int ty_b1, int lane)
+                                               int ty_a0, int ty_b1, int lane, int wave = 0)
 {
+    int batch = 0;
+    auto mine = [&]() __attribute__((always_inline)) { return !SHARED || (batch++ & 3) == wave; };
     const int s2 = 2 * P.s;
     const size_t img = (size_t)P.C * P.H * P.W;
     const size_t row_bytes = (size_t)P.W * sizeof(T);
@@ -119,11 +122,13 @@ __device__ __forceinline__ void stage_channels(const DevPlan& P, const InLdsArgs
                 float* xdr = xd + r_lo * A.row_floats;
                 int left = r_hi - r_lo;
                 for (; left >= kInLdsBatch; left -= kInLdsBatch) {
-                    stage_rows<kInLdsBatch, NC, false, T>(xrow, voff, row_bytes, chan_bytes, xdr, A.row_floats,
-                                                          chan_floats, iw_ok, kInLdsBatch);
+                    if (mine())
+                        stage_rows<kInLdsBatch, NC, false, T>(xrow, voff, row_bytes, chan_bytes, xdr, A.row_floats,
+                                                              chan_floats, iw_ok, kInLdsBatch);
                     xrow += kInLdsBatch * row_bytes;
                     xdr += kInLdsBatch * A.row_floats;
                 }
+                if (left > 0 && !mine()) left = 0;
                 if (left > 8)
                     stage_rows<kInLdsBatch, NC, true, T>(xrow, voff, row_bytes, chan_bytes, xdr, A.row_floats,
                                                          chan_floats, iw_ok, left);
