@@ -355,9 +355,9 @@ DWM_API dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan,
  * of classes where there is one (the same arithmetic in the same order: for tests).
  * (plan, "wide", v): 1 = the kernel from x to y for layers with many input channels (V stays in LDS, the products go
  * straight into the 2x2 outputs, same rounding points), DWM_ERR_INVALID_ARG where it does not apply or the planner expects
- * nothing of it (it needs 16 channels or more, an even W and a staged region that fits in LDS); 0 = never; v < 0: the
- * planner's choice (wherever it applies, unless a path or a stage's variant was asked for).  An x that is not on a
- * four-byte boundary takes the staged path.  It too needs the workspace to be set; forward_path stays 0.
+ * nothing of it (it needs 16 channels or more and a staged region that fits in LDS); 0 = never; v < 0: the
+ * planner's choice (wherever it applies, unless a path or a stage's variant was asked for).  It too needs the
+ * workspace to be set; forward_path stays 0.
  * dwm_f16_conv_forward_f32out is the same computation with y left in FP32 (not rounded): it
  * exists so that tests can compare everything before the last rounding.
  * dwm_f16_input_transform / dwm_f16_contract_output are the two stages of dwm_f16_conv_forward,

@@ -220,7 +220,7 @@ bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out)
     const DevPlan& d = p.d;
     Wide16Args f{};
     if (d.om.sy != 1 || d.om.sx != 1 || d.om.oy != 0 || d.om.ox != 0 || d.om.YH != d.OH || d.om.YW != d.OW) return false;
-    if (d.Ph < 0 || d.Pw < 0 || d.C < kWideC || d.s > 64 || (d.W & 1)) return false;
+    if (d.Ph < 0 || d.Pw < 0 || d.C < kWideC || d.s > 64) return false;
     int max_oh = 0, max_ow = 0, planes = 0;
     for (int i = 0; i < d.nh; ++i) max_oh = std::max(max_oh, d.s * (d.ph[i].j + d.ph[i].l) + d.ph[i].p);
     for (int i = 0; i < d.nw; ++i) max_ow = std::max(max_ow, d.s * (d.pw[i].j + d.pw[i].l) + d.pw[i].p);
@@ -234,7 +234,7 @@ bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out)
     f.lwp = (f.lw_in + f.nphase - 1) / f.nphase;
     f.row_px = f.nphase * f.lwp;
     f.rows_full = (int)rows_full;
-    f.npairs = d.W / 2;
+    f.npairs = (d.W + 1) / 2;
     const int s2 = 2 * d.s;
     const long long row_bytes = (long long)f.row_px * 2 * kWideC, px_bytes = 2 * kWideC,
                     room = 160 * 1024 - 2LL * f.v_bytes - 2 * px_bytes - 16LL * p.info.n_parts;
@@ -293,12 +293,14 @@ bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out)
 
     // Into how many pieces the channels are cut, and whether the kernel is worth taking (us; fitted to 23 layers, within 20 %
     // on most: csrc/half_wide.inc lists some).  A workgroup fills a CU; its launch, first loads and last stores take 9; a stage
-    // 0.75 and 0.055 for each of its planes (a share of pixels that no longer fits beside the products 0.7 per 1024 items);
+    // 0.75 and 0.055 for each of its planes (a share of pixels that no longer fits beside the products 0.7 per 1024 items;
+    // pixels one by one, where W is odd, 0.15 for every item of a thread);
     // pieces are added up by a kernel of its own, 4 and 0.2 per MB.
     double stages = 0.0;  // of one chunk
     const double items = (double)f.max_rows * f.npairs * 4 / f.nparts;
     for (int i = 0; i < kMaxClasses; ++i)
-        stages += f.cls[i].n * (0.75 + 0.055 * (4 - i / 3) * (4 - i % 3) + 0.7 * std::floor(items / 1024.0));
+        stages += f.cls[i].n * (0.75 + 0.055 * (4 - i / 3) * (4 - i % 3) + 0.7 * std::floor(items / 1024.0) +
+                               (d.W & 1 ? 0.15 * (items <= 256 ? 1 : items <= 512 ? 2 : 4) : 0.0));
     f.us = 1e30;
     for (int n = 1; n <= kWideMaxPieces && n <= f.chunks; ++n) {
         const int cpw = (f.chunks + n - 1) / n, pieces = (f.chunks + cpw - 1) / cpw;
@@ -315,7 +317,8 @@ bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out)
     // what few tiles cannot hide of a chunk's latency (49.6 us for 240 chunks of seven tiles, 18.4 for 16 of two)
     const double v = (double)p.info.mults_per_tile * d.C * d.T;
     const double staged = 15.0 + (4.0 * v + 2.0 * d.N * d.C * d.H * d.W) / 5e6 + 2.0 * v * d.K / 4e8 + 0.15 * p.geo.n_iter;
-    if (f.us >= staged) return false;
+    // (an odd W counts on less: 3x3 at stride 2 over 57x57 maps 63.9 -> 65.2, 7x7 over 27x27 maps 294 -> 195)
+    if (f.us >= (d.W & 1 ? 0.85 : 1.0) * staged) return false;
     *out = f;
     return true;
 }

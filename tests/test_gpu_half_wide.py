@@ -29,6 +29,10 @@ SHAPES = [  # N, C, H, W, K, R, S, stride, pad
     (1, 20, 66, 226, 24, 3, 3, 1, 0),    # wide rows: more than 1024 pairs of pixels a stage
     (3, 33, 5, 4, 17, 8, 8, 1, 4),       # kernel larger than the image
     (1, 30, 30, 34, 30, 7, 7, 4, 2),     # stride 4
+    (3, 120, 13, 17, 40, 3, 3, 2, 1),    # odd W: pixels one by one, a last pair of one pixel
+    (64, 40, 7, 7, 70, 3, 3, 1, 1),      # odd W, several images a block, two items a thread
+    (5, 67, 35, 29, 93, 5, 5, 2, 2),     # odd W, nothing a multiple of anything
+    (1, 40, 66, 225, 24, 3, 3, 1, 0),    # odd W, wide rows
 ]
 
 
@@ -84,7 +88,7 @@ def test_infinities_and_nan_stay_where_the_staged_path_has_them(fmt):
     assert float(np.max(np.abs(a[ok] - b[ok]))) <= th.TOL_F32OUT * float(np.max(np.abs(b[ok])))
 
 
-def test_x_off_a_four_byte_boundary_takes_the_staged_path():
+def test_x_off_a_four_byte_boundary():
     shape = (2, 32, 10, 12, 40, 3, 3, 1, 1)
     x, w, ref = _draw("f16", shape)
     r = _runner("f16", shape)
