@@ -527,7 +527,7 @@ static dwm_status_t launch_variant(const dwm_plan& p, const float* U, float* ws,
                        static_cast<const float*>(ws), y, partial);
     if (a.g.n_sk_tiles > 0) {
         const float* part = partial;
-        if (a.g.n_sk_tiles * WM * 4 < 2 * kNumCUs)
+        if (a.g.n_sk_tiles * WM * 4 < kNumCUs / 2)
             hipLaunchKernelGGL((split_sum_kernel<WGM, WGN, WM, true>), dim3((unsigned)a.g.n_sk_tiles, WM * 4 * WGM * WGN, 2), dim3(64), 0,
                                (hipStream_t)stream, a, part, y);
         else

@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) void input_transform_kernel(DevPlan P, const f
 // workgroups of four channels leave CUs without one, where a wave's chain of loads, rows and parts is the time: 13.0 ->
 // 11.7 us for a 5x5 layer at stride 2 (67 channels, five 35x29 images).
 // ---------------------------------------------------------------------------------
-template <int LH, int LW, bool SHARED>
+template <int LH, int LW, bool SHARED, bool TAIL>
 __device__ __forceinline__ void lds_class_rows(const DevPlan& P, const InLdsArgs& A, const DevClass& q,
                                                const float* __restrict__ xl, float* __restrict__ vb, int c0,
                                                int cn, int wave, bool valid, int& part)
@@ -310,16 +310,17 @@ __device__ __forceinline__ void lds_class_rows(const DevPlan& P, const InLdsArgs
 #pragma unroll
                     for (int j = 0; j < TW_; ++j) rowv[j] = tmp[i][j];
                     bt_apply<LW>(rowv, o);
-                    if (valid) {
+                    if (TAIL || valid) {
 #pragma unroll
-                        for (int j = 0; j < TW_; ++j) vp[(size_t)(i * TW_ + j) * plane] = o[j];
+                        for (int j = 0; j < TW_; ++j) vp[(size_t)(i * TW_ + j) * plane] = valid ? o[j] : 0.f;
                     }
                 }
             }
         }
 }
 
-// TAIL: the columns past the last tile of the last block are written as zeros (a run-time switch cost the 7x7 layer 1 %)
+// TAIL: the columns past the last tile of the last block are written as zeros (a launch of its own took 4 us; stores after
+// the rows' 2.5 for a 9x9 layer at stride 4, whose rows are many)
 template <bool SHARED, bool TAIL>
 __global__ __launch_bounds__(256) void input_transform_lds_kernel(DevPlan P, InLdsArgs A,
                                                                   const float* __restrict__ x,
@@ -372,31 +373,21 @@ __global__ __launch_bounds__(256) void input_transform_lds_kernel(DevPlan P, InL
     for (int qi = 0; qi < P.ncls; ++qi) {
         const DevClass q = P.cls[qi];
         switch (q.lh * 4 + q.lw) {
-            case 3 * 4 + 3: lds_class_rows<3, 3, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            case 3 * 4 + 2: lds_class_rows<3, 2, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            case 3 * 4 + 1: lds_class_rows<3, 1, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            case 2 * 4 + 3: lds_class_rows<2, 3, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            case 2 * 4 + 2: lds_class_rows<2, 2, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            case 2 * 4 + 1: lds_class_rows<2, 1, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            case 1 * 4 + 3: lds_class_rows<1, 3, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            case 1 * 4 + 2: lds_class_rows<1, 2, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
-            default: lds_class_rows<1, 1, SHARED>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 3 * 4 + 3: lds_class_rows<3, 3, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 3 * 4 + 2: lds_class_rows<3, 2, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 3 * 4 + 1: lds_class_rows<3, 1, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 2 * 4 + 3: lds_class_rows<2, 3, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 2 * 4 + 2: lds_class_rows<2, 2, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 2 * 4 + 1: lds_class_rows<2, 1, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 1 * 4 + 3: lds_class_rows<1, 3, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            case 1 * 4 + 2: lds_class_rows<1, 2, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
+            default: lds_class_rows<1, 1, SHARED, TAIL>(P, A, q, xl, vb, c0, cn, wave, valid, part); break;
         }
         // rows past the class's reduction length are zeros (the contraction multiplies them)
-        if (bc == 0 && valid && write_pad_rows) {
+        if (bc == 0 && (TAIL || valid) && write_pad_rows) {
             const int planes = (q.lh + 1) * (q.lw + 1);
             for (int l = q.L + wave; l < q.Lpad; l += 4)
                 for (int pl = 0; pl < planes; ++pl) vb[((size_t)q.v_row0 + (size_t)pl * q.Lpad + l) * 64] = 0.f;
-        }
-    }
-    if (TAIL && !valid) {
-        for (int qi = 0; qi < P.ncls; ++qi) {
-            const DevClass q = P.cls[qi];
-            const int planes = (q.lh + 1) * (q.lw + 1), pads = bc == 0 && write_pad_rows ? q.Lpad - q.L : 0;
-            for (int i = wave; i < q.hn * q.wn * cn + pads; i += 4) {
-                const int l = i < q.hn * q.wn * cn ? i / cn * P.C + c0 + i % cn : q.L + i - q.hn * q.wn * cn;
-                for (int pl = 0; pl < planes; ++pl) vb[((size_t)q.v_row0 + (size_t)pl * q.Lpad + l) * 64] = 0.f;
-            }
         }
     }
 }
