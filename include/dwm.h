@@ -356,12 +356,13 @@ DWM_API dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan,
  * (plan, "wide", v): 1 = the kernel from x to y for layers with many input channels (V stays in LDS, the products go
  * straight into the 2x2 outputs, same rounding points), DWM_ERR_INVALID_ARG where it does not apply or the planner expects
  * nothing of it (it needs 16 channels or more and a staged region that fits in LDS); 0 = never; v < 0: the
- * planner's choice (wherever it applies, unless a path or a stage's variant was asked for).  It too needs the
- * workspace to be set; forward_path stays 0.
+ * planner's choice (1 wherever that is accepted, unless a path or a stage's variant was asked for or the single kernel for
+ * few channels is in use).  It too needs the workspace to be set; forward_path stays 0, so that 0 stands for either.
  * dwm_f16_conv_forward_f32out is the same computation with y left in FP32 (not rounded): it
  * exists so that tests can compare everything before the last rounding.
- * dwm_f16_input_transform / dwm_f16_contract_output are the two stages of dwm_f16_conv_forward,
- * exposed for timing.
+ * dwm_f16_input_transform / dwm_f16_contract_output are the two stages of the staged path, exposed for timing: V of x in
+ * the workspace, then y from it.  dwm_f16_conv_forward runs them only where it takes that path (asked for with
+ * (plan, "forward", 0)); on the other two it neither makes V nor touches the one in the workspace.
  */
 typedef struct dwm_f16_plan dwm_f16_plan_t;
 typedef unsigned short dwm_half_t;

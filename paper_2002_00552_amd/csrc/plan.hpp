@@ -274,7 +274,8 @@ struct Wide16Args {
     size_t lds_bytes, u_bytes, uw_words;
     double us;                  // time by the planner's model
 };
-// partial_room: bytes that the pieces' outputs may take in the workspace; false where it does not apply or does not pay
+// partial_room: bytes that the pieces' outputs may take in the workspace (they lie behind V; V's own size is allowed, so that
+// the workspace grows by no more than that); false where it does not apply or does not pay
 bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out);
 
 // Geometry of the LDS-staged input transform (transforms.hip): a workgroup stages the input

@@ -104,3 +104,30 @@ def test_x_off_a_four_byte_boundary():
     finally:
         r.close()
     assert float(np.max(np.abs(y.cpu().numpy() - ref))) <= th.TOL_F32OUT * float(np.max(np.abs(ref)))
+
+
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", [
+    (1, 256, 14, 14, 256, 3, 3, 1, 1),   # cut into eight pieces
+    (2, 100, 21, 16, 96, 6, 6, 2, 2),    # seven, the filter in a copy of its own
+    (1, 16, 8, 8, 16, 3, 3, 1, 1),       # uncut
+])
+def test_a_whole_call_between_the_two_stages_leaves_v_alone(shape, fmt):
+    x, w, _ = _draw(fmt, shape)
+    staged = (th.HalfRunner if fmt == "f16" else tb.Bf16Runner)(*shape, forward=0)
+    r = _runner(fmt, shape)
+    fn = lambda name: getattr(dwm, "dwm_%s_%s" % (fmt, name))  # noqa: E731
+    try:
+        want = staged.run(x, w)
+        r.run(x, w)  # (transforms the filter)
+        st = torch.cuda.current_stream().cuda_stream
+        xd = torch.from_numpy(np.ascontiguousarray(x)).to(torch.float16 if fmt == "f16" else torch.bfloat16).cuda()
+        y, y2 = (torch.full(r.shape_y, float("nan"), dtype=xd.dtype, device="cuda") for _ in range(2))
+        fn("input_transform")(r.plan, xd.data_ptr(), st)
+        fn("conv_forward")(r.plan, xd.data_ptr(), r.U.data_ptr(), y.data_ptr(), st)
+        fn("contract_output")(r.plan, r.U.data_ptr(), y2.data_ptr(), st)
+        torch.cuda.synchronize()
+    finally:
+        staged.close()
+        r.close()
+    assert np.array_equal(y2.float().cpu().numpy(), np.asarray(want, np.float32))
