@@ -228,9 +228,11 @@ def bench_backward_filter(args, L, x, w):
 def bench_half(args, L, x, w, bf16=False):
     """A step = one dwm_f16_conv_forward (binary16 x, U, V, y; FP16 MFMA with FP32 accumulation) or,
     with bf16, one dwm_bf16_conv_forward (the same with bfloat16) on resident buffers; the filter
-    transform runs once before.  With 16-bit operands the contraction's arithmetic intensity (about
-    200 flop per byte of V, U and y) is below the chip's balance of 2.5 PFLOP/s : 8 TB/s, so both
-    stages are priced against the HBM roofline."""
+    transform runs once before.  Three paths, each described as what it is: the staged one, whose
+    contraction's arithmetic intensity (about 200 flop per byte of V, U and y) is below the chip's
+    balance of 2.5 PFLOP/s : 8 TB/s, so both its stages are priced against the HBM roofline; the
+    single kernel for few input channels, priced likewise; the one for many, which multiplies as
+    often as the plain convolution does and is priced against the 16-bit matrix cores."""
     import numpy as np
     import torch
 
@@ -248,6 +250,14 @@ def bench_half(args, L, x, w, bf16=False):
         fn("set_variant")(plan, "forward", args.forward_variant)
     info = fn("plan_info")(plan)
     single = info.forward_path == 1
+    # forward_path says 0 for the staged path and for the kernel for many channels; the latter is the default wherever it
+    # can be asked for, if nothing else was
+    wide = not single and args.contract_variant < 0 and args.forward_variant < 0
+    if wide:
+        try:
+            fn("set_variant")(plan, "wide", 1)
+        except dwm.DwmError:
+            wide = False
     U = torch.empty(fn("filter_bytes")(plan) // 2, dtype=tdt, device="cuda")
     ws = torch.empty(max(fn("workspace_bytes")(plan), 256), dtype=torch.uint8, device="cuda")
     y = torch.empty((L.N, L.K, info.OH, info.OW), dtype=tdt, device="cuda")
@@ -274,7 +284,19 @@ def bench_half(args, L, x, w, bf16=False):
         return e0.elapsed_time(e1) / args.steps
 
     x_bytes, y_bytes = 2.0 * x.size, 2.0 * y.numel()
-    if single:
+    if wide:
+        # one kernel (and, where the channels are cut, the sum of the pieces): V never leaves the CU
+        k_ms = timed(lambda: fn("conv_forward")(plan, xp, Up, yp, st))
+        stages = {
+            "wide16_forward": {"ms": k_ms, "bound": "mfma", "algorithmic_flops": info.direct_flops,
+                               "achieved_TFLOPs": info.direct_flops / k_ms / 1e9,
+                               "frac_of_f16_mfma_peak": info.direct_flops / k_ms / 1e9 / PEAK_MFMA_F16,
+                               "algorithmic_bytes": x_bytes + y_bytes,
+                               "achieved_GBps": (x_bytes + y_bytes) / k_ms / 1e6,
+                               "frac_of_hbm_peak": (x_bytes + y_bytes) / k_ms / 1e6 / PEAK_HBM},
+        }
+        dom = "wide16_forward"
+    elif single:
         # one kernel: x and y cross HBM once, V never leaves the registers
         k_ms = timed(lambda: fn("conv_forward")(plan, xp, Up, yp, st))
         stages = {
@@ -309,10 +331,13 @@ def bench_half(args, L, x, w, bf16=False):
         "value": info.direct_flops / dt / 1e12, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": dt * 1e3, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "bf16" if bf16 else "f16", "data": "synthetic",
-        "config": {"workload": L.name + ("_bf16" if bf16 else "_half"), "path": "single kernel" if single else "staged",
+        "config": {"workload": L.name + ("_bf16" if bf16 else "_half"), "path": "single kernel for many channels" if wide else "single kernel" if single else "staged",
                    "parts": info.n_parts, "mults_per_tile": info.mults_per_tile,
                    "direct_GFLOP": info.direct_flops / 1e9, "winograd_GFLOP": info.winograd_flops / 1e9},
-        "roofline": {"kernel": {"contract_output": "contract16_kernel", "input_transform": "input_transform_f16_kernel",
+        "roofline": {"kernel": "wide16_kernel", "bound": "mfma", "achieved": stages[dom]["achieved_TFLOPs"],
+                     "peak": PEAK_MFMA_F16, "unit": "TFLOP/s", "frac": stages[dom]["frac_of_f16_mfma_peak"],
+                     "traffic": None} if wide else
+                    {"kernel": {"contract_output": "contract16_kernel", "input_transform": "input_transform_f16_kernel",
                                 "fused16_forward": "fused16_forward_kernel"}[dom],
                      "bound": "hbm", "achieved": stages[dom]["achieved_GBps"], "peak": PEAK_HBM, "unit": "GB/s",
                      "frac": stages[dom]["frac_of_hbm_peak"], "traffic": None},
@@ -320,6 +345,9 @@ def bench_half(args, L, x, w, bf16=False):
     }
     if not args.no_check:
         import oracle
+        y.fill_(float("nan"))  # (the stages above write y too: what is checked is the timed call's)
+        fn("conv_forward")(plan, xp, Up, yp, st)
+        torch.cuda.synchronize()
         yh = y.float().cpu().numpy()
         idx = np.random.default_rng(99).choice(yh.size, min(yh.size, 40000), replace=False)
         ref = oracle.direct_f64_at(x16.astype(np.float32), w16.astype(np.float32), L.stride, L.pad, idx)
