@@ -315,10 +315,112 @@ static int walk_fused16(int N, int C, int H, int W, int K, int R, int S, int s, 
     return 1;
 }
 
+// The 16-bit kernel for many channels: its geometry (setup.cpp) on the plan cut as eq. 8 prints it, and the kernel's address
+// arithmetic replayed from it.  Every pixel of the image that a block of tiles needs has one place in the staged region, every
+// patch element of every tile is read from its pixel's place (or from a place that nobody writes, where it lies outside the
+// image), the regions fit in LDS, the filter's words lie inside its copy, and the pieces cover the channels.
+// got, if given: parts, pieces, chunks of a piece, pixels a thread stages beside a stage's products (1, 2 or 4).
+static int walk_wide16(int N, int C, int H, int W, int K, int R, int S, int s, int P, int* got = nullptr)
+{
+    using namespace dwm;
+    if (N < 1 || C < 1 || H < 1 || W < 1 || K < 1 || R < 1 || S < 1 || s < 1 || P < 0) return 0;
+    if (H + 2 * P < R || W + 2 * P < S) return 0;
+    PlanSpec sp{};
+    sp.N = N; sp.C = C; sp.H = H; sp.W = W; sp.K = K; sp.R = R; sp.S = S; sp.stride = s;
+    sp.pad_h = sp.pad_w = P;
+    sp.OH = (H + 2 * P - R) / s + 1;
+    sp.OW = (W + 2 * P - S) / s + 1;
+    sp.om = OutMap{sp.OH, sp.OW, 1, 0, 1, 0};
+    dwm_plan_t* p = nullptr;
+    if (plan_from_spec_as_printed(&p, sp) != DWM_OK) return 0;
+    Wide16Args f;
+    const size_t room = (p->v_floats * 2 + 255) / 256 * 256;
+    if (!contract_geometry(*p, p->lgran >= 64 ? (K > 64 ? 44 : 32) : p->lgran >= 32 ? 31 : 30, &p->geo) || !wide16_setup(*p, room, &f)) {
+        dwm_plan_destroy(p);
+        return 0;
+    }
+    const DevPlan& d = p->d;
+    const int px = 8, s2 = 2 * s;
+    int planes = 0, parts = 0;
+    for (int i = 0; i < d.ncls; ++i) {
+        planes = (d.cls[i].lh + 1) * (d.cls[i].lw + 1) > planes ? (d.cls[i].lh + 1) * (d.cls[i].lw + 1) : planes;
+        parts += d.cls[i].hn * d.cls[i].wn;
+    }
+    CHECK(C >= kWideC && f.chunks == (C + kWideC - 1) / kWideC && f.nparts == parts && f.nparts == p->info.n_parts);
+    CHECK(f.nkt * kWideK >= K && f.ntt * kWideT >= d.T && (f.ntt - 1) * kWideT < d.T);
+    CHECK(f.nsplit >= 1 && f.nsplit <= kWideMaxPieces && f.nsplit * f.cpw >= f.chunks && (f.nsplit - 1) * f.cpw < f.chunks);
+    CHECK(f.nsplit == 1 || (size_t)f.nkt * f.ntt * f.nsplit * kWideK * kWideT * 16 <= room);
+    // LDS: two stages' V, two chunks' pixels, the tables; at the end the two groups' outputs
+    CHECK(f.v_bytes == planes * kWideT * kWideC * 2 && f.x_bytes >= f.x_px * 4 * px && f.x_bytes % 16 == 0);
+    CHECK((size_t)2 * f.v_bytes + 2 * f.x_bytes + 16 * f.nparts + 8 * (size_t)f.max_rows * f.npairs <= f.lds_bytes);
+    CHECK(f.lds_bytes >= (size_t)kWideExchangeBytes && f.lds_bytes <= 160 * 1024);
+    CHECK(4 * f.x_px < 65536);  // a pixel's place among four groups of channels travels in 16 bits
+    // the filter: every word that a wave reads (128 filters a block, a row of eight channels a word) lies inside the copy
+    for (int i = 0; i < d.ncls; ++i) {
+        const DevClass& q = d.cls[i];
+        const Wide16Class& c = f.cls[(3 - q.lh) * 3 + (3 - q.lw)];
+        const size_t np = (size_t)(q.lh + 1) * (q.lw + 1);
+        CHECK((f.has >> ((3 - q.lh) * 3 + (3 - q.lw)) & 1) && c.n == q.hn * q.wn && c.wn == q.wn && c.h0 == q.h0 && c.w0 == q.w0);
+        CHECK((size_t)f.nkt * kWideK <= (size_t)d.Kpad + kWideK - 1);
+        const size_t last_row = ((size_t)(c.n - 1) * f.rows_per_part + (size_t)f.chunks * kWideC) / 8;  // past the last
+        CHECK(last_row * d.Kpad * 16 <= c.plane_bytes && c.u_off + np * c.plane_bytes <= f.u_bytes && f.u_bytes < ((size_t)1 << 31));
+        if (!f.own_copy) CHECK((long long)c.u_off == 2 * q.u_off && c.plane_bytes == (unsigned)q.Lpad * d.Kpad * 2 && f.rows_per_part == C);
+    }
+    CHECK(f.own_copy ? f.uw_words * 16 == f.u_bytes : f.uw_words == 0 && f.u_bytes <= p->filter_floats * 2);
+    // blocks of tiles: the first, the second, the last and one between
+    const int blocks[4] = {0, f.ntt > 1 ? 1 : 0, f.ntt - 1, (int)(rnd() % (unsigned)f.ntt)};
+    for (const int bt : blocks) {
+        const int t0 = bt * kWideT, t1 = t0 + kWideT - 1 < d.T - 1 ? t0 + kWideT - 1 : d.T - 1;
+        const int g0 = t0 / d.TW, g1 = t1 / d.TW, n0 = g0 / d.TH, n1 = g1 / d.TH, ty_a0 = g0 - n0 * d.TH, ty_b1 = g1 - n1 * d.TH;
+        const int rows0 = s2 * ((n1 == n0 ? ty_b1 : d.TH - 1) - ty_a0) + f.foot_h;
+        std::vector<long long> place((size_t)f.x_px, -1);  // the pixel of x each place holds (channel 0)
+        long long pairs = 0;
+        int row = 0;
+        for (int n = n0; n <= n1; ++n) {
+            const int ty_a = n == n0 ? ty_a0 : 0, ty_b = n == n1 ? ty_b1 : d.TH - 1;
+            const int cnt = s2 * (ty_b - ty_a) + f.foot_h, ih0 = s2 * ty_a - d.Ph;
+            const int below = -ih0 > 0 ? -ih0 : 0, lo = below < cnt ? below : cnt;
+            const int inside = H - ih0 < cnt ? H - ih0 : cnt, hi = inside > lo ? inside : lo;
+            pairs += (long long)(hi - lo) * f.npairs;
+            for (int r = lo; r < hi; ++r)
+                for (int c = 0; c < 2 * f.npairs; ++c) {
+                    const int col = c + d.Pw;
+                    if (col >= f.lw_in || c >= W) continue;
+                    const int at = (row + r) * f.row_px + col % f.nphase * f.lwp + col / f.nphase;
+                    CHECK(at < f.x_px - 1 && place[(size_t)at] < 0);
+                    place[(size_t)at] = ((long long)n * C * H + ih0 + r) * W + c;
+                    CHECK(2 * (place[(size_t)at] - (long long)n0 * C * H * W + (long long)(C - 1) * H * W) + 4 < (1LL << 31));
+                }
+            row += cnt;
+        }
+        CHECK(row <= f.max_rows && pairs <= (long long)f.max_rows * f.npairs);
+        for (int t = t0; t <= t1; ++t) {
+            const int gg = t / d.TW, tx = t - gg * d.TW, n = gg / d.TH, ty = gg - n * d.TH;
+            const int r0 = n == n0 ? s2 * (ty - ty_a0) : rows0 + (n - n0 - 1) * f.rows_full + s2 * ty;
+            for (int a = 0; a < d.nh; ++a)
+                for (int b = 0; b < d.nw; ++b)
+                    for (int i = 0; i <= d.ph[a].l; ++i)
+                        for (int j = 0; j <= d.pw[b].l; ++j) {
+                            const int bytes = (r0 * f.row_px + tx) * px + f.roff[a] + i * f.row_step + f.coff[b][j & 1] + (j >> 1) * px;
+                            CHECK(bytes % px == 0 && bytes / px < f.x_px - 1);
+                            const int ih = s * (2 * ty + d.ph[a].j + i) + d.ph[a].p - d.Ph, iw = s * (2 * tx + d.pw[b].j + j) + d.pw[b].p - d.Pw;
+                            const bool in = ih >= 0 && ih < H && iw >= 0 && iw < W;
+                            CHECK(place[(size_t)(bytes / px)] == (in ? ((long long)n * C * H + ih) * W + iw : -1));
+                        }
+        }
+    }
+    if (got) {
+        const int per = (f.max_rows * f.npairs * 4 + f.nparts - 1) / f.nparts;
+        got[0] = f.nparts; got[1] = f.nsplit; got[2] = f.cpw; got[3] = per <= 256 ? 1 : per <= 512 ? 2 : 4;
+    }
+    dwm_plan_destroy(p);
+    return 1;
+}
+
 int main(int argc, char** argv)
 {
     const int iters = argc > 1 ? std::atoi(argv[1]) : 3000;
-    int ok = 0, tried = 0, small = 0, single16 = 0;
+    int ok = 0, tried = 0, small = 0, single16 = 0, wide16 = 0;
     // the benchmark layers and corner shapes first
     const int fixed[][9] = {
         {1, 16, 32, 32, 16, 5, 5, 1, 2},   {32, 128, 56, 56, 256, 3, 3, 2, 1}, {32, 256, 28, 28, 256, 7, 7, 1, 3},
@@ -335,6 +437,7 @@ int main(int argc, char** argv)
         ok += walk(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7], f[8]);
         small += walk_bwd_small(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7], f[8]);
         single16 += walk_fused16(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7], f[8]);
+        wide16 += walk_wide16(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7], f[8]);
     }
     // the contraction the planner picks: the three-stage ring of 32-row chunks (11) for three rounds of tiles and for
     // long reductions above one tile per CU, the two-stage ring of 64-row chunks (12) otherwise
@@ -370,6 +473,37 @@ int main(int argc, char** argv)
             CHECK(dwm_plan_destroy(p) == DWM_OK);
         }
     }
+    // the 16-bit kernel for many channels: what the layers of tests/test_gpu_half_wide.py (STAGED_LATER) are there for -- parts,
+    // pieces, chunks of a piece (three and more: pixels staged beside the products, in both buffers), pixels a thread stages
+    {
+        const int pinned[][13] = {
+            {3, 83, 6, 30, 130, 4, 4, 1, 1, 4, 2, 3, 1},
+            {1, 99, 7, 6, 260, 3, 3, 2, 1, 4, 3, 3, 1},
+            {16, 65, 9, 6, 260, 7, 7, 1, 3, 9, 2, 3, 1},
+            {23, 61, 36, 40, 20, 10, 10, 1, 4, 16, 1, 4, 1},
+            {2, 132, 34, 5, 260, 4, 4, 1, 1, 4, 3, 3, 1},
+            {8, 41, 9, 9, 260, 7, 7, 1, 3, 9, 1, 3, 1},
+            {18, 102, 29, 39, 20, 10, 10, 1, 4, 16, 3, 3, 1},
+            {7, 35, 7, 8, 20, 3, 5, 1, 1, 2, 1, 3, 2},
+            {16, 131, 10, 10, 20, 3, 3, 2, 1, 4, 3, 3, 2},
+            {24, 40, 4, 6, 40, 5, 5, 1, 2, 4, 3, 1, 2},
+            {2, 108, 14, 14, 300, 3, 3, 1, 1, 1, 1, 7, 4},
+            {4, 34, 31, 37, 20, 4, 4, 1, 1, 4, 1, 3, 2},
+            {13, 112, 23, 5, 20, 3, 3, 2, 1, 4, 3, 3, 2},
+            {1, 108, 38, 5, 130, 3, 3, 1, 1, 1, 3, 3, 2},
+            {6, 39, 9, 32, 20, 3, 3, 2, 1, 4, 1, 3, 4},
+            {17, 66, 8, 18, 20, 3, 3, 2, 1, 4, 2, 3, 4},
+            {64, 48, 28, 28, 300, 3, 3, 1, 1, 1, 1, 3, 4},
+            {9, 44, 23, 33, 130, 6, 6, 2, 2, 4, 1, 3, 4},
+            {12, 69, 5, 5, 130, 3, 5, 1, 1, 2, 2, 3, 4},
+            {1, 40, 66, 226, 24, 3, 3, 1, 0, 1, 1, 3, 4},
+        };
+        for (const auto& f : pinned) {
+            int got[4] = {0, 0, 0, 0};
+            CHECK(walk_wide16(f[0], f[1], f[2], f[3], f[4], f[5], f[6], f[7], f[8], got) == 1);
+            for (int i = 0; i < 4; ++i) CHECK(got[i] == f[9 + i]);
+        }
+    }
     CHECK(dwm_plan_create(nullptr, 1, 1, 3, 3, 1, 3, 3, 1, 1) == DWM_ERR_INVALID_ARG);
     CHECK(dwm_plan_destroy(nullptr) == DWM_ERR_INVALID_ARG);
     CHECK(dwm_plan_filter_bytes(nullptr) == 0 && dwm_plan_workspace_bytes(nullptr) == 0);
@@ -383,9 +517,11 @@ int main(int argc, char** argv)
         ok += walk(N, C, H, W, K, R, S, s, P);
         small += walk_bwd_small(N, C < 20 ? C : C % 9 + 1, H, W, K, R, S, s, P);
         single16 += walk_fused16(N, C < 20 ? C : C % 9 + 1, H, W, K, R, S, s, P);
+        wide16 += walk_wide16(N, C < 16 ? C + 16 : C, H, W, K, R, S, s, P);
     }
-    CHECK(small > tried / 8 && single16 > tried / 8);
-    std::printf("planner fuzz: %d shapes tried, %d planned, %d with a single-kernel data gradient, %d with a 16-bit single kernel\n",
-                tried, ok, small, single16);
+    CHECK(small > tried / 8 && single16 > tried / 8 && wide16 > tried / 8);
+    std::printf("planner fuzz: %d shapes tried, %d planned, %d with a single-kernel data gradient, %d with a 16-bit single kernel, "
+                "%d with the one for many channels\n",
+                tried, ok, small, single16, wide16);
     return ok > tried / 2 ? 0 : 3;
 }

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [  # N, C, H, W, K, R, S, stride, pad
     (5, 67, 35, 29, 93, 5, 5, 2, 2),     # unequal grids, pieces that do not divide a tile's chunks
     (1, 17, 9, 8, 200, 3, 3, 2, 1),      # one tile a sub-convolution; 1-tap phases: a piece count of one beside longer ones
-    (2, 20, 21, 21, 40, 7, 7, 2, 3),     # sub-convolutions of sixteen pieces of the kernel, odd image
+    (2, 20, 21, 21, 40, 7, 7, 2, 3),     # sub-convolutions of up to four parts, odd image
     (2, 33, 20, 20, 64, 4, 4, 3, 1),     # stride 3: nine sub-convolutions
     (1, 18, 23, 19, 70, 5, 5, 4, 2),     # stride 4: more sub-convolutions than one filter launch takes
     (1, 65, 31, 30, 130, 6, 3, 2, 0),    # R != S, filters one past a tile, rows and columns no tap reaches

@@ -268,7 +268,7 @@ def test_repeated_calls_give_identical_bits():
 
 @pytest.mark.parametrize("index", [1, 2])
 def test_full_size_layers_sampled(index):
-    """The benchmark layers at full size, in the launch configuration bench.py times: sampled
+    """The benchmark layers at full size on the staged path (the planner takes another): sampled
     outputs against the exact convolution of the binary16 inputs.  The half-precision result may
     be off by what binary16 storage of U, V and y costs: a few 2^-11 of the largest output."""
     L = wl.CONFIGS[index]

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import dwm_workloads as wl
 import oracle
 import paper_2002_00552_amd as dwm
 import test_gpu_bf16 as tb
@@ -22,7 +23,7 @@ SHAPES = [  # N, C, H, W, K, R, S, stride, pad
     (1, 64, 14, 14, 129, 7, 7, 1, 3),    # nine parts, one filter over a block
     (2, 48, 12, 12, 33, 7, 3, 3, 1),     # stride 3, R != S
     (5, 35, 7, 10, 130, 4, 4, 1, 1),     # (3,3) (3,1) ..., five images in few blocks
-    (9, 24, 4, 6, 40, 5, 5, 1, 2),       # six tiles an image: eleven images a block
+    (9, 24, 4, 6, 40, 5, 5, 1, 2),       # six tiles an image: all nine images in one block
     (1, 19, 40, 40, 20, 11, 11, 1, 5),   # sixteen parts
     (2, 100, 21, 16, 96, 6, 6, 2, 2),    # seven chunks
     (1, 256, 14, 14, 256, 3, 3, 1, 1),   # one stage a chunk, cut into pieces
@@ -30,10 +31,49 @@ SHAPES = [  # N, C, H, W, K, R, S, stride, pad
     (3, 33, 5, 4, 17, 8, 8, 1, 4),       # kernel larger than the image
     (1, 30, 30, 34, 30, 7, 7, 4, 2),     # stride 4
     (3, 120, 13, 17, 40, 3, 3, 2, 1),    # odd W: pixels one by one, a last pair of one pixel
-    (64, 40, 7, 7, 70, 3, 3, 1, 1),      # odd W, several images a block, two items a thread
+    (64, 40, 7, 7, 70, 3, 3, 1, 1),      # odd W, several images a block, four items a thread
     (5, 67, 35, 29, 93, 5, 5, 2, 2),     # odd W, nothing a multiple of anything
     (1, 40, 66, 225, 24, 3, 3, 1, 0),    # odd W, wide rows
 ]
+
+
+# Layers whose workgroups take three chunks of channels and more, so that pixels are staged beside the products, in both
+# buffers, and are read there: every form of the kernel (one, two or four items a thread, pairs or single pixels), one to
+# sixteen parts a chunk, whole and cut (tests/sanitize/planner_fuzz.cpp holds the planner to these geometries).
+STAGED_LATER = [
+    (3, 83, 6, 30, 130, 4, 4, 1, 1),     # four parts a chunk, two pieces of three
+    (1, 99, 7, 6, 260, 3, 3, 2, 1),      # stride 2, three filter blocks, the last piece one chunk
+    (16, 65, 9, 6, 260, 7, 7, 1, 3),     # nine parts, three filter blocks, the last piece shorter
+    (23, 61, 36, 40, 20, 10, 10, 1, 4),  # sixteen parts, 130 blocks of tiles, uncut
+    (2, 132, 34, 5, 260, 4, 4, 1, 1),    # odd W
+    (8, 41, 9, 9, 260, 7, 7, 1, 3),      # odd W, nine parts, uncut
+    (18, 102, 29, 39, 20, 10, 10, 1, 4), # odd W, sixteen parts, many workgroups, the last piece one chunk
+    (7, 35, 7, 8, 20, 3, 5, 1, 1),       # two pixels a thread, two parts, uncut
+    (16, 131, 10, 10, 20, 3, 3, 2, 1),   # two, stride 2, the last chunk three channels
+    (24, 40, 4, 6, 40, 5, 5, 1, 2),      # two; six tiles an image: eleven images and more a block
+    (2, 108, 14, 14, 300, 3, 3, 1, 1),   # four, one part a chunk, seven chunks
+    (4, 34, 31, 37, 20, 4, 4, 1, 1),     # two, odd W, uncut
+    (13, 112, 23, 5, 20, 3, 3, 2, 1),    # two, odd W, stride 2
+    (1, 108, 38, 5, 130, 3, 3, 1, 1),    # two, odd W, one part, the last piece one chunk
+    (6, 39, 9, 32, 20, 3, 3, 2, 1),      # four, stride 2, uncut
+    (17, 66, 8, 18, 20, 3, 3, 2, 1),     # four, stride 2
+    (64, 48, 28, 28, 300, 3, 3, 1, 1),   # four, one part, three filter blocks, 588 workgroups
+    (9, 44, 23, 33, 130, 6, 6, 2, 2),    # four, odd W, stride 2, uncut
+    (12, 69, 5, 5, 130, 3, 5, 1, 1),     # four, odd W, two parts
+    (1, 40, 66, 226, 24, 3, 3, 1, 0),    # more than 1024 pairs of pixels a stage in later chunks
+]
+
+# Long sums into one FP32 accumulator, uncut but for the third, at sizes of real use: error against the oracle relative to the
+# largest output, staged path / this kernel: 4.3e-7 / 9.5e-7, 1.9e-7 / 3.0e-7, 7.3e-7 / 8.4e-7, 2.5e-7 / 8.5e-7; all-positive
+# data 7.4e-7 / 1.3e-6 at most.  An output of the first layer adds up 392 MFMAs in each of its two accumulators (49 taps, half
+# of sixteen chunks), each rounding to 2^-24 of the sum so far: 2^-24 * sqrt(392) = 1.2e-6 if independent; the bar is four times that.
+LONG_SUMS = [
+    (32, 256, 28, 28, 256, 7, 7, 1, 3),
+    (32, 128, 56, 56, 256, 3, 3, 2, 1),
+    (32, 384, 14, 14, 384, 11, 11, 1, 5),
+    (128, 384, 14, 14, 256, 5, 5, 1, 2),
+]
+TOL_LONG = 5e-6
 
 
 def _draw(fmt, shape):
@@ -55,7 +95,7 @@ def _runner(fmt, shape):
 
 
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", SHAPES + STAGED_LATER)
 def test_wide_kernel_against_the_oracle(shape, fmt):
     x, w, ref = _draw(fmt, shape)
     r = _runner(fmt, shape)
@@ -131,3 +171,56 @@ def test_a_whole_call_between_the_two_stages_leaves_v_alone(shape, fmt):
         staged.close()
         r.close()
     assert np.array_equal(y2.float().cpu().numpy(), np.asarray(want, np.float32))
+
+
+@pytest.mark.parametrize("dist", ["uniform", "relu", "positive"])
+@pytest.mark.parametrize("shape", LONG_SUMS)
+def test_long_sums_with_the_planners_choice(shape, dist):
+    """The whole batch through the planner's choice; its first image, left in FP32, element by element, in both formats."""
+    N, C, H, W, K, R, S, s, P = shape
+    rng = np.random.default_rng(5)
+    x = rng.uniform(-1, 1, (N, C, H, W)).astype(np.float32) if dist == "uniform" else rng.standard_normal((N, C, H, W), dtype=np.float32)
+    w = (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32)
+    x = np.maximum(x, 0) if dist == "relu" else np.abs(x) if dist == "positive" else x
+    w = np.abs(w) if dist == "positive" else w
+    for fmt, cls in (("f16", th.HalfRunner), ("bf16", tb.Bf16Runner)):
+        if fmt == "f16":
+            a, b = x.astype(np.float16), w.astype(np.float16)
+            ref = oracle.dwm_half_f64(a[:1], b, s, P)
+        else:
+            a, b = (torch.from_numpy(v).to(torch.bfloat16).float().numpy() for v in (x, w))
+            ref = oracle.dwm_bf16_f64(a[:1], b, s, P)
+        r = cls(*shape, forward=-1)
+        try:
+            getattr(dwm, "dwm_%s_set_variant" % fmt)(r.plan, "wide", 1)  # accepted: what the planner chooses
+            getattr(dwm, "dwm_%s_set_variant" % fmt)(r.plan, "wide", -1)
+            y = r.run(a, b, f32out=True)
+        finally:
+            r.close()
+        assert np.all(np.isfinite(y))
+        assert float(np.max(np.abs(y[:1] - ref))) <= TOL_LONG * float(np.max(np.abs(ref))), fmt
+
+
+@pytest.mark.parametrize("fmt", ["f16", "bf16"])
+@pytest.mark.parametrize("index", [1, 2])
+def test_full_size_layers_sampled_with_the_planners_choice(index, fmt):
+    """The two benchmark layers at full size, as bench.py times them: sampled 16-bit outputs against the exact convolution of the
+    16-bit inputs.  Bars: what 16-bit storage of U, V and y costs, as in the formats' own suites."""
+    L = wl.CONFIGS[index]
+    unit = 2.0 ** -11 if fmt == "f16" else 2.0 ** -8
+    x, w = wl.make_layer_tensors(L, index)
+    if fmt == "f16":
+        x, w = x.astype(np.float16), w.astype(np.float16)
+    else:
+        x, w = (torch.from_numpy(a).to(torch.bfloat16).float().numpy() for a in (x, w))
+    r = (th.HalfRunner if fmt == "f16" else tb.Bf16Runner)(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad, forward=-1)
+    try:
+        y = r.run(x, w)
+    finally:
+        r.close()
+    assert np.all(np.isfinite(y))
+    idx = np.random.default_rng(index).choice(y.size, size=4000, replace=False)
+    ref = oracle.direct_f64_at(np.asarray(x, np.float32), np.asarray(w, np.float32), L.stride, L.pad, idx)
+    got = y.reshape(-1)[idx].astype(np.float64)
+    assert np.max(np.abs(got - ref)) <= 8 * unit * float(np.max(np.abs(ref)))
+    assert np.sqrt(np.mean((got - ref) ** 2)) <= 2 * unit * np.sqrt(np.mean(ref ** 2))

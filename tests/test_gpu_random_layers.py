@@ -4,8 +4,8 @@ The shapes are drawn from a seeded generator that mixes what the hand-picked cas
 at a time: kernels of 1..13 taps (square or not), strides 1..8 (also above the kernel size), paddings up to the
 kernel size, few or many channels, images down to one pixel wide.  Every case runs the forward pass (the
 planner's path and the staged path), the entry point that allocates nothing, the data gradient (both paths where
-the single kernel applies), the filter gradient, and the binary16 and bfloat16 forward passes (staged and single
-kernel) -- the first mismatch names the path and the shape.
+the single kernel applies), the filter gradient, and the binary16 and bfloat16 forward passes (staged, single
+kernel, planner's choice) -- the first mismatch names the path and the shape.
 """
 import numpy as np
 import pytest
@@ -99,7 +99,7 @@ def _check_layer(shape, rng):
     wb = torch.from_numpy(w).to(torch.bfloat16).float().numpy()
     refb = oracle.dwm_bf16_f64(xb, wb, s, P)
     for name, cls, a, b_, r16 in (("binary16", HalfRunner, x16, w16, ref16), ("bfloat16", Bf16Runner, xb, wb, refb)):
-        for forward in (0, 1):
+        for forward in (0, 1, -1):  # staged, single kernel, the planner's choice (the kernel for many channels among them)
             try:
                 h = cls(*shape, forward=forward)
             except dwm.DwmError:
@@ -214,6 +214,12 @@ def test_random_medium_layers_split_modes_variants_and_repeats(seed):
             h.close()
         # against the exact convolution of the 16-bit inputs: the band of the format
         assert np.all(np.isfinite(y0)) and np.max(np.abs(y0.ravel()[idx] - ref16)) / np.max(np.abs(ref16)) <= 3e-3, shape
+        h = HalfRunner(*shape, forward=-1)  # (mostly the kernel for many channels)
+        try:
+            y = h.run(x16, w16, f32out=True)
+        finally:
+            h.close()
+        assert np.max(np.abs(y - y0)) / np.max(np.abs(ref16)) <= TOL16, ("binary16, planner's choice", shape)
         for _ in range(2):
             try:
                 h = HalfRunner(*shape, forward=0, variant=int(rng.integers(30, 48)), input_variant=int(rng.integers(0, 2)))
