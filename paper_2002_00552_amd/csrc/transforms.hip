@@ -395,8 +395,6 @@ __global__ __launch_bounds__(256) void input_transform_lds_kernel(DevPlan P, InL
 // ---------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------
-constexpr long long kSharedInput = kNumCUs;
-
 static dwm_status_t check_launch()
 {
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
@@ -453,8 +451,7 @@ static dwm_status_t launch_input(const dwm_plan& p, const float* x, float* V, vo
         auto kernel = zero_tail ? input_transform_lds_kernel<false, true> : input_transform_lds_kernel<false, false>;
         // a channel a workgroup: up to one workgroup of four channels a CU (beyond, others' waves hide a wave's chain: 5x5
         // at stride 2 over 73 channels with 437 of them, whole call, 36.0 -> 37.8), and a part for every wave
-        if (p.variant_input < 0 && a.cg == 4 && (long long)((d.T + 63) / 64) * a.ncg <= kSharedInput &&
-            parts >= 4) {
+        if (p.variant_input < 0 && a.cg == 4 && (long long)((d.T + 63) / 64) * a.ncg <= kNumCUs && parts >= 4) {
             a.cg = 1;
             a.ncg = d.C;
             a.lds_bytes = (size_t)a.chan_floats * sizeof(float);

@@ -950,11 +950,11 @@ dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan, const f
     float* dM = plan->ws + plan->fwd_ws_bytes / sizeof(float);
     float* partial = dM + plan->dm_bytes / sizeof(float);
     // 1. V = B^T d B (and zeros in the columns past the last tile)
-    const bool tail = (d.T & 63) != 0, with_v = tail && input_zeroes_tail(*plan->fwd);
+    const bool has_tail = (d.T & 63) != 0, with_v = has_tail && input_zeroes_tail(*plan->fwd);
     dwm_status_t st = with_v ? launch_input_transform_zero_tail(*plan->fwd, x_dev, V, stream)
-                                   : launch_input_transform(*plan->fwd, x_dev, V, stream);
+                             : launch_input_transform(*plan->fwd, x_dev, V, stream);
     if (st != DWM_OK) return st;
-    if (tail && !with_v) {
+    if (has_tail && !with_v) {
         const size_t tail = (size_t)a.vblock_rows * (64 - (d.T & 63));
         hipLaunchKernelGGL(wgrad_zero_tail_kernel, dim3((unsigned)std::min<size_t>((tail + 255) / 256, 4096)), dim3(256), 0, s,
                            V + (size_t)(a.tblocks - 1) * a.vblock_rows * 64, a.vblock_rows, d.T & 63);
