@@ -249,15 +249,7 @@ def bench_half(args, L, x, w, bf16=False):
     if args.forward_variant >= 0:
         fn("set_variant")(plan, "forward", args.forward_variant)
     info = fn("plan_info")(plan)
-    single = info.forward_path == 1
-    # forward_path says 0 for the staged path and for the kernel for many channels; the latter is the default wherever it
-    # can be asked for, if nothing else was
-    wide = not single and args.contract_variant < 0 and args.forward_variant < 0
-    if wide:
-        try:
-            fn("set_variant")(plan, "wide", 1)
-        except dwm.DwmError:
-            wide = False
+    single, wide = (fn("forward_kernel")(plan) == i for i in (1, 2))
     U = torch.empty(fn("filter_bytes")(plan) // 2, dtype=tdt, device="cuda")
     ws = torch.empty(max(fn("workspace_bytes")(plan), 256), dtype=torch.uint8, device="cuda")
     y = torch.empty((L.N, L.K, info.OH, info.OW), dtype=tdt, device="cuda")

@@ -354,10 +354,12 @@ DWM_API dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan,
  * (plan, "classes", v): 0 = always the general single kernel, v < 0: the one built for the layer's list
  * of classes where there is one (the same arithmetic in the same order: for tests).
  * (plan, "wide", v): 1 = the kernel from x to y for layers with many input channels (V stays in LDS, the products go
- * straight into the 2x2 outputs, same rounding points), DWM_ERR_INVALID_ARG where it does not apply or the planner expects
- * nothing of it (it needs 16 channels or more and a staged region that fits in LDS); 0 = never; v < 0: the
- * planner's choice (1 wherever that is accepted, unless a path or a stage's variant was asked for or the single kernel for
- * few channels is in use).  It too needs the workspace to be set; forward_path stays 0, so that 0 stands for either.
+ * straight into the 2x2 outputs, same rounding points), DWM_ERR_INVALID_ARG where it does not apply (it needs 16 channels or
+ * more and a staged region that fits in LDS) or a rough estimate already puts it behind the staged path; 0 = never;
+ * v < 0: the planner's choice (1 where it expects it to be faster than the staged path, unless a path or a stage's variant
+ * was asked for or the single kernel for few channels is in use).  It too needs the workspace to be set; forward_path stays 0.
+ * dwm_f16_forward_kernel says what dwm_f16_conv_forward runs as the plan stands: 0 = the staged path, 1 = the single kernel
+ * for few channels, 2 = the one for many (-1: no plan).
  * dwm_f16_conv_forward_f32out is the same computation with y left in FP32 (not rounded): it
  * exists so that tests can compare everything before the last rounding.
  * dwm_f16_input_transform / dwm_f16_contract_output are the two stages of the staged path, exposed for timing: V of x in
@@ -371,6 +373,7 @@ DWM_API dwm_status_t dwm_f16_plan_create(dwm_f16_plan_t** out, int N, int C, int
                                          int stride, int pad);
 DWM_API dwm_status_t dwm_f16_plan_destroy(dwm_f16_plan_t* plan);
 DWM_API dwm_status_t dwm_f16_plan_info(const dwm_f16_plan_t* plan, dwm_plan_info_t* info);
+DWM_API int dwm_f16_forward_kernel(const dwm_f16_plan_t* plan);
 DWM_API size_t dwm_f16_filter_bytes(const dwm_f16_plan_t* plan);
 DWM_API size_t dwm_f16_workspace_bytes(const dwm_f16_plan_t* plan);
 DWM_API dwm_status_t dwm_f16_set_workspace(dwm_f16_plan_t* plan, void* ws_dev, size_t bytes);
@@ -401,6 +404,7 @@ DWM_API dwm_status_t dwm_bf16_plan_create(dwm_bf16_plan_t** out, int N, int C, i
                                           int stride, int pad);
 DWM_API dwm_status_t dwm_bf16_plan_destroy(dwm_bf16_plan_t* plan);
 DWM_API dwm_status_t dwm_bf16_plan_info(const dwm_bf16_plan_t* plan, dwm_plan_info_t* info);
+DWM_API int dwm_bf16_forward_kernel(const dwm_bf16_plan_t* plan);
 DWM_API size_t dwm_bf16_filter_bytes(const dwm_bf16_plan_t* plan);
 DWM_API size_t dwm_bf16_workspace_bytes(const dwm_bf16_plan_t* plan);
 DWM_API dwm_status_t dwm_bf16_set_workspace(dwm_bf16_plan_t* plan, void* ws_dev, size_t bytes);

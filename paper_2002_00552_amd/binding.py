@@ -105,6 +105,7 @@ _SIGNATURES = {
     "dwm_f16_plan_create": (_I, [ctypes.POINTER(_P)] + [_I] * 9),
     "dwm_f16_plan_destroy": (_I, [_P]),
     "dwm_f16_plan_info": (_I, [_P, ctypes.POINTER(dwm_plan_info_t)]),
+    "dwm_f16_forward_kernel": (_I, [_P]),
     "dwm_f16_filter_bytes": (ctypes.c_size_t, [_P]),
     "dwm_f16_workspace_bytes": (ctypes.c_size_t, [_P]),
     "dwm_f16_set_workspace": (_I, [_P, _P, ctypes.c_size_t]),
@@ -117,6 +118,7 @@ _SIGNATURES = {
     "dwm_bf16_plan_create": (_I, [ctypes.POINTER(_P)] + [_I] * 9),
     "dwm_bf16_plan_destroy": (_I, [_P]),
     "dwm_bf16_plan_info": (_I, [_P, ctypes.POINTER(dwm_plan_info_t)]),
+    "dwm_bf16_forward_kernel": (_I, [_P]),
     "dwm_bf16_filter_bytes": (ctypes.c_size_t, [_P]),
     "dwm_bf16_workspace_bytes": (ctypes.c_size_t, [_P]),
     "dwm_bf16_set_workspace": (_I, [_P, _P, ctypes.c_size_t]),
@@ -333,6 +335,10 @@ def dwm_f16_plan_info(plan):
     return info
 
 
+def dwm_f16_forward_kernel(plan):
+    return int(lib().dwm_f16_forward_kernel(plan))
+
+
 def dwm_f16_filter_bytes(plan):
     return int(lib().dwm_f16_filter_bytes(plan))
 
@@ -383,6 +389,10 @@ def dwm_bf16_plan_info(plan):
     info = dwm_plan_info_t()
     _check(lib().dwm_bf16_plan_info(plan, ctypes.byref(info)), "dwm_bf16_plan_info")
     return info
+
+
+def dwm_bf16_forward_kernel(plan):
+    return int(lib().dwm_bf16_forward_kernel(plan))
 
 
 def dwm_bf16_filter_bytes(plan):

@@ -273,10 +273,13 @@ struct Wide16Args {
     Wide16Class cls[kMaxClasses];
     size_t lds_bytes, u_bytes, uw_words;
     double us;                  // time by the planner's model
+    bool pays;                  // by that model, enough below the staged path's to be the default
 };
+struct InLdsArgs;
 // partial_room: bytes that the pieces' outputs may take in the workspace (they lie behind V; V's own size is allowed, so that
-// the workspace grows by no more than that); false where it does not apply or does not pay
-bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out);
+// the workspace grows by no more than that); staged_lds: the staged path's input transform, nullptr where it gathers.  false
+// where it does not apply or cannot pay
+bool wide16_setup(const dwm_plan& p, size_t partial_room, const InLdsArgs* staged_lds, Wide16Args* out);
 
 // Geometry of the LDS-staged input transform (transforms.hip): a workgroup stages the input
 // rows that one 64-tile block needs, for `cg` channels, and builds every part's V from LDS.

@@ -215,7 +215,40 @@ bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish)
 // ---------------------------------------------------------------------------------
 // 16-bit kernel from x to y for many input channels (half_wide.inc)
 // ---------------------------------------------------------------------------------
-bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out)
+// What the staged path takes (us): its input transform in one of three forms (gather; staged in LDS by groups of eight
+// channels, or all channels in a workgroup), then its contraction, tiles whole or cut into ranges.  Fitted by least squares of
+// the relative error to 9000 layers of 17-1024 channels, each stage timed alone: nine in ten of 15000 others within -25 and +13 %.
+static double staged16_us(const dwm_plan& p, const InLdsArgs* lds)
+{
+    const DevPlan& d = p.d;
+    const ContractGeometry& g = p.geo;
+    int planes = 0, parts = p.info.n_parts;  // planes summed over the parts
+    for (int i = 0; i < d.ncls; ++i) planes += d.cls[i].hn * d.cls[i].wn * (d.cls[i].lh + 1) * (d.cls[i].lw + 1);
+    const double v = 2e-6 * p.info.mults_per_tile * d.C * d.T, x = 2e-6 * d.N * d.C * d.H * d.W, y = 2e-6 * d.N * d.K * d.OH * d.OW;  // MB
+    const double blocks = (double)((d.T + 63) / 64), per_part = (double)planes / parts;
+    double in;
+    if (!lds) {
+        in = 1.6 * std::ceil(blocks * std::ceil((double)parts * d.C / 32.0) / (8 * kNumCUs)) + 0.5 * v + 1.3 * d.ncls + 0.97 * per_part;
+    } else {
+        const double kb = (double)lds->lds_bytes / 1024.0, per_cu = std::min(8.0, std::max(1.0, std::floor(160.0 / (kb + 1.0))));
+        const double rounds = std::ceil(blocks * lds->ncg / (kNumCUs * per_cu)), items = std::ceil(lds->cg / 8.0 * parts / 4.0);
+        in = d.C % 8 == 0 ? 5.0 + rounds * (2.1 + 0.0265 * kb + 0.1 * items * per_part) + 0.127 * v + 0.141 * x
+                          : 4.8 + rounds * (items * (1.29 + 0.415 * per_part) + 0.084 * kb) + 0.066 * v + 1.72 * d.ncls;
+    }
+    // start, a chunk of the longest workgroup, chunks per CU of all tiles, a class, pieces per CU, a MB of y, of V
+    struct Ct { double start, chunk, all, cls, piece, y, v; };
+    const bool whole = g.n_full > 0;
+    const Ct c = g.variant == 44   ? (whole ? Ct{1.5, 0.229, 0.144, 2.21, 30.3, 0.51, 0.057} : Ct{13.7, 0.302, 0.125, 1.41, 19.1, 0.32, 0.0})
+                 : g.variant == 32 ? (whole ? Ct{3.7, 0.311, 0.0, 1.10, 3.2, 0.22, 0.047} : Ct{10.3, 0.242, 0.0, 1.17, 10.2, 0.44, 0.032})
+                 : g.variant == 31 ? (whole ? Ct{7.2, 0.114, 0.0, 2.77, 7.6, 0.02, 0.083} : Ct{9.9, 0.179, 0.0, 1.53, 12.6, 0.85, 0.0})
+                                   : (whole ? Ct{9.6, 0.077, 0.0, 3.42, 4.9, 0.0, 0.044} : Ct{10.1, 0.148, 0.0, 1.43, 13.6, 0.31, 0.0});
+    const double longest = whole ? g.n_iter * std::ceil((double)g.n_full / kNumCUs) + (g.n_sk_tiles > 0 ? g.sk_ipw : 0) : g.sk_ipw;
+    const double contract = c.start + c.chunk * longest + c.all * (double)g.ntiles * g.n_iter / kNumCUs + c.cls * d.ncls +
+                            c.piece * (double)g.n_sk_tiles * std::max(g.sk_f, 1) / kNumCUs + c.y * y + c.v * v;
+    return 1.02 * (in + contract);
+}
+
+bool wide16_setup(const dwm_plan& p, size_t partial_room, const InLdsArgs* staged_lds, Wide16Args* out)
 {
     const DevPlan& d = p.d;
     Wide16Args f{};
@@ -291,34 +324,39 @@ bool wide16_setup(const dwm_plan& p, size_t partial_room, Wide16Args* out)
     f.u_bytes = (size_t)words * 16;
     f.uw_words = f.own_copy ? (size_t)words : 0;
 
-    // Into how many pieces the channels are cut, and whether the kernel is worth taking (us; fitted to 23 layers, within 20 %
-    // on most: csrc/half_wide.inc lists some).  A workgroup fills a CU; its launch, first loads and last stores take 9; a stage
+    // Into how many pieces the channels are cut, by a rough estimate (us): a workgroup fills a CU; its launch, first loads and last stores take 9; a stage
     // 0.75 and 0.055 for each of its planes (a share of pixels that no longer fits beside the products 0.7 per 1024 items;
-    // pixels one by one, where W is odd, 0.15 for every item of a thread);
-    // pieces are added up by a kernel of its own, 4 and 0.2 per MB.
-    double stages = 0.0;  // of one chunk
-    const double items = (double)f.max_rows * f.npairs * 4 / f.nparts;
-    for (int i = 0; i < kMaxClasses; ++i)
-        stages += f.cls[i].n * (0.75 + 0.055 * (4 - i / 3) * (4 - i % 3) + 0.7 * std::floor(items / 1024.0) +
-                               (d.W & 1 ? 0.15 * (items <= 256 ? 1 : items <= 512 ? 2 : 4) : 0.0));
-    f.us = 1e30;
+    // pixels one by one, where W is odd, 0.15 for every item of a thread); pieces are added up by a kernel of its own, 4 and
+    // 0.2 per MB.
+    const double items = (double)f.max_rows * f.npairs * 4 / f.nparts, batch = items <= 256 ? 1 : items <= 512 ? 2 : 4;
+    int all_planes = 0;  // of a chunk's stages
+    for (int i = 0; i < kMaxClasses; ++i) all_planes += f.cls[i].n * (4 - i / 3) * (4 - i % 3);
+    const double stages = f.nparts * (0.75 + 0.7 * std::floor(items / 1024.0) + (d.W & 1 ? 0.15 * batch : 0.0)) + 0.055 * all_planes;
+    double best = 1e30;
     for (int n = 1; n <= kWideMaxPieces && n <= f.chunks; ++n) {
         const int cpw = (f.chunks + n - 1) / n, pieces = (f.chunks + cpw - 1) / cpw;
         const long long wgs = (long long)f.nkt * f.ntt * pieces;
         const size_t partial = (size_t)wgs * kWideK * kWideT * 4 * sizeof(float);
         if (pieces != n || (n > 1 && partial > partial_room)) continue;
         const double us = (double)((wgs + kNumCUs - 1) / kNumCUs) * (9.0 + cpw * stages) + (n > 1 ? 4.0 + 0.2e-6 * (double)partial : 0.0);
-        if (us >= f.us) continue;
-        f.us = us;
+        if (us >= best) continue;
+        best = us;
         f.nsplit = n;
         f.cpw = cpw;
     }
-    // the staged path: V written and read and x read at 5 TB/s, its products at 400 TFLOP/s, 15 for launches and start-up, and
-    // what few tiles cannot hide of a chunk's latency (49.6 us for 240 chunks of seven tiles, 18.4 for 16 of two)
+    // Not where that is above as rough an estimate of the staged path: V written and read and x read at 5 TB/s, its products at
+    // 400 TFLOP/s, 15 for launches and start-up, and what few tiles cannot hide of a chunk's latency.
     const double v = (double)p.info.mults_per_tile * d.C * d.T;
-    const double staged = 15.0 + (4.0 * v + 2.0 * d.N * d.C * d.H * d.W) / 5e6 + 2.0 * v * d.K / 4e8 + 0.15 * p.geo.n_iter;
-    // (an odd W counts on less: 3x3 at stride 2 over 57x57 maps 63.9 -> 65.2, 7x7 over 27x27 maps 294 -> 195)
-    if (f.us >= (d.W & 1 ? 0.85 : 1.0) * staged) return false;
+    const double rough = 15.0 + (4.0 * v + 2.0 * d.N * d.C * d.H * d.W) / 5e6 + 2.0 * v * d.K / 4e8 + 0.15 * p.geo.n_iter;
+    if (best >= (d.W & 1 ? 0.85 : 1.0) * rough) return false;
+    // Whether it is the default: its time as a call (us), fitted like the staged path's (nine in ten within 16 %), at least 8 %
+    // below; where all parts are of one tap (V is x itself, and staged16_us 10 % high) 26 %.  Of 28700 layers that come here,
+    // 1121 were more than 2 % slower than on the staged path, by up to 80 %; of the 25400 that are left 54 are, by up to 21 %.
+    const double wgs = (double)f.nkt * f.ntt * f.nsplit, rounds = std::ceil(wgs / kNumCUs);
+    f.us = 3.9 + 0.29e-6 * 2.0 * d.N * d.K * d.OH * d.OW +
+           rounds * (11.9 + f.cpw * (0.08 * all_planes + f.nparts * (0.36 * std::floor(items / 1024.0) + (0.088 + (d.W & 1 ? 0.141 : 0.0)) * batch))) +
+           (f.nsplit > 1 ? 0.315e-6 * wgs * kWideK * kWideT * 16 : 0.0);
+    f.pays = f.us < (all_planes == 4 * f.nparts ? 0.736 : 0.92) * staged16_us(p, staged_lds);
     *out = f;
     return true;
 }

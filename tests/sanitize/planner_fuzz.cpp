@@ -335,7 +335,7 @@ static int walk_wide16(int N, int C, int H, int W, int K, int R, int S, int s, i
     if (plan_from_spec_as_printed(&p, sp) != DWM_OK) return 0;
     Wide16Args f;
     const size_t room = (p->v_floats * 2 + 255) / 256 * 256;
-    if (!contract_geometry(*p, p->lgran >= 64 ? (K > 64 ? 44 : 32) : p->lgran >= 32 ? 31 : 30, &p->geo) || !wide16_setup(*p, room, &f)) {
+    if (!contract_geometry(*p, p->lgran >= 64 ? (K > 64 ? 44 : 32) : p->lgran >= 32 ? 31 : 30, &p->geo) || !wide16_setup(*p, room, rnd() % 2 && p->inlds_ok ? &p->inlds : nullptr, &f)) {
         dwm_plan_destroy(p);
         return 0;
     }

@@ -192,8 +192,7 @@ def test_long_sums_with_the_planners_choice(shape, dist):
             ref = oracle.dwm_bf16_f64(a[:1], b, s, P)
         r = cls(*shape, forward=-1)
         try:
-            getattr(dwm, "dwm_%s_set_variant" % fmt)(r.plan, "wide", 1)  # accepted: what the planner chooses
-            getattr(dwm, "dwm_%s_set_variant" % fmt)(r.plan, "wide", -1)
+            assert getattr(dwm, "dwm_%s_forward_kernel" % fmt)(r.plan) == 2
             y = r.run(a, b, f32out=True)
         finally:
             r.close()
