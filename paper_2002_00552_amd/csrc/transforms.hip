@@ -446,12 +446,18 @@ static dwm_status_t launch_input(const dwm_plan& p, const float* x, float* V, vo
     if (variant >= 2) {
         if (!p.inlds_ok) return DWM_ERR_INVALID_ARG;
         InLdsArgs a = p.inlds;
-        int parts = 0;
-        for (int i = 0; i < d.ncls; ++i) parts += d.cls[i].hn * d.cls[i].wn;
+        int parts = 0, planes = 0;  // planes: summed over the parts
+        for (int i = 0; i < d.ncls; ++i) {
+            parts += d.cls[i].hn * d.cls[i].wn;
+            planes += d.cls[i].hn * d.cls[i].wn * (d.cls[i].lh + 1) * (d.cls[i].lw + 1);
+        }
         auto kernel = zero_tail ? input_transform_lds_kernel<false, true> : input_transform_lds_kernel<false, false>;
-        // a channel a workgroup: up to one workgroup of four channels a CU (beyond, others' waves hide a wave's chain: 5x5
-        // at stride 2 over 73 channels with 437 of them, whole call, 36.0 -> 37.8), and a part for every wave
-        if (p.variant_input < 0 && a.cg == 4 && (long long)((d.T + 63) / 64) * a.ncg <= kNumCUs && parts >= 4) {
+        // A channel a workgroup, where there is a part for every wave and workgroups of four channels would leave half the CUs
+        // without one, or three in eight where a part has ten planes and more: of 900 layers with up to 256 of them the 850
+        // that this takes go at 0.5 to 1.03 times, the others at 0.8 to 1.5 (2x2 at stride 3, 144 channels, 25 images of
+        // 23x22, 252 workgroups: 8.1 -> 12.0 us; others' waves hide a wave's chain there).
+        const long long wgs = (long long)((d.T + 63) / 64) * a.ncg;
+        if (p.variant_input < 0 && a.cg == 4 && parts >= 4 && wgs * 8 <= kNumCUs * (planes >= 10 * parts ? 5 : 4)) {
             a.cg = 1;
             a.ncg = d.C;
             a.lds_bytes = (size_t)a.chan_floats * sizeof(float);
