@@ -37,6 +37,16 @@ def test_planner_under_sanitizers(tmp_path):
     assert "planner fuzz:" in out
 
 
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_data_gradient_planning_under_sanitizers(tmp_path):
+    csrc = os.path.join(ROOT, "paper_2002_00552_amd", "csrc")
+    sanitize = os.path.join(ROOT, "tests", "sanitize")
+    out = _build_and_run(tmp_path, "g++",
+                         [os.path.join(sanitize, "backward_fuzz.cpp"), os.path.join(csrc, "plan.cpp"), os.path.join(csrc, "setup.cpp")],
+                         ["-std=c++17", "-Wall", "-I" + os.path.join(sanitize, "host")], ["2000"])
+    assert "backward fuzz:" in out
+
+
 @pytest.mark.skipif(shutil.which("gcc") is None, reason="needs gcc")
 def test_oracle_under_sanitizers(tmp_path):
     out = _build_and_run(tmp_path, "gcc", [os.path.join(ROOT, "tests", "sanitize", "oracle_fuzz.c")],
