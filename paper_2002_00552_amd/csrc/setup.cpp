@@ -215,9 +215,18 @@ bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish)
 // ---------------------------------------------------------------------------------
 // 16-bit kernel from x to y for many input channels (half_wide.inc)
 // ---------------------------------------------------------------------------------
+// images that a block of 64 tiles spans beyond its first
+static double more_images(const DevPlan& d)
+{
+    const double per = (double)d.TH * d.TW;
+    return per < 64.0 ? std::min(d.N - 1.0, 64.0 / per) : 0.0;
+}
+
 // What the staged path takes (us): its input transform in one of three forms (gather; staged in LDS by groups of eight
-// channels, or all channels in a workgroup), then its contraction, tiles whole or cut into ranges.  Fitted by least squares of
-// the relative error to 9000 layers of 17-1024 channels, each stage timed alone: nine in ten of 15000 others within -25 and +13 %.
+// channels, or all channels in a workgroup; a wave stages its channels image by image), then its contraction, tiles whole or cut
+// into ranges.  V past 220 MB no longer stays in the memory-side cache.  Fitted by least squares of the relative error: each
+// stage timed alone on 9000 layers of 17-1024 channels, what images, a large V and parts of one tap (V is x itself) add on
+// 6000 whole calls: nine in ten of those within -11 and +22 %.
 static double staged16_us(const dwm_plan& p, const InLdsArgs* lds)
 {
     const DevPlan& d = p.d;
@@ -234,6 +243,7 @@ static double staged16_us(const dwm_plan& p, const InLdsArgs* lds)
         const double rounds = std::ceil(blocks * lds->ncg / (kNumCUs * per_cu)), items = std::ceil(lds->cg / 8.0 * parts / 4.0);
         in = d.C % 8 == 0 ? 5.0 + rounds * (2.1 + 0.0265 * kb + 0.1 * items * per_part) + 0.127 * v + 0.141 * x
                           : 4.8 + rounds * (items * (1.29 + 0.415 * per_part) + 0.084 * kb) + 0.066 * v + 1.72 * d.ncls;
+        in += 0.1 * rounds * lds->cg * more_images(d);
     }
     // start, a chunk of the longest workgroup, chunks per CU of all tiles, a class, pieces per CU, a MB of y, of V
     struct Ct { double start, chunk, all, cls, piece, y, v; };
@@ -245,7 +255,7 @@ static double staged16_us(const dwm_plan& p, const InLdsArgs* lds)
     const double longest = whole ? g.n_iter * std::ceil((double)g.n_full / kNumCUs) + (g.n_sk_tiles > 0 ? g.sk_ipw : 0) : g.sk_ipw;
     const double contract = c.start + c.chunk * longest + c.all * (double)g.ntiles * g.n_iter / kNumCUs + c.cls * d.ncls +
                             c.piece * (double)g.n_sk_tiles * std::max(g.sk_f, 1) / kNumCUs + c.y * y + c.v * v;
-    return 1.02 * (in + contract);
+    return 1.02 * (in + contract) + 0.6 + 0.15 * std::max(0.0, v - 220.0) - (planes == 4 * parts ? 2.9 : 0.0);
 }
 
 bool wide16_setup(const dwm_plan& p, size_t partial_room, const InLdsArgs* staged_lds, Wide16Args* out)
@@ -349,14 +359,15 @@ bool wide16_setup(const dwm_plan& p, size_t partial_room, const InLdsArgs* stage
     const double v = (double)p.info.mults_per_tile * d.C * d.T;
     const double rough = 15.0 + (4.0 * v + 2.0 * d.N * d.C * d.H * d.W) / 5e6 + 2.0 * v * d.K / 4e8 + 0.15 * p.geo.n_iter;
     if (best >= (d.W & 1 ? 0.85 : 1.0) * rough) return false;
-    // Whether it is the default: its time as a call (us), fitted like the staged path's (nine in ten within 16 %), at least 8 %
-    // below; where all parts are of one tap (V is x itself, and staged16_us 10 % high) 26 %.  Of 28700 layers that come here,
-    // 1121 were more than 2 % slower than on the staged path, by up to 80 %; of the 25400 that are left 54 are, by up to 21 %.
+    // Whether it is the default: its time as a call (us), fitted like the staged path's (nine in ten within 8 %), at least 5 %
+    // below it.  Of 8000 other layers that come here 278 are more than 2 % slower than on the staged path, by up to 54 %; of the
+    // 7521 that this takes 36 are, by up to 19 %, and 170 of those it leaves would be faster by more than 2 %, by up to 27 %.
     const double wgs = (double)f.nkt * f.ntt * f.nsplit, rounds = std::ceil(wgs / kNumCUs);
-    f.us = 3.9 + 0.29e-6 * 2.0 * d.N * d.K * d.OH * d.OW +
-           rounds * (11.9 + f.cpw * (0.08 * all_planes + f.nparts * (0.36 * std::floor(items / 1024.0) + (0.088 + (d.W & 1 ? 0.141 : 0.0)) * batch))) +
-           (f.nsplit > 1 ? 0.315e-6 * wgs * kWideK * kWideT * 16 : 0.0);
-    f.pays = f.us < (all_planes == 4 * f.nparts ? 0.736 : 0.92) * staged16_us(p, staged_lds);
+    f.us = 3.9 + 0.29e-6 * 2.0 * d.N * d.K * d.OH * d.OW + (d.W & 1 ? 0.5 : 0.0) +
+           rounds * (11.9 + 0.25 * more_images(d) +
+                     f.cpw * (0.08 * all_planes + f.nparts * (0.36 * std::floor(items / 1024.0) + (0.088 + (d.W & 1 ? 0.141 : 0.0)) * batch))) +
+           (f.nsplit > 1 ? 0.31 * f.nsplit - 3.5 + 0.264e-6 * wgs * kWideK * kWideT * 16 : 0.0);
+    f.pays = f.us < 0.95 * staged16_us(p, staged_lds);
     *out = f;
     return true;
 }

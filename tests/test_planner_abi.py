@@ -315,7 +315,8 @@ def test_data_gradient_filter_buffer_holds_what_is_used(shape, gathers):
 def test_16bit_route(fmt):
     """forward_kernel names what conv_forward runs: 0 the staged path, 1 the single kernel for few channels, 2 the one for many.
     The last is the planner's choice only where it is ahead: of the layers below, which it can run, the first four were
-    measured at 1.44, 1.40, 1.39 and 1.80 times the staged path's time on it, the others at 0.60, 0.85, 0.68 and 0.46."""
+    measured at 1.44, 1.40, 1.39 and 1.80 times the staged path's time on it, the others at 0.60, 0.85, 0.68, 0.46, 0.75, 0.50 and
+    0.58 (the last three: many small images, which the staged path's input transform takes one by one; many pieces)."""
     fn = lambda name: getattr(dwm, "dwm_%s_%s" % (fmt, name))  # noqa: E731
     for i, L in enumerate(wl.CONFIGS):
         p = fn("plan_create")(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad)
@@ -332,7 +333,9 @@ def test_16bit_route(fmt):
     for shape, route in (((4, 216, 92, 92, 784, 3, 3, 1, 1), 0), ((11, 304, 17, 17, 258, 3, 3, 1, 0), 0),
                          ((76, 40, 36, 33, 179, 6, 6, 1, 3), 0), ((256, 36, 27, 27, 32, 1, 1, 2, 0), 0),
                          ((32, 256, 28, 28, 256, 7, 7, 1, 3), 2), ((32, 128, 56, 56, 256, 3, 3, 2, 1), 2),
-                         ((64, 128, 28, 28, 128, 3, 3, 1, 1), 2), ((5, 67, 35, 29, 93, 5, 5, 2, 2), 2)):
+                         ((64, 128, 28, 28, 128, 3, 3, 1, 1), 2), ((5, 67, 35, 29, 93, 5, 5, 2, 2), 2),
+                         ((8, 256, 14, 14, 256, 3, 3, 1, 1), 2), ((25, 48, 8, 5, 32, 2, 2, 1, 0), 2),
+                         ((9, 480, 8, 7, 32, 2, 2, 1, 1), 2)):
         p = fn("plan_create")(*shape)
         assert fn("forward_kernel")(p) == route, shape
         fn("set_variant")(p, "wide", 1)  # it can run all of them
