@@ -51,6 +51,11 @@ struct dwm_bwd_data_plan {
     // ... and, where their pieces and classes fit one plan, ONE input transform for all of them: a plan that
     // holds every sub-convolution's pieces and classes (used by the input transform only)
     dwm_plan_t* merged;
+    // ... or the whole gradient as one direct convolution of all phases (direct.hip): a plan that holds nothing else, its filter
+    // u_direct_off floats into Ugw.  The planner's choice wherever it is planned
+    dwm_plan_t* direct;
+    size_t u_direct_off;
+    bool use_direct() const { return direct && variant_path < 0; }
     // few input channels: the whole gradient in one kernel (backward_small.hip), its filter copy
     // u_small_off floats into Ugw; variant_path < 0: the planner's choice, 0: sub-convolutions, 1: that kernel
     bool small_ok;
@@ -351,6 +356,44 @@ static void setup_batch(dwm_bwd_data_plan& bp)
     setup_filter_batch(bp, subs);
 }
 
+// All phases that a tap reaches as one direct convolution (direct.hip), where its model has it below the time of the
+// sub-convolutions' fewest launches: 18 us at least, Winograd products at 95 TFLOP/s on the fp32 matrix cores, transformed
+// inputs written and read at 4.3 TB/s, 5 us for each input transform.  Of 110 layers drawn with strides 2 and 3 (up to 150
+// GFLOP) it was ahead on all, at 0.26 of their time in the mean: nine input transforms of stride 3, 76 <- 18 channels, 46
+// images of 8x8, 180 -> 7 us; 5x5 at stride 2, 67 <- 93 channels, five 35x29 images 30 -> 14; 7x7 at stride 2, 256 <- 256
+// channels, 256 14x14 images 603 -> 456.  The line is at 0.93 of that: 3x3 at stride 2, 256 <- 512 channels, 16 14x14
+// images 41.5 -> 46 (it stays); 64 <- 512 channels, 64 7x7 images 72 -> 55.
+static void setup_direct(dwm_bwd_data_plan& bp)
+{
+    using namespace dwm;
+    std::vector<DirectProb> p;
+    double us = 18.0;
+    for (const auto& ph : bp.phases) {
+        if (!ph.sub) continue;
+        const DevPlan& d = ph.sub->d;
+        DirectProb q{};
+        q.R = ph.na; q.S = ph.nb; q.Ph = d.Ph; q.Pw = d.Pw; q.OH = ph.UH; q.OW = ph.UW; q.oy = ph.oy; q.ox = ph.ox;
+        q.base = (long long)(bp.s * (ph.na - 1) + ph.a) * bp.S + bp.s * (ph.nb - 1) + ph.b;
+        p.push_back(q);
+        us += ph.sub->info.winograd_flops / 95e6 + (double)ph.sub->v_floats * 8.0 / 4.3e6 + (bp.merged ? 0.0 : 5.0);
+    }
+    if (p.empty() || p.size() > (size_t)kDirectMaxProbs) return;
+    std::stable_sort(p.begin(), p.end(), [](const DirectProb& a, const DirectProb& b) { return a.R * a.S > b.R * b.S; });
+    DirectArgs a;
+    if (!direct_choose(bp.N, bp.K, bp.OH, bp.OW, bp.C, 1, bp.H, bp.W, bp.s, bp.s, p.data(), (int)p.size(), &a) || a.us >= 0.93 * us) return;
+    dwm_plan* m = new (std::nothrow) dwm_plan;
+    if (!m) return;
+    std::memset(m, 0, sizeof(*m));
+    m->direct = a;
+    m->direct_only = true;
+    bp.direct = m;
+    bp.u_direct_off = bp.filter_floats;
+    bp.filter_floats += (a.filter_floats() + 63) / 64 * 64;
+    bp.filter_batch.direct_blocks = a.all_steps * ((a.Kpad + 127) / 128);
+    bp.filter_batch.direct_off = (long long)bp.u_direct_off;
+    bp.filter_batch.direct = a;
+}
+
 extern "C" {
 
 dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, int H, int W, int K, int R, int S,
@@ -427,6 +470,8 @@ dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, i
     if (bp->small_ok) off += (bp->small.u_floats + 63) / 64 * 64;
     bp->filter_floats = off;
     setup_batch(*bp);
+    bp->direct = nullptr;
+    if (stride > 1 && !bp->small_default) setup_direct(*bp);
     *out = bp;
     return DWM_OK;
 }
@@ -437,6 +482,7 @@ dwm_status_t dwm_bwd_data_plan_destroy(dwm_bwd_data_plan_t* plan)
     for (auto& ph : plan->phases)
         if (ph.sub) dwm_plan_destroy(ph.sub);
     delete plan->merged;
+    delete plan->direct;
     delete plan;
     return DWM_OK;
 }
@@ -470,6 +516,8 @@ dwm_status_t dwm_bwd_data_plan_phase(const dwm_bwd_data_plan_t* plan, int i, dwm
     out->has_subconv = ph.sub != nullptr;
     return DWM_OK;
 }
+
+int dwm_bwd_data_kernel(const dwm_bwd_data_plan_t* plan) { return !plan ? -1 : plan->use_small() ? 1 : plan->use_direct() ? 2 : 0; }
 
 dwm_status_t dwm_bwd_data_set_variant(dwm_bwd_data_plan_t* plan, const char* stage, int variant)
 {
@@ -513,6 +561,12 @@ dwm_status_t dwm_bwd_data_filter_transform(const dwm_bwd_data_plan_t* plan, cons
     // (a layer in which no tap reaches any pixel of dx -- stride above the kernel size on a narrow image -- has no
     // transformed filter at all: zero bytes, and no buffer to ask for)
     if (!plan || !w_dev || (!Ugw_dev && plan->filter_floats > 0)) return DWM_ERR_INVALID_ARG;
+    if (plan->direct && !plan->filter_batched) {
+        const long long rs = (long long)plan->R * plan->S;
+        const dwm::FilterSource src{0, rs, rs * plan->C, -plan->s * plan->S, -plan->s};
+        const dwm_status_t st = dwm::launch_filter_transform_from(*plan->direct, src, w_dev, Ugw_dev + plan->u_direct_off, stream);
+        if (st != DWM_OK) return st;
+    }
     if (plan->filter_batched) {
         const dwm_status_t st = dwm::launch_filter_batch(plan->filter_batch, w_dev, Ugw_dev, stream);
         if (st != DWM_OK) return st;
@@ -549,8 +603,10 @@ dwm_status_t dwm_conv_backward_data(const dwm_bwd_data_plan_t* plan, const float
 {
     if (!plan || !dy_dev || (!Ugw_dev && plan->filter_floats > 0) || !dx_dev) return DWM_ERR_INVALID_ARG;
     if (plan->use_small()) return dwm::launch_bwd_small(plan->small, dy_dev, Ugw_dev + plan->u_small_off, dx_dev, stream);
+    const bool direct = plan->use_direct();
+    if (direct && !plan->ws) return DWM_ERR_WORKSPACE;  // (it needs none; the other paths do)
     for (const auto& ph : plan->phases) {
-        if (ph.UH <= 0 || ph.UW <= 0) continue;
+        if (ph.UH <= 0 || ph.UW <= 0 || (direct && ph.sub)) continue;
         if (!ph.sub) {  // no tap reaches these pixels
             const size_t total = (size_t)plan->N * plan->C * ph.UH * ph.UW;
             const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 8192);
@@ -569,6 +625,7 @@ dwm_status_t dwm_conv_backward_data(const dwm_bwd_data_plan_t* plan, const float
         const dwm_status_t st = dwm_conv_forward(ph.sub, dy_dev, Ugw_dev + ph.u_off, dx_dev, stream);
         if (st != DWM_OK) return st;
     }
+    if (direct) return dwm::launch_fused_forward(*plan->direct, dy_dev, Ugw_dev + plan->u_direct_off, dx_dev, stream);
     if (plan->merged) {
         if (!plan->ws) return DWM_ERR_WORKSPACE;
         const dwm_status_t st = dwm::launch_input_transform(*plan->merged, dy_dev, plan->ws, stream);

@@ -593,6 +593,7 @@ dwm_status_t launch_fused_filter(const dwm_plan& p, const float* w, float* U, vo
 
 dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, void* stream)
 {
+    if (p.direct_only) return launch_direct(p.direct, x, U + p.ud_begin, y, stream);
     if (!p.fused_ok) return DWM_ERR_INVALID_ARG;
     const FusedArgs& f = p.fused;
     using Kernel = void (*)(DevPlan, FusedArgs, const float*, const float*, float*);

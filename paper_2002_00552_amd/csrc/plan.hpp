@@ -361,6 +361,50 @@ struct BatchArgs {
     BatchProb p[kMaxBatch];
 };
 
+// Geometry of the direct convolution on the bfloat16 matrix cores (direct.hip): one or several problems (the phases of a
+// data gradient) that read the same input with the same stride and number of channels.  The output pixels, of the largest
+// problem's extent, are flattened over (image, strip of bw columns, row, column); a workgroup owns npx of them, kt filters
+// and one problem, and walks the channels a chunk of groups of eight at a time.  LDS: [group][staged pixel][part h, m, l][8],
+// staged pixels being rows of [column phase][lwp].  A step is two units of (tap, group), one per half of a wave.
+struct DirectShape {
+    int wf, wp, wk, mb;  // waves along the filters, the pixels and the steps; blocks of 32 filters a wave (two of 32 pixels)
+    int kt() const { return 32 * mb * wf; }
+    int px() const { return 64 * wp; }
+    int threads() const { return 64 * wf * wp * wk; }
+};
+constexpr DirectShape kDirectShapes[] = {{4, 2, 1, 2}, {2, 2, 1, 2}, {1, 1, 8, 1}, {1, 1, 4, 1}, {1, 1, 4, 2}};
+constexpr int kNumDirectShapes = sizeof(kDirectShapes) / sizeof(kDirectShapes[0]);
+constexpr int kDirectMaxProbs = 16;
+constexpr int kDirectSlots = 3;      // staged pixels a thread takes of a group at most
+constexpr int kDirectMaxUnits = 512; // of a chunk
+struct DirectProb {
+    int R, S, Ph, Pw, OH, OW, oy, ox;
+    int steps[2];         // of every chunk but the last, of the last
+    int step0;            // its first step in Wd
+    int pad_;
+    long long w32;        // floats from the start of W32 to its taps
+    long long base;       // of its taps in w (FilterSource)
+};
+struct DirectArgs {
+    int shape, kt, npx;
+    int N, C, H, W, K, s;
+    int YH, YW, sy, sx;
+    int OH, bw, nstrips, total_px;
+    int ntt, nkt, nprob, ntiles, full8;
+    int rstep, rows_full, run;   // staged rows from one output row to the next, of a whole image, of a lone output row
+    int row_px, lwp, P, ns;      // pixels per staged row, per phase; per group; ceil(P / threads)
+    int nchunks, groups[2];      // groups of every chunk but the last, of the last
+    int Kpad, bias;              // bias: floats that the first pixel may lie before the image
+    int all_steps;
+    unsigned wd_bytes;
+    FastDiv div_bw, div_oh, div_strips, div_row, div_lwp, div_rows, div_rstep;
+    DirectProb p[kDirectMaxProbs];
+    // (not read by the kernels)
+    size_t w32_floats, lds_bytes;
+    double us;                   // time by direct_setup's model
+    size_t filter_floats() const { return wd_bytes / 4 + w32_floats; }
+};
+
 // The transformed filters of several sub-convolutions in one launch (transforms.hip): of each what DevPlan says, in short
 // (their pieces have phase 0).
 constexpr int kMaxFilterBatch = 9;
@@ -380,6 +424,10 @@ struct FilterBatchArgs {
     long long sk, sc;
     int sr, ss;
     FilterBatchProb p[kMaxFilterBatch];
+    // and the direct convolution's filter (direct.hip), where planned: direct_blocks workgroups, its copy's place in the buffer
+    int direct_blocks;
+    long long direct_off;
+    DirectArgs direct;
 };
 
 }  // namespace dwm
@@ -413,6 +461,12 @@ struct dwm_plan {
     size_t us_begin;
     bool use_split() const { return split_ok && !contract_forced && sk_mode == 0; }
     const dwm::ContractGeometry& active() const { return use_split() ? split : geo; }
+
+    // the direct convolution (direct.hip), its filter ud_begin floats into Ugw: at present of plans that hold nothing else (the
+    // phases of a data gradient, backward.hip)
+    bool direct_only;
+    dwm::DirectArgs direct;
+    size_t ud_begin;
 
     // workspace layout: [ V | partial outputs | arrival counters ]
     size_t ws_need_bytes() const { return (v_floats + active().partial_floats) * sizeof(float) + counters_bytes(); }
@@ -467,6 +521,14 @@ dwm_status_t launch_contract_output(const dwm_plan& p, const float* U, float* ws
 bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish);
 // contract_split.hip
 dwm_status_t launch_contract_split(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
+// setup.cpp, direct.hip: problems p[0..n) of which R, S, Ph, Pw, OH, OW, oy, ox and base are set, with one shape; false where the
+// staged pixels or a table do not fit
+bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, int shape,
+                  DirectArgs* out);
+// ... with the shape that takes the least time by its model
+bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out);
+dwm_status_t launch_direct(const DirectArgs& a, const float* x, const float* U, float* y, void* stream);
+dwm_status_t launch_direct_filter(const DirectArgs& a, const FilterSource& src, const float* w, float* U, void* stream);
 // contract_batch.hip
 dwm_status_t launch_contract_batch(const BatchArgs& a, const PlaneTable& pt, int lc, const float* U, const float* V,
                                    float* partial, float* y, void* stream);

@@ -149,6 +149,139 @@ bool fused_setup(const dwm_plan& p, FusedArgs* out)
     return true;
 }
 
+// The time (us) of a direct convolution, fitted to 1700 (layer, shape) pairs drawn from the timed cases' ranges (forward and
+// strided data gradients; rms of the logarithm 0.17, the shape that it picks at 1.03 of the best one's time): cycles at 2.1
+// GHz of a workgroup -- its MFMAs, 340 a staged pixel and wave of a SIMD, 5400 a chunk (first loads, barriers), stores --, shared by the
+// workgroups on a CU (registers allow two of 64-row wave tiles, three of 32), the address unit's 19 for each load and store,
+// and the matrix cores' power-limited 1.19 PFLOP/s.
+static double direct_us(const DirectArgs& a, const DirectShape& sh)
+{
+    const double w = sh.threads() / 256.0, waves = sh.threads() / 64.0, groups = (a.C + 7) / 8;
+    double mean = 0.0, longest = 0.0;
+    for (int i = 0; i < a.nprob; ++i) {
+        auto share = [&](int steps) { return (steps + sh.wk - 1) / sh.wk; };
+        const double t = (double)(a.nchunks - 1) * share(a.p[i].steps[0]) + share(a.p[i].steps[1]);
+        mean += t / a.nprob;
+        longest = std::max(longest, t);
+    }
+    const int fits = (int)(160 * 1024 / a.lds_bytes);
+    const double on_cu = sh.threads() > 256 ? 1 : std::max(1, std::min(fits, sh.mb == 2 ? 2 : 3));
+    const double slots = groups * a.ns, store = 1180.0 * sh.mb * w / sh.wk;
+    const double simd = mean * 368.0 * sh.mb * w + slots * 340.0 * w + store;
+    const double address = 19.0 * (slots * waves * 8 + mean * waves * 3 * sh.mb + sh.mb * 32 * waves / sh.wk * (a.sx > 1 ? 2 : 1));
+    const double lone = longest * 368.0 * sh.mb * w + slots * 340.0 * w + a.nchunks * 5400.0 + store;
+    const double per_cu = a.ntiles / (double)kNumCUs, rounds = std::max(1.0, per_cu / on_cu < 3 ? std::ceil(per_cu / on_cu) : per_cu / on_cu + 0.5);
+    const double cycles = rounds * std::max(lone, std::min(on_cu, std::ceil(per_cu)) * std::max(simd, address));
+    const double flops = a.ntiles * mean * waves * sh.mb * 2 * 6 * 32768.0;
+    return std::max(cycles / 2100.0, flops / 1.19e9) + 4.3;
+}
+
+// The direct convolution with one of its shapes.
+bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, int shape,
+                  DirectArgs* out)
+{
+    const DirectShape& sh = kDirectShapes[shape];
+    DirectArgs a{};
+    if (n < 1 || n > kDirectMaxProbs || s > 64) return false;
+    a.shape = shape; a.kt = sh.kt(); a.npx = sh.px();
+    a.N = N; a.C = C; a.H = H; a.W = W; a.K = K; a.s = s;
+    a.YH = YH; a.YW = YW; a.sy = sy; a.sx = sx;
+    a.nprob = n;
+    int R = 0, S = 0, Ph = 0, Pw = 0, OH = 0, OW = 0;
+    for (int i = 0; i < n; ++i) {
+        if (p[i].R > 64 || p[i].S > 64) return false;
+        R = std::max(R, p[i].R); S = std::max(S, p[i].S);
+        Ph = std::max(Ph, p[i].Ph); Pw = std::max(Pw, p[i].Pw);
+        OH = std::max(OH, p[i].OH); OW = std::max(OW, p[i].OW);
+        a.p[i] = p[i];
+    }
+    int taps = 0;
+    for (int i = 0; i < n; ++i) taps = std::max(taps, p[i].R * p[i].S);
+    a.OH = OH;
+    const long long image = (long long)C * H * W, oplane = (long long)YH * YW, bias = (long long)Ph * W + Pw;
+    if (image > (1LL << 29) || bias > (1LL << 28)) return false;
+    a.bias = (int)bias;
+    const int threads = sh.threads(), nph = std::min(s, S), ngroups = (C + 7) / 8;
+    const long long rstep = std::min(s, R), rows_full = rstep * (long long)(OH - 1) + R;
+    if (rows_full > (1 << 24)) return false;
+    a.rstep = (int)rstep; a.run = R; a.rows_full = (int)rows_full;
+    const size_t tables = 2 * kDirectMaxUnits * sizeof(int), reduce = sh.wk > 1 ? (size_t)threads * sh.mb * 128 : 0;
+    const size_t lds_max = (threads <= 256 ? 80 : 160) * 1024 - tables;
+    double best = 0.0;
+    for (int nstrips = 1; nstrips <= 64 && nstrips <= OW; ++nstrips) {
+        const int bw = (OW + nstrips - 1) / nstrips;
+        const long long total_rows = (long long)N * nstrips * OH, total = total_rows * bw;
+        if (total >= (1LL << 31) - 65536) continue;
+        const long long nr = std::min<long long>(total_rows, a.npx % bw == 0 ? a.npx / bw : (a.npx + bw - 2) / bw + 1);
+        const long long cross = nr <= 1 ? 0 : std::min<long long>((nr - 2) / OH + 1, (long long)N * nstrips - 1);
+        const long long rows = rstep * nr + (cross + 1) * (R - rstep);
+        const int lwp = bw + (S + s - 1) / s - 1;
+        const long long row_px = (long long)lwp * nph, P = rows * row_px;
+        if (P > (long long)kDirectSlots * threads || P < 1) continue;
+        if ((cross + 1) * image * 4 + bias * 4 >= 0x7fff0000LL || ((cross + 1) * K + 256) * oplane * 4 >= 0x7fff0000LL) continue;
+        const int ns = (int)((P + threads - 1) / threads);
+        for (int G = 1; G <= ngroups; ++G) {
+            if ((size_t)G * P * 48 > lds_max || G * taps + 1 > kDirectMaxUnits) break;
+            const int nchunks = (ngroups + G - 1) / G, gl = ngroups - (nchunks - 1) * G;
+            // cycles of a tile of the longest problem, as in direct_us
+            const double steps = (double)(nchunks - 1) * ((G * taps + 1) / 2 + sh.wk - 1) + (gl * taps + 1) / 2 + sh.wk - 1;
+            const double cost = (steps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) + (double)ngroups * ns * 400 * (threads / 256.0) + nchunks * 3000.0) *
+                                bw * nstrips / OW;
+            if (best > 0.0 && cost >= best) continue;
+            best = cost;
+            a.bw = bw; a.nstrips = nstrips; a.total_px = (int)total;
+            a.lwp = lwp; a.row_px = (int)row_px; a.P = (int)P; a.ns = ns;
+            a.nchunks = nchunks;
+            a.groups[0] = nchunks > 1 ? G : gl; a.groups[1] = gl;
+            a.lds_bytes = std::max<size_t>((size_t)a.groups[0] * P * 48, reduce) + tables;
+        }
+    }
+    if (best == 0.0) return false;
+    a.ntt = (int)(((long long)a.total_px + a.npx - 1) / a.npx);
+    a.nkt = (K + a.kt - 1) / a.kt;
+    const long long per = (long long)a.nkt * n;
+    if (a.ntt * per > 0x3fffffffLL) return false;
+    a.ntiles = (int)(a.ntt * per);
+    a.full8 = (int)(8 * per * (a.ntt / 8));
+    a.Kpad = a.nkt * a.kt;
+    long long steps = 0, w32 = 0;
+    for (int i = 0; i < n; ++i) {
+        DirectProb& q = a.p[i];
+        const int t = q.R * q.S;
+        q.steps[0] = (a.groups[0] * t + 1) / 2;
+        q.steps[1] = (a.groups[1] * t + 1) / 2;
+        q.step0 = (int)steps;
+        q.w32 = w32;
+        steps += (long long)(a.nchunks - 1) * q.steps[0] + q.steps[1];
+        w32 += (long long)t * C * a.Kpad;
+        if (steps * 96 * a.Kpad >= 0x7fff0000LL) return false;
+    }
+    a.all_steps = (int)steps;
+    a.wd_bytes = (unsigned)(steps * 96 * a.Kpad);
+    a.w32_floats = (size_t)w32;
+    a.div_bw.init((unsigned)a.bw);
+    a.div_oh.init((unsigned)OH);
+    a.div_strips.init((unsigned)a.nstrips);
+    a.div_row.init((unsigned)a.row_px);
+    a.div_lwp.init((unsigned)a.lwp);
+    a.div_rows.init((unsigned)a.rows_full);
+    a.div_rstep.init((unsigned)a.rstep);
+    a.us = direct_us(a, sh);
+    *out = a;
+    return true;
+}
+
+bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out)
+{
+    bool found = false;
+    for (int shape = 0; shape < kNumDirectShapes; ++shape) {
+        DirectArgs a;
+        if (!direct_setup(N, C, H, W, K, s, YH, YW, sy, sx, p, n, shape, &a) || (found && a.us >= out->us)) continue;
+        *out = a;
+        found = true;
+    }
+    return found;
+}
 
 // Does the LDS-staged form apply, and with how many channels per workgroup: the rows a block
 // stages must fit in LDS.  The row count depends on where a block of 64 tiles starts; the

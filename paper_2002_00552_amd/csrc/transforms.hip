@@ -5,6 +5,7 @@
 // two-multiplication forms for 2-tap and 1-tap pieces.
 #include <hip/hip_runtime.h>
 
+#include "direct_filter.hpp"
 #include "plan.hpp"
 #include "split.hpp"
 #include "xform.hpp"
@@ -66,9 +67,15 @@ __global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, Filter
 }
 
 // The same for several stride-1 sub-convolutions that read one w (the phases of a data gradient), one grid plane each: four
-// launches of 4.3 us and the gaps between them for a 5x5 layer at stride 2 with 67 and 93 channels become one.
+// launches of 4.3 us and the gaps between them for a 5x5 layer at stride 2 with 67 and 93 channels become one.  Further grid
+// planes write the direct convolution's filter.
 __global__ __launch_bounds__(256) void filter_transform_batch_kernel(FilterBatchArgs A, const float* __restrict__ w, float* __restrict__ U)
 {
+    if ((int)blockIdx.z >= A.nprob) {
+        const int b = ((blockIdx.z - A.nprob) * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, nk = (A.direct.Kpad + 127) / 128;
+        if (b < A.direct_blocks) direct_filter(A.direct, FilterSource{0, A.sk, A.sc, A.sr, A.ss}, w, U + A.direct_off, b / nk, b % nk);
+        return;
+    }
     const FilterBatchProb& P = A.p[blockIdx.z];
     const int row = blockIdx.x * blockDim.x + threadIdx.x, k = blockIdx.y;
     if (row >= P.rows_total) return;
@@ -403,6 +410,7 @@ static dwm_status_t check_launch()
 dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource& src, const float* w, float* U, void* stream)
 {
     const DevPlan& d = p.d;
+    if (p.direct_only) return launch_direct_filter(p.direct, src, w, U + p.ud_begin, stream);
     if (p.split_ok) {
         hipLaunchKernelGGL(filter_transform_split_kernel, dim3((d.rows_total + kFtRows - 1) / kFtRows, d.Kpad / kFtK), dim3(256), 0,
                            (hipStream_t)stream, d, src, w, U, reinterpret_cast<uint32_t*>(U + p.us_begin));
@@ -415,8 +423,9 @@ dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource&
 
 dwm_status_t launch_filter_batch(const FilterBatchArgs& a, const float* w, float* U, void* stream)
 {
-    hipLaunchKernelGGL(filter_transform_batch_kernel, dim3((a.max_rows + 255) / 256, a.Kpad, a.nprob), dim3(256), 0, (hipStream_t)stream,
-                       a, w, U);
+    static_assert(sizeof(FilterBatchArgs) <= 4000, "kernel arguments");
+    const int gx = (a.max_rows + 255) / 256, nd = (a.direct_blocks + gx * a.Kpad - 1) / (gx * a.Kpad);
+    hipLaunchKernelGGL(filter_transform_batch_kernel, dim3(gx, a.Kpad, a.nprob + nd), dim3(256), 0, (hipStream_t)stream, a, w, U);
     return check_launch();
 }
 
