@@ -120,7 +120,7 @@ def bench_backward_data(args, L, x, w):
     except dwm.DwmError:
         raise SystemExit("bench.py: --bwd-path %d does not apply to %s" % (args.bwd_path, L.name))
     info = dwm.dwm_bwd_data_plan_info(plan)
-    single = bool(info.single_kernel)
+    single, plain = bool(info.single_kernel), dwm.dwm_bwd_data_kernel(plan) == 2
     dyd, wd = torch.from_numpy(dy).cuda(), torch.from_numpy(w).cuda()
     U = torch.empty(dwm.dwm_bwd_data_filter_bytes(plan) // 4, dtype=torch.float32, device="cuda")
     ws = torch.empty(max(dwm.dwm_bwd_data_workspace_bytes(plan) // 4, 64), dtype=torch.float32, device="cuda")
@@ -137,7 +137,10 @@ def bench_backward_data(args, L, x, w):
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / args.steps
     peak = PEAK_MFMA_F32
-    if L.stride == 1 and not single and L.R == L.S:  # one sub-convolution: this one
+    flops = info.direct_flops if plain else info.winograd_flops  # the plain convolution's, where its taps are multiplied as they are
+    if plain:
+        peak = PEAK_SPLIT_F32
+    elif L.stride == 1 and not single and L.R == L.S:  # one sub-convolution: this one
         sub = dwm.dwm_plan_create(L.N, L.K, OH, OW, L.C, L.R, L.S, 1, L.R - 1 - L.pad)
         if contracts_split(dwm, sub):
             peak = PEAK_SPLIT_F32
@@ -148,10 +151,10 @@ def bench_backward_data(args, L, x, w):
         "warmup": args.warmup, "ms_per_step": dt * 1e3, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": L.name + "_backward_data", "phases": info.n_phases, "subconvs": info.n_subconvs,
-                   "path": "single kernel" if single else "sub-convolutions",
+                   "path": "single kernel" if single else "direct convolution on split operands" if plain else "sub-convolutions",
                    "direct_GFLOP": info.direct_flops / 1e9, "winograd_GFLOP": info.winograd_flops / 1e9},
-        "roofline": {"kernel": "bwd_small_kernel" if single else "all sub-convolutions", "bound": "mfma", "achieved": info.winograd_flops / dt / 1e12,
-                     "peak": peak, "unit": "TFLOP/s", "frac": info.winograd_flops / dt / 1e12 / peak,
+        "roofline": {"kernel": "bwd_small_kernel" if single else "direct_kernel" if plain else "all sub-convolutions", "bound": "mfma",
+                     "achieved": flops / dt / 1e12, "peak": peak, "unit": "TFLOP/s", "frac": flops / dt / 1e12 / peak,
                      "traffic": None},
     }
     if not args.no_check:
@@ -413,7 +416,23 @@ def measure_forward(L, index, steps, warmup, args, check=True):
     path = dwm.dwm_plan_info(plan).forward_path
     v_bytes = 4.0 * info.mults_per_tile * L.C * info.T
     x_bytes, y_bytes = 4.0 * x.size, 4.0 * y.numel()
-    if path != 0:
+    if dwm.dwm_plan_forward_kernel(plan) == 2:
+        # the layer's taps as they are, six bfloat16 products for each: priced by the plain convolution's operations
+        f_ms = timed(lambda: dwm.dwm_conv_forward(plan, xp, Up, yp, st), steps)
+        path = 2
+        stages = {
+            "direct_forward": {"ms": f_ms, "algorithmic_flops": info.direct_flops,
+                               "achieved_TFLOPs": info.direct_flops / f_ms / 1e9,
+                               "frac_of_mfma_peak": info.direct_flops / f_ms / 1e9 / PEAK_SPLIT_F32,
+                               "hbm_GBps_on_x_y": (x_bytes + y_bytes) / f_ms / 1e6,
+                               "frac_of_hbm_peak": (x_bytes + y_bytes) / f_ms / 1e6 / PEAK_HBM},
+            "filter_transform_once": {"ms": filter_ms},
+        }
+        roofline = {"kernel": "direct_kernel", "bound": "mfma",
+                    "achieved": info.direct_flops / f_ms / 1e9, "peak": PEAK_SPLIT_F32, "unit": "TFLOP/s",
+                    "frac": info.direct_flops / f_ms / 1e9 / PEAK_SPLIT_F32,
+                    "traffic": hbm_traffic(L.name, "direct_kernel")}
+    elif path != 0:
         kname = "fused_forward_kernel"
         f_ms = timed(lambda: dwm.dwm_conv_forward(plan, xp, Up, yp, st), steps)
         stages = {
@@ -461,7 +480,7 @@ def measure_forward(L, index, steps, warmup, args, check=True):
                    "mults_per_tile": info.mults_per_tile, "direct_GFLOP": info.direct_flops / 1e9,
                    "winograd_GFLOP": info.winograd_flops / 1e9},
         "roofline": roofline, "stages": stages,
-        "path": ["input transform + contraction", "single kernel (V in registers)"][path],
+        "path": ["input transform + contraction", "single kernel (V in registers)", "direct convolution on split operands"][path],
     }
     if check:
         import oracle

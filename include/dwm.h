@@ -67,8 +67,9 @@ typedef struct {
     int Kpad;                 /* rows per plane of the transformed filter (K rounded up) */
     long long Tpad;           /* tiles covered by the transformed input (T rounded up to 256) */
     long long Vblock;         /* floats of one block of the transformed input: all planes' rows for 64 tiles */
-    int forward_path;         /* what dwm_conv_forward runs now: 0 = input transform + contraction,
-                                 1 = single kernel (layers with few input channels) */
+    int forward_path;         /* which of the method's ways the plan takes now: 0 = input transform + contraction,
+                                 1 = single kernel (layers with few input channels).  (dwm_conv_forward may run another
+                                 kernel altogether: dwm_plan_forward_kernel) */
 } dwm_plan_info_t;
 
 /* One sub-kernel.  Its taps are w[.,.,stride*(off_h+a)+phase_h, stride*(off_w+b)+phase_w],
@@ -138,6 +139,13 @@ DWM_API dwm_status_t dwm_plan_destroy(dwm_plan_t* plan);
 
 /* Introspection of the decomposition (host only). */
 DWM_API dwm_status_t dwm_plan_info(const dwm_plan_t* plan, dwm_plan_info_t* info);
+/* What dwm_conv_forward runs as the plan stands: 0 = input transform + contraction, 1 = the single kernel for few input
+ * channels (both as info.forward_path says), 2 = the layer's taps multiplied as they are, in one launch, on the bfloat16 matrix
+ * cores with every binary32 operand as the sum of three bfloat16 numbers (C >= 16, where it takes less time than what
+ * forward_path names; infinities, NaN, operands of about 2^112 or more and sums of 2^96 or more take fp32 matrix cores for the
+ * outputs that they reach).  A variant of any stage asked for with dwm_plan_set_variant takes the layer to that stage instead.
+ * -1: null plan. */
+DWM_API int dwm_plan_forward_kernel(const dwm_plan_t* plan);
 DWM_API dwm_status_t dwm_plan_part(const dwm_plan_t* plan, int i, dwm_part_t* part);     /* i < n_parts   */
 DWM_API dwm_status_t dwm_plan_class(const dwm_plan_t* plan, int i, dwm_class_t* cls);   /* i < n_classes */
 /* The single-kernel path's filter copy: counts (all 0 where the path does not apply), classes, rows. */
@@ -166,7 +174,7 @@ DWM_API dwm_status_t dwm_plan_set_workspace(dwm_plan_t* plan, void* ws_dev, size
  *               library's internal table of variants (a variant whose chunk depth does not divide
  *               the plan's reduction padding does not apply);
  *   "forward":  0 = input transform + contraction, 1 = single kernel (layers with few input channels
- *               only; the planner's choice where it applies);
+ *               only), -1 = the planner's choice (dwm_plan_forward_kernel);
  *   "input":    0, 1 = gather form of the input transform (blocks-fast / rows-fast workgroup order),
  *               2, 3 = LDS-staged form (channel groups fastest / blocks fastest; refused when the
  *               rows one block of 64 tiles needs do not fit in LDS);

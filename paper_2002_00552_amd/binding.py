@@ -107,6 +107,7 @@ _SIGNATURES = {
     "dwm_f16_plan_destroy": (_I, [_P]),
     "dwm_f16_plan_info": (_I, [_P, ctypes.POINTER(dwm_plan_info_t)]),
     "dwm_f16_forward_kernel": (_I, [_P]),
+    "dwm_plan_forward_kernel": (_I, [_P]),
     "dwm_f16_filter_bytes": (ctypes.c_size_t, [_P]),
     "dwm_f16_workspace_bytes": (ctypes.c_size_t, [_P]),
     "dwm_f16_set_workspace": (_I, [_P, _P, ctypes.c_size_t]),
@@ -338,6 +339,10 @@ def dwm_f16_plan_info(plan):
     info = dwm_plan_info_t()
     _check(lib().dwm_f16_plan_info(plan, ctypes.byref(info)), "dwm_f16_plan_info")
     return info
+
+
+def dwm_plan_forward_kernel(plan):
+    return int(lib().dwm_plan_forward_kernel(plan))
 
 
 def dwm_f16_forward_kernel(plan):

@@ -33,7 +33,8 @@ struct dwm_bwd_data_plan {
         size_t u_off;        // its transformed filter inside Ugw (floats)
     };
     std::vector<Phase> phases;
-    size_t wtmp_floats;      // start of Ugw: gathered, flipped weights of a phase on the single-kernel forward path, if any is
+    size_t wtmp_floats;      // start of Ugw: room for the weights of a phase on the single-kernel forward path, if any is (not used:
+                             // they are read where they lie; the buffer's layout is as callers know it)
     size_t filter_floats, ws_bytes;
     double direct_flops;
     // all sub-convolutions contracted in one launch (contract_batch.hip): each then has its own
@@ -56,6 +57,8 @@ struct dwm_bwd_data_plan {
     dwm_plan_t* direct;
     size_t u_direct_off;
     bool use_direct() const { return direct && variant_path < 0; }
+    // (stride 1: its one sub-convolution's plan has the direct convolution itself)
+    bool use_sub_direct() const { return s == 1 && phases[0].sub && phases[0].sub->use_direct(); }
     // few input channels: the whole gradient in one kernel (backward_small.hip), its filter copy
     // u_small_off floats into Ugw; variant_path < 0: the planner's choice, 0: sub-convolutions, 1: that kernel
     bool small_ok;
@@ -67,21 +70,6 @@ struct dwm_bwd_data_plan {
 };
 
 namespace dwm {
-
-// wt[c][k][i][j] = w[k][c][s*(na-1-i) + a][s*(nb-1-j) + b]
-__global__ __launch_bounds__(256) void bwd_gather_weights_kernel(const float* __restrict__ w, float* __restrict__ wt,
-                                                                 int K, int C, int R, int S, int s, int a, int b,
-                                                                 int na, int nb)
-{
-    const size_t total = (size_t)C * K * na * nb;
-    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-        const int j = (int)(e % nb);
-        const int i = (int)((e / nb) % na);
-        const int k = (int)((e / ((size_t)nb * na)) % K);
-        const int c = (int)(e / ((size_t)nb * na * K));
-        wt[e] = w[(((size_t)k * C + c) * R + (s * (na - 1 - i) + a)) * S + (s * (nb - 1 - j) + b)];
-    }
-}
 
 // dx[n][c][sy*o + oy][sx*o' + ox] = 0 for o < UH, o' < UW
 __global__ __launch_bounds__(256) void bwd_zero_phase_kernel(float* __restrict__ dx, int planes, int H, int W, int s,
@@ -413,6 +401,13 @@ dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, i
     bp->direct_flops = 2.0 * N * K * C * R * S * bp->OH * bp->OW;
     bp->wtmp_floats = 0;
     bp->ws_bytes = 256;
+    // the single-kernel form: chosen where the sub-convolutions would have only a handful of filters
+    bp->small_ok = bwd_small_setup(N, C, H, W, K, R, S, stride, pad, &bp->small);
+    // (LDS: room for the workgroups per CU its registers allow -- one where a wave holds several column blocks of
+    // sixteen planes, else at least two)
+    const size_t small_lds_max = (bp->small.nb > 1 && bp->small.four ? 152 : 78) * 1024;
+    bp->small_default = bp->small_ok && C <= 16 && bp->small.nf <= 64 && bp->small.lds_bytes <= small_lds_max &&
+                        bp->small.eff_pct >= 50;
     const int s = stride;
     dwm_status_t st = DWM_OK;
     for (int a = 0; a < s && st == DWM_OK; ++a)
@@ -436,6 +431,7 @@ dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, i
                 sp.pad_h = ph.na - 1 - u0; sp.pad_w = ph.nb - 1 - v0;
                 sp.OH = ph.UH; sp.OW = ph.UW;
                 sp.om = OutMap{H, W, s, ph.oy, s, ph.ox};
+                sp.direct = s == 1 && !bp->small_default;
                 sp.no_split = s > 1;  // (several sub-convolutions are contracted together, on fp32 MFMAs)
                 st = plan_from_spec(&ph.sub, sp);
                 if (st == DWM_OK) {
@@ -458,13 +454,6 @@ dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, i
             ph.u_off = off;
             off += (dwm_plan_filter_bytes(ph.sub) / sizeof(float) + 63) / 64 * 64;
         }
-    // the single-kernel form: chosen where the sub-convolutions would have only a handful of filters
-    bp->small_ok = bwd_small_setup(N, C, H, W, K, R, S, stride, pad, &bp->small);
-    // (LDS: room for the workgroups per CU its registers allow -- one where a wave holds several column blocks of
-    // sixteen planes, else at least two)
-    const size_t small_lds_max = (bp->small.nb > 1 && bp->small.four ? 152 : 78) * 1024;
-    bp->small_default = bp->small_ok && C <= 16 && bp->small.nf <= 64 && bp->small.lds_bytes <= small_lds_max &&
-                        bp->small.eff_pct >= 50;
     bp->variant_path = -1;
     bp->u_small_off = off;
     if (bp->small_ok) off += (bp->small.u_floats + 63) / 64 * 64;
@@ -517,7 +506,7 @@ dwm_status_t dwm_bwd_data_plan_phase(const dwm_bwd_data_plan_t* plan, int i, dwm
     return DWM_OK;
 }
 
-int dwm_bwd_data_kernel(const dwm_bwd_data_plan_t* plan) { return !plan ? -1 : plan->use_small() ? 1 : plan->use_direct() ? 2 : 0; }
+int dwm_bwd_data_kernel(const dwm_bwd_data_plan_t* plan) { return !plan ? -1 : plan->use_small() ? 1 : plan->use_direct() || plan->use_sub_direct() ? 2 : 0; }
 
 dwm_status_t dwm_bwd_data_set_variant(dwm_bwd_data_plan_t* plan, const char* stage, int variant)
 {
@@ -526,6 +515,7 @@ dwm_status_t dwm_bwd_data_set_variant(dwm_bwd_data_plan_t* plan, const char* sta
     if (variant < -1 || variant > 1) return DWM_ERR_INVALID_ARG;
     if (variant == 1 && !plan->small_ok) return DWM_ERR_UNSUPPORTED;
     plan->variant_path = variant;
+    if (plan->s == 1 && plan->phases[0].sub) plan->phases[0].sub->no_direct = variant >= 0;
     return DWM_OK;
 }
 
@@ -573,24 +563,13 @@ dwm_status_t dwm_bwd_data_filter_transform(const dwm_bwd_data_plan_t* plan, cons
     }
     for (const auto& ph : plan->phases) {
         if (!ph.sub || plan->filter_batched) continue;
-        if (!ph.sub->fused_ok) {
-            // straight from w: flipped taps of the phase, filters and channels swapped (gathering them first took 17 us of
-            // 58 for 256x256 filters of 7x7)
-            const int s = plan->s;
-            const long long rs = (long long)plan->R * plan->S;
-            const dwm::FilterSource src{(long long)(s * (ph.na - 1) + ph.a) * plan->S + s * (ph.nb - 1) + ph.b, rs,
-                                        rs * plan->C, -s * plan->S, -s};
-            const dwm_status_t st = dwm::launch_filter_transform_from(*ph.sub, src, w_dev, Ugw_dev + ph.u_off, stream);
-            if (st != DWM_OK) return st;
-            continue;
-        }
-        const size_t total = (size_t)plan->C * plan->K * ph.na * ph.nb;
-        const unsigned blocks = (unsigned)std::min<size_t>((total + 255) / 256, 4096);
-        // the scratch at the start of Ugw is reused phase after phase: stream order keeps it safe
-        hipLaunchKernelGGL(dwm::bwd_gather_weights_kernel, dim3(blocks), dim3(256), 0, (hipStream_t)stream, w_dev,
-                           Ugw_dev, plan->K, plan->C, plan->R, plan->S, plan->s, ph.a, ph.b, ph.na, ph.nb);
-        if (hipGetLastError() != hipSuccess) return DWM_ERR_HIP;
-        const dwm_status_t st = dwm_filter_transform(ph.sub, Ugw_dev, Ugw_dev + ph.u_off, stream);
+        // straight from w: flipped taps of the phase, filters and channels swapped (gathering them first took 17 us of
+        // 58 for 256x256 filters of 7x7)
+        const int s = plan->s;
+        const long long rs = (long long)plan->R * plan->S;
+        const dwm::FilterSource src{(long long)(s * (ph.na - 1) + ph.a) * plan->S + s * (ph.nb - 1) + ph.b, rs,
+                                    rs * plan->C, -s * plan->S, -s};
+        const dwm_status_t st = dwm::launch_filter_transform_from(*ph.sub, src, w_dev, Ugw_dev + ph.u_off, stream);
         if (st != DWM_OK) return st;
     }
     if (plan->small_ok)

@@ -20,7 +20,7 @@
 // falls from 2.1 to 1.6 GHz with bf16 MFMAs on all CUs, 0.9 to 1.2 PFLOP/s of them.  Whole training steps with it as the
 // data gradient, before -> now: 5x5 at stride 2, 67 -> 93 channels, five 35x29 images 111 -> 101 us; drawn strided layers
 // 173 -> 136, 205 -> 105, 248 -> 129, 208 -> 180.  Errors against 64 bits are 2 to 5 times below those of the transforms.
-// As the forward pass of a large first layer it loses (7x7 at stride 2 141 -> 168, 11x11 at stride 4 188 -> 260 us).
+// Forward passes: plan.cpp, at the rule that takes it.  As that of a large first layer it loses (7x7 at stride 2 141 -> 168, 11x11 at stride 4 188 -> 260 us).
 #include <hip/hip_runtime.h>
 
 #include "direct_filter.hpp"

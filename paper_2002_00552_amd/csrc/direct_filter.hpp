@@ -27,7 +27,7 @@ __device__ __forceinline__ void direct_filter(const DirectArgs& A, const FilterS
     for (int e = 0; e < 8; ++e) {
         v[e] = 0.f;
         if (r < q.R && c0 + e < A.C) {
-            if (k < A.K) v[e] = w[q.base + (long long)k * F.sk + (long long)(c0 + e) * F.sc + (long long)r * F.sr + (long long)s * F.ss];
+            if (k < A.K) v[e] = w[q.at(F, k, c0 + e, r, s)];
             W32[q.w32 + ((long long)tap * A.C + c0 + e) * A.Kpad + k] = v[e];
         }
         v[e] *= kSplitScale;

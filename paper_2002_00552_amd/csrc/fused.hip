@@ -34,68 +34,6 @@ namespace dwm {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// (G_l g)[i] with the 2-tap case run as 3 taps with a zero third tap.
-__device__ __forceinline__ float fused_g_row(int l, int i, float v0, float v1, float v2)
-{
-    if (l == 1) return v0;
-    switch (i) {
-        case 0: return v0;
-        case 1: return 0.5f * (v0 + v1 + v2);
-        case 2: return 0.5f * (v0 - v1 + v2);
-        default: return v2;
-    }
-}
-
-// ---------------------------------------------------------------------------------
-// Filter copy for this path: UF[class][slice][plane][row][i][half], filter = 32*slice +
-// 16*half + i; zero for filters >= K, padding rows and frequencies a part does not have.
-// One thread per (row, filter).
-// ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void fused_filter_kernel(DevPlan P, FusedArgs F, const float* __restrict__ w,
-                                                        float* __restrict__ U, int gap0, int gap1)
-{
-    // the alignment gap before this copy belongs to the filter buffer: it is written too
-    if (blockIdx.x == 0 && blockIdx.y == 0)
-        for (int i = gap0 + threadIdx.x; i < gap1; i += blockDim.x) U[i] = 0.f;
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = blockIdx.y;
-    if (row >= F.rows_total) return;
-    int fi = 0;
-    while (fi + 1 < F.nfc && row >= F.fc[fi + 1].row0) ++fi;
-    const FusedClass fc = F.fc[fi];
-    const unsigned desc = F.rowdesc[row];
-    const bool real = (desc >> 15) != 0 && k < P.K;
-    const DevPiece hp = P.ph[desc & 15], wp = P.pw[(desc >> 4) & 15];
-    const int c = (desc >> 8) & 127;
-    float g[3][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            float v = 0.f;
-            if (real && i < hp.l && j < wp.l) {
-                const int r = P.s * (hp.j + i) + hp.p, q = P.s * (wp.j + j) + wp.p;
-                v = w[(((size_t)k * P.C + c) * P.R + r) * P.S + q];
-            }
-            g[i][j] = v;
-        }
-    float t[4][3];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) t[i][j] = fused_g_row(hp.l, i, g[0][j], g[1][j], g[2][j]);
-    const int slice = k >> 5, half = (k >> 4) & 1, ki = k & 15;
-    float* dst = U + fc.uf_off + ((size_t)slice * fc.nfh * fc.nfw * fc.rows + (row - fc.row0)) * 32 + ki * 2 + half;
-#pragma unroll
-    for (int fh = 0; fh < 4; ++fh)
-#pragma unroll
-        for (int fw = 0; fw < 4; ++fw)
-            if (fh < fc.nfh && fw < fc.nfw) {
-                const float u = fused_g_row(wp.l, fw, t[fh][0], t[fh][1], t[fh][2]);
-                dst[(size_t)(fh * fc.nfw + fw) * fc.rows * 32] = (real && fh <= hp.l && fw <= wp.l) ? u : 0.f;
-            }
-}
-
 // ---------------------------------------------------------------------------------
 // One class (a pair of families) for one slice of 32 filters: every step of four rows is
 // patch from LDS -> B^T d B -> one MFMA per plane and filter half; then the output transform.
@@ -582,18 +520,9 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
     }  // blocks of this workgroup
 }
 
-dwm_status_t launch_fused_filter(const dwm_plan& p, const float* w, float* U, void* stream)
-{
-    if (!p.fused_ok) return DWM_ERR_INVALID_ARG;
-    const FusedArgs& f = p.fused;
-    dim3 grid((f.rows_total + 255) / 256, f.nslices * 32), block(256);
-    hipLaunchKernelGGL(fused_filter_kernel, grid, block, 0, (hipStream_t)stream, p.d, f, w, U, (int)p.uf_gap, (int)p.uf_begin);
-    return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
-}
-
 dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, void* stream)
 {
-    if (p.direct_only) return launch_direct(p.direct, x, U + p.ud_begin, y, stream);
+    if (p.use_direct()) return launch_direct(p.direct, x, U + p.ud_begin, y, stream);
     if (!p.fused_ok) return DWM_ERR_INVALID_ARG;
     const FusedArgs& f = p.fused;
     using Kernel = void (*)(DevPlan, FusedArgs, const float*, const float*, float*);

@@ -50,6 +50,8 @@ dwm_status_t dwm_conv_forward_static(const dwm_plan_t* plan, const float* x_dev,
     // the single-kernel path keeps V in registers and has no scratch at all
     if (plan->use_fused()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, stream);
     if (plan->ws_need_bytes() > kScratchBytes) return DWM_ERR_WORKSPACE;
+    // (nor has the direct convolution; what fits does not depend on which kernel the planner has chosen)
+    if (plan->use_direct()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, stream);
     float* ws = nullptr;
     dwm_status_t st = scratch_of_current_device(&ws);
     if (st != DWM_OK) return st;

@@ -238,6 +238,27 @@ bool split_geometry(const dwm_plan& p, ContractGeometry* out)
 
 extern "C" {
 
+// Whether the direct convolution (direct.hip) takes the layer, beside what it has: where its model has it below 0.85 of the time of
+// the path it would replace -- the fp32 contraction behind an input transform (within 11 % of 53 measured layers) or, of
+// layers that fused.hip can run, Winograd products at 50 TFLOP/s after 13 us (within 25 % of 19).  Measured, before -> now (us): 5x5,
+// 16 -> 16 channels, one 32x32 image 12.1 -> 7.5; 3x3 at stride 2, 128 -> 256, 32 56x56 images 122 -> 86; 3x3, 128 -> 128, 64
+// 28x28 images 89 -> 82; 3x3, 40 -> 61, 78 images of 17x21 40.5 -> 13.3; 5x1, 56 -> 27, 36 images of 32x38 60 -> 19.6.  Of 72
+// drawn layers it took 0.49 of the time in the mean.  From 16 channels: below, a step's groups of eight are half empty, and
+// first layers are faster on fused.hip (7x7 at stride 2, 3 -> 64, 141 against 168).  Layers that the bfloat16 contraction takes
+// (contract_split.hip) stay with it.
+static bool direct_ahead(dwm_plan& p, const dwm::PlanSpec& sp)
+{
+    const dwm::DevPlan& d = p.d;
+    if (d.C < 16) return false;
+    dwm::DirectProb q{};
+    q.R = d.R; q.S = d.S; q.Ph = d.Ph; q.Pw = d.Pw; q.OH = d.OH; q.OW = d.OW;
+    q.oy = d.om.oy; q.ox = d.om.ox;
+    const double x_bytes = 4.0 * d.N * d.C * d.H * d.W, y_bytes = 4.0 * d.N * d.K * d.OH * d.OW;
+    const double us = p.fused_ok ? 13.0 + p.info.winograd_flops / 50e6 + (x_bytes + y_bytes) / 4e6
+                                 : 5.7 + 1.03 * dwm::fp32_contract_us(p) + ((double)p.v_floats * 4.0 + x_bytes) / 4.31e6;
+    return dwm::direct_choose(d.N, d.C, d.H, d.W, d.K, d.s, d.om.YH, d.om.YW, d.om.sy, d.om.sx, &q, 1, &p.direct) && p.direct.us < 0.85 * us;
+}
+
 // One planning pass with the given splitting policy; *out is set on DWM_OK only.
 static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool even_tail, bool with_split,
                                bool widen2 = false)
@@ -386,6 +407,12 @@ static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool e
         }
         p->filter_floats = uf;
     }
+    if (sp.direct && (p->fused_ok || with_split) && !p->split_ok && direct_ahead(*p, sp)) {
+        p->direct_ok = true;
+        p->ud_gap = p->filter_floats;
+        p->ud_begin = (p->filter_floats + 63) / 64 * 64;
+        p->filter_floats = p->ud_begin + p->direct.filter_floats();
+    }
     *out = p;
     return DWM_OK;
 }
@@ -417,6 +444,23 @@ dwm_status_t plan_from_spec_widened(dwm_plan_t** out, const PlanSpec& sp)
 {
     return plan_build(out, sp, true, false, true);
 }
+
+dwm_status_t plan_from_layer(dwm_plan_t** out, int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool direct)
+{
+    if (!out) return DWM_ERR_INVALID_ARG;
+    if (N < 1 || C < 1 || H < 1 || W < 1 || K < 1 || R < 1 || S < 1 || stride < 1 || pad < 0)
+        return DWM_ERR_INVALID_ARG;
+    if ((long long)H + 2LL * pad < R || (long long)W + 2LL * pad < S) return DWM_ERR_INVALID_ARG;
+    if (pad > (1 << 20) || H > (1 << 20) || W > (1 << 20)) return DWM_ERR_UNSUPPORTED;
+    PlanSpec sp{};
+    sp.N = N; sp.C = C; sp.H = H; sp.W = W; sp.K = K; sp.R = R; sp.S = S; sp.stride = stride;
+    sp.pad_h = sp.pad_w = pad;
+    sp.OH = (H + 2 * pad - R) / stride + 1;
+    sp.OW = (W + 2 * pad - S) / stride + 1;
+    sp.om = OutMap{sp.OH, sp.OW, 1, 0, 1, 0};
+    sp.direct = direct;
+    return plan_from_spec(out, sp);
+}
 }  // namespace dwm
 
 extern "C" {
@@ -424,18 +468,7 @@ extern "C" {
 dwm_status_t dwm_plan_create(dwm_plan_t** out, int N, int C, int H, int W, int K, int R, int S,
                              int stride, int pad)
 {
-    if (!out) return DWM_ERR_INVALID_ARG;
-    if (N < 1 || C < 1 || H < 1 || W < 1 || K < 1 || R < 1 || S < 1 || stride < 1 || pad < 0)
-        return DWM_ERR_INVALID_ARG;
-    if ((long long)H + 2LL * pad < R || (long long)W + 2LL * pad < S) return DWM_ERR_INVALID_ARG;
-    if (pad > (1 << 20) || H > (1 << 20) || W > (1 << 20)) return DWM_ERR_UNSUPPORTED;
-    dwm::PlanSpec sp{};
-    sp.N = N; sp.C = C; sp.H = H; sp.W = W; sp.K = K; sp.R = R; sp.S = S; sp.stride = stride;
-    sp.pad_h = sp.pad_w = pad;
-    sp.OH = (H + 2 * pad - R) / stride + 1;
-    sp.OW = (W + 2 * pad - S) / stride + 1;
-    sp.om = dwm::OutMap{sp.OH, sp.OW, 1, 0, 1, 0};
-    return dwm::plan_from_spec(out, sp);
+    return dwm::plan_from_layer(out, N, C, H, W, K, R, S, stride, pad, true);
 }
 
 dwm_status_t dwm_plan_destroy(dwm_plan_t* plan)
@@ -452,6 +485,8 @@ dwm_status_t dwm_plan_info(const dwm_plan_t* plan, dwm_plan_info_t* info)
     info->forward_path = plan->use_fused() ? 1 : 0;
     return DWM_OK;
 }
+
+int dwm_plan_forward_kernel(const dwm_plan_t* plan) { return !plan ? -1 : plan->use_direct() ? 2 : plan->use_fused() ? 1 : 0; }
 
 dwm_status_t dwm_plan_part(const dwm_plan_t* plan, int i, dwm_part_t* part)
 {
@@ -531,6 +566,7 @@ dwm_status_t dwm_plan_set_variant(dwm_plan_t* plan, const char* stage, int varia
         if (!dwm::input_lds_setup(*plan, &a, variant) || (variant > 0 && a.cg != variant)) return DWM_ERR_INVALID_ARG;
         plan->inlds = a;
         plan->inlds_ok = true;
+        plan->cg_asked = variant > 0;
         return DWM_OK;
     }
     if (!std::strcmp(stage, "forward")) {
@@ -561,9 +597,7 @@ dwm_status_t dwm_plan_set_variant(dwm_plan_t* plan, const char* stage, int varia
 dwm_status_t dwm_filter_transform(const dwm_plan_t* plan, const float* w_dev, float* Ugw_dev, void* stream)
 {
     if (!plan || !w_dev || !Ugw_dev) return DWM_ERR_INVALID_ARG;
-    const dwm_status_t st = dwm::launch_filter_transform(*plan, w_dev, Ugw_dev, stream);
-    if (st != DWM_OK || !plan->fused_ok) return st;
-    return dwm::launch_fused_filter(*plan, w_dev, Ugw_dev, stream);
+    return dwm::launch_filter_transform(*plan, w_dev, Ugw_dev, stream);
 }
 
 dwm_status_t dwm_input_transform(const dwm_plan_t* plan, const float* x_dev, void* stream)
@@ -585,7 +619,7 @@ dwm_status_t dwm_conv_forward(const dwm_plan_t* plan, const float* x_dev, const 
 {
     if (!plan || !x_dev || !Ugw_dev || !y_dev) return DWM_ERR_INVALID_ARG;
     if (!plan->ws) return DWM_ERR_WORKSPACE;
-    if (plan->use_fused()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, stream);
+    if (plan->use_fused() || plan->use_direct()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, stream);
     dwm_status_t st = dwm::launch_input_transform(*plan, x_dev, plan->ws, stream);
     if (st != DWM_OK) return st;
     return dwm::launch_contract_output(*plan, Ugw_dev, plan->ws, y_dev, stream);

@@ -377,13 +377,23 @@ constexpr int kNumDirectShapes = sizeof(kDirectShapes) / sizeof(kDirectShapes[0]
 constexpr int kDirectMaxProbs = 16;
 constexpr int kDirectSlots = 3;      // staged pixels a thread takes of a group at most
 constexpr int kDirectMaxUnits = 512; // of a chunk
+// Where a filter lies in w: tap (r, s) of filter k and channel c is element base + k*sk + c*sc + r*sr + s*ss
+struct FilterSource {
+    long long base, sk, sc;
+    int sr, ss;
+};
 struct DirectProb {
     int R, S, Ph, Pw, OH, OW, oy, ox;
     int steps[2];         // of every chunk but the last, of the last
     int step0;            // its first step in Wd
     int pad_;
     long long w32;        // floats from the start of W32 to its taps
-    long long base;       // of its taps in w (FilterSource)
+    long long base;       // of its taps in w, from the source's base
+    // its tap (r, s) of filter k and channel c in w
+    constexpr long long at(const FilterSource& F, int k, int c, int r, int s) const
+    {
+        return F.base + base + k * F.sk + c * F.sc + (long long)r * F.sr + (long long)s * F.ss;
+    }
 };
 struct DirectArgs {
     int shape, kt, npx;
@@ -462,11 +472,17 @@ struct dwm_plan {
     bool use_split() const { return split_ok && !contract_forced && sk_mode == 0; }
     const dwm::ContractGeometry& active() const { return use_split() ? split : geo; }
 
-    // the direct convolution (direct.hip), its filter ud_begin floats into Ugw: at present of plans that hold nothing else (the
-    // phases of a data gradient, backward.hip)
-    bool direct_only;
+    // the direct convolution (direct.hip), its filter ud_begin floats into Ugw, after a gap from ud_gap: planned beside the
+    // others (direct_ok), or all that the plan holds (direct_only: the phases of a data gradient, backward.hip).  The planner's
+    // choice where it is planned; a variant of another stage that was asked for takes the layer's path to that stage.
+    bool direct_ok, direct_only;
+    bool no_direct, cg_asked;  // asked for: the transforms (a data gradient's), a channel group
     dwm::DirectArgs direct;
-    size_t ud_begin;
+    size_t ud_gap, ud_begin;
+    bool use_direct() const
+    {
+        return direct_only || (direct_ok && !no_direct && variant_forward < 0 && variant_input < 0 && !cg_asked && !contract_forced && sk_mode == 0);
+    }
 
     // workspace layout: [ V | partial outputs | arrival counters ]
     size_t ws_need_bytes() const { return (v_floats + active().partial_floats) * sizeof(float) + counters_bytes(); }
@@ -487,9 +503,12 @@ struct PlanSpec {
     int pad_h, pad_w;
     int OH, OW;
     OutMap om;
+    bool direct;    // the direct convolution may be planned beside the rest
     bool no_split;  // not contracted on the bfloat16 matrix cores: no split copy of U
 };
 dwm_status_t plan_from_spec(dwm_plan_t** out, const PlanSpec& sp);
+// dwm_plan_create, with the direct convolution planned or left out
+dwm_status_t plan_from_layer(dwm_plan_t** out, int N, int C, int H, int W, int K, int R, int S, int stride, int pad, bool direct);
 // For the filter gradient of layers with few channels: phases cut 3,...,3,2,2 and every two-tap
 // piece transformed as a three-tap one (its third tap is a neighbour's, or lies past the kernel: the
 // gradient of that tap is computed and dropped), so that all parts share the 16 planes of F(2,3)^2.
@@ -503,12 +522,7 @@ bool contract_geometry(const dwm_plan& p, int variant, ContractGeometry* out);
 bool split_geometry(const dwm_plan& p, ContractGeometry* out);
 // transforms.hip, contract.hip
 dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U, void* stream);
-// the same for a plan whose filter lies in w with other strides: tap (r, s) of its filter k and channel c is element
-// base + k*sk + c*sc + r*sr + s*ss
-struct FilterSource {
-    long long base, sk, sc;
-    int sr, ss;
-};
+// the same for a plan whose filter lies in w with other strides
 dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource& src, const float* w, float* U, void* stream);
 // `ws` is the base of a workspace laid out as the plan says: V first, then the partial outputs and
 // the arrival counters of the contraction's split tiles
@@ -539,6 +553,5 @@ dwm_status_t launch_bwd_small_filter(const BwdSmallArgs& a, int R, int S, const 
 dwm_status_t launch_bwd_small(const BwdSmallArgs& a, const float* dy, const float* U, float* dx, void* stream);
 // fused.hip
 bool fused_setup(const dwm_plan& p, FusedArgs* out);
-dwm_status_t launch_fused_filter(const dwm_plan& p, const float* w, float* U, void* stream);
 dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, void* stream);
 }  // namespace dwm

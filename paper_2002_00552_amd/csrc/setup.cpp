@@ -220,6 +220,10 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
         if (P > (long long)kDirectSlots * threads || P < 1) continue;
         if ((cross + 1) * image * 4 + bias * 4 >= 0x7fff0000LL || ((cross + 1) * K + 256) * oplane * 4 >= 0x7fff0000LL) continue;
         const int ns = (int)((P + threads - 1) / threads);
+        // (no number of groups is below this)
+        if (best > 0.0 && best <= (0.5 * ngroups * taps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) +
+                                   (double)ngroups * ns * 400 * (threads / 256.0) + 3000.0) * bw * nstrips / OW)
+            continue;
         for (int G = 1; G <= ngroups; ++G) {
             if ((size_t)G * P * 48 > lds_max || G * taps + 1 > kDirectMaxUnits) break;
             const int nchunks = (ngroups + G - 1) / G, gl = ngroups - (nchunks - 1) * G;

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "direct_filter.hpp"
+#include "fused_filter.hpp"
 #include "plan.hpp"
 #include "split.hpp"
 #include "xform.hpp"
@@ -44,11 +45,9 @@ __device__ __forceinline__ void filter_part(const DevPlan& P, const DevClass& q,
         for (int j = 0; j < 4; ++j) u[i][j] = (i < th && j < tw) ? g_row(q.lw, j, t[i][0], t[i][1], t[i][2]) : 0.f;
 }
 
-__global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, FilterSource F, const float* __restrict__ w,
-                                                               float* __restrict__ U)
+__device__ __forceinline__ void filter_rows(const DevPlan& P, const FilterSource& F, const float* __restrict__ w, float* __restrict__ U,
+                                            int row, int k)
 {
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = blockIdx.y;
     if (row >= P.rows_total) return;
     const int qi = find_class(P, row);
     const DevClass q = P.cls[qi];
@@ -65,6 +64,41 @@ __global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, Filter
                 U[(size_t)q.u_off + ((size_t)(i * tw + j) * P.Kpad + k) * q.Lpad + l] = u[i][j];
             }
 }
+
+__global__ __launch_bounds__(256) void filter_transform_kernel(DevPlan P, FilterSource F, const float* __restrict__ w,
+                                                               float* __restrict__ U)
+{
+    filter_rows(P, F, w, U, blockIdx.x * 256 + threadIdx.x, blockIdx.y);
+}
+
+// The same, and beside it the copies of the single-kernel path (fused.hip) and of the direct convolution (direct.hip), where the
+// plan has them: workgroups 0.. write the class layout, fused0.. the first, direct0.. the second; gap: floats between the copies,
+// which belong to the buffer.  A copy is a microsecond of work behind four of a launch: with the copies of fused.hip in a launch
+// of their own, and w gathered by a third where a data gradient reads it, training steps of first layers took 4 us more (7x7 at
+// stride 2, 64 224x224 images, 471 -> 466 us; 6x6 at stride 4, 7 101x101 images, 50 -> 46) and with nine such phases 97.
+struct FilterCopies {
+    int gx;  // workgroups of rows of the class layout
+    int fused0, direct0, end;
+    long long gap0, gap1, gap2, gap3;
+};
+__global__ __launch_bounds__(256) void filter_copies_kernel(DevPlan P, FilterSource F, FusedArgs Fu, DirectArgs D, FilterCopies B,
+                                                            const float* __restrict__ w, float* __restrict__ U)
+{
+    const int b = blockIdx.x, t = threadIdx.x;
+    if (b < B.fused0) {
+        filter_rows(P, F, w, U, (b % B.gx) * 256 + t, b / B.gx);
+        if (b == 0) {
+            for (long long i = B.gap0 + t; i < B.gap1; i += 256) U[i] = 0.f;
+            for (long long i = B.gap2 + t; i < B.gap3; i += 256) U[i] = 0.f;
+        }
+    } else if (b < B.direct0) {
+        fused_filter(P, Fu, F, w, U, t, b - B.fused0);  // (kFusedMaxRows is one workgroup's)
+    } else {
+        const int nk = (D.Kpad + 127) / 128, e = b - B.direct0;
+        direct_filter(D, F, w, U + B.gap3, e / nk, e % nk);
+    }
+}
+static_assert(kFusedMaxRows <= 256, "rows of fused_filter");
 
 // The same for several stride-1 sub-convolutions that read one w (the phases of a data gradient), one grid plane each: four
 // launches of 4.3 us and the gaps between them for a 5x5 layer at stride 2 with 67 and 93 channels become one.  Further grid
@@ -411,7 +445,16 @@ dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource&
 {
     const DevPlan& d = p.d;
     if (p.direct_only) return launch_direct_filter(p.direct, src, w, U + p.ud_begin, stream);
-    if (p.split_ok) {
+    if (p.fused_ok || p.direct_ok) {
+        FilterCopies b{};
+        b.gx = (d.rows_total + 255) / 256;
+        b.fused0 = b.gx * d.Kpad;
+        b.direct0 = b.fused0 + (p.fused_ok ? p.fused.nslices * 32 : 0);
+        b.end = b.direct0 + (p.direct_ok ? p.direct.all_steps * ((p.direct.Kpad + 127) / 128) : 0);
+        if (p.fused_ok) { b.gap0 = (long long)p.uf_gap; b.gap1 = (long long)p.uf_begin; }
+        if (p.direct_ok) { b.gap2 = (long long)p.ud_gap; b.gap3 = (long long)p.ud_begin; }
+        hipLaunchKernelGGL(filter_copies_kernel, dim3(b.end), dim3(256), 0, (hipStream_t)stream, d, src, p.fused, p.direct, b, w, U);
+    } else if (p.split_ok) {
         hipLaunchKernelGGL(filter_transform_split_kernel, dim3((d.rows_total + kFtRows - 1) / kFtRows, d.Kpad / kFtK), dim3(256), 0,
                            (hipStream_t)stream, d, src, w, U, reinterpret_cast<uint32_t*>(U + p.us_begin));
     } else {

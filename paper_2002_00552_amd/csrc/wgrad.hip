@@ -875,7 +875,7 @@ dwm_status_t dwm_bwd_filter_plan_create(dwm_bwd_filter_plan_t** out, int N, int 
     using namespace dwm;
     if (!out) return DWM_ERR_INVALID_ARG;
     dwm_plan_t* fwd = nullptr;
-    dwm_status_t st = dwm_plan_create(&fwd, N, C, H, W, K, R, S, stride, pad);
+    dwm_status_t st = plan_from_layer(&fwd, N, C, H, W, K, R, S, stride, pad, false);
     if (st != DWM_OK) return st;
     dwm_bwd_filter_plan* bp = nullptr;
     st = wgrad_build(&bp, fwd, K, 32);

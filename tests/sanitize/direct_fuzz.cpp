@@ -12,7 +12,6 @@ namespace dwm {
 dwm_status_t launch_filter_transform(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_input_transform(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_contract_output(const dwm_plan&, const float*, float*, float*, void*) { return DWM_OK; }
-dwm_status_t launch_fused_filter(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_fused_forward(const dwm_plan&, const float*, const float*, float*, void*) { return DWM_OK; }
 }
 using namespace dwm;
@@ -28,6 +27,17 @@ static int pick(int lo, int hi) { return lo + (int)(rnd() % (uint32_t)(hi - lo +
     } while (0)
 
 static int dv(const FastDiv& f, int n) { int q = (int)(((((unsigned long long)(unsigned)n * f.mul) >> 32) + (unsigned)n) >> f.shift); return q; }
+
+// Every tap that the filter transform reads from `F` for these problems: the one meant (tap r, s of problem i is tap
+// (oy_i + step*r, ox_i + step*s) of the R x S filter whose element strides are ks, cs), and so inside w
+struct Taps { int oh, ow, step; };
+static void reads(const DirectArgs& A, const FilterSource& F, const std::vector<Taps>& taps, long long ks, long long cs, int R, int S) {
+    for (int i = 0; i < A.nprob; ++i) for (int r = 0; r < A.p[i].R; ++r) for (int s = 0; s < A.p[i].S; ++s) {
+        const int wr = taps[i].oh + taps[i].step * r, ws = taps[i].ow + taps[i].step * s;
+        CHECK(wr >= 0 && wr < R && ws >= 0 && ws < S);
+        for (int k : {0, A.K - 1}) for (int c : {0, A.C - 1}) CHECK(A.p[i].at(F, k, c, r, s) == k * ks + c * cs + (long long)wr * S + ws);
+    }
+}
 
 static void replay(const DirectArgs& A, bool full) {
     const DirectShape& sh = kDirectShapes[A.shape];
@@ -149,9 +159,11 @@ int main(int argc, char** argv)
             ++n;
             if (direct_setup(N, C, H, W, K, st, OH, OW, 1, 1, &q, 1, v, &A)) {
                 ++took; replay(A, it != 4);
+                reads(A, FilterSource{0, (long long)C * R * S, R * S, S, 1}, {{0, 0, 1}}, (long long)C * R * S, R * S, R, S);
             }
             // data gradient: all phases
             std::vector<DirectProb> ps;
+            std::vector<Taps> tp;
             for (int a = 0; a < st; ++a) for (int b = 0; b < st; ++b) {
                 DirectProb q{};
                 const int na = a < R ? (R - a + st - 1) / st : 0, nb = b < S ? (S - b + st - 1) / st : 0;
@@ -159,11 +171,18 @@ int main(int argc, char** argv)
                 const int u1 = H + P - 1 - a >= 0 ? (H + P - 1 - a) / st : -1, v1 = W + P - 1 - b >= 0 ? (W + P - 1 - b) / st : -1;
                 q.R = na; q.S = nb; q.OH = u1 - u0 + 1; q.OW = v1 - v0 + 1; q.Ph = na - 1 - u0; q.Pw = nb - 1 - v0;
                 q.oy = st * u0 + a - P; q.ox = st * v0 + b - P;
-                if (na > 0 && nb > 0 && q.OH > 0 && q.OW > 0) ps.push_back(q);
+                q.base = (long long)(st * (na - 1) + a) * S + st * (nb - 1) + b;
+                if (na > 0 && nb > 0 && q.OH > 0 && q.OW > 0) { ps.push_back(q); tp.push_back({st * (na - 1) + a, st * (nb - 1) + b, -st}); }
             }
             ++n;
             if (!ps.empty() && direct_setup(N, K, OH, OW, C, 1, H, W, st, st, ps.data(), (int)ps.size(), v, &A)) {
                 ++took; replay(A, it != 4);
+                FilterSource F{0, R * S, (long long)R * S * C, -st * S, -st};
+                reads(A, F, tp, R * S, (long long)R * S * C, R, S);
+                if (st == 1) {  // (a plan of its own: the base is the source's)
+                    std::swap(F.base, A.p[0].base);
+                    reads(A, F, tp, R * S, (long long)R * S * C, R, S);
+                }
             }
         }
     }

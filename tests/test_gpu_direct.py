@@ -1,12 +1,13 @@
-"""The direct convolution on the bfloat16 matrix cores (three-way split operands, no transforms) through the C ABI: the strided
-data gradient in one launch, at the edges of its tiles, chunks, groups of channels and strips, against FP64 and against the
-sub-convolutions by the method's transforms."""
+"""The direct convolution on the bfloat16 matrix cores (three-way split operands, no transforms) through the C ABI: forward and
+the data gradient in one launch, at the edges of its tiles, chunks, groups of channels and strips, against FP64 and against
+the method's transforms."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import paper_2002_00552_amd as dwm
+from dwm_gpu import Runner
 from test_gpu_backward import BwdRunner
 
 pytestmark = pytest.mark.gpu
@@ -23,6 +24,20 @@ BWD = [
     (4, 35, 9, 11, 7, 2, 2, 3, 1),       # stride above the kernel: phases without a tap; fewer than eight channels of dy
     (24, 130, 36, 36, 71, 2, 2, 2, 1),   # tiles of 128 filters
     (36, 300, 28, 28, 150, 3, 3, 2, 1),  # several rounds of the chip
+]
+
+# the same for the forward pass; "1": the single-kernel path is what it would be otherwise
+FWD = [
+    ((1, 16, 32, 32, 16, 5, 5, 1, 2), 1),       # one small image
+    ((3, 29, 49, 44, 23, 3, 3, 3, 0), 0),       # three phases of columns, odd rows past the last window
+    ((10, 45, 28, 27, 78, 3, 3, 1, 0), 1),      # three slices of filters
+    ((105, 28, 32, 36, 62, 2, 2, 1, 1), 1),     # pixels of one tile in two images
+    ((1, 65, 7, 9, 33, 1, 1, 1, 0), 0),         # one tap, a channel past a group, a filter past a tile
+    ((2, 33, 12, 230, 70, 3, 7, 1, 2), 1),      # wide rows: strips; R != S
+    ((3, 17, 25, 31, 300, 4, 4, 2, 3), 0),      # padding of a whole kernel but one tap
+    ((200, 18, 5, 5, 33, 3, 3, 1, 0), 0),       # tiles of several images
+    ((16, 128, 56, 55, 256, 3, 3, 2, 1), 0),    # tiles of 256 filters
+    ((16, 96, 40, 40, 128, 2, 3, 1, 1), 0),     # many workgroups
 ]
 
 
@@ -110,3 +125,92 @@ def test_values_that_the_split_cannot_carry(shape, where, value):
         assert np.all(np.isnan(dx[hit]))
     else:
         assert np.array_equal(dx[hit], np.where(sign[hit] > 0, value, -value))
+
+
+def _forward(shape, x, w, variants=None):
+    r = Runner(*shape, variants=variants)
+    try:
+        r.Ugw.fill_(float("nan"))
+        r.set_filter(w)
+        y = r.forward(x)
+        assert bool(torch.isfinite(r.Ugw).all()) or not np.all(np.isfinite(w))  # every copy, and what lies between them
+        return y, dwm.dwm_plan_forward_kernel(r.plan)
+    finally:
+        r.close()
+
+
+def _layer(shape, seed):
+    N, C, H, W, K, R, S, s, P = shape
+    rng = np.random.default_rng(seed)
+    return (rng.uniform(-1, 1, (N, C, H, W)).astype(np.float32),
+            (rng.standard_normal((K, C, R, S)) * np.sqrt(2.0 / (C * R * S))).astype(np.float32))
+
+
+@pytest.mark.parametrize("shape, other", FWD)
+def test_forward(shape, other):
+    """Sampled outputs within 1e-6 of the largest, in the 2-norm no further from FP64 than the transforms' path; the same bits
+    again, and without a workspace; and the paths that a variant asks for run."""
+    x, w = _layer(shape, 6)
+    y, kernel = _forward(shape, x, w)
+    assert kernel == 2
+    idx = np.random.default_rng(7).choice(y.size, min(y.size, 6000), replace=False)
+    ref = oracle.direct_f64_at(x, w, shape[7], shape[8], idx)
+    err = y.ravel()[idx] - ref
+    assert np.all(np.isfinite(y))
+    assert np.max(np.abs(err)) <= 1e-6 * np.max(np.abs(ref))
+    for variants in [{"forward": 0}, {"input": 0}] + ([{"forward": 1}] if other else []):
+        z, kernel = _forward(shape, x, w, variants)
+        assert kernel == (other if variants != {"forward": 0} else 0)
+        assert np.max(np.abs(z.ravel()[idx] - ref)) <= 2e-6 * np.max(np.abs(ref))
+        assert np.linalg.norm(err) <= 1.05 * np.linalg.norm(z.ravel()[idx] - ref)
+    r = Runner(*shape)
+    try:
+        r.set_filter(w)
+        assert np.array_equal(r.forward(x), y)
+        if other or dwm.dwm_plan_workspace_bytes(r.plan) <= dwm.dwm_static_scratch_bytes():
+            r.y.fill_(float("nan"))
+            dwm.dwm_conv_forward_static(r.plan, r.x.data_ptr(), r.Ugw.data_ptr(), r.y.data_ptr(), r.stream())
+            torch.cuda.synchronize()
+            assert np.array_equal(r.y.cpu().numpy(), y)
+        else:
+            with pytest.raises(dwm.DwmError):
+                dwm.dwm_conv_forward_static(r.plan, r.x.data_ptr(), r.Ugw.data_ptr(), r.y.data_ptr(), r.stream())
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("shape", [(2, 24, 14, 14, 40, 7, 7, 1, 3), (5, 19, 17, 23, 66, 3, 5, 1, 0), (3, 40, 9, 9, 21, 3, 3, 1, 4)])
+def test_data_gradient_at_stride_1(shape):
+    N, C, H, W, K, R, S, s, P = shape
+    dy, w = _data(shape, 8)
+    dx = _grad(shape, dy, w)
+    ref = oracle.backward_data_f64(dy, w, (N, C, H, W), s, P)
+    assert np.max(np.abs(dx - ref)) <= 1e-6 * np.max(np.abs(ref)), shape
+    assert np.linalg.norm(dx - ref) <= 1.05 * np.linalg.norm(_grad(shape, dy, w, 0) - ref)
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan, -3.4e38])
+def test_forward_of_values_that_the_split_cannot_carry(value):
+    """One such value in x: the outputs that its window reaches are infinite, NaN or large as the definition says, all others as
+    without it: where a wave's other outputs are computed again, to the rounding of 405 products of 1e-3 added in binary32, whose
+    sums lie below the largest output (sqrt(405) half roundings of it, 1.2e-6)."""
+    shape = FWD[2][0]
+    N, C, H, W, K, R, S, s, P = shape
+    x, w = _layer(shape, 9)
+    w *= np.float32(1e-3)
+    rest, _ = _forward(shape, x, w)
+    at = (N // 2, C // 2, H // 2, W // 2)
+    x[at] = value
+    y, _ = _forward(shape, x, w)
+    tap = np.zeros_like(y)  # the tap of w that meets it
+    for r in range(R):
+        for q in range(S):
+            tap[at[0], :, at[2] - r, at[3] - q] = w[:, at[1], r, q]
+    hit = tap != 0
+    assert np.max(np.abs(y[~hit] - rest[~hit])) <= 1.2e-6 * np.max(np.abs(rest))
+    assert np.mean(y[~hit] != rest[~hit]) < 0.01
+    if np.isnan(value):
+        assert np.all(np.isnan(y[hit]))
+    else:
+        expect = tap[hit].astype(np.float64) * value
+        assert np.all((y[hit] == expect) | (np.abs(y[hit] - expect) <= 1e-6 * np.abs(expect)))
