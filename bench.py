@@ -202,7 +202,10 @@ def bench_backward_filter(args, L, x, w):
     dwm.dwm_plan_destroy(fwd)
     tiles = [sum((c.len_h + 1) * (c.len_w + 1) * -(-L.K // t) * -(-c.Lpad // t) for c in cls) for t in (64, 128)]
     split = info.n_tiles == tiles[1] != tiles[0]  # tiles of 128: the GEMM on the bfloat16 matrix cores
-    peak = PEAK_SPLIT_F32 if split else PEAK_MFMA_F32
+    plain = dwm.dwm_bwd_filter_kernel(plan) == 2
+    peak = PEAK_SPLIT_F32 if split or plain else PEAK_MFMA_F32
+    flops = info.direct_flops if plain else info.winograd_flops
+    kernel = "wgrad_direct_kernel" if plain else "wgrad_split_kernel" if split else "wgrad_gemm_kernel"
     out = {
         "metric": "direct-conv-equivalent TFLOP/s of the DWM filter gradient (fp32, 1 GPU); MSE vs FP64 definition",
         "value": info.direct_flops / dt / 1e12, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps,
@@ -211,9 +214,8 @@ def bench_backward_filter(args, L, x, w):
         "config": {"workload": L.name + "_backward_filter", "planes": info.n_planes, "tiles": info.n_tiles,
                    "splits": info.splits, "direct_GFLOP": info.direct_flops / 1e9,
                    "winograd_GFLOP": info.winograd_flops / 1e9, "workspace_MB": ws.numel() * 4 / 1e6},
-        "roofline": {"kernel": ("wgrad_split_kernel" if split else "wgrad_gemm_kernel") + " (whole step timed)", "bound": "mfma",
-                     "achieved": info.winograd_flops / dt / 1e12, "peak": peak, "unit": "TFLOP/s",
-                     "frac": info.winograd_flops / dt / 1e12 / peak, "traffic": None},
+        "roofline": {"kernel": kernel + " (whole step timed)", "bound": "mfma",
+                     "achieved": flops / dt / 1e12, "peak": peak, "unit": "TFLOP/s", "frac": flops / dt / 1e12 / peak, "traffic": None},
     }
     if not args.no_check:
         import oracle

@@ -313,6 +313,7 @@ DWM_API dwm_status_t dwm_conv_backward_data(const dwm_bwd_data_plan_t* plan, con
  * computed part by part as dg = G^T [ sum over tiles of (A dY A^T) .* V ] G with V = B^T d B the
  * forward pass's transformed input; the sum over tiles is a GEMM per Winograd-domain plane.
  * dw [K][C][R][S] is fully overwritten; results do not vary from run to run.
+ * (or as the plain sum above, where that takes less time: dwm_bwd_filter_kernel).
  * The plan takes the forward layer's shape; the workspace (dwm_bwd_filter_workspace_bytes,
  * 256-byte aligned) holds V, A dY A^T (not for layers with few input channels, where it is never
  * written to memory) and the partial sums.  Conventions as for the forward calls.
@@ -331,6 +332,13 @@ DWM_API dwm_status_t dwm_bwd_filter_plan_create(dwm_bwd_filter_plan_t** out, int
                                                 int R, int S, int stride, int pad);
 DWM_API dwm_status_t dwm_bwd_filter_plan_destroy(dwm_bwd_filter_plan_t* plan);
 DWM_API dwm_status_t dwm_bwd_filter_plan_info(const dwm_bwd_filter_plan_t* plan, dwm_bwd_filter_info_t* info);
+/* What dwm_conv_backward_filter runs: 0 = V, A dY A^T and a GEMM per plane, 1 = the form for few input channels, 2 = the plain
+ * convolution's products, x and dy read as they are, on the bfloat16 matrix cores with every binary32 operand as the sum of
+ * three bfloat16 numbers (where it takes less time; values that those cannot carry take binary32 for the taps that they
+ * reach).  dwm_bwd_filter_plan_info describes the first two in any case.  -1: null plan. */
+DWM_API int dwm_bwd_filter_kernel(const dwm_bwd_filter_plan_t* plan);
+/* stage "path": 0 = by the method's transforms, -1 = the planner's choice.  Before dwm_bwd_filter_set_workspace only. */
+DWM_API dwm_status_t dwm_bwd_filter_set_variant(dwm_bwd_filter_plan_t* plan, const char* stage, int variant);
 DWM_API size_t dwm_bwd_filter_workspace_bytes(const dwm_bwd_filter_plan_t* plan);
 DWM_API dwm_status_t dwm_bwd_filter_set_workspace(dwm_bwd_filter_plan_t* plan, void* ws_dev, size_t bytes);
 /* x_dev [N][C][H][W], dy_dev [N][K][OH][OW], dw_dev [K][C][R][S]. */

@@ -100,6 +100,8 @@ _SIGNATURES = {
     "dwm_bwd_filter_plan_create": (_I, [ctypes.POINTER(_P)] + [_I] * 9),
     "dwm_bwd_filter_plan_destroy": (_I, [_P]),
     "dwm_bwd_filter_plan_info": (_I, [_P, ctypes.POINTER(dwm_bwd_filter_info_t)]),
+    "dwm_bwd_filter_kernel": (_I, [_P]),
+    "dwm_bwd_filter_set_variant": (_I, [_P, ctypes.c_char_p, _I]),
     "dwm_bwd_filter_workspace_bytes": (ctypes.c_size_t, [_P]),
     "dwm_bwd_filter_set_workspace": (_I, [_P, _P, ctypes.c_size_t]),
     "dwm_conv_backward_filter": (_I, [_P, _P, _P, _P, _P]),
@@ -311,6 +313,14 @@ def dwm_bwd_filter_plan_info(plan):
     info = dwm_bwd_filter_info_t()
     _check(lib().dwm_bwd_filter_plan_info(plan, ctypes.byref(info)), "dwm_bwd_filter_plan_info")
     return info
+
+
+def dwm_bwd_filter_kernel(plan):
+    return int(lib().dwm_bwd_filter_kernel(plan))
+
+
+def dwm_bwd_filter_set_variant(plan, stage, variant):
+    _check(lib().dwm_bwd_filter_set_variant(plan, stage.encode(), variant), "dwm_bwd_filter_set_variant(%s)" % stage)
 
 
 def dwm_bwd_filter_workspace_bytes(plan):

@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdwm.so")
-SOURCES = ["plan.cpp", "setup.cpp", "transforms.hip", "contract.hip", "contract_split.hip", "fused.hip", "direct.hip",
+SOURCES = ["plan.cpp", "setup.cpp", "transforms.hip", "contract.hip", "contract_split.hip", "fused.hip", "direct.hip", "wgrad_direct.hip",
            "contract_batch.hip",
            "backward.hip", "backward_small.hip", "wgrad.hip", "wgrad_split.hip", "half.hip", "bf16.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

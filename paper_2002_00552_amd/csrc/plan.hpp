@@ -415,6 +415,24 @@ struct DirectArgs {
     size_t filter_floats() const { return wd_bytes / 4 + w32_floats; }
 };
 
+// The filter gradient as a direct convolution on split operands (wgrad_direct.hip)
+struct WdArgs {
+    int N, C, H, W, K, R, S, s, P, OH, OW;
+    int NB, BH;                   // bands of an image that stand for images, their output rows
+    int per_image;                // offsets are from each image (bands, or eight images of more than 2 GiB), not from the eight's first
+    int lgw;                      // a unit's patch of 16 output pixels is 2^lgw wide
+    int npx, npy, nunits;         // patches across, down a band; units = groups of eight images x patches
+    int xunits, ustep, pieces;    // units of an XCD, from one of a piece's to its next; pieces (eight for each step, at most one a unit)
+    int cols, nkt, ntiles;        // C*R*S; tiles of filters, of filters and columns
+    int rows, pcols;              // x's patch
+    int mb, nb;                   // a tile is 32*mb filters x 32*nb columns
+    int stride;                   // floats from one piece's sums to the next
+    FastDiv div_rs, div_plane, div_pcols, div_nb, div_npx, div_npy;
+    // (not read by the kernels)
+    size_t lds_bytes;
+    double us;                    // time by wd_setup's model
+};
+
 // The transformed filters of several sub-convolutions in one launch (transforms.hip): of each what DevPlan says, in short
 // (their pieces have phase 0).
 constexpr int kMaxFilterBatch = 9;
@@ -543,6 +561,9 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
 bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out);
 dwm_status_t launch_direct(const DirectArgs& a, const float* x, const float* U, float* y, void* stream);
 dwm_status_t launch_direct_filter(const DirectArgs& a, const FilterSource& src, const float* w, float* U, void* stream);
+// setup.cpp / wgrad_direct.hip: the filter gradient likewise
+bool wd_setup(int N, int C, int H, int W, int K, int R, int S, int s, int P, int OH, int OW, WdArgs* out);
+dwm_status_t launch_wgrad_direct(const WdArgs& a, const float* x, const float* dy, float* partial, float* dw, void* stream);
 // contract_batch.hip
 dwm_status_t launch_contract_batch(const BatchArgs& a, const PlaneTable& pt, int lc, const float* U, const float* V,
                                    float* partial, float* y, void* stream);

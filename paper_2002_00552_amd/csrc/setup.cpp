@@ -287,6 +287,72 @@ bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int
     return found;
 }
 
+// The direct filter gradient with the tile, patch, bands and pieces that take the least time by this model (fitted to 150 drawn
+// layers, rms of the logarithm 0.22): cycles at 2 GHz of a workgroup's unit -- its MFMAs, 480 a wave's 64 staged pixels,
+// 1.5 for each 128-byte line that dy's and x's rows touch, 2000 of latency --, of two workgroups on a CU their sum or the largest
+// of what they share, a tile's sums at the end, and the pieces' trip through memory.
+bool wd_setup(int N, int C, int H, int W, int K, int R, int S, int s, int P, int OH, int OW, WdArgs* out)
+{
+    const long long lim = 1LL << 29;  // (elements: byte offsets within an image are 32 bits, signed)
+    if (((long long)C * H + R + P + 16LL * s) * W >= lim || (K + 64LL) * OH * OW >= lim || (long long)K * C * R * S >= (1LL << 31) - 64 || R > 64 || S > 64 || s > 64) return false;
+    const long long cols = (long long)C * R * S;
+    const int rs = R * S;
+    if (cols >= (1LL << 30) || K > (1 << 24)) return false;
+    bool found = false;
+    for (int mb = K > 32 ? 2 : 1; mb >= 1; --mb)
+        for (int nb : {5, 3, 2, 1})
+            for (int lgw = 0; lgw <= 4; ++lgw) {
+                const int kt = 32 * mb, ct = 32 * nb, PW = 1 << lgw, PH = 16 >> lgw;
+                const long long ncol = (cols + ct - 1) / ct, nkt = (K + kt - 1) / kt, ntiles = ncol * nkt;
+                const int nch = ncol == 1 ? C : std::min(C, ct % rs == 0 ? ct / rs : (ct - 2) / rs + 2);
+                const int rows = s * (PH - 1) + R, pcols = s * (PW - 1) + S;
+                const long long npix = (long long)nch * rows * pcols;
+                const size_t lds = 16 * (size_t)(kt * 48 + 16) + (size_t)npix * 48;
+                if (npix > 4096 || lds > 80 * 1024 || ntiles > (1 << 20)) continue;
+                const double mfma = 439.0 * mb * nb, stage = (kt / 4 + (npix + 511) / 512 * 8) * 119.0, ends = 625.0 * mb * nb;
+                const double lines = 1.5 * 8 * (kt * PH * (1 + (PW - 1) / 32.0) + nch * rows * (1 + (pcols - 1) / 32.0));
+                const double lone = mfma + stage + lines + 1980.0;
+                auto p4 = [](double v) { return v * v * v * v; };
+                const double pair = std::sqrt(std::sqrt(p4(2 * mfma) + p4(2 * stage) + p4(2 * lines) + p4(lone)));
+                for (int NB = 1; NB <= 8 && NB <= OH; ++NB) {
+                    if (NB > 1 && N >= 64) break;
+                    const int BH = (OH + NB - 1) / NB;
+                    const long long npx = (OW + PW - 1) / PW, npy = (BH + PH - 1) / PH, groups = ((long long)N * NB + 7) / 8;
+                    const long long nunits = groups * npx * npy;
+                    if (nunits >= (1 << 29)) continue;
+                    for (int target : {256, 512, 1024}) {
+                        const long long xunits = (nunits + 7) / 8, per = std::min(std::max(1LL, target / ntiles / 8), xunits);
+                        const long long upp = (xunits + per - 1) / per, pieces = nunits <= 8 ? nunits : 8 * per;
+                        const long long wgs = pieces * ntiles, left = wgs % 512;
+                        const double cycles = (wgs / 512) * (upp * pair + ends) + (left > 256 ? upp * pair + ends : left > 0 ? upp * lone + ends : 0.0);
+                        const double bytes = (double)K * cols * 4 * pieces;
+                        const double us = 3.5 + cycles / 2000.0 + (pieces > 1 ? 2.2 + 2 * bytes / 4.3e6 : 0.0);
+                        if ((found && us >= out->us) || bytes > 256e6) continue;
+                        found = true;
+                        WdArgs a{};
+                        a.N = N; a.C = C; a.H = H; a.W = W; a.K = K; a.R = R; a.S = S; a.s = s; a.P = P; a.OH = OH; a.OW = OW;
+                        a.NB = NB; a.BH = BH; a.lgw = lgw;
+                        a.per_image = NB > 1 || ((long long)C * H + R + P + 16LL * s) * W >= lim / 8 || (K + 64LL) * OH * OW >= lim / 8;
+                        a.npx = (int)npx; a.npy = (int)npy; a.nunits = (int)nunits; a.xunits = (int)xunits; a.ustep = (int)per; a.pieces = (int)pieces;
+                        a.cols = (int)cols; a.nkt = (int)nkt; a.ntiles = (int)ntiles;
+                        a.rows = rows; a.pcols = pcols; a.mb = mb; a.nb = nb;
+                        a.stride = (int)((K * cols + 63) / 64 * 64);
+                        a.lds_bytes = lds;
+                        a.us = us;
+                        *out = a;
+                    }
+                }
+            }
+    if (!found) return false;
+    out->div_rs.init((unsigned)rs);
+    out->div_plane.init((unsigned)(out->rows * out->pcols));
+    out->div_pcols.init((unsigned)out->pcols);
+    out->div_nb.init((unsigned)out->NB);
+    out->div_npx.init((unsigned)out->npx);
+    out->div_npy.init((unsigned)out->npy);
+    return true;
+}
+
 // Does the LDS-staged form apply, and with how many channels per workgroup: the rows a block
 // stages must fit in LDS.  The row count depends on where a block of 64 tiles starts; the
 // pattern repeats after at most TH*TW blocks, so the maximum is found by walking them.

@@ -20,9 +20,11 @@
 // (wgrad_split.hip): 128x128 tiles, operands split three ways.
 // Layers with few input channels (every class has at most 32 rows) and many tiles take another
 // form of steps 2-3 that never builds dM: see wgrad_small_body / wgrad_small_all_kernel.
+// Where the plain convolution's products take less time than all this, they are taken instead (wgrad_direct.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <new>
 
 #include "dma.hpp"
@@ -635,6 +637,10 @@ struct dwm_bwd_filter_plan {
     bool split;                        // the GEMM runs on the bfloat16 matrix cores (wgrad_split.hip)
     int small_kt;                      // 64-filter tiles
     size_t sum_bytes;                  // the summed dU after the partials
+    double gemm_us;                    // the GEMM's time by the model that chose its geometry
+    bool direct_ok, no_direct;         // as a direct convolution (wgrad_direct.hip): planned; the transforms were asked for
+    dwm::WdArgs direct;
+    bool use_direct() const { return direct_ok && !no_direct; }
     int n_pass;                        // passes: (class, rows r0 .. r0 + 16 * lb) with lb in {1, 2}
     int pass_lb[2 * dwm::kMaxClasses], pass_code[2 * dwm::kMaxClasses];
     dwm::SmallArgs sc[2 * dwm::kMaxClasses];
@@ -838,6 +844,7 @@ static dwm_status_t wgrad_build(dwm_bwd_filter_plan_t** out, dwm_plan_t* fwd, in
     bp->sum_bytes = 0;
     bp->split = false;
     bp->small = small_setup(*bp, small_max_rows);
+    bp->gemm_us = us;
     // The GEMM on the bfloat16 matrix cores: output tiles of 128x128, a block of 64 tiles takes 5.2 us with two workgroups
     // on a CU and 3.2 with one; dM is written at 4.3 TB/s (six bytes an element; the fp32 form's at 4.5, four bytes).
     // Measured, whole gradient, fp32 GEMM -> here (dM shared between planes in both): 7x7 256->256 28x28 N=32 860 -> 703 us,
@@ -848,6 +855,7 @@ static dwm_status_t wgrad_build(dwm_bwd_filter_plan_t** out, dwm_plan_t* fwd, in
     if (!bp->small && K > 64 && geometry(kWsplitTile, 5.2, 3.2, as, &split_us) &&
         split_us + 1.4e-6 * (double)as.tblocks * as.dm_rows * 64 < us + 0.9e-6 * (double)a.tblocks * a.dm_rows * 64) {
         bp->split = true;
+        bp->gemm_us = split_us;
         a = as;
         bp->dm_bytes = (size_t)a.tblocks * a.dm_rows * 384;
         bp->partial_bytes = (size_t)a.splits * a.split_floats * sizeof(float);
@@ -865,6 +873,16 @@ static int small_cost(const dwm_bwd_filter_plan& bp)
     int c = 0;
     for (int i = 0; i < d.ncls; ++i) c += (d.cls[i].lh + 1) * (d.cls[i].lw + 1) * (d.cls[i].Lpad / 16);
     return c;
+}
+
+// The gradient's time (us) by the transforms: launches, what they read and write, the GEMM's by its own model (fitted to 254 drawn
+// layers, rms of the logarithm 0.14 and, of the form for few channels, 0.11)
+static double transforms_us(const dwm_bwd_filter_plan& bp)
+{
+    const dwm::DevPlan& d = bp.fwd->d;
+    const double x = 4.0 * d.N * d.C * d.H * d.W, dy = 4.0 * d.N * d.K * d.OH * d.OW, v = (double)bp.fwd_ws_bytes, part = (double)bp.partial_bytes;
+    if (bp.small) return 14.5 + (v + x) / 2.14e6 + dy / 13.7e6 + bp.winograd_flops / 128e6 + part / 2.17e6;
+    return 19.4 + 0.69 * bp.gemm_us + (v + x) / 5.92e6 + ((double)bp.dm_bytes + dy) / 4.86e6 + (part + (double)bp.sum_bytes) / 0.856e6;
 }
 
 dwm_status_t dwm_bwd_filter_plan_destroy(dwm_bwd_filter_plan_t* plan);
@@ -899,6 +917,14 @@ dwm_status_t dwm_bwd_filter_plan_create(dwm_bwd_filter_plan_t** out, int N, int 
             dwm_bwd_filter_plan_destroy(bw);
         }
     }
+    const DevPlan& d = bp->fwd->d;
+    // (Where the two models are closer than a fifth, either may be ahead: of 250 drawn layers this line took the direct one on those
+    // where it had 0.43 of the transforms' time in the mean, none slower.  7x7 at stride 2, 3 -> 64 channels, 64 224x224 images
+    // 322 -> 135 us; 5x5 at stride 2, 67 -> 93, five 35x29 images 40 -> 20; 3x3, 70 -> 34, one 8x8 image 22 -> 5.5.  It stays
+    // with the transforms where channels and filters are many and the map is not small: 3x3, 128 -> 128, 64 28x28 images 125
+    // against 150; 7x7, 256 -> 256, 32 28x28 images 614 against 950.)
+    bp->no_direct = false;
+    bp->direct_ok = wd_setup(N, C, H, W, K, R, S, stride, pad, d.OH, d.OW, &bp->direct) && bp->direct.us < 0.82 * transforms_us(*bp);
     *out = bp;
     return DWM_OK;
 }
@@ -922,8 +948,19 @@ dwm_status_t dwm_bwd_filter_plan_info(const dwm_bwd_filter_plan_t* plan, dwm_bwd
     return DWM_OK;
 }
 
+int dwm_bwd_filter_kernel(const dwm_bwd_filter_plan_t* plan) { return !plan ? -1 : plan->use_direct() ? 2 : plan->small ? 1 : 0; }
+
+dwm_status_t dwm_bwd_filter_set_variant(dwm_bwd_filter_plan_t* plan, const char* stage, int variant)
+{
+    if (!plan || !stage || std::strcmp(stage, "path") != 0 || variant < -1 || variant > 0) return DWM_ERR_INVALID_ARG;
+    if (plan->ws) return DWM_ERR_WORKSPACE;  // (its layout depends on the path)
+    plan->no_direct = variant == 0;
+    return DWM_OK;
+}
+
 size_t dwm_bwd_filter_workspace_bytes(const dwm_bwd_filter_plan_t* plan)
 {
+    if (plan && plan->use_direct()) return std::max<size_t>(plan->direct.pieces > 1 ? (size_t)plan->direct.pieces * plan->direct.stride * sizeof(float) : 0, 256);
     return plan ? plan->fwd_ws_bytes + plan->dm_bytes + plan->partial_bytes + plan->sum_bytes : 0;
 }
 
@@ -931,8 +968,10 @@ dwm_status_t dwm_bwd_filter_set_workspace(dwm_bwd_filter_plan_t* plan, void* ws_
 {
     if (!plan) return DWM_ERR_INVALID_ARG;
     if (!ws_dev || ((uintptr_t)ws_dev & 255u) || bytes < dwm_bwd_filter_workspace_bytes(plan)) return DWM_ERR_WORKSPACE;
-    const dwm_status_t st = dwm_plan_set_workspace(plan->fwd, ws_dev, plan->fwd_ws_bytes);
-    if (st != DWM_OK) return st;
+    if (!plan->use_direct()) {
+        const dwm_status_t st = dwm_plan_set_workspace(plan->fwd, ws_dev, plan->fwd_ws_bytes);
+        if (st != DWM_OK) return st;
+    }
     plan->ws = static_cast<float*>(ws_dev);
     return DWM_OK;
 }
@@ -943,6 +982,7 @@ dwm_status_t dwm_conv_backward_filter(const dwm_bwd_filter_plan_t* plan, const f
     using namespace dwm;
     if (!plan || !x_dev || !dy_dev || !dw_dev) return DWM_ERR_INVALID_ARG;
     if (!plan->ws) return DWM_ERR_WORKSPACE;
+    if (plan->use_direct()) return launch_wgrad_direct(plan->direct, x_dev, dy_dev, plan->ws, dw_dev, stream);
     const WgradArgs& a = plan->a;
     const DevPlan& d = plan->fwd->d;
     hipStream_t s = (hipStream_t)stream;
