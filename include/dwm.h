@@ -140,10 +140,11 @@ DWM_API dwm_status_t dwm_plan_destroy(dwm_plan_t* plan);
 /* Introspection of the decomposition (host only). */
 DWM_API dwm_status_t dwm_plan_info(const dwm_plan_t* plan, dwm_plan_info_t* info);
 /* What dwm_conv_forward runs as the plan stands: 0 = input transform + contraction, 1 = the single kernel for few input
- * channels (both as info.forward_path says), 2 = the layer's taps multiplied as they are, in one launch, on the bfloat16 matrix
- * cores with every binary32 operand as the sum of three bfloat16 numbers (C >= 16, where it takes less time than what
- * forward_path names; infinities, NaN, operands of about 2^112 or more and sums of 2^96 or more take fp32 matrix cores for the
- * outputs that they reach).  A variant of any stage asked for with dwm_plan_set_variant takes the layer to that stage instead.
+ * channels (both as info.forward_path says), 2 = the layer's taps multiplied as they are, in one launch (and a second one that
+ * adds up, where a few tiles are shared by many workgroups), on the bfloat16 matrix cores with every binary32 operand as the sum
+ * of three bfloat16 numbers (C >= 16, where it takes less time than what forward_path names; infinities, NaN, operands of about
+ * 2^112 or more and sums of 2^96 or more take fp32 matrix cores for the outputs that they reach).  A variant of any stage asked
+ * for with dwm_plan_set_variant takes the layer to that stage instead.
  * -1: null plan. */
 DWM_API int dwm_plan_forward_kernel(const dwm_plan_t* plan);
 DWM_API dwm_status_t dwm_plan_part(const dwm_plan_t* plan, int i, dwm_part_t* part);     /* i < n_parts   */

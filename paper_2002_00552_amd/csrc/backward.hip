@@ -431,7 +431,7 @@ dwm_status_t dwm_bwd_data_plan_create(dwm_bwd_data_plan_t** out, int N, int C, i
                 sp.pad_h = ph.na - 1 - u0; sp.pad_w = ph.nb - 1 - v0;
                 sp.OH = ph.UH; sp.OW = ph.UW;
                 sp.om = OutMap{H, W, s, ph.oy, s, ph.ox};
-                sp.direct = s == 1 && !bp->small_default;
+                sp.direct = sp.over_split = s == 1 && !bp->small_default;
                 sp.no_split = s > 1;  // (several sub-convolutions are contracted together, on fp32 MFMAs)
                 st = plan_from_spec(&ph.sub, sp);
                 if (st == DWM_OK) {
@@ -604,7 +604,7 @@ dwm_status_t dwm_conv_backward_data(const dwm_bwd_data_plan_t* plan, const float
         const dwm_status_t st = dwm_conv_forward(ph.sub, dy_dev, Ugw_dev + ph.u_off, dx_dev, stream);
         if (st != DWM_OK) return st;
     }
-    if (direct) return dwm::launch_fused_forward(*plan->direct, dy_dev, Ugw_dev + plan->u_direct_off, dx_dev, stream);
+    if (direct) return dwm::launch_fused_forward(*plan->direct, dy_dev, Ugw_dev + plan->u_direct_off, dx_dev, nullptr, stream);
     if (plan->merged) {
         if (!plan->ws) return DWM_ERR_WORKSPACE;
         const dwm_status_t st = dwm::launch_input_transform(*plan->merged, dy_dev, plan->ws, stream);

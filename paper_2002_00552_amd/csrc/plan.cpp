@@ -186,7 +186,7 @@ static double fp32_contract_us(const dwm_plan& p)
 // tile: 16 pieces 16.8 us, 32 pieces 20.5).  Measured, contraction, fp32 -> here: 7x7 256->256 28x28 N=32 698 -> 508 us,
 // 9x9 14x14 293 -> 205, 3x3 256->256 14x14 N=1 29 -> 18, N=8 30 -> 22; layers of about 200 of its tiles and short planes
 // (3x3 stride 2 128->256 56x56 N=32: 91 against 103) leave a quarter of the CUs idle and stay with the fp32 kernel.
-bool split_geometry(const dwm_plan& p, ContractGeometry* out)
+bool split_geometry(const dwm_plan& p, ContractGeometry* out, double* us)
 {
     if (plane_rows(p) < 1024 || p.d.K < 32) return false;
     bool found = false;
@@ -231,6 +231,7 @@ bool split_geometry(const dwm_plan& p, ContractGeometry* out)
             *out = c;
         }
     }
+    *us = best;
     return found && best < 0.97 * fp32_contract_us(p);
 }
 
@@ -244,8 +245,14 @@ extern "C" {
 // 16 -> 16 channels, one 32x32 image 12.1 -> 7.5; 3x3 at stride 2, 128 -> 256, 32 56x56 images 122 -> 86; 3x3, 128 -> 128, 64
 // 28x28 images 89 -> 82; 3x3, 40 -> 61, 78 images of 17x21 40.5 -> 13.3; 5x1, 56 -> 27, 36 images of 32x38 60 -> 19.6.  Of 72
 // drawn layers it took 0.49 of the time in the mean.  From 16 channels: below, a step's groups of eight are half empty, and
-// first layers are faster on fused.hip (7x7 at stride 2, 3 -> 64, 141 against 168).  Layers that the bfloat16 contraction takes
-// (contract_split.hip) stay with it.
+// first layers are faster on fused.hip (7x7 at stride 2, 3 -> 64, 141 against 168).
+// Layers that the bfloat16 contraction takes (contract_split.hip) stay with it in the forward pass, whose filter buffer has its
+// copy at the end; as data gradients at stride 1 they change over from 0.70 of the time of the three launches there, the filter's
+// further copy added (0.6 us a MB, written for every change of the weights).  Of 115 drawn gradients, filter transform included,
+// 85 change over, at 0.66 of the time in the mean and 0.94 at most; three that a copy at 0.3 us a MB let in were slower (7x7, 365 ->
+// 348, one 10x10 image, 66 MB: 111 against 134 us).  The convolution alone, before -> now (us): 3x3, 256 -> 256 channels, one
+// 14x14 image 20.7 -> 11.7, four 26.0 -> 16.2; 3x3, 224 -> 38, 8 27x27 29.0 -> 18.8; 7x7, 150 -> 140, one 33x33 47 -> 25.  Kept
+// away: 7x7, 256 -> 256, 32 28x28 613 -> 692.
 static bool direct_ahead(dwm_plan& p, const dwm::PlanSpec& sp)
 {
     const dwm::DevPlan& d = p.d;
@@ -255,8 +262,13 @@ static bool direct_ahead(dwm_plan& p, const dwm::PlanSpec& sp)
     q.oy = d.om.oy; q.ox = d.om.ox;
     const double x_bytes = 4.0 * d.N * d.C * d.H * d.W, y_bytes = 4.0 * d.N * d.K * d.OH * d.OW;
     const double us = p.fused_ok ? 13.0 + p.info.winograd_flops / 50e6 + (x_bytes + y_bytes) / 4e6
-                                 : 5.7 + 1.03 * dwm::fp32_contract_us(p) + ((double)p.v_floats * 4.0 + x_bytes) / 4.31e6;
-    return dwm::direct_choose(d.N, d.C, d.H, d.W, d.K, d.s, d.om.YH, d.om.YW, d.om.sy, d.om.sx, &q, 1, &p.direct) && p.direct.us < 0.85 * us;
+                                 : 5.7 + (p.split_ok ? p.split_us : 1.03 * dwm::fp32_contract_us(p)) + ((double)p.v_floats * 4.0 + x_bytes) / 4.31e6;
+    // (the contraction's partial outputs have a place in the workspace; the single kernel's layers need none)
+    const bool whole = d.om.sy == 1 && d.om.sx == 1 && d.om.oy == 0 && d.om.ox == 0 && d.OH == d.om.YH && d.OW == d.om.YW;
+    if (!dwm::direct_choose(d.N, d.C, d.H, d.W, d.K, d.s, d.om.YH, d.om.YW, d.om.sy, d.om.sx, &q, 1, &p.direct,
+                            p.fused_ok || !whole ? 0 : p.active().partial_floats))
+        return false;
+    return p.split_ok ? p.direct.us + 2.4e-6 * p.direct.filter_floats() < 0.70 * us : p.direct.us < 0.85 * us;
 }
 
 // One planning pass with the given splitting policy; *out is set on DWM_OK only.
@@ -389,7 +401,7 @@ static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool e
     // (the single-kernel path goes with the even-tail splitting only)
     p->fused_ok = even_tail && dwm::fused_setup(*p, &p->fused);
     p->inlds_ok = dwm::input_lds_setup(*p, &p->inlds, 0);
-    if (!p->fused_ok && with_split && !sp.no_split && dwm::split_geometry(*p, &p->split)) {
+    if (!p->fused_ok && with_split && !sp.no_split && dwm::split_geometry(*p, &p->split, &p->split_us)) {
         // the split copy of U: six bytes an element (padding included)
         p->split_ok = true;
         p->us_begin = p->filter_floats;  // (a multiple of 64: the class layout's sizes are)
@@ -407,7 +419,7 @@ static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool e
         }
         p->filter_floats = uf;
     }
-    if (sp.direct && (p->fused_ok || with_split) && !p->split_ok && direct_ahead(*p, sp)) {
+    if (sp.direct && (p->fused_ok || with_split) && (!p->split_ok || sp.over_split) && direct_ahead(*p, sp)) {
         p->direct_ok = true;
         p->ud_gap = p->filter_floats;
         p->ud_begin = (p->filter_floats + 63) / 64 * 64;
@@ -619,7 +631,7 @@ dwm_status_t dwm_conv_forward(const dwm_plan_t* plan, const float* x_dev, const 
 {
     if (!plan || !x_dev || !Ugw_dev || !y_dev) return DWM_ERR_INVALID_ARG;
     if (!plan->ws) return DWM_ERR_WORKSPACE;
-    if (plan->use_fused() || plan->use_direct()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, stream);
+    if (plan->use_fused() || plan->use_direct()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, plan->ws, stream);
     dwm_status_t st = dwm::launch_input_transform(*plan, x_dev, plan->ws, stream);
     if (st != DWM_OK) return st;
     return dwm::launch_contract_output(*plan, Ugw_dev, plan->ws, y_dev, stream);

@@ -377,6 +377,7 @@ constexpr int kNumDirectShapes = sizeof(kDirectShapes) / sizeof(kDirectShapes[0]
 constexpr int kDirectMaxProbs = 16;
 constexpr int kDirectSlots = 3;      // staged pixels a thread takes of a group at most
 constexpr int kDirectMaxUnits = 512; // of a chunk
+constexpr int kDirectMaxPieces = 16;
 // Where a filter lies in w: tap (r, s) of filter k and channel c is element base + k*sk + c*sc + r*sr + s*ss
 struct FilterSource {
     long long base, sk, sc;
@@ -404,6 +405,8 @@ struct DirectArgs {
     int rstep, rows_full, run;   // staged rows from one output row to the next, of a whole image, of a lone output row
     int row_px, lwp, P, ns;      // pixels per staged row, per phase; per group; ceil(P / threads)
     int nchunks, groups[2];      // groups of every chunk but the last, of the last
+    int pieces, cpp;             // workgroups that share a tile, each cpp chunks of it (the last what is left)
+    size_t piece_floats;         // from one piece's outputs to the next one's
     int Kpad, bias;              // bias: floats that the first pixel may lie before the image
     int all_steps;
     unsigned wd_bytes;
@@ -486,6 +489,7 @@ struct dwm_plan {
     // Ugw); a contraction variant or a way of sharing out the tiles that was asked for by number is contract.hip's
     bool split_ok, contract_forced;
     dwm::ContractGeometry split;
+    double split_us;  // its time by split_geometry's model
     size_t us_begin;
     bool use_split() const { return split_ok && !contract_forced && sk_mode == 0; }
     const dwm::ContractGeometry& active() const { return use_split() ? split : geo; }
@@ -522,6 +526,7 @@ struct PlanSpec {
     int OH, OW;
     OutMap om;
     bool direct;    // the direct convolution may be planned beside the rest
+    bool over_split; // ... of a layer that the bfloat16 contraction takes, too
     bool no_split;  // not contracted on the bfloat16 matrix cores: no split copy of U
 };
 dwm_status_t plan_from_spec(dwm_plan_t** out, const PlanSpec& sp);
@@ -537,7 +542,7 @@ dwm_status_t plan_from_spec_as_printed(dwm_plan_t** out, const PlanSpec& sp);
 // plan.cpp: geometry of a contraction variant for this plan; false if the variant does not apply
 bool contract_geometry(const dwm_plan& p, int variant, ContractGeometry* out);
 // ... and the shape and the sharing out of the contraction on the bfloat16 matrix cores; false where it does not pay
-bool split_geometry(const dwm_plan& p, ContractGeometry* out);
+bool split_geometry(const dwm_plan& p, ContractGeometry* out, double* us);
 // transforms.hip, contract.hip
 dwm_status_t launch_filter_transform(const dwm_plan& p, const float* w, float* U, void* stream);
 // the same for a plan whose filter lies in w with other strides
@@ -553,13 +558,16 @@ dwm_status_t launch_contract_output(const dwm_plan& p, const float* U, float* ws
 bool input_lds_setup(const dwm_plan& p, InLdsArgs* out, int cg_wish);
 // contract_split.hip
 dwm_status_t launch_contract_split(const dwm_plan& p, const float* U, float* ws, float* y, void* stream);
+// (direct_choose: tiles cut into pieces where their outputs fit partial_floats)
 // setup.cpp, direct.hip: problems p[0..n) of which R, S, Ph, Pw, OH, OW, oy, ox and base are set, with one shape; false where the
 // staged pixels or a table do not fit
 bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, int shape,
-                  DirectArgs* out);
+                  DirectArgs* out, int pieces = 1);
 // ... with the shape that takes the least time by its model
-bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out);
-dwm_status_t launch_direct(const DirectArgs& a, const float* x, const float* U, float* y, void* stream);
+bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out,
+                   size_t partial_floats = 0);
+// (partial: room for the pieces' outputs, where a tile is cut into pieces)
+dwm_status_t launch_direct(const DirectArgs& a, const float* x, const float* U, float* y, float* partial, void* stream);
 dwm_status_t launch_direct_filter(const DirectArgs& a, const FilterSource& src, const float* w, float* U, void* stream);
 // setup.cpp / wgrad_direct.hip: the filter gradient likewise
 bool wd_setup(int N, int C, int H, int W, int K, int R, int S, int s, int P, int OH, int OW, WdArgs* out);
@@ -574,5 +582,5 @@ dwm_status_t launch_bwd_small_filter(const BwdSmallArgs& a, int R, int S, const 
 dwm_status_t launch_bwd_small(const BwdSmallArgs& a, const float* dy, const float* U, float* dx, void* stream);
 // fused.hip
 bool fused_setup(const dwm_plan& p, FusedArgs* out);
-dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, void* stream);
+dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, float* ws, void* stream);
 }  // namespace dwm

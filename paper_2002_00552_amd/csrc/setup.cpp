@@ -156,11 +156,11 @@ bool fused_setup(const dwm_plan& p, FusedArgs* out)
 // and the matrix cores' power-limited 1.19 PFLOP/s.
 static double direct_us(const DirectArgs& a, const DirectShape& sh)
 {
-    const double w = sh.threads() / 256.0, waves = sh.threads() / 64.0, groups = (a.C + 7) / 8;
+    const double w = sh.threads() / 256.0, waves = sh.threads() / 64.0, groups = std::min((a.C + 7) / 8, a.cpp * a.groups[0]);
     double mean = 0.0, longest = 0.0;
     for (int i = 0; i < a.nprob; ++i) {
         auto share = [&](int steps) { return (steps + sh.wk - 1) / sh.wk; };
-        const double t = (double)(a.nchunks - 1) * share(a.p[i].steps[0]) + share(a.p[i].steps[1]);
+        const double t = a.pieces > 1 ? (double)a.cpp * share(a.p[i].steps[0]) : (double)(a.nchunks - 1) * share(a.p[i].steps[0]) + share(a.p[i].steps[1]);
         mean += t / a.nprob;
         longest = std::max(longest, t);
     }
@@ -169,20 +169,23 @@ static double direct_us(const DirectArgs& a, const DirectShape& sh)
     const double slots = groups * a.ns, store = 1180.0 * sh.mb * w / sh.wk;
     const double simd = mean * 368.0 * sh.mb * w + slots * 340.0 * w + store;
     const double address = 19.0 * (slots * waves * 8 + mean * waves * 3 * sh.mb + sh.mb * 32 * waves / sh.wk * (a.sx > 1 ? 2 : 1));
-    const double lone = longest * 368.0 * sh.mb * w + slots * 340.0 * w + a.nchunks * 5400.0 + store;
-    const double per_cu = a.ntiles / (double)kNumCUs, rounds = std::max(1.0, per_cu / on_cu < 3 ? std::ceil(per_cu / on_cu) : per_cu / on_cu + 0.5);
+    const double lone = longest * 368.0 * sh.mb * w + slots * 340.0 * w + a.cpp * 5400.0 + store;
+    const double wgs = (double)a.ntiles * a.pieces, per_cu = wgs / kNumCUs, rounds = std::max(1.0, per_cu / on_cu < 3 ? std::ceil(per_cu / on_cu) : per_cu / on_cu + 0.5);
     const double cycles = rounds * std::max(lone, std::min(on_cu, std::ceil(per_cu)) * std::max(simd, address));
-    const double flops = a.ntiles * mean * waves * sh.mb * 2 * 6 * 32768.0;
-    return std::max(cycles / 2100.0, flops / 1.19e9) + 4.3;
+    const double flops = wgs * mean * waves * sh.mb * 2 * 6 * 32768.0;
+    const double sum = a.pieces > 1 ? 3.0 + (2.0 * a.pieces + 1.0) * 4.0 * a.piece_floats / 5e6 : 0.0;
+    return std::max(cycles / 2100.0, flops / 1.19e9) + 4.3 + sum;
 }
 
-// The direct convolution with one of its shapes.
+// The direct convolution with one of its shapes, a tile's chunks shared by `pieces` workgroups.
 bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, int shape,
-                  DirectArgs* out)
+                  DirectArgs* out, int pieces)
 {
     const DirectShape& sh = kDirectShapes[shape];
     DirectArgs a{};
     if (n < 1 || n > kDirectMaxProbs || s > 64) return false;
+    if (pieces < 1 || pieces > kDirectMaxPieces || (pieces > 1 && (n > 1 || sy != 1 || sx != 1))) return false;  // (a piece's outputs lie as all of y)
+    a.pieces = pieces;
     a.shape = shape; a.kt = sh.kt(); a.npx = sh.px();
     a.N = N; a.C = C; a.H = H; a.W = W; a.K = K; a.s = s;
     a.YH = YH; a.YW = YW; a.sy = sy; a.sx = sx;
@@ -221,21 +224,23 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
         if ((cross + 1) * image * 4 + bias * 4 >= 0x7fff0000LL || ((cross + 1) * K + 256) * oplane * 4 >= 0x7fff0000LL) continue;
         const int ns = (int)((P + threads - 1) / threads);
         // (no number of groups is below this)
-        if (best > 0.0 && best <= (0.5 * ngroups * taps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) +
-                                   (double)ngroups * ns * 400 * (threads / 256.0) + 3000.0) * bw * nstrips / OW)
+        const double own = (double)ngroups / pieces;
+        if (best > 0.0 && best <= (0.5 * own * taps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) +
+                                   own * ns * 400 * (threads / 256.0) + 3000.0) * bw * nstrips / OW)
             continue;
         for (int G = 1; G <= ngroups; ++G) {
             if ((size_t)G * P * 48 > lds_max || G * taps + 1 > kDirectMaxUnits) break;
-            const int nchunks = (ngroups + G - 1) / G, gl = ngroups - (nchunks - 1) * G;
+            const int nchunks = (ngroups + G - 1) / G, gl = ngroups - (nchunks - 1) * G, cpp = (nchunks + pieces - 1) / pieces;
+            if ((pieces - 1) * cpp >= nchunks) continue;  // a piece without a chunk
             // cycles of a tile of the longest problem, as in direct_us
-            const double steps = (double)(nchunks - 1) * ((G * taps + 1) / 2 + sh.wk - 1) + (gl * taps + 1) / 2 + sh.wk - 1;
-            const double cost = (steps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) + (double)ngroups * ns * 400 * (threads / 256.0) + nchunks * 3000.0) *
+            const double steps = (double)(cpp - 1) * ((G * taps + 1) / 2 + sh.wk - 1) + ((pieces > 1 ? G : gl) * taps + 1) / 2 + sh.wk - 1;
+            const double cost = (steps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) + (pieces > 1 ? cpp * G : ngroups) * (double)ns * 400 * (threads / 256.0) + cpp * 3000.0) *
                                 bw * nstrips / OW;
             if (best > 0.0 && cost >= best) continue;
             best = cost;
             a.bw = bw; a.nstrips = nstrips; a.total_px = (int)total;
             a.lwp = lwp; a.row_px = (int)row_px; a.P = (int)P; a.ns = ns;
-            a.nchunks = nchunks;
+            a.nchunks = nchunks; a.cpp = cpp;
             a.groups[0] = nchunks > 1 ? G : gl; a.groups[1] = gl;
             a.lds_bytes = std::max<size_t>((size_t)a.groups[0] * P * 48, reduce) + tables;
         }
@@ -245,6 +250,7 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
     a.nkt = (K + a.kt - 1) / a.kt;
     const long long per = (long long)a.nkt * n;
     if (a.ntt * per > 0x3fffffffLL) return false;
+    a.piece_floats = pieces > 1 ? ((size_t)N * K * YH * YW + 63) / 64 * 64 : 0;
     a.ntiles = (int)(a.ntt * per);
     a.full8 = (int)(8 * per * (a.ntt / 8));
     a.Kpad = a.nkt * a.kt;
@@ -275,15 +281,22 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
     return true;
 }
 
-bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out)
+bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out,
+                   size_t partial_floats)
 {
     bool found = false;
-    for (int shape = 0; shape < kNumDirectShapes; ++shape) {
-        DirectArgs a;
-        if (!direct_setup(N, C, H, W, K, s, YH, YW, sy, sx, p, n, shape, &a) || (found && a.us >= out->us)) continue;
-        *out = a;
-        found = true;
-    }
+    for (int shape = 0; shape < kNumDirectShapes; ++shape)
+        for (int pieces : {1, 2, 3, 4, 6, 8, 12, 16}) {
+            DirectArgs a;
+            if (pieces > 1 && pieces * ((size_t)N * K * YH * YW + 63) > partial_floats) break;
+            if (!direct_setup(N, C, H, W, K, s, YH, YW, sy, sx, p, n, shape, &a, pieces)) {
+                if (pieces == 1) break;
+                continue;
+            }
+            if (!found || a.us < out->us) *out = a;
+            found = true;
+            if ((long long)a.ntiles * pieces >= 2 * kNumCUs) break;  // (the chip is full)
+        }
     return found;
 }
 

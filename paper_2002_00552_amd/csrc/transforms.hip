@@ -145,11 +145,11 @@ __global__ __launch_bounds__(256) void filter_transform_batch_kernel(FilterBatch
 // 256x256 filters of 7x7, read flipped and transposed by the data gradient; 58 us as a gather of w, a transform and a
 // pass that split U.  (A thread with eight rows of its own and no LDS leaves the chip short of waves: 40 us.)
 constexpr int kFtRows = 32, kFtK = 8, kFtPitch = kFtRows + 4;
-__global__ __launch_bounds__(256) void filter_transform_split_kernel(DevPlan P, FilterSource F, const float* __restrict__ w,
-                                                                     float* __restrict__ U, uint32_t* __restrict__ US)
+__device__ __forceinline__ void filter_split_rows(const DevPlan& P, const FilterSource& F, const float* __restrict__ w,
+                                                  float* __restrict__ U, uint32_t* __restrict__ US, int bx, int by)
 {
     __shared__ alignas(16) float sm[16][kFtK][kFtPitch];
-    const int t = threadIdx.x, rbase = blockIdx.x * kFtRows, kbase = blockIdx.y * kFtK;
+    const int t = threadIdx.x, rbase = bx * kFtRows, kbase = by * kFtK;
     {
         const int r = t & (kFtRows - 1), kk = t / kFtRows, row = rbase + r, k = kbase + kk;
         if (row < P.rows_total) {
@@ -188,6 +188,27 @@ __global__ __launch_bounds__(256) void filter_transform_split_kernel(DevPlan P, 
         for (int part = 0; part < 3; ++part)
             *reinterpret_cast<puint4*>(dp + (size_t)part * 2 * P.Kpad * 4) = __builtin_bit_cast(puint4, f[part]);
     }
+}
+
+__global__ __launch_bounds__(256) void filter_transform_split_kernel(DevPlan P, FilterSource F, const float* __restrict__ w,
+                                                                     float* __restrict__ U, uint32_t* __restrict__ US)
+{
+    filter_split_rows(P, F, w, U, US, blockIdx.x, blockIdx.y);
+}
+
+// The same, and beside it the direct convolution's copy: workgroups from direct0 on (the gap before it: filter_copies_kernel)
+__global__ __launch_bounds__(256) void filter_split_copies_kernel(DevPlan P, FilterSource F, DirectArgs D, FilterCopies B,
+                                                                  const float* __restrict__ w, float* __restrict__ U, uint32_t* __restrict__ US)
+{
+    const int b = blockIdx.x;
+    if (b >= B.direct0) {
+        const int nk = (D.Kpad + 127) / 128, e = b - B.direct0;
+        direct_filter(D, F, w, U + B.gap3, e / nk, e % nk);
+        return;
+    }
+    if (b == 0)
+        for (long long i = B.gap2 + threadIdx.x; i < B.gap3; i += 256) U[i] = 0.f;
+    filter_split_rows(P, F, w, U, US, b % B.gx, b / B.gx);
 }
 
 // ---------------------------------------------------------------------------------
@@ -445,7 +466,15 @@ dwm_status_t launch_filter_transform_from(const dwm_plan& p, const FilterSource&
 {
     const DevPlan& d = p.d;
     if (p.direct_only) return launch_direct_filter(p.direct, src, w, U + p.ud_begin, stream);
-    if (p.fused_ok || p.direct_ok) {
+    if (p.split_ok && p.direct_ok) {
+        FilterCopies b{};
+        b.gx = (d.rows_total + kFtRows - 1) / kFtRows;
+        b.direct0 = b.gx * (d.Kpad / kFtK);
+        b.end = b.direct0 + p.direct.all_steps * ((p.direct.Kpad + 127) / 128);
+        b.gap2 = (long long)p.ud_gap; b.gap3 = (long long)p.ud_begin;
+        hipLaunchKernelGGL(filter_split_copies_kernel, dim3(b.end), dim3(256), 0, (hipStream_t)stream, d, src, p.direct, b, w, U,
+                           reinterpret_cast<uint32_t*>(U + p.us_begin));
+    } else if (p.fused_ok || p.direct_ok) {
         FilterCopies b{};
         b.gx = (d.rows_total + 255) / 256;
         b.fused0 = b.gx * d.Kpad;

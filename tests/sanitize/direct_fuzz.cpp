@@ -12,7 +12,7 @@ namespace dwm {
 dwm_status_t launch_filter_transform(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_input_transform(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_contract_output(const dwm_plan&, const float*, float*, float*, void*) { return DWM_OK; }
-dwm_status_t launch_fused_forward(const dwm_plan&, const float*, const float*, float*, void*) { return DWM_OK; }
+dwm_status_t launch_fused_forward(const dwm_plan&, const float*, const float*, float*, float*, void*) { return DWM_OK; }
 }
 using namespace dwm;
 static uint64_t g = 0x9E3779B97F4A7C15ull;
@@ -44,6 +44,10 @@ static void replay(const DirectArgs& A, bool full) {
     const int NT = sh.threads(), NPX = A.npx;
     CHECK(A.P <= A.ns * NT && A.ns <= kDirectSlots && A.lds_bytes <= (NT <= 256 ? 80 : 160) * 1024u);
     CHECK(A.groups[1] <= A.groups[0] && A.groups[1] >= 1);
+    // the pieces take every chunk once, none is without one, and their outputs lie apart
+    CHECK(A.pieces >= 1 && A.pieces <= kDirectMaxPieces && (A.pieces - 1) * A.cpp < A.nchunks && A.pieces * A.cpp >= A.nchunks);
+    CHECK(A.pieces == 1 ? A.piece_floats == 0 && A.cpp == A.nchunks : A.nprob == 1 && A.piece_floats >= (size_t)A.N * A.K * A.YH * A.YW);
+    CHECK((A.nchunks - 1) * A.groups[0] + A.groups[1] == (A.C + 7) / 8);
     const size_t total = (size_t)A.N * A.C * A.H * A.W, image = (size_t)A.C * A.H * A.W;
     const int per = A.nkt * A.nprob;
     std::vector<char> tiles(A.ntiles, 0);
@@ -139,7 +143,7 @@ static int cdiv(int x, int d) { return x >= 0 ? (x + d - 1) / d : -((-x) / d); }
 int main(int argc, char** argv)
 {
     const int iters = argc > 1 ? std::atoi(argv[1]) : 60;
-    int n = 0, took = 0;
+    int n = 0, took = 0, cut = 0;
     const int fixed[][9] = {{5, 67, 35, 29, 93, 5, 5, 2, 2}, {4, 76, 8, 8, 18, 3, 3, 3, 0}, {1, 300, 2, 2, 40, 3, 3, 1, 1},
                             {70, 9, 1, 1, 17, 1, 1, 1, 0}, {2, 16, 60, 230, 20, 3, 5, 1, 2}};
     for (int it = 0; it < iters + 5; ++it) {
@@ -160,6 +164,11 @@ int main(int argc, char** argv)
             if (direct_setup(N, C, H, W, K, st, OH, OW, 1, 1, &q, 1, v, &A)) {
                 ++took; replay(A, it != 4);
                 reads(A, FilterSource{0, (long long)C * R * S, R * S, S, 1}, {{0, 0, 1}}, (long long)C * R * S, R * S, R, S);
+            }
+            // a tile's chunks shared by several workgroups
+            const int pieces = pick(2, rnd() % 4 ? 4 : kDirectMaxPieces);
+            if (direct_setup(N, C, H, W, K, st, OH, OW, 1, 1, &q, 1, v, &A, pieces)) {
+                ++cut; CHECK(A.pieces == pieces); replay(A, it != 4);
             }
             // data gradient: all phases
             std::vector<DirectProb> ps;
@@ -186,6 +195,6 @@ int main(int argc, char** argv)
             }
         }
     }
-    CHECK(took * 2 > n);
-    std::printf("direct fuzz: %d of %d (layer, shape) pairs planned and replayed\n", took, n);
+    CHECK(took * 2 > n && cut > 0);
+    std::printf("direct fuzz: %d of %d (layer, shape) pairs planned and replayed, %d more in pieces\n", took, n, cut);
 }
