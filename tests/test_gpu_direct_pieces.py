@@ -19,8 +19,8 @@ FORWARD = [  # N, C, H, W, K, R, S, stride, pad
 GRADIENT = [
     (1, 256, 14, 14, 256, 3, 3, 1, 1),   # sixteen pieces of one chunk
     (4, 255, 14, 14, 250, 3, 3, 1, 1),   # eight pieces of two blocks of filters, channels past the last
-    (1, 140, 33, 31, 150, 7, 7, 1, 3),   # four
-    (3, 79, 13, 13, 233, 11, 11, 1, 5),  # the last piece shorter
+    (1, 140, 33, 31, 150, 7, 7, 1, 3),   # three
+    (3, 79, 13, 13, 233, 11, 11, 1, 5),  # eight, the last one's chunk shorter
     (8, 38, 27, 27, 224, 3, 3, 1, 1),
     (2, 190, 20, 18, 100, 5, 3, 1, 0),   # no padding: dy's patches reach past it
 ]
