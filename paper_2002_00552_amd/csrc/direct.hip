@@ -18,10 +18,17 @@
 // the parts cannot carry (|x| or |w| from about 2^112 on, infinities, NaN, sums from 2^96 on) makes outputs non-finite; the
 // wave that finds one among its outputs computes them again on fp32 MFMAs, from x and an fp32 copy of the filter.
 //
+// Long sums (two_level, setup.cpp): where a wave adds up many steps in one accumulator, each step's rounding is one of the whole
+// sum: with positive operands errors grew to three times those of the transforms (11x11 at stride 2, 214 filters of dy, 486 steps: 4.1e-7
+// against 1.4e-7 in the 2-norm).  There all six products go to one accumulator, which is added to the other every eight steps:
+// 1.1e-7; the same of dy of zero mean 4.9e-7 -> 2.3e-7 (transforms 4.8e-7); 11x11, 384 filters, 28x28 6.4e-7 -> 3.1e-7.  Time: 7x7 at
+// stride 2, 256 channels, 256 14x14 images 468 -> 473 us, others within 1 %; folds every 4 steps 487 us and no better, every 16 as fast
+// and less exact with operands of zero mean (each small product rounds at the first level's size, so that has to stay short).
+//
 // Bound by latency where the chip is not full (first loads, the barrier of each chunk), and where it is by power: the clock
 // falls from 2.1 to 1.6 GHz with bf16 MFMAs on all CUs, 0.9 to 1.2 PFLOP/s of them.  Whole training steps with it as the
 // data gradient, before -> now: 5x5 at stride 2, 67 -> 93 channels, five 35x29 images 111 -> 101 us; drawn strided layers
-// 173 -> 136, 205 -> 105, 248 -> 129, 208 -> 180.  Errors against 64 bits are 2 to 5 times below those of the transforms.
+// 173 -> 136, 205 -> 105, 248 -> 129, 208 -> 180.  Errors against 64 bits, operands of zero mean: 1.2 to 5 times below those of the transforms.
 // Forward passes: plan.cpp, at the rule that takes it.  As that of a large first layer it loses (7x7 at stride 2 141 -> 168, 11x11 at stride 4 188 -> 260 us).
 #include <hip/hip_runtime.h>
 
@@ -49,7 +56,8 @@ __device__ __forceinline__ ColdArgs& cold_args()
 constexpr uint32_t kDirectTable = 2 * kDirectMaxUnits * 4;  // LDS bytes of the units' offsets, before the staged pixels
 
 // Workgroup of WF x WP x WK waves: 32*MB*WF filters x 64*WP output pixels; a wave 32*MB x 64 and every WK-th step.
-template <int WF, int WP, int WK, int MB>
+// LONG: sums in two levels (see the head of the file)
+template <int WF, int WP, int WK, int MB, bool LONG>
 __global__ __launch_bounds__(64 * WF * WP * WK, 2) void direct_kernel(DirectArgs A, const float* __restrict__ x,
                                                                       const unsigned char* __restrict__ Wd,
                                                                       const float* __restrict__ W32, float* __restrict__ out_y)
@@ -231,7 +239,23 @@ __global__ __launch_bounds__(64 * WF * WP * WK, 2) void direct_kernel(DirectArgs
         for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
             for (int ni = 0; ni < NB; ++ni)
-                acc[mi][ni][which] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni][which], 0, 0, 0);
+                acc[mi][ni][LONG ? 0 : which] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni][LONG ? 0 : which], 0, 0, 0);
+    };
+    int run = 0;  // steps since the last fold
+    auto fold = [&] {
+        if constexpr (LONG) {
+            if (++run < kDirectFold) return;
+            run = 0;
+#pragma unroll
+            for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        acc[mi][ni][1][e] += acc[mi][ni][0][e];
+                        acc[mi][ni][0][e] = 0.f;
+                    }
+        }
     };
     // A step: the MFMAs of two units, while the operands of the next one (at `to` in Wd, at unext in LDS) replace those that are
     // done with, part by part.  The sections' order is kept.
@@ -291,8 +315,12 @@ __global__ __launch_bounds__(64 * WF * WP * WK, 2) void direct_kernel(DirectArgs
         if (chunk + 1 < chunk1) load_ahead(chunk + 1);
         if (some) {
             step(wchunk + (uint32_t)min(wk + WK, top) * step_bytes, min(wk + 2 * WK, top));
+            fold();
 #pragma unroll 1
-            for (int st = wk + WK; st < nst; st += WK) step(wchunk + (uint32_t)min(st + WK, top) * step_bytes, min(st + 2 * WK, top));
+            for (int st = wk + WK; st < nst; st += WK) {
+                step(wchunk + (uint32_t)min(st + WK, top) * step_bytes, min(st + 2 * WK, top));
+                fold();
+            }
         }
         barrier();
     }
@@ -418,11 +446,13 @@ __global__ __launch_bounds__(256) void direct_sum_kernel(const float* __restrict
 // ---------------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------------
-template <int WF, int WP, int WK, int MB>
+template <int WF, int WP, int WK, int MB, bool LONG = false>
 static dwm_status_t launch_shape(const DirectArgs& a, const float* x, const unsigned char* Wd, const float* W32, float* y, float* partial, void* stream)
 {
+    if constexpr (!LONG)
+        if (a.two_level) return launch_shape<WF, WP, WK, MB, true>(a, x, Wd, W32, y, partial, stream);
     if (a.kt != 32 * MB * WF || a.npx != 64 * WP || (a.pieces > 1 && !partial)) return DWM_ERR_INVALID_ARG;
-    auto kernel = direct_kernel<WF, WP, WK, MB>;
+    auto kernel = direct_kernel<WF, WP, WK, MB, LONG>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return DWM_ERR_HIP;
     hipLaunchKernelGGL(kernel, dim3((unsigned)a.ntiles, (unsigned)a.pieces), dim3(64 * WF * WP * WK), a.lds_bytes, (hipStream_t)stream, a, x, Wd, W32,

@@ -378,6 +378,7 @@ constexpr int kDirectMaxProbs = 16;
 constexpr int kDirectSlots = 3;      // staged pixels a thread takes of a group at most
 constexpr int kDirectMaxUnits = 512; // of a chunk
 constexpr int kDirectMaxPieces = 16;
+constexpr int kDirectFold = 8;       // steps of a sum's first level, where it has two (direct.hip)
 // Where a filter lies in w: tap (r, s) of filter k and channel c is element base + k*sk + c*sc + r*sr + s*ss
 struct FilterSource {
     long long base, sk, sc;
@@ -405,6 +406,8 @@ struct DirectArgs {
     int rstep, rows_full, run;   // staged rows from one output row to the next, of a whole image, of a lone output row
     int row_px, lwp, P, ns;      // pixels per staged row, per phase; per group; ceil(P / threads)
     int nchunks, groups[2];      // groups of every chunk but the last, of the last
+    int longest;                 // steps of the longest of a wave's sums
+    bool two_level;              // sums are added up kDirectFold steps at a time
     int pieces, cpp;             // workgroups that share a tile, each cpp chunks of it (the last what is left)
     size_t piece_floats;         // from one piece's outputs to the next one's
     int Kpad, bias;              // bias: floats that the first pixel may lie before the image

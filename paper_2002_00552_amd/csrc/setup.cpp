@@ -149,6 +149,13 @@ bool fused_setup(const dwm_plan& p, FusedArgs* out)
     return true;
 }
 
+// Steps that a wave adds up of a problem's tile (of a piece of it)
+static int direct_sum_steps(const DirectArgs& a, const DirectShape& sh, const DirectProb& q)
+{
+    auto share = [&](int steps) { return (steps + sh.wk - 1) / sh.wk; };
+    return a.pieces > 1 ? a.cpp * share(q.steps[0]) : (a.nchunks - 1) * share(q.steps[0]) + share(q.steps[1]);
+}
+
 // The time (us) of a direct convolution, fitted to 1700 (layer, shape) pairs drawn from the timed cases' ranges (forward and
 // strided data gradients; rms of the logarithm 0.17, the shape that it picks at 1.03 of the best one's time): cycles at 2.1
 // GHz of a workgroup -- its MFMAs, 340 a staged pixel and wave of a SIMD, 5400 a chunk (first loads, barriers), stores --, shared by the
@@ -157,19 +164,14 @@ bool fused_setup(const dwm_plan& p, FusedArgs* out)
 static double direct_us(const DirectArgs& a, const DirectShape& sh)
 {
     const double w = sh.threads() / 256.0, waves = sh.threads() / 64.0, groups = std::min((a.C + 7) / 8, a.cpp * a.groups[0]);
-    double mean = 0.0, longest = 0.0;
-    for (int i = 0; i < a.nprob; ++i) {
-        auto share = [&](int steps) { return (steps + sh.wk - 1) / sh.wk; };
-        const double t = a.pieces > 1 ? (double)a.cpp * share(a.p[i].steps[0]) : (double)(a.nchunks - 1) * share(a.p[i].steps[0]) + share(a.p[i].steps[1]);
-        mean += t / a.nprob;
-        longest = std::max(longest, t);
-    }
+    double mean = 0.0;
+    for (int i = 0; i < a.nprob; ++i) mean += (double)direct_sum_steps(a, sh, a.p[i]) / a.nprob;
     const int fits = (int)(160 * 1024 / a.lds_bytes);
     const double on_cu = sh.threads() > 256 ? 1 : std::max(1, std::min(fits, sh.mb == 2 ? 2 : 3));
     const double slots = groups * a.ns, store = 1180.0 * sh.mb * w / sh.wk;
     const double simd = mean * 368.0 * sh.mb * w + slots * 340.0 * w + store;
     const double address = 19.0 * (slots * waves * 8 + mean * waves * 3 * sh.mb + sh.mb * 32 * waves / sh.wk * (a.sx > 1 ? 2 : 1));
-    const double lone = longest * 368.0 * sh.mb * w + slots * 340.0 * w + a.cpp * 5400.0 + store;
+    const double lone = a.longest * 368.0 * sh.mb * w + slots * 340.0 * w + a.cpp * 5400.0 + store;
     const double wgs = (double)a.ntiles * a.pieces, per_cu = wgs / kNumCUs, rounds = std::max(1.0, per_cu / on_cu < 3 ? std::ceil(per_cu / on_cu) : per_cu / on_cu + 0.5);
     const double cycles = rounds * std::max(lone, std::min(on_cu, std::ceil(per_cu)) * std::max(simd, address));
     const double flops = wgs * mean * waves * sh.mb * 2 * 6 * 32768.0;
@@ -276,6 +278,10 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
     a.div_lwp.init((unsigned)a.lwp);
     a.div_rows.init((unsigned)a.rows_full);
     a.div_rstep.init((unsigned)a.rstep);
+    for (int i = 0; i < n; ++i) a.longest = std::max(a.longest, direct_sum_steps(a, sh, a.p[i]));
+    // (Measured where the other form begins to be further from 64 bits, with operands of zero mean and with positive ones: a tile's sum
+    // in one wave from 88 steps on, shared by four waves from 117; at 82 to 97 steps of four waves one level is as good or better.)
+    a.two_level = a.longest > (sh.wk > 1 ? 112 : 80);
     a.us = direct_us(a, sh);
     *out = a;
     return true;

@@ -52,7 +52,7 @@ static void replay(const DirectArgs& A, bool full) {
     const int per = A.nkt * A.nprob;
     std::vector<char> tiles(A.ntiles, 0);
     // filter: every tap and channel of every problem once; Wd and W32 inside their sizes
-    int steps = 0; long long w32 = 0;
+    int steps = 0, longest = 0; long long w32 = 0;
     for (int i = 0; i < A.nprob; ++i) {
         const DirectProb& q = A.p[i];
         CHECK(q.step0 == steps && q.w32 == w32);
@@ -67,7 +67,15 @@ static void replay(const DirectArgs& A, bool full) {
         }
         for (int v : seen) CHECK(v == 1);
         steps += n; w32 += (long long)taps * A.C * A.Kpad;
+        // the longest of a wave's sums: its share of every chunk of its piece (of the longest piece)
+        for (int first = 0; first < A.nchunks; first += A.cpp) {
+            int sum = 0;
+            for (int c = first; c < std::min(first + A.cpp, A.nchunks); ++c)
+                for (int st = 0; st < q.steps[c == A.nchunks - 1]; st += sh.wk) ++sum;
+            longest = std::max(longest, sum);
+        }
     }
+    CHECK(longest <= A.longest && (A.pieces > 1 || longest == A.longest) && A.two_level == (A.longest > (sh.wk > 1 ? 112 : 80)));
     CHECK(steps == A.all_steps && (size_t)w32 == A.w32_floats && A.wd_bytes == (unsigned)steps * 96u * A.Kpad);
     std::vector<std::vector<char>> outs(A.nprob);
     for (int i = 0; i < A.nprob; ++i) outs[i].assign(full ? (size_t)A.N * A.p[i].OH * A.p[i].OW : 0, 0);
