@@ -17,6 +17,8 @@
 // Operands: x and w are split as x * 2^16 and w * 2^16, sums multiplied by 2^-32: exact at every scale up to 2^112.  What
 // the parts cannot carry (|x| or |w| from about 2^112 on, infinities, NaN, sums from 2^96 on) makes outputs non-finite; the
 // wave that finds one among its outputs computes them again on fp32 MFMAs, from x and an fp32 copy of the filter.
+// 3x3, 128 -> 128 channels, 64 28x28 images: 93 us, with one infinity in x 192, NaN throughout 294 (one block of 32 x 32 at a
+// time, each load waited for, 476 and 823); 3x3 at stride 2, 128 -> 256, 32 56x56 images 99, 289, 299 (556 and 700).
 //
 // Long sums (two_level, setup.cpp): where a wave adds up many steps in one accumulator, each step's rounding is one of the whole
 // sum: with positive operands errors grew to three times those of the transforms (11x11 at stride 2, 214 filters of dy, 486 steps: 4.1e-7
@@ -383,47 +385,98 @@ __global__ __launch_bounds__(64 * WF * WP * WK, 2) void direct_kernel(DirectArgs
         lost |= __builtin_amdgcn_ballot_w64(t != 0.f && a.in);
     }
     if (__builtin_expect(lost != 0, 0)) {
-        // operands or sums that the parts cannot carry: the wave's outputs again, on fp32 MFMAs, from x and W32
+        // operands or sums that the parts cannot carry: the wave's outputs again, on fp32 MFMAs, from x and W32 -- all of a tile that
+        // is the wave's alone, of a shared one the block of 32 x 32 that holds its values -- 16 channels of a tap at a time, the next
+        // ones on their way.  What is not there (channels past the piece's last, pixels outside x) is loaded as zero.
+        constexpr bool ALL = WK == 1;
+        static_assert(ALL || OWN <= 16, "values of one block");
+        constexpr int RM = ALL ? MB : 1, RN = ALL ? NB : 1;
+        const int v0 = ALL ? 0 : wk * OWN, mi0 = v0 / 32, ni0 = v0 / 16 % 2;
         const int c_begin = (int)blockIdx.y * B.cpp * B.groups[0] * 8, c_end = min(B.C, c_begin + B.cpp * B.groups[0] * 8);
-#pragma unroll 1
-        for (int b = 0; b < OWN / SPAN; ++b) {
-            const int v0 = wk * OWN + b * SPAN, mi = v0 / 32, ni = v0 / 16 % 2;
-            const Place pl = place(ni);
-            const int image = B.H * B.W;
-            const float* xn = x + (size_t)pl.n * B.C * image;
-            const float* wq = W32 + q.w32 + kw + mi * 32 + li;
-            floatx16 sum;
+        const int image = B.C * B.H * B.W, taps = q.R * q.S;
+        const uint32_t krow = (uint32_t)B.Kpad * 4u;
+        const size_t left = ((size_t)(B.N - n0) * image + B.bias) * 4;
+        const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x + (size_t)n0 * image) - B.bias, 0,
+                                                                            (int)(left < 0x7ffffff0u ? left : 0x7ffffff0u), 0x00020000);
+        const __amdgpu_buffer_rsrc_t ws = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(W32 + q.w32), 0, taps * B.C * (int)krow, 0x00020000);
+        Place pl[RN];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) sum[e] = 0.f;
-#pragma unroll 1
-            for (int t = 0; t < q.R * q.S; ++t) {
-                const int r = t / q.S, s = t - r * q.S;
-                const int ih = B.s * pl.oh - q.Ph + r, iw = B.s * pl.ow - q.Pw + s;
-                const bool ok = pl.in && (unsigned)ih < (unsigned)B.H && (unsigned)iw < (unsigned)B.W;
-                const float* xp = xn + (ok ? ih * B.W + iw : 0);
-                const float* wt = wq + (size_t)t * B.C * B.Kpad;
-                floatx16 m;
+        for (int ni = 0; ni < RN; ++ni) pl[ni] = place(ni0 + ni);
+        const uint32_t wo = (uint32_t)(half * 8) * krow + (uint32_t)(kw + mi0 * 32 + li) * 4u;
+        uint32_t xo[RN];
+        int t = -1, c = c_end;
+        auto next = [&] {  // the next 16 channels, or the next tap's first
+            c += 16;
+            if (c < c_end) return;
+            c = c_begin;
+            ++t;
+            const int r = t / q.S, s = t - r * q.S;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) m[e] = 0.f;
-#pragma unroll 1
-                for (int c0 = c_begin; c0 < c_end; c0 += 16) {
-                    float a[8], v[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int c = c0 + half * 8 + e, cc = min(c, B.C - 1);
-                        const float wv = wt[(size_t)cc * B.Kpad], xv = xp[(size_t)cc * image];
-                        a[e] = c < c_end ? wv : 0.f;
-                        v[e] = c < c_end && ok ? xv : 0.f;
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) m = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], v[e], m, 0, 0, 0);
-                }
-                sum += m;
+            for (int ni = 0; ni < RN; ++ni) {
+                const int ih = B.s * pl[ni].oh - q.Ph + r, iw = B.s * pl[ni].ow - q.Pw + s;
+                const bool ok = pl[ni].in && (unsigned)ih < (unsigned)B.H && (unsigned)iw < (unsigned)B.W;
+                xo[ni] = ok ? (uint32_t)((pl[ni].n - n0) * image + ih * B.W + iw + B.bias) * 4u + (uint32_t)(half * 8) * hw : 0x80000000u;
             }
+        };
+        auto load = [&](float (&a)[RM][8], float (&v)[RN][8]) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (e >= v0 % 16 && e < v0 % 16 + SPAN) store(pl, mi * 32 + 8 * (e >> 2) + (e & 3), sum[e]);
+            for (int e = 0; e < 8; ++e) {
+                const bool there = c + half * 8 + e < c_end;
+                const int ce = min(c + e, B.C - 1);  // (no scalar offset lies past its buffer)
+#pragma unroll
+                for (int mi = 0; mi < RM; ++mi)
+                    a[mi][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ws, there ? wo + mi * 128u : 0x80000000u,
+                                                                                              (uint32_t)(t * B.C + ce) * krow, 0));
+#pragma unroll
+                for (int ni = 0; ni < RN; ++ni)
+                    v[ni][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xs, there ? xo[ni] : 0x80000000u, (uint32_t)ce * hw, 0));
+            }
+        };
+        floatx16 sum[RM][RN];
+#pragma unroll
+        for (int mi = 0; mi < RM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < RN; ++ni)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) sum[mi][ni][e] = 0.f;
+        auto multiply = [&](const float (&a)[RM][8], const float (&v)[RN][8]) {
+#pragma unroll
+            for (int mi = 0; mi < RM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < RN; ++ni) {
+                    floatx16 m;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) m[e] = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) m = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mi][e], v[ni][e], m, 0, 0, 0);
+                    sum[mi][ni] += m;
+                }
+        };
+        float a0f[RM][8], v0f[RN][8], a1f[RM][8], v1f[RN][8];
+        next();
+        load(a0f, v0f);
+#pragma unroll 1
+        for (int left_over = taps * ((c_end - c_begin + 15) / 16);;) {
+            if (left_over > 1) {
+                next();
+                load(a1f, v1f);
+            }
+            multiply(a0f, v0f);
+            if (--left_over == 0) break;
+            if (left_over > 1) {
+                next();
+                load(a0f, v0f);
+            }
+            multiply(a1f, v1f);
+            if (--left_over == 0) break;
         }
+#pragma unroll
+        for (int mi = 0; mi < RM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < RN; ++ni)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (ALL || (e >= v0 % 16 && e < v0 % 16 + OWN)) store(pl[ni], (mi0 + mi) * 32 + 8 * (e >> 2) + (e & 3), sum[mi][ni][e]);
     }
 }
 

@@ -6,7 +6,8 @@ import torch
 
 import oracle
 import paper_2002_00552_amd as dwm
-from test_gpu_backward import WgradRunner
+from dwm_gpu import Runner
+from test_gpu_backward import BwdRunner, WgradRunner
 from test_gpu_wgrad_direct import SHAPES as WGRAD_SHAPES
 
 pytestmark = pytest.mark.gpu
@@ -82,3 +83,93 @@ def test_time_of_a_filter_gradient_that_is_not_finite(shape):
         r.close()
     print("%s: %.1f us, one infinity %.1f, NaN throughout %.1f" % (shape, plain, one, every))
     assert max(one, every) <= 4 * plain
+
+
+# (shape, whether the forward pass and the data gradient take the direct convolution): every shape of its workgroup
+DIRECT = [
+    ((32, 128, 56, 56, 256, 3, 3, 2, 1), (True, True)),    # 256 filters x 128 pixels, 128 x 128
+    ((20, 128, 30, 28, 130, 3, 3, 1, 1), (True, True)),    # four waves of 64 filters share a tile, 128 x 128
+    ((1, 16, 32, 32, 16, 5, 5, 1, 2), (True, False)),      # four of 32
+    ((5, 67, 35, 29, 93, 5, 5, 2, 2), (False, True)),
+    ((46, 76, 8, 8, 18, 3, 3, 3, 0), (True, True)),        # eight, in pieces
+    ((2, 33, 12, 230, 70, 3, 7, 1, 2), (True, True)),      # strips
+    ((1, 256, 14, 14, 256, 3, 3, 1, 1), (False, True)),    # pieces
+    ((2, 206, 12, 14, 284, 9, 9, 2, 4), (False, True)),    # sums in two levels
+]
+
+
+def _forward(shape, x, w):
+    r = Runner(*shape)
+    try:
+        r.set_filter(w)
+        return r.forward(x).astype(np.float64), dwm.dwm_plan_forward_kernel(r.plan)
+    finally:
+        r.close()
+
+
+def _gradient(shape, dy, w):
+    r = BwdRunner(*shape)
+    try:
+        return r.run(dy, w).astype(np.float64), dwm.dwm_bwd_data_kernel(r.plan)
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("corner", [0, -1])
+@pytest.mark.parametrize("shape, direct", DIRECT)
+def test_direct_convolution_of_a_value_in_a_corner(shape, direct, corner):
+    """An infinity in the first or last pixel and channel: infinite, of the tap's sign, where a tap meets it, all else as without it
+    (what a wave computes again rounds a tile's products in binary32: 1.2e-6 of the largest, as in the other tests)."""
+    N, C, H, W, K, R, S, s, P = shape
+    x, dy, w = _operands(shape, 43)
+    at = (corner,) * 4
+    for run, a, takes in ((_forward, x, direct[0]), (_gradient, dy, direct[1])):
+        a[at] = 0.0
+        rest, kernel = run(shape, a, w)
+        assert (kernel == 2) == takes
+        if not takes:
+            continue
+        a[at] = np.inf
+        out, _ = run(shape, a, w)
+        tap = np.zeros_like(out)  # the tap of w that meets it
+        n, c, h, v = (corner % m for m in a.shape)
+        for r in range(R):
+            for q in range(S):
+                if run is _forward:
+                    oh, ow = h + P - r, v + P - q
+                    if oh % s == 0 and ow % s == 0 and 0 <= oh // s < out.shape[2] and 0 <= ow // s < out.shape[3]:
+                        tap[n, :, oh // s, ow // s] = w[:, c, r, q]
+                elif 0 <= s * h + r - P < H and 0 <= s * v + q - P < W:
+                    tap[n, :, s * h + r - P, s * v + q - P] = w[c, :, r, q]
+        hit = tap != 0
+        assert np.max(np.abs(out[~hit] - rest[~hit])) <= 1.2e-6 * np.max(np.abs(rest))
+        assert np.array_equal(out[hit], np.where(tap[hit] > 0, np.inf, -np.inf))
+
+
+@pytest.mark.parametrize("shape", [(64, 128, 28, 28, 128, 3, 3, 1, 1), (32, 128, 56, 56, 256, 3, 3, 2, 1), (36, 300, 28, 28, 150, 3, 3, 2, 1),
+                                   (5, 67, 35, 29, 93, 5, 5, 2, 2)])
+def test_time_of_a_direct_convolution_that_is_not_finite(shape):
+    x, dy, w = _operands(shape, 44)
+    st = torch.cuda.current_stream().cuda_stream
+    f, b = Runner(*shape), BwdRunner(*shape)
+    try:
+        kernels = dwm.dwm_plan_forward_kernel(f.plan), dwm.dwm_bwd_data_kernel(b.plan)
+        f.set_filter(w)
+        f.forward(x)
+        b.run(dy, w)
+        calls = ((f.x, f.y, lambda: dwm.dwm_conv_forward(f.plan, f.x.data_ptr(), f.Ugw.data_ptr(), f.y.data_ptr(), st)),
+                 (b.dy, b.dx, lambda: dwm.dwm_conv_backward_data(b.plan, b.dy.data_ptr(), b.Ugw.data_ptr(), b.dx.data_ptr(), st)))
+        for kernel, (a, out, call) in zip(kernels, calls):
+            if kernel != 2:
+                continue
+            plain = _us(call)
+            a[tuple(n // 2 for n in a.shape)] = float("inf")
+            one = _us(call)
+            a.fill_(float("nan"))
+            every = _us(call)
+            assert bool(torch.isnan(out).any())
+            print("%s: %.1f us, one infinity %.1f, NaN throughout %.1f" % (shape, plain, one, every), flush=True)
+            assert max(one, every) <= 4.5 * plain
+    finally:
+        f.close()
+        b.close()
