@@ -251,7 +251,7 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
     a.ntt = (int)(((long long)a.total_px + a.npx - 1) / a.npx);
     a.nkt = (K + a.kt - 1) / a.kt;
     const long long per = (long long)a.nkt * n;
-    if (a.ntt * per > 0x3fffffffLL) return false;
+    if (a.ntt * per > 0x3fffffffLL || a.ntt * per * threads > 0xffffffffLL) return false;  // (a launch counts threads in 32 bits)
     a.piece_floats = pieces > 1 ? ((size_t)N * K * YH * YW + 63) / 64 * 64 : 0;
     a.ntiles = (int)(a.ntt * per);
     a.full8 = (int)(8 * per * (a.ntt / 8));

@@ -203,6 +203,25 @@ int main(int argc, char** argv)
             }
         }
     }
+    // the most pixels that a call may have: no launch of 2^32 threads or more
+    const int large[][7] = {{107374182, 1, 5, 4, 6, 3, 2}, {238609294, 1, 3, 3, 4, 2, 2}, {429496729, 1, 1, 5, 5, 4, 2}};  // N, C, H, W, R, stride, pad; one filter
+    for (const auto& l : large)
+        for (int v = 0; v < kNumDirectShapes; ++v) {
+            const int OH = (l[2] + 2 * l[6] - l[4]) / l[5] + 1, OW = (l[3] + 2 * l[6] - l[4]) / l[5] + 1;
+            std::vector<DirectProb> ps;
+            for (int a = 0; a < l[5]; ++a) for (int b = 0; b < l[5]; ++b) {
+                DirectProb q{};
+                const int u0 = cdiv(l[6] - a, l[5]), v0 = cdiv(l[6] - b, l[5]);
+                q.R = (l[4] - a + l[5] - 1) / l[5]; q.S = (l[4] - b + l[5] - 1) / l[5];
+                q.OH = (l[2] + l[6] - 1 - a) / l[5] - u0 + 1; q.OW = (l[3] + l[6] - 1 - b) / l[5] - v0 + 1;
+                q.Ph = q.R - 1 - u0; q.Pw = q.S - 1 - v0;
+                if (l[2] + l[6] - 1 >= a && l[3] + l[6] - 1 >= b && q.OH > 0 && q.OW > 0) ps.push_back(q);
+            }
+            DirectArgs A;
+            CHECK(!ps.empty());
+            if (direct_setup(l[0], 1, OH, OW, l[1], 1, l[2], l[3], l[5], l[5], ps.data(), (int)ps.size(), v, &A))
+                CHECK((long long)A.ntiles * kDirectShapes[v].threads() < 1LL << 32);
+        }
     CHECK(took * 2 > n && cut > 0);
     std::printf("direct fuzz: %d of %d (layer, shape) pairs planned and replayed, %d more in pieces\n", took, n, cut);
 }
