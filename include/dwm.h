@@ -142,9 +142,11 @@ DWM_API dwm_status_t dwm_plan_info(const dwm_plan_t* plan, dwm_plan_info_t* info
 /* What dwm_conv_forward runs as the plan stands: 0 = input transform + contraction, 1 = the single kernel for few input
  * channels (both as info.forward_path says), 2 = the layer's taps multiplied as they are, in one launch (and a second one that
  * adds up, where a few tiles are shared by many workgroups), on the bfloat16 matrix cores with every binary32 operand as the sum
- * of three bfloat16 numbers (C >= 16, where it takes less time than what forward_path names; infinities, NaN, operands of about
- * 2^112 or more and sums of 2^96 or more take fp32 matrix cores for the outputs that they reach).  A variant of any stage asked
- * for with dwm_plan_set_variant takes the layer to that stage instead.
+ * of three bfloat16 numbers (C >= 16, where it takes less time than what forward_path names).  Infinities, NaN, operands of about
+ * 2^112 or more and sums of 2^96 or more take fp32 matrix cores for the outputs that they reach, and time: a call takes up to three
+ * times as long with one such value, up to three and a half times if every output is such.  Sums that a second launch adds up
+ * lie in the workspace.  A variant that dwm_plan_set_variant is asked for by number takes the layer to that stage instead; those that
+ * restore the planner's choice ("split" 0, "input_cg" 0, negative ones) leave it here.
  * -1: null plan. */
 DWM_API int dwm_plan_forward_kernel(const dwm_plan_t* plan);
 DWM_API dwm_status_t dwm_plan_part(const dwm_plan_t* plan, int i, dwm_part_t* part);     /* i < n_parts   */
@@ -282,10 +284,11 @@ DWM_API size_t dwm_bwd_data_filter_bytes(const dwm_bwd_data_plan_t* plan);
 DWM_API size_t dwm_bwd_data_workspace_bytes(const dwm_bwd_data_plan_t* plan);
 DWM_API dwm_status_t dwm_bwd_data_set_workspace(dwm_bwd_data_plan_t* plan, void* ws_dev, size_t bytes);
 /* What dwm_conv_backward_data runs as the plan stands: 0 = the sub-convolutions described above by the method's transforms,
- * 1 = the single kernel for layers with few input channels, 2 = the sub-convolutions' taps multiplied as they are, all phases
- * in one launch on the bfloat16 matrix cores with every binary32 operand as the sum of three bfloat16 numbers (stride > 1, where
- * it takes less time; reads no workspace; infinities, NaN, operands of about 2^112 or more and sums of 2^96 or more take fp32
- * matrix cores, for the parts of dx that they reach).  -1: null plan. */
+ * 1 = the single kernel for layers with few input channels, 2 = the sub-convolutions' taps multiplied as they are, on the
+ * bfloat16 matrix cores with every binary32 operand as the sum of three bfloat16 numbers, where that takes less time: with a stride all
+ * phases in one launch that uses no workspace, at stride 1 as dwm_conv_forward's kernel 2 -- a few tiles shared by many workgroups
+ * add up in the plan's workspace, in a second launch, so that calls on one plan must not overlap.  What is said there of infinities,
+ * NaN and large operands holds for the parts of dx that they reach.  -1: null plan. */
 DWM_API int dwm_bwd_data_kernel(const dwm_bwd_data_plan_t* plan);
 /* stage "path": 0 = the sub-convolutions described above, by the method's transforms, 1 = the whole gradient in one kernel (all
  * phases and channels of dx as the columns of a single stride-1 correlation of dy whose window is
@@ -313,11 +316,11 @@ DWM_API dwm_status_t dwm_conv_backward_data(const dwm_bwd_data_plan_t* plan, con
  *     dw[k,c,r,q] = sum_{n,oh,ow} dy[n,k,oh,ow] * xp[n,c,oh*stride+r,ow*stride+q]
  * computed part by part as dg = G^T [ sum over tiles of (A dY A^T) .* V ] G with V = B^T d B the
  * forward pass's transformed input; the sum over tiles is a GEMM per Winograd-domain plane.
+ * -- or as the plain sum above, where that takes less time (dwm_bwd_filter_kernel).
  * dw [K][C][R][S] is fully overwritten; results do not vary from run to run.
- * (or as the plain sum above, where that takes less time: dwm_bwd_filter_kernel).
  * The plan takes the forward layer's shape; the workspace (dwm_bwd_filter_workspace_bytes,
  * 256-byte aligned) holds V, A dY A^T (not for layers with few input channels, where it is never
- * written to memory) and the partial sums.  Conventions as for the forward calls.
+ * written to memory) and the partial sums; of the plain sum only those.  Conventions as for the forward calls.
  */
 typedef struct dwm_bwd_filter_plan dwm_bwd_filter_plan_t;
 
@@ -335,8 +338,9 @@ DWM_API dwm_status_t dwm_bwd_filter_plan_destroy(dwm_bwd_filter_plan_t* plan);
 DWM_API dwm_status_t dwm_bwd_filter_plan_info(const dwm_bwd_filter_plan_t* plan, dwm_bwd_filter_info_t* info);
 /* What dwm_conv_backward_filter runs: 0 = V, A dY A^T and a GEMM per plane, 1 = the form for few input channels, 2 = the plain
  * convolution's products, x and dy read as they are, on the bfloat16 matrix cores with every binary32 operand as the sum of
- * three bfloat16 numbers (where it takes less time; values that those cannot carry take binary32 for the taps that they
- * reach).  dwm_bwd_filter_plan_info describes the first two in any case.  -1: null plan. */
+ * three bfloat16 numbers (where it takes less time; values that those cannot carry take fp32 matrix cores for the taps that they
+ * reach, and a call that meets some up to two and a half times its time).  dwm_bwd_filter_plan_info describes the first two in any
+ * case.  -1: null plan. */
 DWM_API int dwm_bwd_filter_kernel(const dwm_bwd_filter_plan_t* plan);
 /* stage "path": 0 = by the method's transforms, -1 = the planner's choice.  Before dwm_bwd_filter_set_workspace only. */
 DWM_API dwm_status_t dwm_bwd_filter_set_variant(dwm_bwd_filter_plan_t* plan, const char* stage, int variant);
