@@ -216,8 +216,9 @@ def test_backward_data_benchmark_layers_full_size(index):
 # ---- gradient with respect to the filter ----
 
 class WgradRunner:
-    def __init__(self, N, C, H, W, K, R, S, stride, pad):
+    def __init__(self, N, C, H, W, K, R, S, stride, pad, path=-1):
         self.plan = dwm.dwm_bwd_filter_plan_create(N, C, H, W, K, R, S, stride, pad)
+        dwm.dwm_bwd_filter_set_variant(self.plan, "path", path)
         dev = torch.device("cuda:0")
         self.ws = torch.full((dwm.dwm_bwd_filter_workspace_bytes(self.plan) // 4,), float("nan"),
                              dtype=torch.float32, device=dev)

@@ -26,16 +26,19 @@ def _setup(shape, forward_variant):
     return plan, x, w, U, ws, y
 
 
-@pytest.mark.parametrize("shape,forward_variant", [
-    ((1, 16, 32, 32, 16, 5, 5, 1, 2), None),   # single-kernel path
-    ((1, 16, 32, 32, 16, 5, 5, 1, 2), 0),      # staged path with split tiles (arrival counters)
-    ((2, 64, 30, 30, 64, 3, 3, 1, 1), 0),      # staged path, whole and split tiles
-    ((2, 64, 9, 9, 33, 4, 4, 1, 1), None),     # bfloat16 matrix cores: pieces and the kernel that adds them up
-    ((256, 128, 28, 28, 128, 3, 3, 1, 1), None),  # ... whole tiles
+@pytest.mark.parametrize("shape,forward_variant,kernel", [
+    ((1, 16, 32, 32, 16, 5, 5, 1, 2), 1, 1),      # single-kernel path
+    ((1, 16, 32, 32, 16, 5, 5, 1, 2), 0, 0),      # staged path with split tiles (arrival counters)
+    ((2, 64, 30, 30, 64, 3, 3, 1, 1), 0, 0),      # staged path, whole and split tiles
+    ((2, 64, 9, 9, 33, 4, 4, 1, 1), None, 0),     # bfloat16 matrix cores: pieces and the kernel that adds them up
+    ((256, 128, 28, 28, 128, 3, 3, 1, 1), None, 0),  # ... whole tiles
+    ((1, 16, 32, 32, 16, 5, 5, 1, 2), None, 2),   # direct convolution
+    ((16, 256, 14, 14, 256, 3, 3, 1, 1), None, 2),  # ... tiles in pieces and the kernel that adds them up
 ])
-def test_forward_replays_from_a_graph(shape, forward_variant):
+def test_forward_replays_from_a_graph(shape, forward_variant, kernel):
     plan, x, w, U, ws, y = _setup(shape, forward_variant)
     try:
+        assert dwm.dwm_plan_forward_kernel(plan) == kernel
         side = torch.cuda.Stream()
         with torch.cuda.stream(side):
             st = side.cuda_stream
@@ -76,13 +79,16 @@ def _replay_and_compare(g, out, eager, eager_again):
         assert not torch.equal(out, eager)
 
 
-@pytest.mark.parametrize("shape", [
-    (2, 10, 20, 24, 150, 3, 3, 2, 1),    # four sub-convolutions, one merged input transform, one batched contraction
-    (2, 24, 14, 14, 40, 7, 7, 1, 3),     # one sub-convolution on the forward kernels (tiles cut into ranges)
-    (2, 3, 37, 35, 33, 7, 7, 2, 3),      # three channels: the whole gradient in one kernel
-    (1, 67, 14, 14, 259, 3, 3, 1, 1),    # one sub-convolution on the bfloat16 matrix cores
+@pytest.mark.parametrize("shape, path, kernel", [
+    ((2, 10, 20, 24, 150, 3, 3, 2, 1), 0, 0),    # four sub-convolutions, one merged input transform, one batched contraction
+    ((2, 24, 14, 14, 40, 7, 7, 1, 3), 0, 0),     # one sub-convolution on the forward kernels (tiles cut into ranges)
+    ((2, 3, 37, 35, 33, 7, 7, 2, 3), -1, 1),     # three channels: the whole gradient in one kernel
+    ((1, 67, 14, 14, 259, 3, 3, 1, 1), 0, 0),    # one sub-convolution on the bfloat16 matrix cores
+    ((2, 10, 20, 24, 150, 3, 3, 2, 1), -1, 2),   # direct convolution: four phases in one launch
+    ((2, 24, 14, 14, 40, 7, 7, 1, 3), -1, 2),    # ... at stride 1
+    ((1, 256, 14, 14, 256, 3, 3, 1, 1), -1, 2),  # ... tiles in pieces and the kernel that adds them up
 ])
-def test_backward_data_replays_from_a_graph(shape):
+def test_backward_data_replays_from_a_graph(shape, path, kernel):
     N, C, H, W, K, R, S, s, P = shape
     rng = np.random.default_rng(6)
     OH, OW = (H + 2 * P - R) // s + 1, (W + 2 * P - S) // s + 1
@@ -90,6 +96,8 @@ def test_backward_data_replays_from_a_graph(shape):
     dy = torch.from_numpy(rng.uniform(-1, 1, (N, K, OH, OW)).astype(np.float32)).cuda()
     plan = dwm.dwm_bwd_data_plan_create(N, C, H, W, K, R, S, s, P)
     try:
+        dwm.dwm_bwd_data_set_variant(plan, "path", path)
+        assert dwm.dwm_bwd_data_kernel(plan) == kernel
         U = torch.empty(dwm.dwm_bwd_data_filter_bytes(plan) // 4, dtype=torch.float32, device="cuda")
         ws = torch.empty(max(dwm.dwm_bwd_data_workspace_bytes(plan) // 4, 64), dtype=torch.float32, device="cuda")
         dwm.dwm_bwd_data_set_workspace(plan, ws.data_ptr(), ws.numel() * 4)
@@ -113,13 +121,15 @@ def test_backward_data_replays_from_a_graph(shape):
         dwm.dwm_bwd_data_plan_destroy(plan)
 
 
-@pytest.mark.parametrize("shape", [
-    (2, 66, 12, 12, 67, 3, 3, 1, 1),     # GEMM form: input transform, dy transform, GEMM over ranges, final
-    (16, 6, 130, 127, 16, 3, 3, 2, 1),   # short-reduction form: class kernels in one launch, reduce, final
-    (8, 128, 20, 18, 209, 4, 4, 1, 1),   # bfloat16 matrix cores: three ranges, added up by a kernel of their own
-    (25, 297, 31, 17, 79, 4, 4, 2, 1),   # ... two ranges, added up by the final kernel
+@pytest.mark.parametrize("shape, path, kernel", [
+    ((2, 66, 12, 12, 67, 3, 3, 1, 1), 0, 0),     # GEMM form: input transform, dy transform, GEMM over ranges, final
+    ((16, 6, 130, 127, 16, 3, 3, 2, 1), 0, 1),   # short-reduction form: class kernels in one launch, reduce, final
+    ((8, 128, 20, 18, 209, 4, 4, 1, 1), 0, 0),   # bfloat16 matrix cores: three ranges, added up by a kernel of their own
+    ((25, 297, 31, 17, 79, 4, 4, 2, 1), 0, 0),   # ... two ranges, added up by the final kernel
+    ((16, 6, 130, 127, 16, 3, 3, 2, 1), -1, 2),  # direct convolution: pieces and the kernel that adds them up
+    ((1, 70, 8, 8, 34, 3, 3, 1, 1), -1, 2),      # ... one piece
 ])
-def test_backward_filter_replays_from_a_graph(shape):
+def test_backward_filter_replays_from_a_graph(shape, path, kernel):
     N, C, H, W, K, R, S, s, P = shape
     rng = np.random.default_rng(7)
     OH, OW = (H + 2 * P - R) // s + 1, (W + 2 * P - S) // s + 1
@@ -127,6 +137,8 @@ def test_backward_filter_replays_from_a_graph(shape):
     dy = torch.from_numpy(rng.uniform(-1, 1, (N, K, OH, OW)).astype(np.float32)).cuda()
     plan = dwm.dwm_bwd_filter_plan_create(N, C, H, W, K, R, S, s, P)
     try:
+        dwm.dwm_bwd_filter_set_variant(plan, "path", path)
+        assert dwm.dwm_bwd_filter_kernel(plan) == kernel
         ws = torch.empty(dwm.dwm_bwd_filter_workspace_bytes(plan) // 4, dtype=torch.float32, device="cuda")
         dwm.dwm_bwd_filter_set_workspace(plan, ws.data_ptr(), ws.numel() * 4)
         dw = torch.zeros((K, C, R, S), dtype=torch.float32, device="cuda")

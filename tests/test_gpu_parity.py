@@ -341,19 +341,23 @@ def test_benchmark_layers_full_size(index):
 
 @pytest.mark.parametrize("index", [1, 2])
 def test_split_tile_summing_repeats_bit_for_bit(index):
-    """The two layers whose contraction cuts tiles into ranges summed across workgroups (and XCDs):
+    """The two layers whose contraction ("forward" 0) cuts tiles into ranges summed across workgroups (and XCDs):
     200 launches on the same input, every y compared on the device with the first, stopping at the
-    first mismatch; the first is checked against the oracle by the test above."""
+    first mismatch, and 2000 outputs of the first against the oracle."""
     L = wl.CONFIGS[index]
     x, w = wl.make_layer_tensors(L, index)
-    r = Runner(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad)
+    r = Runner(L.N, L.C, L.H, L.W, L.K, L.R, L.S, L.stride, L.pad, variants={"forward": 0})
     try:
+        assert dwm.dwm_plan_forward_kernel(r.plan) == 0
         r.set_filter(w)
         r.x = torch.from_numpy(x).cuda()
         args = (r.plan, r.x.data_ptr(), r.Ugw.data_ptr(), r.y.data_ptr(), r.stream())
         dwm.dwm_conv_forward(*args)
         first = r.y.clone()
         assert bool(torch.isfinite(first).all())
+        idx = np.random.default_rng(778).choice(first.numel(), 2000, replace=False)
+        ref = oracle.direct_f64_at(x, w, L.stride, L.pad, idx)
+        assert _relerr(first.cpu().numpy().ravel()[idx], ref) <= TOL
         for i in range(200):
             r.y.fill_(float("nan"))
             dwm.dwm_conv_forward(*args)

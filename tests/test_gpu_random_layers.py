@@ -3,8 +3,9 @@
 The shapes are drawn from a seeded generator that mixes what the hand-picked cases of the other files fix one
 at a time: kernels of 1..13 taps (square or not), strides 1..8 (also above the kernel size), paddings up to the
 kernel size, few or many channels, images down to one pixel wide.  Every case runs the forward pass (the
-planner's path and the staged path), the entry point that allocates nothing, the data gradient (both paths where
-the single kernel applies), the filter gradient, and the binary16 and bfloat16 forward passes (staged, single
+planner's path, the staged path and, where it applies, the single kernel), the entry point that allocates nothing, the data
+gradient (the planner's path, the sub-convolutions and, where it applies, the single kernel), the filter gradient (the
+planner's path and the transforms), and the binary16 and bfloat16 forward passes (staged, single
 kernel, planner's choice) -- the first mismatch names the path and the shape.
 """
 import numpy as np
@@ -48,16 +49,20 @@ def _check_layer(shape, rng):
     OH, OW = (H + 2 * P - R) // s + 1, (W + 2 * P - S) // s + 1
     dy = rng.uniform(-1, 1, (N, K, OH, OW)).astype(np.float32)
     ref = oracle.direct_f64(x, w, s, P)
-    for staged in (False, True):
+    for forward in (-1, 0, 1):
         r = Runner(*shape)
         try:
-            if staged:
-                dwm.dwm_plan_set_variant(r.plan, "forward", 0)
+            try:
+                dwm.dwm_plan_set_variant(r.plan, "forward", forward)
+            except dwm.DwmError:
+                assert forward == 1  # the single kernel does not apply to every layer
+                continue
+            assert forward < 0 or dwm.dwm_plan_forward_kernel(r.plan) == forward
             r.set_filter(w)
             y = r.forward(x)
         finally:
             r.close()
-        assert np.all(np.isfinite(y)) and _rel(y, ref) <= TOL, ("forward, staged" if staged else "forward", shape)
+        assert np.all(np.isfinite(y)) and _rel(y, ref) <= TOL, ("forward, variant %d" % forward, shape)
     # the entry point that allocates nothing: a plan of its own, no workspace handed over
     plan = dwm.dwm_plan_create(*shape)
     try:
@@ -75,24 +80,27 @@ def _check_layer(shape, rng):
     finally:
         dwm.dwm_plan_destroy(plan)
     ref_dx = oracle.backward_data_f64(dy, w, (N, C, H, W), s, P)
-    for path in (0, 1):
+    for path in (-1, 0, 1):
         try:
             b = BwdRunner(*shape, path=path)
         except dwm.DwmError:
             assert path == 1  # the single kernel does not apply to every layer
             continue
         try:
+            assert path < 0 or dwm.dwm_bwd_data_kernel(b.plan) == path
             dx = b.run(dy, w)
         finally:
             b.close()
         assert np.all(np.isfinite(dx)) and _rel(dx, ref_dx) <= TOL, ("data gradient, path %d" % path, shape)
-    g = WgradRunner(*shape)
-    try:
-        dw = g.run(x, dy)
-    finally:
-        g.close()
-    assert np.all(np.isfinite(dw)) and _rel(dw, oracle.backward_filter_f64(x, dy, (K, C, R, S), s, P)) <= TOL, \
-        ("filter gradient", shape)
+    ref_dw = oracle.backward_filter_f64(x, dy, (K, C, R, S), s, P)
+    for path in (-1, 0):
+        g = WgradRunner(*shape, path=path)
+        try:
+            assert path < 0 or dwm.dwm_bwd_filter_kernel(g.plan) < 2
+            dw = g.run(x, dy)
+        finally:
+            g.close()
+        assert np.all(np.isfinite(dw)) and _rel(dw, ref_dw) <= TOL, ("filter gradient, path %d" % path, shape)
     x16, w16 = x.astype(np.float16), w.astype(np.float16)
     ref16 = oracle.dwm_half_f64(x16, w16, s, P)
     xb = torch.from_numpy(x).to(torch.bfloat16).float().numpy()
@@ -138,10 +146,10 @@ def _draw_medium(rng):
 
 @pytest.mark.parametrize("seed", [5, 77])
 def test_random_medium_layers_split_modes_variants_and_repeats(seed):
-    """Layers of 40-4000 contraction tiles (many channels and filters) against sampled oracle outputs: the three
-    ways of sharing out the tiles, a random contraction variant and input-transform form, twelve more launches
-    through the same plan (bit-identical: split tiles are summed in a fixed order), the data gradient, the filter
-    gradient on the smaller ones, and the binary16 path with random variants of its own."""
+    """Layers of 40-4000 contraction tiles (many channels and filters) against sampled oracle outputs: the planner's forward
+    pass, the contraction with the three ways of sharing out its tiles, a random contraction variant and input-transform form, twelve more launches
+    through the same plan (bit-identical: split tiles are summed in a fixed order), the data gradient and, on the smaller
+    ones, the filter gradient (the planner's path and the transforms), and the binary16 path with random variants of its own."""
     rng = np.random.default_rng(seed)
     done = 0
     while done < 25:
@@ -162,12 +170,13 @@ def test_random_medium_layers_split_modes_variants_and_repeats(seed):
         idx = rng.choice(N * K * OH * OW, min(N * K * OH * OW, 6000), replace=False)
         ref = oracle.direct_f64_at(x, w, s, P, idx)
         scale = np.max(np.abs(ref))
-        for split in (0, 1, 2):
-            r = Runner(*shape, variants={"split": split})
+        for split in (None, 0, 1, 2):
+            r = Runner(*shape, variants={} if split is None else {"forward": 0, "split": split})
             try:
+                assert split is None or dwm.dwm_plan_forward_kernel(r.plan) == 0
                 r.set_filter(w)
                 y = r.forward(x)
-                if split == 0:
+                if not split:
                     xs = torch.from_numpy(x).cuda()
                     for _ in range(12):
                         dwm.dwm_conv_forward(r.plan, xs.data_ptr(), r.Ugw.data_ptr(), r.y.data_ptr(), r.stream())
@@ -190,21 +199,23 @@ def test_random_medium_layers_split_modes_variants_and_repeats(seed):
             assert np.all(np.isfinite(y)) and np.max(np.abs(y.ravel()[idx] - ref)) / scale <= TOL, (variants, shape)
         idx2 = rng.choice(N * C * H * W, min(N * C * H * W, 6000), replace=False)
         ref_dx = oracle.backward_data_f64_at(dy, w, (N, C, H, W), s, P, idx2)
-        b = BwdRunner(*shape)
-        try:
-            dx = b.run(dy, w)
-        finally:
-            b.close()
-        assert np.all(np.isfinite(dx))
-        assert np.max(np.abs(dx.ravel()[idx2] - ref_dx)) / max(np.max(np.abs(ref_dx)), 1e-30) <= TOL, ("data gradient", shape)
-        if flops <= 3e9:
-            g = WgradRunner(*shape)
+        for path in (-1, 0):
+            b = BwdRunner(*shape, path=path)
             try:
-                dw = g.run(x, dy)
+                dx = b.run(dy, w)
             finally:
-                g.close()
-            assert np.all(np.isfinite(dw)) and _rel(dw, oracle.backward_filter_f64(x, dy, (K, C, R, S), s, P)) <= TOL, \
-                ("filter gradient", shape)
+                b.close()
+            assert np.all(np.isfinite(dx))
+            assert np.max(np.abs(dx.ravel()[idx2] - ref_dx)) / max(np.max(np.abs(ref_dx)), 1e-30) <= TOL, ("data gradient", path, shape)
+        if flops <= 3e9:
+            ref_dw = oracle.backward_filter_f64(x, dy, (K, C, R, S), s, P)
+            for path in (-1, 0):
+                g = WgradRunner(*shape, path=path)
+                try:
+                    dw = g.run(x, dy)
+                finally:
+                    g.close()
+                assert np.all(np.isfinite(dw)) and _rel(dw, ref_dw) <= TOL, ("filter gradient", path, shape)
         x16, w16 = x.astype(np.float16), w.astype(np.float16)
         ref16 = oracle.direct_f64_at(x16.astype(np.float32), w16.astype(np.float32), s, P, idx)
         h = HalfRunner(*shape, forward=0)
