@@ -144,7 +144,7 @@ DWM_API dwm_status_t dwm_plan_info(const dwm_plan_t* plan, dwm_plan_info_t* info
  * adds up, where a few tiles are shared by many workgroups), on the bfloat16 matrix cores with every binary32 operand as the sum
  * of three bfloat16 numbers (C >= 16, where it takes less time than what forward_path names).  Infinities, NaN, operands of about
  * 2^112 or more and sums of 2^96 or more take fp32 matrix cores for the outputs that they reach, and time: a call takes up to three
- * times as long with one such value, up to three and a half times if every output is such.  Sums that a second launch adds up
+ * times as long with one such value, up to four times if every output is such.  Sums that a second launch adds up
  * lie in the workspace.  A variant that dwm_plan_set_variant is asked for by number takes the layer to that stage instead; those that
  * restore the planner's choice ("split" 0, "input_cg" 0, negative ones) leave it here.
  * -1: null plan. */

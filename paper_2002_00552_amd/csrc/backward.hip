@@ -604,7 +604,7 @@ dwm_status_t dwm_conv_backward_data(const dwm_bwd_data_plan_t* plan, const float
         const dwm_status_t st = dwm_conv_forward(ph.sub, dy_dev, Ugw_dev + ph.u_off, dx_dev, stream);
         if (st != DWM_OK) return st;
     }
-    if (direct) return dwm::launch_fused_forward(*plan->direct, dy_dev, Ugw_dev + plan->u_direct_off, dx_dev, nullptr, stream);
+    if (direct) return dwm::launch_direct(*plan->direct, dy_dev, Ugw_dev + plan->u_direct_off, dx_dev, nullptr, stream);
     if (plan->merged) {
         if (!plan->ws) return DWM_ERR_WORKSPACE;
         const dwm_status_t st = dwm::launch_input_transform(*plan->merged, dy_dev, plan->ws, stream);

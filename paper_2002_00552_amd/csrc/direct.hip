@@ -517,10 +517,12 @@ static dwm_status_t launch_shape(const DirectArgs& a, const float* x, const unsi
     return hipGetLastError() == hipSuccess ? DWM_OK : DWM_ERR_HIP;
 }
 
-dwm_status_t launch_direct(const DirectArgs& a, const float* x, const float* U, float* y, float* partial, void* stream)
+dwm_status_t launch_direct(const dwm_plan& p, const float* x, const float* U, float* y, float* ws, void* stream)
 {
-    const unsigned char* Wd = reinterpret_cast<const unsigned char*>(U);
-    const float* W32 = U + a.wd_bytes / 4;
+    const DirectArgs& a = p.direct;
+    const unsigned char* Wd = reinterpret_cast<const unsigned char*>(U + p.ud_begin);
+    const float* W32 = U + p.ud_begin + a.wd_bytes / 4;
+    float* partial = p.sk_partial(ws);
     switch (a.shape) {
         case 0: return launch_shape<4, 2, 1, 2>(a, x, Wd, W32, y, partial, stream);
         case 1: return launch_shape<2, 2, 1, 2>(a, x, Wd, W32, y, partial, stream);

@@ -520,9 +520,8 @@ __global__ __launch_bounds__(256, 2) void fused_forward_kernel(DevPlan P, FusedA
     }  // blocks of this workgroup
 }
 
-dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, float* ws, void* stream)
+dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, void* stream)
 {
-    if (p.use_direct()) return launch_direct(p.direct, x, U + p.ud_begin, y, p.sk_partial(ws), stream);
     if (!p.fused_ok) return DWM_ERR_INVALID_ARG;
     const FusedArgs& f = p.fused;
     using Kernel = void (*)(DevPlan, FusedArgs, const float*, const float*, float*);

@@ -47,16 +47,15 @@ dwm_status_t dwm_conv_forward_static(const dwm_plan_t* plan, const float* x_dev,
                                      void* stream)
 {
     if (!plan || !x_dev || !Ugw_dev || !y_dev) return DWM_ERR_INVALID_ARG;
-    // the single-kernel path keeps V in registers and has no scratch at all
-    // (and a tile of its layers' direct convolution is never cut into pieces)
-    if (plan->use_fused()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, nullptr, stream);
-    if (plan->ws_need_bytes() > kScratchBytes) return DWM_ERR_WORKSPACE;
-    // (nor has the direct convolution of whole tiles; what fits does not depend on which kernel the planner has chosen)
-    if (plan->use_direct() && plan->direct.pieces == 1) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, nullptr, stream);
+    // the single-kernel path keeps V in registers and has no scratch at all, and a tile of its layers' direct convolution is
+    // never cut into pieces; of other layers what fits does not depend on which kernel the planner has chosen
+    if (!plan->use_fused() && plan->ws_need_bytes() > kScratchBytes) return DWM_ERR_WORKSPACE;
+    if (plan->use_direct() && plan->direct.pieces == 1) return dwm::launch_direct(*plan, x_dev, Ugw_dev, y_dev, nullptr, stream);
+    if (plan->use_fused() && !plan->use_direct()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, stream);
     float* ws = nullptr;
     dwm_status_t st = scratch_of_current_device(&ws);
     if (st != DWM_OK) return st;
-    if (plan->use_direct()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, ws, stream);
+    if (plan->use_direct()) return dwm::launch_direct(*plan, x_dev, Ugw_dev, y_dev, ws, stream);
     // the input transform writes every element of V that the contraction reads and clears the
     // arrival counters, so nothing of the previous call's contents survives into this one
     st = dwm::launch_input_transform(*plan, x_dev, ws, stream);

@@ -253,7 +253,7 @@ extern "C" {
 // 348, one 10x10 image, 66 MB: 111 against 134 us).  The convolution alone, before -> now (us): 3x3, 256 -> 256 channels, one
 // 14x14 image 20.7 -> 11.7, four 26.0 -> 16.2; 3x3, 224 -> 38, 8 27x27 29.0 -> 18.8; 7x7, 150 -> 140, one 33x33 47 -> 25.  Kept
 // away: 7x7, 256 -> 256, 32 28x28 613 -> 692.
-static bool direct_ahead(dwm_plan& p, const dwm::PlanSpec& sp)
+static bool direct_ahead(dwm_plan& p)
 {
     const dwm::DevPlan& d = p.d;
     if (d.C < 16) return false;
@@ -419,7 +419,7 @@ static dwm_status_t plan_build(dwm_plan_t** out, const dwm::PlanSpec& sp, bool e
         }
         p->filter_floats = uf;
     }
-    if (sp.direct && (p->fused_ok || with_split) && (!p->split_ok || sp.over_split) && direct_ahead(*p, sp)) {
+    if (sp.direct && (p->fused_ok || with_split) && (!p->split_ok || sp.over_split) && direct_ahead(*p)) {
         p->direct_ok = true;
         p->ud_gap = p->filter_floats;
         p->ud_begin = (p->filter_floats + 63) / 64 * 64;
@@ -631,7 +631,8 @@ dwm_status_t dwm_conv_forward(const dwm_plan_t* plan, const float* x_dev, const 
 {
     if (!plan || !x_dev || !Ugw_dev || !y_dev) return DWM_ERR_INVALID_ARG;
     if (!plan->ws) return DWM_ERR_WORKSPACE;
-    if (plan->use_fused() || plan->use_direct()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, plan->ws, stream);
+    if (plan->use_direct()) return dwm::launch_direct(*plan, x_dev, Ugw_dev, y_dev, plan->ws, stream);
+    if (plan->use_fused()) return dwm::launch_fused_forward(*plan, x_dev, Ugw_dev, y_dev, stream);
     dwm_status_t st = dwm::launch_input_transform(*plan, x_dev, plan->ws, stream);
     if (st != DWM_OK) return st;
     return dwm::launch_contract_output(*plan, Ugw_dev, plan->ws, y_dev, stream);

@@ -569,8 +569,8 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
 // ... with the shape that takes the least time by its model
 bool direct_choose(int N, int C, int H, int W, int K, int s, int YH, int YW, int sy, int sx, const DirectProb* p, int n, DirectArgs* out,
                    size_t partial_floats = 0);
-// (partial: room for the pieces' outputs, where a tile is cut into pieces)
-dwm_status_t launch_direct(const DirectArgs& a, const float* x, const float* U, float* y, float* partial, void* stream);
+// a plan's (U: its whole filter buffer; ws: as launch_contract_output has it, for tiles that are cut into pieces, else not used)
+dwm_status_t launch_direct(const dwm_plan& p, const float* x, const float* U, float* y, float* ws, void* stream);
 dwm_status_t launch_direct_filter(const DirectArgs& a, const FilterSource& src, const float* w, float* U, void* stream);
 // setup.cpp / wgrad_direct.hip: the filter gradient likewise
 bool wd_setup(int N, int C, int H, int W, int K, int R, int S, int s, int P, int OH, int OW, WdArgs* out);
@@ -585,5 +585,5 @@ dwm_status_t launch_bwd_small_filter(const BwdSmallArgs& a, int R, int S, const 
 dwm_status_t launch_bwd_small(const BwdSmallArgs& a, const float* dy, const float* U, float* dx, void* stream);
 // fused.hip
 bool fused_setup(const dwm_plan& p, FusedArgs* out);
-dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, float* ws, void* stream);
+dwm_status_t launch_fused_forward(const dwm_plan& p, const float* x, const float* U, float* y, void* stream);
 }  // namespace dwm

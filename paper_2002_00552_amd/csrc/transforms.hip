@@ -99,6 +99,7 @@ __global__ __launch_bounds__(256) void filter_copies_kernel(DevPlan P, FilterSou
     }
 }
 static_assert(kFusedMaxRows <= 256, "rows of fused_filter");
+static_assert(sizeof(DevPlan) + sizeof(FilterSource) + sizeof(FusedArgs) + sizeof(DirectArgs) + sizeof(FilterCopies) + 16 <= 4096, "kernel arguments");
 
 // The same for several stride-1 sub-convolutions that read one w (the phases of a data gradient), one grid plane each: four
 // launches of 4.3 us and the gaps between them for a 5x5 layer at stride 2 with 67 and 93 channels become one.  Further grid

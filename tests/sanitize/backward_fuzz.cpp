@@ -14,8 +14,8 @@ dwm_status_t launch_filter_batch(const FilterBatchArgs&, const float*, float*, v
 dwm_status_t launch_input_transform(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_contract_output(const dwm_plan&, const float*, float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_contract_batch(const BatchArgs&, const PlaneTable&, int, const float*, const float*, float*, float*, void*) { return DWM_OK; }
-dwm_status_t launch_fused_filter(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
-dwm_status_t launch_fused_forward(const dwm_plan&, const float*, const float*, float*, float*, void*) { return DWM_OK; }
+dwm_status_t launch_fused_forward(const dwm_plan&, const float*, const float*, float*, void*) { return DWM_OK; }
+dwm_status_t launch_direct(const dwm_plan&, const float*, const float*, float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_bwd_small_filter(const BwdSmallArgs&, int, int, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_bwd_small(const BwdSmallArgs&, const float*, const float*, float*, void*) { return DWM_OK; }
 }  // namespace dwm

@@ -12,7 +12,8 @@ namespace dwm {
 dwm_status_t launch_filter_transform(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_input_transform(const dwm_plan&, const float*, float*, void*) { return DWM_OK; }
 dwm_status_t launch_contract_output(const dwm_plan&, const float*, float*, float*, void*) { return DWM_OK; }
-dwm_status_t launch_fused_forward(const dwm_plan&, const float*, const float*, float*, float*, void*) { return DWM_OK; }
+dwm_status_t launch_fused_forward(const dwm_plan&, const float*, const float*, float*, void*) { return DWM_OK; }
+dwm_status_t launch_direct(const dwm_plan&, const float*, const float*, float*, float*, void*) { return DWM_OK; }
 }
 using namespace dwm;
 static uint64_t g = 0x9E3779B97F4A7C15ull;
