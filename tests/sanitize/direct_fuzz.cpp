@@ -82,7 +82,8 @@ static void replay(const DirectArgs& A, bool full) {
     for (int i = 0; i < A.nprob; ++i) outs[i].assign(full ? (size_t)A.N * A.p[i].OH * A.p[i].OW : 0, 0);
     for (int t = 0; t < A.ntiles; ++t) {
         const bool low = t < A.full8; const int r0 = low ? t >> 3 : t - A.full8;
-        const int inner = r0 % per, tt = low ? (r0 / per) * 8 + (t & 7) : (A.ntt / 8) * 8 + r0 / per, pi = inner / A.nkt, kt = inner - pi * A.nkt;
+        const int place = r0 % per, tt = low ? (r0 / per) * 8 + (t & 7) : (A.ntt / 8) * 8 + r0 / per;
+        const int inner = (r0 - place) / 32 % 2 == 0 ? place : per - 1 - place, pi = inner / A.nkt, kt = inner - pi * A.nkt;
         CHECK(kt < A.nkt && tt < A.ntt && pi < A.nprob);
         CHECK(!tiles[tt * per + inner]); tiles[tt * per + inner] = 1;
         if (kt != 0 || (!full && t > 0 && rnd() % 8)) continue;

@@ -1,0 +1,61 @@
+"""The planner's choice of the direct convolutions (csrc/direct.hip, csrc/wgrad_direct.hip): not behind the paths that they replace, on
+layers where it was -- tiles of several lengths in step with the CUs."""
+import pytest
+import torch
+
+import paper_2002_00552_amd as dwm
+
+pytestmark = pytest.mark.gpu
+
+GRADIENT = [(32, 128, 56, 56, 256, 3, 3, 2, 1)]
+
+
+def _not_behind(calls):
+    """calls[0] in turn with the others: its lower quartile at most 1.1 times the best one's (runs of one differ by up to 0.05)."""
+    times = [[] for _ in calls]
+    e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for r in range(12):
+        for t, call in zip(times, calls):
+            call()
+            e0.record()
+            for _ in range(10):
+                call()
+            e1.record()
+            torch.cuda.synchronize()
+            t.append(e0.elapsed_time(e1))
+    own, best = sorted(times[0])[3], min(sorted(t)[3] for t in times[1:])
+    print("%.1f us, the other path %.1f" % (own * 100, best * 100), flush=True)
+    assert own <= 1.1 * best
+
+
+def _buffer(nbytes):
+    return torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device="cuda")
+
+
+def _tensors(shape):
+    N, C, H, W, K, R, S, s, P = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    OH, OW = (H + 2 * P - R) // s + 1, (W + 2 * P - S) // s + 1
+    return (torch.randn((N, C, H, W), generator=g, device="cuda"), torch.randn((K, C, R, S), generator=g, device="cuda"),
+            torch.randn((N, K, OH, OW), generator=g, device="cuda"), torch.cuda.current_stream().cuda_stream)
+
+
+@pytest.mark.parametrize("shape", GRADIENT)
+def test_data_gradient(shape):
+    x, w, dy, st = _tensors(shape)
+    plans, kept, calls = [], [], []
+    try:
+        for path in (-1, 0):
+            p = dwm.dwm_bwd_data_plan_create(*shape)
+            plans.append(p)
+            dwm.dwm_bwd_data_set_variant(p, "path", path)
+            U, ws = _buffer(dwm.dwm_bwd_data_filter_bytes(p)), _buffer(dwm.dwm_bwd_data_workspace_bytes(p))
+            kept += [U, ws]
+            dwm.dwm_bwd_data_set_workspace(p, ws.data_ptr(), ws.numel())
+            dwm.dwm_bwd_data_filter_transform(p, w.data_ptr(), U.data_ptr(), st)
+            calls.append(lambda p=p, U=U: dwm.dwm_conv_backward_data(p, dy.data_ptr(), U.data_ptr(), x.data_ptr(), st))
+        _not_behind(calls)
+    finally:
+        for p in plans:
+            dwm.dwm_bwd_data_plan_destroy(p)
