@@ -344,18 +344,35 @@ static void setup_batch(dwm_bwd_data_plan& bp)
     setup_filter_batch(bp, subs);
 }
 
-// All phases that a tap reaches as one direct convolution (direct.hip), where its model has it below the time of the
-// sub-convolutions' fewest launches: 18 us at least, Winograd products at 95 TFLOP/s on the fp32 matrix cores, transformed
-// inputs written and read at 4.3 TB/s, 5 us for each input transform.  Of 110 layers drawn with strides 2 and 3 (up to 150
-// GFLOP) it was ahead on all, at 0.26 of their time in the mean: nine input transforms of stride 3, 76 <- 18 channels, 46
-// images of 8x8, 180 -> 7 us; 5x5 at stride 2, 67 <- 93 channels, five 35x29 images 30 -> 14; 7x7 at stride 2, 256 <- 256
-// channels, 256 14x14 images 603 -> 456.  The line is at 0.93 of that: 3x3 at stride 2, 256 <- 512 channels, 16 14x14
-// images 41.5 -> 46 (it stays); 64 <- 512 channels, 64 7x7 images 72 -> 55.
+// The time (us) of the sub-convolutions by the method's transforms (what writes zeros left out): contracted in one launch, behind one
+// input transform (350 measured, rms of the logarithm 0.11) or one for each, a 32-step chunk of a tile 0.55 to 1 us on its CU, V written
+// and read; or one after the other.
+static double subconv_us(const dwm_bwd_data_plan& bp)
+{
+    double n = 0.0, alone = 1.0, chunks = 0.0;
+    for (const auto& ph : bp.phases)
+        if (ph.sub) {
+            n += 1.0;
+            alone += 0.98 * dwm::transforms_us(*ph.sub);
+        }
+    if (!bp.batched) return alone;
+    const dwm::BatchArgs& A = bp.batch;
+    for (int q = 0; q < A.nprob; ++q) chunks += (double)((q + 1 < A.nprob ? A.p[q + 1].tile0 : A.ntiles) - A.p[q].tile0) * A.p[q].n_iter;
+    chunks *= bp.batch_lc / 32.0 / dwm::kNumCUs;
+    if (!bp.merged) return 13.0 + chunks + 8.0 * n;
+    return 22.0 + 0.55 * chunks + 0.44 * (double)bp.merged->v_floats * 8.0 / 4.3e6 + 1.5 * (double)bp.N * bp.C * bp.H * bp.W / 1e6 + 0.4 * n;
+}
+
+// All phases that a tap reaches as one direct convolution (direct.hip), where its model and its filter's copy (0.6 us a MB, and a launch
+// where it is not written with the others) come to less than 0.85 of the sub-convolutions' time, 0.75 where waves share its tiles.  Of 875
+// layers drawn with strides 2 to 4 (up to 150 GFLOP) it takes 698, at 0.46 of the time in the mean of all, the copy included, none slower
+// (1.03 at worst).  At 0.93 of a rougher estimate one in twenty was, by up to 1.65 (5x5, 258 <- 147 channels, 37 images of 63x68).
+// Nine input transforms of stride 3, 76 <- 18 channels, 46 images of 8x8, 180 -> 7 us; 5x5 at stride 2, 67 <- 93 channels, five 35x29 images
+// 30 -> 14; 7x7 at stride 2, 256 <- 256 channels, 256 14x14 images 603 -> 456; 3x3 at stride 2, 128 <- 256, 32 56x56 images 136 -> 132.
 static void setup_direct(dwm_bwd_data_plan& bp)
 {
     using namespace dwm;
     std::vector<DirectProb> p;
-    double us = 18.0;
     for (const auto& ph : bp.phases) {
         if (!ph.sub) continue;
         const DevPlan& d = ph.sub->d;
@@ -363,12 +380,13 @@ static void setup_direct(dwm_bwd_data_plan& bp)
         q.R = ph.na; q.S = ph.nb; q.Ph = d.Ph; q.Pw = d.Pw; q.OH = ph.UH; q.OW = ph.UW; q.oy = ph.oy; q.ox = ph.ox;
         q.base = (long long)(bp.s * (ph.na - 1) + ph.a) * bp.S + bp.s * (ph.nb - 1) + ph.b;
         p.push_back(q);
-        us += ph.sub->info.winograd_flops / 95e6 + (double)ph.sub->v_floats * 8.0 / 4.3e6 + (bp.merged ? 0.0 : 5.0);
     }
     if (p.empty() || p.size() > (size_t)kDirectMaxProbs) return;
     std::stable_sort(p.begin(), p.end(), [](const DirectProb& a, const DirectProb& b) { return a.R * a.S > b.R * b.S; });
     DirectArgs a;
-    if (!direct_choose(bp.N, bp.K, bp.OH, bp.OW, bp.C, 1, bp.H, bp.W, bp.s, bp.s, p.data(), (int)p.size(), &a) || a.us >= 0.93 * us) return;
+    if (!direct_choose(bp.N, bp.K, bp.OH, bp.OW, bp.C, 1, bp.H, bp.W, bp.s, bp.s, p.data(), (int)p.size(), &a)) return;
+    const double line = kDirectShapes[a.shape].wk == 1 ? 0.85 : 0.75;
+    if (a.us + 2.4e-6 * a.filter_floats() + (bp.filter_batched ? 1.0 : 4.5) >= line * subconv_us(bp)) return;
     dwm_plan* m = new (std::nothrow) dwm_plan;
     if (!m) return;
     std::memset(m, 0, sizeof(*m));

@@ -175,6 +175,15 @@ static double fp32_contract_us(const dwm_plan& p)
            0.45 * p.planes.n / (g.sk_f > 1 ? g.sk_f : 1) + (g.sk_f > 1 ? 1.7 * g.sk_f : 0.0) + 9.0;
 }
 
+// Of layers that fused.hip can run: 369 measured, rms of the logarithm 0.33.
+double transforms_us(const dwm_plan& p)
+{
+    const DevPlan& d = p.d;
+    const double x_bytes = 4.0 * d.N * d.C * d.H * d.W, y_bytes = 4.0 * d.N * d.K * d.OH * d.OW;
+    if (p.fused_ok) return 13.4 + p.info.winograd_flops / d.K * ((d.K + 31) / 32 * 32) / 67e6 + (x_bytes + y_bytes) / 2.65e6;
+    return 5.7 + (p.split_ok ? p.split_us : 1.03 * fp32_contract_us(p)) + ((double)p.v_floats * 4.0 + x_bytes) / 4.31e6;
+}
+
 // The contraction on the bfloat16 matrix cores: whether it takes the layer, with which shape of its workgroup, and into
 // how many pieces each tile is cut.  It is worth considering from 1024 rows of reduction per tile (all planes together)
 // and 32 filters on: below, a tile ends before its loads have caught up, and the input transform is most of the time.
@@ -240,11 +249,14 @@ bool split_geometry(const dwm_plan& p, ContractGeometry* out, double* us)
 extern "C" {
 
 // Whether the direct convolution (direct.hip) takes the layer, beside what it has: where its model has it below 0.85 of the time of
-// the path it would replace -- the fp32 contraction behind an input transform (within 11 % of 53 measured layers) or, of
-// layers that fused.hip can run, Winograd products at 50 TFLOP/s after 13 us (within 25 % of 19).  Measured, before -> now (us): 5x5,
+// the path it would replace (transforms_us: the fp32 contraction behind an input transform, or fused.hip's single kernel), 0.72 where waves
+// share its tiles, which is modelled less closely.  The lines lie where measured calls begin to be slower.  Of 1385 drawn passes on the
+// contraction (forward, and data gradients at stride 1; up to 150 GFLOP) it takes 1076, at 0.57 of the time in the mean of all, two of them
+// slower (1.06 at most); of 482 on the single kernel 384, at 0.59, two of them slower (1.14).  At 0.85 for all, by a model that did not
+// count what narrow strips move (setup.cpp), one in forty was slower, by up to 2.0.  Measured, before -> now (us): 5x5,
 // 16 -> 16 channels, one 32x32 image 12.1 -> 7.5; 3x3 at stride 2, 128 -> 256, 32 56x56 images 122 -> 86; 3x3, 128 -> 128, 64
-// 28x28 images 89 -> 82; 3x3, 40 -> 61, 78 images of 17x21 40.5 -> 13.3; 5x1, 56 -> 27, 36 images of 32x38 60 -> 19.6.  Of 72
-// drawn layers it took 0.49 of the time in the mean.  From 16 channels: below, a step's groups of eight are half empty, and
+// 28x28 images 89 -> 82; 3x3, 40 -> 61, 78 images of 17x21 40.5 -> 13.3; 5x1, 56 -> 27, 36 images of 32x38 60 -> 19.6.
+// From 16 channels: below, a step's groups of eight are half empty, and
 // first layers are faster on fused.hip (7x7 at stride 2, 3 -> 64, 141 against 168).
 // Layers that the bfloat16 contraction takes (contract_split.hip) stay with it in the forward pass, whose filter buffer has its
 // copy at the end; as data gradients at stride 1 they change over from 0.70 of the time of the three launches there, the filter's
@@ -260,15 +272,14 @@ static bool direct_ahead(dwm_plan& p)
     dwm::DirectProb q{};
     q.R = d.R; q.S = d.S; q.Ph = d.Ph; q.Pw = d.Pw; q.OH = d.OH; q.OW = d.OW;
     q.oy = d.om.oy; q.ox = d.om.ox;
-    const double x_bytes = 4.0 * d.N * d.C * d.H * d.W, y_bytes = 4.0 * d.N * d.K * d.OH * d.OW;
-    const double us = p.fused_ok ? 13.0 + p.info.winograd_flops / 50e6 + (x_bytes + y_bytes) / 4e6
-                                 : 5.7 + (p.split_ok ? p.split_us : 1.03 * dwm::fp32_contract_us(p)) + ((double)p.v_floats * 4.0 + x_bytes) / 4.31e6;
+    const double us = dwm::transforms_us(p);
     // (the contraction's partial outputs have a place in the workspace; the single kernel's layers need none)
     const bool whole = d.om.sy == 1 && d.om.sx == 1 && d.om.oy == 0 && d.om.ox == 0 && d.OH == d.om.YH && d.OW == d.om.YW;
     if (!dwm::direct_choose(d.N, d.C, d.H, d.W, d.K, d.s, d.om.YH, d.om.YW, d.om.sy, d.om.sx, &q, 1, &p.direct,
                             p.fused_ok || !whole ? 0 : p.active().partial_floats))
         return false;
-    return p.split_ok ? p.direct.us + 2.4e-6 * p.direct.filter_floats() < 0.70 * us : p.direct.us < 0.85 * us;
+    if (p.split_ok) return p.direct.us + 2.4e-6 * p.direct.filter_floats() < 0.70 * us;
+    return p.direct.us < (dwm::kDirectShapes[p.direct.shape].wk == 1 ? 0.85 : 0.72) * us;
 }
 
 // One planning pass with the given splitting policy; *out is set on DWM_OK only.

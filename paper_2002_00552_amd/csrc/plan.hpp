@@ -544,6 +544,8 @@ dwm_status_t plan_from_spec_widened(dwm_plan_t** out, const PlanSpec& sp);
 dwm_status_t plan_from_spec_as_printed(dwm_plan_t** out, const PlanSpec& sp);
 // plan.cpp: geometry of a contraction variant for this plan; false if the variant does not apply
 bool contract_geometry(const dwm_plan& p, int variant, ContractGeometry* out);
+// ... and the time (us) of a forward pass by the method's transforms: the single kernel's, or input transform and contraction
+double transforms_us(const dwm_plan& p);
 // ... and the shape and the sharing out of the contraction on the bfloat16 matrix cores; false where it does not pay
 bool split_geometry(const dwm_plan& p, ContractGeometry* out, double* us);
 // transforms.hip, contract.hip

@@ -156,11 +156,25 @@ static int direct_sum_steps(const DirectArgs& a, const DirectShape& sh, const Di
     return a.pieces > 1 ? a.cpp * share(q.steps[0]) : (a.nchunks - 1) * share(q.steps[0]) + share(q.steps[1]);
 }
 
+// What a workgroup of a direct convolution moves (shared: problems and pieces), in bytes of the 64-byte pieces of lines that memory
+// gives and takes: a strip one pixel wide loads and stores sixteen times what it needs (the tiles beside it run on other XCDs).  x is
+// read by a pixel tile's workgroups, all filters and problems, at about the same time on one XCD.
+static double direct_bytes(int C, int K, int kt, int npx, int shared, int bw, int P, int row_px, int lwp, int s, int sx)
+{
+    auto pieces = [](int pixels, int step) { return 64.0 + 4.0 * (pixels - 1) * step; };
+    const int nkt = (K + kt - 1) / kt, wide = (lwp - 1) * s + row_px / lwp;
+    const double load = (double)C * P / row_px * std::min(pieces(wide, 1), 64.0 * row_px) / ((double)nkt * shared);
+    const double store = (double)K / nkt * npx / bw * std::min(pieces(bw, sx), 64.0 * bw);
+    return load + store;
+}
+
 // The time (us) of a direct convolution, fitted to 1700 (layer, shape) pairs drawn from the timed cases' ranges (forward and
-// strided data gradients; rms of the logarithm 0.17, the shape that it picks at 1.03 of the best one's time): cycles at 2.1
-// GHz of a workgroup -- its MFMAs, 340 a staged pixel and wave of a SIMD, 5400 a chunk (first loads, barriers), stores --, shared by the
-// workgroups on a CU (registers allow two of 64-row wave tiles, three of 32), the address unit's 19 for each load and store,
-// and the matrix cores' power-limited 1.19 PFLOP/s.
+// strided data gradients): cycles at 2.1 GHz of a workgroup -- its MFMAs, 340 a staged pixel and wave of a SIMD, 5400 a chunk (first
+// loads, barriers), stores --, shared by the workgroups on a CU (registers allow two of 64-row wave tiles, three of 32), the address unit's
+// 19 for each load and store, and 1.19 PFLOP/s as the most (long runs have reached 1.4: it errs on the side of the other paths); and
+// what all tiles move, at 8 TB/s, as the other side of a right angle.  Over 1738 plans that the planner chose (rms of the logarithm of
+// measured to modelled time) 0.16, 1.6 at worst; without the last term 0.22, and strips of one to three pixels up to 3.5 times as long as
+// modelled: 1x1, 179 -> 218 channels, 49 37x37 images 74 by the model, 215 measured, 107 the contraction.
 static double direct_us(const DirectArgs& a, const DirectShape& sh)
 {
     const double w = sh.threads() / 256.0, waves = sh.threads() / 64.0, groups = std::min((a.C + 7) / 8, a.cpp * a.groups[0]);
@@ -169,14 +183,20 @@ static double direct_us(const DirectArgs& a, const DirectShape& sh)
     const int fits = (int)(160 * 1024 / a.lds_bytes);
     const double on_cu = sh.threads() > 256 ? 1 : std::max(1, std::min(fits, sh.mb == 2 ? 2 : 3));
     const double slots = groups * a.ns, store = 1180.0 * sh.mb * w / sh.wk;
-    const double simd = mean * 368.0 * sh.mb * w + slots * 340.0 * w + store;
-    const double address = 19.0 * (slots * waves * 8 + mean * waves * 3 * sh.mb + sh.mb * 32 * waves / sh.wk * (a.sx > 1 ? 2 : 1));
     const double lone = a.longest * 368.0 * sh.mb * w + slots * 340.0 * w + a.cpp * 5400.0 + store;
-    const double wgs = (double)a.ntiles * a.pieces, per_cu = wgs / kNumCUs, rounds = std::max(1.0, per_cu / on_cu < 3 ? std::ceil(per_cu / on_cu) : per_cu / on_cu + 0.5);
-    const double cycles = rounds * std::max(lone, std::min(on_cu, std::ceil(per_cu)) * std::max(simd, address));
+    auto shared = [&](double steps) {  // a workgroup's part of a CU's time
+        const double simd = steps * 368.0 * sh.mb * w + slots * 340.0 * w + store;
+        return std::max(simd, 19.0 * (slots * waves * 8 + steps * waves * 3 * sh.mb + sh.mb * 32 * waves / sh.wk * (a.sx > 1 ? 2 : 1)));
+    };
+    const double wgs = (double)a.ntiles * a.pieces, per_cu = wgs / kNumCUs, full = per_cu / on_cu, beside = std::min(on_cu, std::ceil(per_cu));
+    const double rounds = std::max(1.0, full < 3 ? std::ceil(full) : full + 0.5);
+    // (problems of several lengths: some of the longest tiles are among the last to start)
+    const double together = a.nprob == 1 ? rounds * shared(mean) : full <= 1 ? shared(a.longest) : full * shared(mean) + 0.5 * shared(a.longest);
+    const double cycles = std::max(rounds * lone, beside * together);
     const double flops = wgs * mean * waves * sh.mb * 2 * 6 * 32768.0;
     const double sum = a.pieces > 1 ? 3.0 + (2.0 * a.pieces + 1.0) * 4.0 * a.piece_floats / 5e6 : 0.0;
-    return std::max(cycles / 2100.0, flops / 1.19e9) + 4.3 + sum;
+    const double alone = std::max(cycles / 2100.0, flops / 1.19e9) + 4.3 + sum, moved = wgs * direct_bytes(a.C, a.K, a.kt, a.npx, a.nprob * a.pieces, a.bw, a.P, a.row_px, a.lwp, a.s, a.sx) / 8e6;
+    return std::sqrt(alone * alone + moved * moved);
 }
 
 // The direct convolution with one of its shapes, a tile's chunks shared by `pieces` workgroups.
@@ -225,19 +245,19 @@ bool direct_setup(int N, int C, int H, int W, int K, int s, int YH, int YW, int 
         if (P > (long long)kDirectSlots * threads || P < 1) continue;
         if ((cross + 1) * image * 4 + bias * 4 >= 0x7fff0000LL || ((cross + 1) * K + 256) * oplane * 4 >= 0x7fff0000LL) continue;
         const int ns = (int)((P + threads - 1) / threads);
+        const double moved = direct_bytes(C, K, a.kt, a.npx, n * pieces, bw, (int)P, (int)row_px, lwp, s, sx) * (kNumCUs * 2100.0 / 8e6);
         // (no number of groups is below this)
         const double own = (double)ngroups / pieces;
-        if (best > 0.0 && best <= (0.5 * own * taps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) +
-                                   own * ns * 400 * (threads / 256.0) + 3000.0) * bw * nstrips / OW)
-            continue;
+        const double least = 0.5 * own * taps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) + own * ns * 400 * (threads / 256.0) + 3000.0;
+        if (best > 0.0 && best <= std::sqrt(least * least + moved * moved) * bw * nstrips / OW) continue;
         for (int G = 1; G <= ngroups; ++G) {
             if ((size_t)G * P * 48 > lds_max || G * taps + 1 > kDirectMaxUnits) break;
             const int nchunks = (ngroups + G - 1) / G, gl = ngroups - (nchunks - 1) * G, cpp = (nchunks + pieces - 1) / pieces;
             if ((pieces - 1) * cpp >= nchunks) continue;  // a piece without a chunk
             // cycles of a tile of the longest problem, as in direct_us
             const double steps = (double)(cpp - 1) * ((G * taps + 1) / 2 + sh.wk - 1) + ((pieces > 1 ? G : gl) * taps + 1) / 2 + sh.wk - 1;
-            const double cost = (steps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) + (pieces > 1 ? cpp * G : ngroups) * (double)ns * 400 * (threads / 256.0) + cpp * 3000.0) *
-                                bw * nstrips / OW;
+            const double busy = steps / sh.wk * sh.mb * 2 * 6 * 32 * (threads / 256.0) + (pieces > 1 ? cpp * G : ngroups) * (double)ns * 400 * (threads / 256.0) + cpp * 3000.0;
+            const double cost = std::sqrt(busy * busy + moved * moved) * bw * nstrips / OW;
             if (best > 0.0 && cost >= best) continue;
             best = cost;
             a.bw = bw; a.nstrips = nstrips; a.total_px = (int)total;

@@ -13,9 +13,9 @@ pytestmark = pytest.mark.gpu
 
 GRADIENT = [  # N, C, H, W, K, R, S, stride, pad; steps of a wave's sum, waves that share a tile
     (64, 30, 28, 28, 384, 11, 11, 1, 5),   # 736, 4
-    (8, 359, 33, 33, 214, 11, 11, 2, 5),   # 486, 1: phases of several lengths
     (256, 256, 14, 14, 256, 7, 7, 2, 3),   # 256, 1: tiles of 256 filters
-    (20, 313, 63, 68, 351, 5, 5, 3, 2),    # 88, 1: the longest phase only just long
+    (16, 247, 32, 30, 139, 5, 5, 2, 2),    # 81, 1: the longest phase only just long
+    (32, 123, 28, 25, 211, 3, 3, 1, 1),    # 123, 1
     (2, 206, 12, 14, 284, 9, 9, 2, 4),     # 113, 4
     (16, 289, 19, 9, 299, 9, 9, 2, 4),     # 121, 4: 64 filters a wave
     (16, 34, 19, 18, 193, 11, 11, 1, 5),   # 194, 8
@@ -23,7 +23,7 @@ GRADIENT = [  # N, C, H, W, K, R, S, stride, pad; steps of a wave's sum, waves t
 ]
 FORWARD = [
     (40, 18, 14, 14, 384, 9, 9, 1, 4),     # 122, 1
-    (16, 168, 19, 18, 288, 7, 7, 1, 3),    # 131, 4
+    (32, 308, 23, 21, 31, 5, 5, 1, 2),     # 122, 4
     (64, 128, 28, 28, 128, 3, 3, 1, 1),    # 72, 1: one level
 ]
 

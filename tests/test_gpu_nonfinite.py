@@ -88,7 +88,7 @@ def test_time_of_a_filter_gradient_that_is_not_finite(shape):
 # (shape, whether the forward pass and the data gradient take the direct convolution): every shape of its workgroup
 DIRECT = [
     ((32, 128, 56, 56, 256, 3, 3, 2, 1), (True, True)),    # 256 filters x 128 pixels, 128 x 128
-    ((20, 128, 30, 28, 130, 3, 3, 1, 1), (True, True)),    # four waves of 64 filters share a tile, 128 x 128
+    ((24, 117, 14, 22, 130, 3, 3, 1, 1), (True, True)),    # four waves of 64 filters share a tile
     ((1, 16, 32, 32, 16, 5, 5, 1, 2), (True, False)),      # four of 32
     ((5, 67, 35, 29, 93, 5, 5, 2, 2), (False, True)),
     ((46, 76, 8, 8, 18, 3, 3, 3, 0), (True, True)),        # eight, in pieces
