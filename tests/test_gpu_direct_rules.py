@@ -1,6 +1,6 @@
 """The planner's choice of the direct convolutions (csrc/direct.hip, csrc/wgrad_direct.hip): not behind the paths that they replace, on
 layers where it was by 1.05 to 2.0 -- maps that the planner cut into strips of one to three pixels, tiles of several lengths in step
-with the CUs."""
+with the CUs, and filter gradients of many channels."""
 import pytest
 import torch
 
@@ -12,6 +12,7 @@ FORWARD = [(49, 179, 37, 37, 218, 1, 1, 1, 0), (6, 25, 61, 61, 307, 3, 3, 1, 1),
            (105, 37, 52, 57, 21, 5, 3, 1, 2)]
 GRADIENT = [(9, 286, 56, 53, 37, 3, 3, 1, 1), (120, 40, 42, 42, 243, 1, 1, 1, 0), (60, 50, 38, 38, 193, 2, 2, 1, 1), (37, 258, 63, 68, 147, 5, 5, 2, 2),
             (88, 288, 41, 37, 179, 5, 5, 2, 2), (32, 128, 56, 56, 256, 3, 3, 2, 1)]
+FILTER = [(4, 341, 21, 26, 322, 3, 3, 1, 1), (6, 334, 61, 61, 83, 3, 7, 2, 0), (29, 174, 30, 30, 69, 2, 7, 1, 1), (6, 158, 18, 18, 336, 9, 9, 3, 4)]
 
 
 def _not_behind(calls):
@@ -86,3 +87,22 @@ def test_data_gradient(shape):
     finally:
         for p in plans:
             dwm.dwm_bwd_data_plan_destroy(p)
+
+
+@pytest.mark.parametrize("shape", FILTER)
+def test_filter_gradient(shape):
+    x, w, dy, st = _tensors(shape)
+    plans, kept, calls = [], [], []
+    try:
+        for path in (-1, 0):
+            p = dwm.dwm_bwd_filter_plan_create(*shape)
+            plans.append(p)
+            dwm.dwm_bwd_filter_set_variant(p, "path", path)
+            ws = _buffer(dwm.dwm_bwd_filter_workspace_bytes(p))
+            kept.append(ws)
+            dwm.dwm_bwd_filter_set_workspace(p, ws.data_ptr(), ws.numel())
+            calls.append(lambda p=p: dwm.dwm_conv_backward_filter(p, x.data_ptr(), dy.data_ptr(), w.data_ptr(), st))
+        _not_behind(calls)
+    finally:
+        for p in plans:
+            dwm.dwm_bwd_filter_plan_destroy(p)
