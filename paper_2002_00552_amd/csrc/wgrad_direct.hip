@@ -16,7 +16,7 @@
 // Operands are split as v * 2^16, sums multiplied by 2^-32, as in direct.hip; a sum that is not finite (infinities, NaN, values
 // from 2^112 on) is computed again in binary32: the workgroup that has one goes through its units a second time, the values
 // staged as they are in the same places, on fp32 MFMAs, one an image and two pixels, and replaces the sums that were not finite.  7x7 at
-// stride 2, 3 -> 64 channels, 64 224x224 images 132 us, with one infinity in x 249, NaN throughout 316 (each such tap summed by a
+// stride 2, 3 -> 64 channels, 64 224x224 images 122 us, with one infinity in x 242, NaN throughout 291 (each such tap summed by a
 // thread of its own 7500 and 16200).
 //
 // Bound by what a unit takes besides its MFMAs: splitting (7 vector instructions an element), the lines of dy that a patch's short
@@ -27,8 +27,6 @@
 // came from memory eight times), one offset for eight images (149 -> 137: 600 scalar instructions a unit fewer).
 // Errors against 64 bits are a third to a tenth of the transforms'.
 #include <hip/hip_runtime.h>
-
-#include <type_traits>
 
 #include "plan.hpp"
 #include "split.hpp"
@@ -45,17 +43,19 @@ __device__ __forceinline__ WdUnit wd_unit(const WdArgs& A, int u)
     return WdUnit{g, py * (16 >> A.lgw), px << A.lgw};
 }
 
-template <int MB, int NB, bool BANDS>
-__global__ __launch_bounds__(256, MB == 1 ? 3 : 2) void wgrad_direct_kernel(WdArgs A, const float* __restrict__ x, const float* __restrict__ dy, float* __restrict__ out)
+// All of workgroup `block`'s units; EXACT: in binary32, in the place of the sums that are not finite.  Returns whether one of the
+// workgroup's is not.
+template <int MB, int NB, bool BANDS, bool EXACT>
+__device__ __forceinline__ bool wd_pass(const WdArgs& A, const float* __restrict__ x, const float* __restrict__ dy, float* __restrict__ out, int tid, int block)
 {
     constexpr int KT = 32 * MB, CT = 32 * NB;
     constexpr uint32_t PITCH = KT * 48 + 16;  // bytes of a pixel's KT elements of dy, banks moved on by four words
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_w[];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), li = tid & 31, half = tid >> 5 & 1;
     // An XCD's units are a range of their own, which its pieces take in turn: patches side by side share lines of dy and x, and
     // are read at about the same time.  A piece's tiles, which read the same, are next to one another.
     // (Fewer than eight units: each is a piece, and its tiles go to all XCDs.)
-    const int ranges = A.nunits < 8 ? A.nunits : 8, range = (int)blockIdx.x % ranges, r0 = (int)blockIdx.x / ranges;
+    const int ranges = A.nunits < 8 ? A.nunits : 8, range = block % ranges, r0 = block / ranges;
     const int tile = r0 % A.ntiles, piece = r0 / A.ntiles * ranges + range;
     const int kt = tile % A.nkt, ct = tile / A.nkt;
     const int first = range * A.xunits, u0 = first + r0 / A.ntiles, u1 = min(first + A.xunits, A.nunits);
@@ -66,8 +66,8 @@ __global__ __launch_bounds__(256, MB == 1 ? 3 : 2) void wgrad_direct_kernel(WdAr
     floatx16 acc[MB][NB];
 
     // (EXACT: the binary32 values as they are, the last third of their place unused)
-    auto put = [&](auto exact, unsigned char* d, float (&v)[8], float scale, int images) {
-        if constexpr (decltype(exact)::value) {
+    auto put = [&](unsigned char* d, float (&v)[8], float scale, int images) {
+        if constexpr (EXACT) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = e < images ? v[e] : 0.f;
             *reinterpret_cast<pfloat4*>(d) = pfloat4{v[0], v[1], v[2], v[3]};
@@ -83,229 +83,227 @@ __global__ __launch_bounds__(256, MB == 1 ? 3 : 2) void wgrad_direct_kernel(WdAr
     };
     const uint32_t ohw = (uint32_t)(A.OH * A.OW);
 
-    // acc: all of the workgroup's units
-    auto multiply = [&](auto exact, int tid) {
-        constexpr bool EXACT = decltype(exact)::value;
-        const int li = tid & 31, half = tid >> 5 & 1;
-        uint32_t bo[NB];  // this lane's columns' taps in the staged patch
+    uint32_t bo[NB];  // this lane's columns' taps in the staged patch
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const int col = min(ct * CT + nb * 32 + li, A.cols - 1), c = A.div_rs.div(col), tap = col - c * RS, r = tap / A.S, q = tap - r * A.S;
-            bo[nb] = (uint32_t)((c - clo) * plane + r * A.pcols + q) * 48u;
-        }
+    for (int nb = 0; nb < NB; ++nb) {
+        const int col = min(ct * CT + nb * 32 + li, A.cols - 1), c = A.div_rs.div(col), tap = col - c * RS, r = tap / A.S, q = tap - r * A.S;
+        bo[nb] = (uint32_t)((c - clo) * plane + r * A.pcols + q) * 48u;
+    }
 #pragma unroll
-        for (int mi = 0; mi < MB; ++mi)
+    for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[mi][nb][e] = 0.f;
+            for (int e = 0; e < 16; ++e) acc[mi][nb][e] = 0.f;
 #pragma unroll 1
-        for (int u = u0; u < u1; u += A.ustep) {
-            const WdUnit un = wd_unit(A, u);
-            // ---- dy: filter k, pixel p of the patch (filters past the last: whatever follows; their sums are not stored) ----
-            float vd[2 * MB][8], vx[2][8];
-            const int p = tid & 15, ol = un.oh + (p >> A.lgw), ow = un.ow + (p & mask);
-            uint32_t off[2 * MB];
+    for (int u = u0; u < u1; u += A.ustep) {
+        const WdUnit un = wd_unit(A, u);
+        // ---- dy: filter k, pixel p of the patch (filters past the last: whatever follows; their sums are not stored) ----
+        float vd[2 * MB][8], vx[2][8];
+        const int p = tid & 15, ol = un.oh + (p >> A.lgw), ow = un.ow + (p & mask);
+        uint32_t off[2 * MB];
 #pragma unroll
-            for (int j = 0; j < 2 * MB; ++j) {
-                const int k = kt * KT + (tid >> 4) + 16 * j;
-                off[j] = k < A.K && ol < A.BH && ow < A.OW ? ((uint32_t)k * ohw + (uint32_t)(ol * A.OW + ow)) * 4u : 0x80000000u;
+        for (int j = 0; j < 2 * MB; ++j) {
+            const int k = kt * KT + (tid >> 4) + 16 * j;
+            off[j] = k < A.K && ol < A.BH && ow < A.OW ? ((uint32_t)k * ohw + (uint32_t)(ol * A.OW + ow)) * 4u : 0x80000000u;
+        }
+        const int n0 = un.g * 8;  // (without bands)
+        const __amdgpu_buffer_rsrc_t drs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dy) + (size_t)n0 * A.K * ohw, 0, 0x7ffffff0, 0x00020000);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if constexpr (BANDS) {
+                const int vi = un.g * 8 + e, n = A.div_nb.div(vi), oh0 = (vi - n * A.NB) * A.BH;
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<float*>(dy) + ((size_t)n * A.K * A.OH + oh0) * A.OW, 0, n < A.N ? 0x7ffffff0 : 0, 0x00020000);
+#pragma unroll
+                for (int j = 0; j < 2 * MB; ++j)
+                    vd[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, ol < A.OH - oh0 ? off[j] : 0x80000000u, 0, 0));
+            } else {
+                const uint32_t image = (uint32_t)(min(n0 + e, A.N - 1) - n0) * (A.K * ohw * 4u);
+#pragma unroll
+                for (int j = 0; j < 2 * MB; ++j) vd[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(drs, off[j], image, 0));
             }
-            const int n0 = un.g * 8;  // (without bands)
-            const __amdgpu_buffer_rsrc_t drs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dy) + (size_t)n0 * A.K * ohw, 0, 0x7ffffff0, 0x00020000);
+        }
+        // ---- x: the patch with the taps' margin, two pixels a turn ----
+        const int iw0 = A.s * un.ow - A.P, ih0 = A.s * un.oh - A.P;
+        const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(x) + ((long long)n0 * A.C * A.H + ih0) * A.W, 0, 0x7ffffff0, 0x00020000);
+        auto load_x = [&](int i0, float (&v)[2][8]) {
+            int row[2];
+            uint32_t at[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int i = i0 + 256 * j, c = A.div_plane.div(i), t = i - c * plane;
+                row[j] = A.div_pcols.div(t);
+                const int iw = iw0 + t - row[j] * A.pcols;
+                const bool ok = i < npix && (unsigned)iw < (unsigned)A.W && (BANDS || (unsigned)(ih0 + row[j]) < (unsigned)A.H);
+                at[j] = ok ? (uint32_t)(((clo + c) * A.H + row[j]) * A.W + iw) * 4u : 0x80000000u;
+            }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 if constexpr (BANDS) {
-                    const int vi = un.g * 8 + e, n = A.div_nb.div(vi), oh0 = (vi - n * A.NB) * A.BH;
+                    const int vi = un.g * 8 + e, n = A.div_nb.div(vi), top = ih0 + A.s * (vi - n * A.NB) * A.BH;
+                    // (the first row may lie before the image: what would be read there is out of range)
                     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                        const_cast<float*>(dy) + ((size_t)n * A.K * A.OH + oh0) * A.OW, 0, n < A.N ? 0x7ffffff0 : 0, 0x00020000);
+                        const_cast<float*>(x) + ((long long)n * A.C * A.H + top) * A.W, 0, n < A.N ? 0x7ffffff0 : 0, 0x00020000);
 #pragma unroll
-                    for (int j = 0; j < 2 * MB; ++j)
-                        vd[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, ol < A.OH - oh0 ? off[j] : 0x80000000u, 0, 0));
+                    for (int j = 0; j < 2; ++j)
+                        v[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                                rs, (unsigned)(top + row[j]) < (unsigned)A.H ? at[j] : 0x80000000u, 0, 0));
                 } else {
-                    const uint32_t image = (uint32_t)(min(n0 + e, A.N - 1) - n0) * (A.K * ohw * 4u);
+                    const uint32_t image = (uint32_t)(min(n0 + e, A.N - 1) - n0) * (uint32_t)(A.C * A.H * A.W * 4);
 #pragma unroll
-                    for (int j = 0; j < 2 * MB; ++j) vd[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(drs, off[j], image, 0));
+                    for (int j = 0; j < 2; ++j) v[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrs, at[j], image, 0));
                 }
             }
-            // ---- x: the patch with the taps' margin, two pixels a turn ----
-            const int iw0 = A.s * un.ow - A.P, ih0 = A.s * un.oh - A.P;
-            const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<float*>(x) + ((long long)n0 * A.C * A.H + ih0) * A.W, 0, 0x7ffffff0, 0x00020000);
-            auto load_x = [&](int i0, float (&v)[2][8]) {
-                int row[2];
-                uint32_t at[2];
+        };
+        load_x(tid, vx);
+        // (the second steps' pixels with the sign turned, see below)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int i = i0 + 256 * j, c = A.div_plane.div(i), t = i - c * plane;
-                    row[j] = A.div_pcols.div(t);
-                    const int iw = iw0 + t - row[j] * A.pcols;
-                    const bool ok = i < npix && (unsigned)iw < (unsigned)A.W && (BANDS || (unsigned)(ih0 + row[j]) < (unsigned)A.H);
-                    at[j] = ok ? (uint32_t)(((clo + c) * A.H + row[j]) * A.W + iw) * 4u : 0x80000000u;
-                }
+        for (int j = 0; j < 2 * MB; ++j)
+            put(smem_w + (uint32_t)p * PITCH + (uint32_t)((tid >> 4) + 16 * j) * 48u, vd[j], p < 8 ? kSplitScale : -kSplitScale, BANDS ? 8 : A.N - n0);
+#pragma unroll 1
+        for (int i0 = tid;;) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    if constexpr (BANDS) {
-                        const int vi = un.g * 8 + e, n = A.div_nb.div(vi), top = ih0 + A.s * (vi - n * A.NB) * A.BH;
-                        // (the first row may lie before the image: what would be read there is out of range)
-                        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                            const_cast<float*>(x) + ((long long)n * A.C * A.H + top) * A.W, 0, n < A.N ? 0x7ffffff0 : 0, 0x00020000);
+            for (int j = 0; j < 2; ++j)
+                if (i0 + 256 * j < npix) put(sx + (uint32_t)(i0 + 256 * j) * 48u, vx[j], kSplitScale, EXACT && !BANDS ? A.N - n0 : 8);
+            i0 += 512;
+            if (i0 - tid >= npix) break;
+            load_x(i0, vx);
+        }
+        __syncthreads();
+        // ---- products: this wave's two steps ----
+        auto pixel_of = [&](int q) { return smem_w + (uint32_t)q * PITCH + (uint32_t)li * 48u; };
+        auto patch_of = [&](int q) { return sx + (uint32_t)((q >> A.lgw) * A.s * A.pcols + (q & mask) * A.s) * 48u; };
+        if constexpr (EXACT) {
+            // one MFMA for each image, two pixels deep.  (Where there is no output pixel an infinity of x meets no zero of dy.)
+            auto eight = [](const unsigned char* from, float (&v)[8]) {
+                const pfloat4 lo = *reinterpret_cast<const pfloat4*>(from), hi = *reinterpret_cast<const pfloat4*>(from + 16);
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            v[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                                    rs, (unsigned)(top + row[j]) < (unsigned)A.H ? at[j] : 0x80000000u, 0, 0));
-                    } else {
-                        const uint32_t image = (uint32_t)(min(n0 + e, A.N - 1) - n0) * (uint32_t)(A.C * A.H * A.W * 4);
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) v[j][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xrs, at[j], image, 0));
-                    }
-                }
+                for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[e + 4] = hi[e]; }
             };
-            load_x(tid, vx);
-            // (the second steps' pixels with the sign turned, see below)
-#pragma unroll
-            for (int j = 0; j < 2 * MB; ++j)
-                put(exact, smem_w + (uint32_t)p * PITCH + (uint32_t)((tid >> 4) + 16 * j) * 48u, vd[j], p < 8 ? kSplitScale : -kSplitScale, BANDS ? 8 : A.N - n0);
 #pragma unroll 1
-            for (int i0 = tid;;) {
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    if (i0 + 256 * j < npix) put(exact, sx + (uint32_t)(i0 + 256 * j) * 48u, vx[j], kSplitScale, EXACT && !BANDS ? A.N - n0 : 8);
-                i0 += 512;
-                if (i0 - tid >= npix) break;
-                load_x(i0, vx);
-            }
-            __syncthreads();
-            // ---- products: this wave's two steps ----
-            auto pixel_of = [&](int q) { return smem_w + (uint32_t)q * PITCH + (uint32_t)li * 48u; };
-            auto patch_of = [&](int q) { return sx + (uint32_t)((q >> A.lgw) * A.s * A.pcols + (q & mask) * A.s) * 48u; };
-            if constexpr (EXACT) {
-                // one MFMA for each image, two pixels deep.  (Where there is no output pixel an infinity of x meets no zero of dy.)
-                auto eight = [](const unsigned char* from, float (&v)[8]) {
-                    const pfloat4 lo = *reinterpret_cast<const pfloat4*>(from), hi = *reinterpret_cast<const pfloat4*>(from + 16);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) { v[e] = lo[e]; v[e + 4] = hi[e]; }
-                };
-#pragma unroll 1
-                for (int t = 0; t < 2; ++t) {
-                    const int q = 2 * (wave + 4 * t) + half, oq = un.oh + (q >> A.lgw);
-                    uint32_t in = 0;
-#pragma unroll 1
-                    for (int e = 0; e < 8; ++e) {
-                        const int vi = un.g * 8 + e, oh0 = BANDS ? (vi - A.div_nb.div(vi) * A.NB) * A.BH : 0;
-                        in |= (uint32_t)(oq < A.BH && oq < A.OH - oh0 && un.ow + (q & mask) < A.OW) << e;
-                    }
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        float b[8];
-                        eight(patch_of(q) + bo[nb], b);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) b[e] = in >> e & 1 ? b[e] : 0.f;
-#pragma unroll
-                        for (int mi = 0; mi < MB; ++mi) {
-                            float a[8];
-                            eight(pixel_of(q) + mi * 32 * 48, a);
-                            floatx16 now;
-#pragma unroll
-                            for (int e = 0; e < 16; ++e) now[e] = 0.f;
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) now = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], now, 0, 0, 0);
-                            acc[mi][nb] += now;
-                            __builtin_amdgcn_sched_barrier(0);  // (registers: what the other products take is not exceeded)
-                        }
-                    }
-                }
-                __syncthreads();
-                continue;
-            }
-#pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const int q = 2 * (wave + 4 * t) + half;
-                const unsigned char* pa = pixel_of(q);
-                const unsigned char* pb = patch_of(q);
-                bf16x8 a[MB][3];
-#pragma unroll
-                for (int mi = 0; mi < MB; ++mi)
-#pragma unroll
-                    for (int w = 0; w < 3; ++w) a[mi][w] = *reinterpret_cast<const bf16x8*>(pa + mi * 32 * 48 + w * 16);
+                const int q = 2 * (wave + 4 * t) + half, oq = un.oh + (q >> A.lgw);
+                uint32_t in = 0;
+#pragma unroll 1
+                for (int e = 0; e < 8; ++e) {
+                    const int vi = un.g * 8 + e, oh0 = BANDS ? (vi - A.div_nb.div(vi) * A.NB) * A.BH : 0;
+                    in |= (uint32_t)(oq < A.BH && oq < A.OH - oh0 && un.ow + (q & mask) < A.OW) << e;
+                }
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    bf16x8 b[3];
+                    float b[8];
+                    eight(patch_of(q) + bo[nb], b);
 #pragma unroll
-                    for (int w = 0; w < 3; ++w) b[w] = *reinterpret_cast<const bf16x8*>(pb + bo[nb] + w * 16);
-                    // A step's products by themselves: one rounding at the sums' size, not six.  These MFMAs round down, which over the
-                    // 800 000 pixels of a first layer is 2e-6 of a sum: of two steps one is multiplied with the sign turned.
-                    constexpr int M = MB * NB < 10 ? MB : 1;  // (both chains at once where registers allow)
+                    for (int e = 0; e < 8; ++e) b[e] = in >> e & 1 ? b[e] : 0.f;
 #pragma unroll
-                    for (int m0 = 0; m0 < MB; m0 += M) {
-                        floatx16 now[M];
+                    for (int mi = 0; mi < MB; ++mi) {
+                        float a[8];
+                        eight(pixel_of(q) + mi * 32 * 48, a);
+                        floatx16 now;
 #pragma unroll
-                        for (int mi = 0; mi < M; ++mi)
+                        for (int e = 0; e < 16; ++e) now[e] = 0.f;
 #pragma unroll
-                            for (int e = 0; e < 16; ++e) now[mi][e] = 0.f;
-#pragma unroll
-                        for (int term = 0; term < 6; ++term) {
-                            constexpr int wa[6] = {2, 0, 1, 1, 0, 0}, wb[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-                            for (int mi = 0; mi < M; ++mi)
-                                now[mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m0 + mi][wa[term]], b[wb[term]], now[mi], 0, 0, 0);
-                        }
-#pragma unroll
-                        for (int mi = 0; mi < M; ++mi) acc[m0 + mi][nb] += t == 0 ? now[mi] : -now[mi];
+                        for (int e = 0; e < 8; ++e) now = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], now, 0, 0, 0);
+                        acc[mi][nb] += now;
+                        __builtin_amdgcn_sched_barrier(0);  // (registers: what the other products take is not exceeded)
                     }
                 }
             }
             __syncthreads();
+            continue;
         }
-    };
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int q = 2 * (wave + 4 * t) + half;
+            const unsigned char* pa = pixel_of(q);
+            const unsigned char* pb = patch_of(q);
+            bf16x8 a[MB][3];
+#pragma unroll
+            for (int mi = 0; mi < MB; ++mi)
+#pragma unroll
+                for (int w = 0; w < 3; ++w) a[mi][w] = *reinterpret_cast<const bf16x8*>(pa + mi * 32 * 48 + w * 16);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                bf16x8 b[3];
+#pragma unroll
+                for (int w = 0; w < 3; ++w) b[w] = *reinterpret_cast<const bf16x8*>(pb + bo[nb] + w * 16);
+                // A step's products by themselves: one rounding at the sums' size, not six.  These MFMAs round down, which over the
+                // 800 000 pixels of a first layer is 2e-6 of a sum: of two steps one is multiplied with the sign turned.
+                constexpr int M = MB * NB < 10 ? MB : 1;  // (both chains at once where registers allow)
+#pragma unroll
+                for (int m0 = 0; m0 < MB; m0 += M) {
+                    floatx16 now[M];
+#pragma unroll
+                    for (int mi = 0; mi < M; ++mi)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) now[mi][e] = 0.f;
+#pragma unroll
+                    for (int term = 0; term < 6; ++term) {
+                        constexpr int wa[6] = {2, 0, 1, 1, 0, 0}, wb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+                        for (int mi = 0; mi < M; ++mi)
+                            now[mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m0 + mi][wa[term]], b[wb[term]], now[mi], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int mi = 0; mi < M; ++mi) acc[m0 + mi][nb] += t == 0 ? now[mi] : -now[mi];
+                }
+            }
+        }
+        __syncthreads();
+    }
 
     // ---- the four waves' sums, a block of 32 x 32 at a time (EXACT: in the place of those that were not finite) ----
     float* sum = reinterpret_cast<float*>(smem_w);
     float* const mine = out + (size_t)piece * A.stride;
     auto finite = [](float v) { return fabsf(v) <= 3.402823466e38f; };
-    bool again = false;
-    auto store = [&](auto exact, int tid) {
-        constexpr bool EXACT = decltype(exact)::value;
-        const int lane = tid & 63, li = lane & 31, half = lane >> 5;
+    int* const lost = reinterpret_cast<int*>(smem_w) + 4096;  // one of the workgroup's was not (behind the waves' sums, 16 KB of at least 24)
+    asm volatile("" : "+v"(tid));  // (where a thread's sums go is not worked out before the units)
+    const int lane = tid & 63;
+    if (!EXACT && tid == 0) *lost = 0;
 #pragma unroll
-        for (int mi = 0; mi < MB; ++mi)
+    for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
+        for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) sum[wave * 1024 + e * 64 + lane] = acc[mi][nb][e] * (EXACT ? 1.f : 1.f / kSplitScale / kSplitScale);
-                __syncthreads();
+            for (int e = 0; e < 16; ++e) sum[wave * 1024 + e * 64 + lane] = acc[mi][nb][e] * (EXACT ? 1.f : 1.f / kSplitScale / kSplitScale);
+            __syncthreads();
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int at = tid + 256 * i, e = at >> 6;
-                    const float v = (sum[at] + sum[1024 + at]) + (sum[2048 + at] + sum[3072 + at]);
-                    const int k = kt * KT + mi * 32 + 8 * (e >> 2) + (e & 3) + 4 * half, col = ct * CT + nb * 32 + li;
-                    if (k < A.K && col < A.cols) {
-                        float* to = mine + (size_t)k * A.cols + col;
-                        if (!EXACT || !finite(*to)) *to = v;
-                        again |= !finite(v);
-                    }
+            for (int i = 0; i < 4; ++i) {
+                const int at = tid + 256 * i, e = at >> 6;
+                const float v = (sum[at] + sum[1024 + at]) + (sum[2048 + at] + sum[3072 + at]);
+                const int k = kt * KT + mi * 32 + 8 * (e >> 2) + (e & 3) + 4 * (lane >> 5), col = ct * CT + nb * 32 + (lane & 31);
+                if (k < A.K && col < A.cols) {
+                    float* to = mine + (size_t)k * A.cols + col;
+                    if (!EXACT || !finite(*to)) *to = v;
+                    if (!EXACT && !finite(v)) *lost = 1;
                 }
-                __syncthreads();
             }
-    };
-    // (nothing that depends on the thread is kept in registers from one pass to another)
-    auto thread = [] {
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        return tid;
-    };
-    multiply(std::false_type{}, thread());
-    store(std::false_type{}, thread());
-    // any thread's: the workgroup's
-    int* lost = reinterpret_cast<int*>(smem_w);
-    if (threadIdx.x == 0) *lost = 0;
+            __syncthreads();
+        }
+    return *lost != 0;
+}
+
+struct WdCall {  // the kernel's arguments
+    WdArgs A;
+    const float *x, *dy;
+    float* out;
+};
+
+template <int MB, int NB, bool BANDS>
+__global__ __launch_bounds__(256, MB == 1 ? 3 : 2) void wgrad_direct_kernel(WdArgs A, const float* __restrict__ x, const float* __restrict__ dy, float* __restrict__ out)
+{
+    int block = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (__builtin_expect(!wd_pass<MB, NB, BANDS, false>(A, x, dy, out, threadIdx.x, block), 1)) return;
+    // (nothing is kept in vector registers from the first pass to this one, not even the thread's number, nor are the arguments)
     __syncthreads();
-    if (again) *lost = 1;
-    __syncthreads();
-    if (__builtin_expect(*lost == 0, 1)) return;
-    __syncthreads();
-    multiply(std::true_type{}, thread());
-    store(std::true_type{}, thread());
+    typedef const __attribute__((address_space(4))) WdCall Args;
+    Args* call = (Args*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(call), "+s"(block), "+s"(wave));
+    const WdCall& c = *(const WdCall*)call;
+    const int tid = wave * 64 + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));
+    wd_pass<MB, NB, BANDS, true>(c.A, c.x, c.dy, c.out, tid, block);
 }
 
 // dw = the pieces' sums, in order: a thread four neighbours of every 16th piece
