@@ -345,8 +345,8 @@ static void setup_batch(dwm_bwd_data_plan& bp)
 }
 
 // The time (us) of the sub-convolutions by the method's transforms (what writes zeros left out): contracted in one launch, behind one
-// input transform (350 measured, rms of the logarithm 0.11) or one for each, a 32-step chunk of a tile 0.55 to 1 us on its CU, V written
-// and read; or one after the other.
+// input transform (711 measured, rms of the logarithm 0.13) or one for each, a 32-step chunk of a tile 0.55 to 1 us on its CU, V written
+// and read; or one after the other (1002 measured, 0.19).
 static double subconv_us(const dwm_bwd_data_plan& bp)
 {
     double n = 0.0, alone = 1.0, chunks = 0.0;
@@ -364,9 +364,9 @@ static double subconv_us(const dwm_bwd_data_plan& bp)
 }
 
 // All phases that a tap reaches as one direct convolution (direct.hip), where its model and its filter's copy (0.6 us a MB, and a launch
-// where it is not written with the others) come to less than 0.85 of the sub-convolutions' time, 0.75 where waves share its tiles.  Of 875
-// layers drawn with strides 2 to 4 (up to 150 GFLOP) it takes 698, at 0.46 of the time in the mean of all, the copy included, none slower
-// (1.03 at worst).  At 0.93 of a rougher estimate one in twenty was, by up to 1.65 (5x5, 258 <- 147 channels, 37 images of 63x68).
+// where it is not written with the others) come to less than 0.85 of the sub-convolutions' time.  Of 1780 layers drawn with strides 2
+// to 4 (up to 150 GFLOP) it takes 1506, at 0.45 of the time in the mean of all, the copy included, nine of them slower by 3 % or
+// more (1.13 at most).  At 0.93 of a rougher estimate one in twenty was, by up to 1.65 (5x5, 258 <- 147 channels, 37 images of 63x68).
 // Nine input transforms of stride 3, 76 <- 18 channels, 46 images of 8x8, 180 -> 7 us; 5x5 at stride 2, 67 <- 93 channels, five 35x29 images
 // 30 -> 14; 7x7 at stride 2, 256 <- 256 channels, 256 14x14 images 603 -> 456; 3x3 at stride 2, 128 <- 256, 32 56x56 images 136 -> 132.
 static void setup_direct(dwm_bwd_data_plan& bp)
@@ -385,8 +385,7 @@ static void setup_direct(dwm_bwd_data_plan& bp)
     std::stable_sort(p.begin(), p.end(), [](const DirectProb& a, const DirectProb& b) { return a.R * a.S > b.R * b.S; });
     DirectArgs a;
     if (!direct_choose(bp.N, bp.K, bp.OH, bp.OW, bp.C, 1, bp.H, bp.W, bp.s, bp.s, p.data(), (int)p.size(), &a)) return;
-    const double line = kDirectShapes[a.shape].wk == 1 ? 0.85 : 0.75;
-    if (a.us + 2.4e-6 * a.filter_floats() + (bp.filter_batched ? 1.0 : 4.5) >= line * subconv_us(bp)) return;
+    if (a.us + 2.4e-6 * a.filter_floats() + (bp.filter_batched ? 1.0 : 4.5) >= 0.85 * subconv_us(bp)) return;
     dwm_plan* m = new (std::nothrow) dwm_plan;
     if (!m) return;
     std::memset(m, 0, sizeof(*m));

@@ -2,6 +2,8 @@
 // (paper Sec. 4.1: eq. 12 groups taps by index modulo the stride, eq. 8 cuts each group
 // into consecutive runs of three) plus the bookkeeping that lays the Winograd-domain
 // planes out in memory.  Pure integer logic; no GPU call is made in this file.
+#include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -175,12 +177,36 @@ static double fp32_contract_us(const dwm_plan& p)
            0.45 * p.planes.n / (g.sk_f > 1 ? g.sk_f : 1) + (g.sk_f > 1 ? 1.7 * g.sk_f : 0.0) + 9.0;
 }
 
-// Of layers that fused.hip can run: 369 measured, rms of the logarithm 0.33.
+// The single kernel's time (us): by how many rounds of the chip its workgroups take, a wave's MFMAs, its steps, what a class takes once for
+// a slice, and the staging of the block's rows by loads of 64 columns; beside it what that moves, a piece of a row with 64 bytes more
+// than it holds (a block may be one tile wide, and then the rows are strided), at 8 TB/s read and 3 written.  The two combine as
+// a right angle.  482 measured, rms of the logarithm 0.13.
+static double fused_us(const dwm_plan& p)
+{
+    const DevPlan& d = p.d;
+    const FusedArgs& f = p.fused;
+    const double wgs = (double)d.N * f.nbh * f.nbw * f.nkw, slices = (double)f.slices_per_wg / (f.share ? 4 : 1);
+    double mfmas = 0.0, steps = 0.0;
+    for (int c = 0; c < f.nfc; ++c)
+        for (int i = 0; i < f.fc[c].nsteps; ++i, ++steps) {
+            const int t = f.step_type[f.fc[c].step0 + i];
+            mfmas += 2.0 * (t / 4 + 1) * (t % 4 + 1);
+        }
+    auto rounds = [](double n) { return n < 3.0 ? std::max(1.0, std::ceil(n)) : n + 0.5; };
+    const double all = rounds(wgs / kNumCUs), pairs = rounds(wgs / kNumCUs / (2 * f.lds_bytes <= 160 * 1024 ? 2 : 1));
+    const double rows = (double)d.C * f.nrows, loads = rows * ((f.lw_in + 63) / 64);
+    const double busy = 6.4 + 1.06 * all * mfmas * slices * 32.0 / 2100.0 + pairs * (0.208 * steps * slices + 0.96 * f.slices_per_wg * f.nfc) +
+                        loads * (0.0108 * pairs + 0.0072 * all);
+    const double w = std::min(2 * f.BW, d.OW), out = (double)d.N * d.K * d.OH * d.OW;
+    const double moved = wgs * rows * (64.0 + 4.0 * (f.lw_in - 1)) / 8e6 + out / w * std::min(64.0 + 4.0 * (w - 1) * d.om.sx, 64.0 * w) / 3e6;
+    return std::sqrt(busy * busy + moved * moved);
+}
+
 double transforms_us(const dwm_plan& p)
 {
     const DevPlan& d = p.d;
-    const double x_bytes = 4.0 * d.N * d.C * d.H * d.W, y_bytes = 4.0 * d.N * d.K * d.OH * d.OW;
-    if (p.fused_ok) return 13.4 + p.info.winograd_flops / d.K * ((d.K + 31) / 32 * 32) / 67e6 + (x_bytes + y_bytes) / 2.65e6;
+    if (p.fused_ok) return fused_us(p);
+    const double x_bytes = 4.0 * d.N * d.C * d.H * d.W;
     return 5.7 + (p.split_ok ? p.split_us : 1.03 * fp32_contract_us(p)) + ((double)p.v_floats * 4.0 + x_bytes) / 4.31e6;
 }
 
@@ -249,11 +275,12 @@ bool split_geometry(const dwm_plan& p, ContractGeometry* out, double* us)
 extern "C" {
 
 // Whether the direct convolution (direct.hip) takes the layer, beside what it has: where its model has it below 0.85 of the time of
-// the path it would replace (transforms_us: the fp32 contraction behind an input transform, or fused.hip's single kernel), 0.72 where waves
-// share its tiles, which is modelled less closely.  The lines lie where measured calls begin to be slower.  Of 1385 drawn passes on the
-// contraction (forward, and data gradients at stride 1; up to 150 GFLOP) it takes 1076, at 0.57 of the time in the mean of all, two of them
-// slower (1.06 at most); of 482 on the single kernel 384, at 0.59, two of them slower (1.14).  At 0.85 for all, by a model that did not
-// count what narrow strips move (setup.cpp), one in forty was slower, by up to 2.0.  Measured, before -> now (us): 5x5,
+// the path it would replace (transforms_us: the fp32 contraction behind an input transform, or fused.hip's single kernel), 0.80 of the
+// contraction's where waves share its tiles, which is modelled less closely.  The lines lie where measured calls begin to be slower: of
+// 1385 drawn passes on the contraction (forward, and data gradients at stride 1; up to 150 GFLOP) it takes 1178, at 0.57 of the time in the
+// mean of all, nine of them slower by 3 % or more (1.18 at most; at 0.85 for all 22); of 482 on the single kernel 436, at 0.55, three of them slower
+// (1.10 at most).  At 0.85 by a model that did not count what narrow strips move (setup.cpp) one in forty was slower, by up to 2.0;
+// and by one that did not count it for the single kernel, some stayed there for up to four times as long.  Measured, before -> now (us): 5x5,
 // 16 -> 16 channels, one 32x32 image 12.1 -> 7.5; 3x3 at stride 2, 128 -> 256, 32 56x56 images 122 -> 86; 3x3, 128 -> 128, 64
 // 28x28 images 89 -> 82; 3x3, 40 -> 61, 78 images of 17x21 40.5 -> 13.3; 5x1, 56 -> 27, 36 images of 32x38 60 -> 19.6.
 // From 16 channels: below, a step's groups of eight are half empty, and
@@ -279,7 +306,7 @@ static bool direct_ahead(dwm_plan& p)
                             p.fused_ok || !whole ? 0 : p.active().partial_floats))
         return false;
     if (p.split_ok) return p.direct.us + 2.4e-6 * p.direct.filter_floats() < 0.70 * us;
-    return p.direct.us < (dwm::kDirectShapes[p.direct.shape].wk == 1 ? 0.85 : 0.72) * us;
+    return p.direct.us < (p.fused_ok || dwm::kDirectShapes[p.direct.shape].wk == 1 ? 0.85 : 0.80) * us;
 }
 
 // One planning pass with the given splitting policy; *out is set on DWM_OK only.

@@ -22,7 +22,7 @@ GRADIENT = [  # N, C, H, W, K, R, S, stride, pad; steps of a wave's sum, waves t
     (16, 47, 9, 18, 340, 11, 11, 1, 5),    # 115, 8, in three pieces
 ]
 FORWARD = [
-    (40, 18, 14, 14, 384, 9, 9, 1, 4),     # 122, 1
+    (40, 24, 14, 14, 384, 9, 9, 1, 4),     # 122, 1
     (32, 308, 23, 21, 31, 5, 5, 1, 2),     # 122, 4
     (64, 128, 28, 28, 128, 3, 3, 1, 1),    # 72, 1: one level
 ]
