@@ -173,7 +173,7 @@ def bench_backward_data(args, L, x, w):
 
 def bench_backward_filter(args, L, x, w):
     """A step = one dwm_conv_backward_filter (input transform of x, A dY A^T, the per-plane GEMMs over
-    the tiles, G^T (.) G) on resident buffers."""
+    the tiles, G^T (.) G; or the plain sum over pixels, where the planner takes it) on resident buffers."""
     import numpy as np
     import torch
 
@@ -205,14 +205,17 @@ def bench_backward_filter(args, L, x, w):
     plain = dwm.dwm_bwd_filter_kernel(plan) == 2
     peak = PEAK_SPLIT_F32 if split or plain else PEAK_MFMA_F32
     flops = info.direct_flops if plain else info.winograd_flops
-    kernel = "wgrad_direct_kernel" if plain else "wgrad_split_kernel" if split else "wgrad_gemm_kernel"
+    few = dwm.dwm_bwd_filter_kernel(plan) == 1
+    kernel = "wgrad_direct_kernel" if plain else "wgrad_small_all_kernel" if few else "wgrad_split_kernel" if split else "wgrad_gemm_kernel"
     out = {
         "metric": "direct-conv-equivalent TFLOP/s of the DWM filter gradient (fp32, 1 GPU); MSE vs FP64 definition",
         "value": info.direct_flops / dt / 1e12, "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": dt * 1e3, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
-        "config": {"workload": L.name + "_backward_filter", "planes": info.n_planes, "tiles": info.n_tiles,
-                   "splits": info.splits, "direct_GFLOP": info.direct_flops / 1e9,
+        "config": {"workload": L.name + "_backward_filter",
+                   "path": "direct convolution on split operands" if plain else "short reductions" if few else "GEMM per plane",
+                   # (of the transforms, whether or not they are what runs)
+                   "planes": info.n_planes, "tiles": info.n_tiles, "splits": info.splits, "direct_GFLOP": info.direct_flops / 1e9,
                    "winograd_GFLOP": info.winograd_flops / 1e9, "workspace_MB": ws.numel() * 4 / 1e6},
         "roofline": {"kernel": kernel + " (whole step timed)", "bound": "mfma",
                      "achieved": flops / dt / 1e12, "peak": peak, "unit": "TFLOP/s", "frac": flops / dt / 1e12 / peak, "traffic": None},

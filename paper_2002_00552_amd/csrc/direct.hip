@@ -3,7 +3,7 @@
 // Why: a layer of few tiles spends its time on launches that wait for one another (input transforms -- one for each phase
 // of a strided layer's data gradient --, contraction, sum of pieces), each with its own start, first loads and last stores.
 // Six bfloat16 products of split operands (contract_split.hip) cost so little there that the taps of the plain convolution,
-// one and a half to two and a quarter times the method's multiplications, are done before the transformed input were written.
+// 1.4 to 2.25 times the method's multiplications, are done before the transformed input were written.
 //
 // What it does: an implicit GEMM of [filters] x [taps, channels] x [output pixels].  x is staged a chunk of channels at a
 // time in LDS, split into its three bfloat16 parts once per pixel and channel (6.5 vector instructions an element, shared by
@@ -27,9 +27,11 @@
 // stride 2, 256 channels, 256 14x14 images 468 -> 473 us, others within 1 %; folds every 4 steps 487 us and no better, every 16 as fast
 // and less exact with operands of zero mean (each small product rounds at the first level's size, so that has to stay short).
 //
-// Bound by latency where the chip is not full (first loads, the barrier of each chunk), and where it is by power: the clock
-// falls from 2.1 to 1.6 GHz with bf16 MFMAs on all CUs, 0.9 to 1.2 PFLOP/s of them.  Whole training steps with it as the
-// data gradient, before -> now: 5x5 at stride 2, 67 -> 93 channels, five 35x29 images 111 -> 101 us; drawn strided layers
+// Bound by latency where the chip is not full (first loads, the barrier of each chunk), and where it is by CUs without a tile and by what
+// does not run beside the MFMAs (a chunk's first loads and splitting, between barriers): at 2.2 GHz MFMAs are busy for 0.40 of all cycles and
+// CUs for 0.66 of 3x3 at stride 2, 128 -> 256 channels, 32 56x56 images (196 tiles), 0.44 and 0.71 of 3x3, 128 -> 128, 64 28x28 images (392
+// tiles of half the size), 0.44 and 0.59 of the gradient of 7x7 at stride 2, 256 channels, 256 14x14 images.  As a
+// data gradient, before -> now: 5x5 at stride 2, 67 -> 93 channels, five 35x29 images, the training step 111 -> 101 us; drawn strided layers
 // 173 -> 136, 205 -> 105, 248 -> 129, 208 -> 180.  Errors against 64 bits, operands of zero mean: 1.2 to 5 times below those of the transforms.
 // Forward passes: plan.cpp, at the rule that takes it.  As that of a large first layer it loses (7x7 at stride 2 141 -> 168, 11x11 at stride 4 188 -> 260 us).
 #include <hip/hip_runtime.h>
