@@ -922,7 +922,7 @@ dwm_status_t dwm_bwd_filter_plan_create(dwm_bwd_filter_plan_t** out, int N, int 
     // 269 of 277 that the form for few channels runs, 1131 of 1701 on the fp32 GEMM and 54 of 802 on the bfloat16 one, at 0.49, 0.59 and 0.97
     // of the transforms' time in the mean of all; eight of them, on the GEMM, are slower by 3 % or more (1.16 at most).  At 0.82 the
     // bfloat16 one's line had fourteen, by up to 1.27.  7x7 at stride 2, 3 -> 64 channels, 64 224x224 images
-    // 322 -> 135 us; 5x5 at stride 2, 67 -> 93, five 35x29 images 40 -> 20; 3x3, 70 -> 34, one 8x8 image 22 -> 5.5.  It stays
+    // 322 -> 122 us; 5x5 at stride 2, 67 -> 93, five 35x29 images 40 -> 20; 3x3, 70 -> 34, one 8x8 image 22 -> 5.5.  It stays
     // with the transforms where channels and filters are many and the map is not small: 3x3, 128 -> 128, 64 28x28 images 125
     // against 150; 7x7, 256 -> 256, 32 28x28 images 614 against 950.)
     bp->no_direct = false;

@@ -21,7 +21,7 @@
 //
 // Bound by what a unit takes besides its MFMAs: splitting (7 vector instructions an element), the lines of dy that a patch's short
 // rows touch, and the latency of both, which only the other workgroup on the CU covers.  Measured, whole gradient, transforms
-// -> here (us): 7x7 at stride 2, 3 -> 64 channels, 64 224x224 images 322 -> 135 (0.67 PFLOP/s of bf16 products; dy alone takes 40
+// -> here (us): 7x7 at stride 2, 3 -> 64 channels, 64 224x224 images 322 -> 122 (0.74 PFLOP/s of bf16 products; dy alone takes 40
 // at 5.2 TB/s); 5x5 at stride 2, 3 -> 31, ten 151x147 images 91 -> 19; 5x5, 16 -> 16, one 32x32 image 27 -> 7.9.  What it
 // took: patches side by side in the hands of one XCD at a time (282 -> 148: with pieces of consecutive units every line of dy
 // came from memory eight times), one offset for eight images (149 -> 137: 600 scalar instructions a unit fewer).
