@@ -365,8 +365,8 @@ static double subconv_us(const dwm_bwd_data_plan& bp)
 
 // All phases that a tap reaches as one direct convolution (direct.hip), where its model and its filter's copy (0.6 us a MB, and a launch
 // where it is not written with the others) come to less than 0.85 of the sub-convolutions' time.  Of 1780 layers drawn with strides 2
-// to 4 (up to 150 GFLOP) it takes 1506, at 0.45 of the time in the mean of all, the copy included, nine of them slower by 3 % or
-// more (1.13 at most).  At 0.93 of a rougher estimate one in twenty was, by up to 1.65 (5x5, 258 <- 147 channels, 37 images of 63x68).
+// to 4 (up to 150 GFLOP) it takes 1585, at 0.45 of the time in the mean of all, the copy included, 14 of them slower by 3 % or
+// more (1.23 at most).  At 0.93 of a rougher estimate one in twenty was, by up to 1.65 (5x5, 258 <- 147 channels, 37 images of 63x68).
 // Nine input transforms of stride 3, 76 <- 18 channels, 46 images of 8x8, 180 -> 7 us; 5x5 at stride 2, 67 <- 93 channels, five 35x29 images
 // 30 -> 14; 7x7 at stride 2, 256 <- 256 channels, 256 14x14 images 603 -> 456; 3x3 at stride 2, 128 <- 256, 32 56x56 images 136 -> 132.
 static void setup_direct(dwm_bwd_data_plan& bp)

@@ -172,8 +172,8 @@ static double direct_bytes(int C, int K, int kt, int npx, int shared, int bw, in
 // strided data gradients): cycles at 2.1 GHz of a workgroup -- its MFMAs, 340 a staged pixel and wave of a SIMD, 5400 a chunk (first
 // loads, barriers), stores --, shared by the workgroups on a CU (registers allow two of 64-row wave tiles, three of 32), the address unit's
 // 19 for each load and store, and 1.19 PFLOP/s as the most (long runs have reached 1.4: it errs on the side of the other paths); and
-// what all tiles move, at 8 TB/s, as the other side of a right angle.  Over 2936 plans that the planner chose (rms of the logarithm of
-// measured to modelled time) 0.15, 1.8 at worst; without the last term 0.22, and strips of one to three pixels up to 3.5 times as long as
+// what all tiles move, at 8 TB/s, as the other side of a right angle.  Over 3015 plans that the planner chose (rms of the logarithm of
+// measured to modelled time) 0.16, 1.8 at worst; without the last term 0.22, and strips of one to three pixels up to 3.5 times as long as
 // modelled: 1x1, 179 -> 218 channels, 49 37x37 images 74 by the model, 215 measured, 107 the contraction.
 static double direct_us(const DirectArgs& a, const DirectShape& sh)
 {
